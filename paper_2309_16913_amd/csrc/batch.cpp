@@ -28,6 +28,7 @@ struct rt_batch {
     uint32_t ntrees = 0, nitems = 0, wave_words = 0;
     uint64_t total_q = 0, cap = 0;
     bool last_plain = false;
+    bool wide = false;       // some tree's nodes pass 4 GiB
     std::vector<const rt_tree *> trees;
     std::vector<uint64_t> q_begin, nq, id_base, id_count, plain_begin;
     void *d_trees = nullptr, *d_items = nullptr, *d_q = nullptr, *d_counts = nullptr, *d_off = nullptr;
@@ -82,7 +83,7 @@ static hipError_t enqueue_count_scan(rt_batch *b, hipStream_t s, const BatchRec 
                               static_cast<const uint32_t *>(b->d_list_begin), b->nitems,
                               static_cast<const uint32_t *>(b->d_qorder), static_cast<float4 *>(b->d_q), SEL_COUNT,
                               static_cast<uint32_t *>(b->d_counts), nullptr, nullptr, 0, b->total_q, ctrl, 0,
-                              b->wave_words, rp, s);
+                              b->wave_words, b->wide, rp, s);
     if (e == hipSuccess)
         e = launch_scan_u32(static_cast<uint32_t *>(b->d_counts), b->total_q, static_cast<uint64_t *>(b->d_off),
                             static_cast<uint64_t *>(b->d_scan), s);
@@ -104,7 +105,7 @@ static hipError_t enqueue_all(rt_batch *b, hipStream_t s) {
                               static_cast<const uint32_t *>(b->d_list_begin), b->nitems,
                               static_cast<const uint32_t *>(b->d_qorder), static_cast<float4 *>(b->d_q), SEL_FILL,
                               static_cast<uint32_t *>(b->d_counts), static_cast<uint64_t *>(b->d_off),
-                              static_cast<uint32_t *>(b->d_ids), b->cap, b->total_q, ctrl, 1, b->wave_words, rp, s);
+                              static_cast<uint32_t *>(b->d_ids), b->cap, b->total_q, ctrl, 1, b->wave_words, b->wide, rp, s);
     if (e == hipSuccess)
         e = launch_segsort(static_cast<uint64_t *>(b->d_off), b->total_q, static_cast<uint32_t *>(b->d_ids),
                            static_cast<uint32_t *>(b->d_scratch), b->cap, static_cast<uint32_t *>(b->d_lists),
@@ -180,7 +181,8 @@ extern "C" int rt_batch_create(const rt_tree *const *trees, uint32_t ntrees, con
             bt[i].t = view_of(t);
             bt[i].q_begin = qb;
             bt[i].nq = (uint32_t)nq[i];
-            bt[i].stack_cap = stack_bound(t->height, t->fanout);
+            bt[i].stack_cap = walk_stack_bound(t->height, t->fanout);
+            if ((uint64_t)t->n_nodes * t->node_bytes > 0xFFFFFFFFull) b->wide = true;
             b->q_begin[i] = qb;
             b->id_range = std::max<uint64_t>(b->id_range, t->n_objects);
             const uint32_t G = group_width(t->fanout);
@@ -381,8 +383,7 @@ extern "C" int rt_batch_run_plain(rt_batch *b, void *stream) {
         const uint64_t cap = base < b->cap ? std::min<uint64_t>(cnt, b->cap - base) : 0;
         e = launch_zero(ctrl->work, sizeof(ctrl->work), s);
         if (e == hipSuccess) e = launch_zero(ctrl->xwork, sizeof(ctrl->xwork) + sizeof(ctrl->hwork), s);
-        if (e == hipSuccess) e = launch_select_pass(v, q, (uint32_t)n, SEL_COUNT, counts, nullptr, nullptr, 0, ctrl, 0, SelectPlan(),
-                                                    (uint32_t)n, s);
+        if (e == hipSuccess) e = launch_walk(v, q, (uint32_t)n, counts, ctrl, SelectPlan(), nullptr, 0, s);
         if (e == hipSuccess) e = launch_scan_u32(counts, n, off, static_cast<uint64_t *>(b->d_scan), s);
         if (e == hipSuccess)
             e = launch_select_pass(v, q, (uint32_t)n, SEL_FILL, counts, off, ids + base, cap, ctrl, 1, SelectPlan(),

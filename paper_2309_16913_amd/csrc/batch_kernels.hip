@@ -13,40 +13,9 @@
 // atomic is spent per item; the queries of a tree are visited in the Morton
 // order of their centres, so consecutive queries share nodes.
 #include "rt_internal.h"
+#include "walk.h"
 
 namespace rtk {
-
-template <int LAYOUT>
-__device__ __forceinline__ void batch_load(const uint8_t *nb, uint32_t F, uint32_t e, float &lx, float &ly, float &hx,
-                                           float &hy) {
-    if constexpr (LAYOUT == LAYOUT_SOA) {
-        const float *f = reinterpret_cast<const float *>(nb);
-        lx = f[e];
-        ly = f[F + e];
-        hx = f[2 * F + e];
-        hy = f[3 * F + e];
-    } else if constexpr (LAYOUT == LAYOUT_AOS) {
-        const float *f = reinterpret_cast<const float *>(nb) + 5 * e;
-        lx = f[0];
-        ly = f[1];
-        hx = f[2];
-        hy = f[3];
-    } else {
-        const float2 *lo = reinterpret_cast<const float2 *>(nb);
-        const float2 a = lo[e], b = lo[F + e];
-        lx = a.x;
-        ly = a.y;
-        hx = b.x;
-        hy = b.y;
-    }
-}
-
-template <int LAYOUT>
-__device__ __forceinline__ uint32_t batch_ptr(const uint8_t *nb, uint32_t F, uint32_t e) {
-    const uint32_t *u = reinterpret_cast<const uint32_t *>(nb);
-    if constexpr (LAYOUT == LAYOUT_AOS) return u[5 * e + 4];
-    return u[4 * F + e];
-}
 
 // Next item for a wave leader: from XCD `home`'s list first, then from the
 // following lists in turn (`visited` counts the lists found drained).
@@ -69,14 +38,64 @@ __device__ __forceinline__ uint32_t grab_item(Ctrl *ctrl, uint32_t slot, const u
     return kNoNode;
 }
 
-// One work item: the queries [item.q0, item.q1) of one tree's processing
-// order, run by the wave's groups of G lanes on a tree of node layout LAYOUT.
-template <int MODE, int G, int LAYOUT, int REC>
-__device__ __forceinline__ void batch_item(const BatchTree &bt, const BatchItem &item, const uint32_t *__restrict__ qorder,
-                                           const float4 *__restrict__ qs, uint32_t *__restrict__ counts,
-                                           const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids,
-                                           Ctrl *__restrict__ ctrl, uint32_t *wstk, uint32_t lane,
-                                           uint64_t lanes_below, const BatchRec &rp, uint4 *wrec) {
+// One work item of the count pass: the queries [item.q0, item.q1) of one
+// tree's processing order, run by the wave's groups of G lanes on a tree of
+// node layout LAYOUT with the batched walk.  rchunk, rcnt: the group's record
+// chunk, kept from one item to the next.
+template <int G, int LAYOUT, bool REC, bool WIDE>
+__device__ __forceinline__ void batch_count_item(const BatchTree &bt, const BatchItem &item,
+                                                 const uint32_t *__restrict__ qorder, const float4 *__restrict__ qs,
+                                                 uint32_t *__restrict__ counts, Ctrl *__restrict__ ctrl,
+                                                 uint32_t *wstk, uint32_t lane, uint64_t lanes_below,
+                                                 const RecArena &ar, uint4 *wrec, uint32_t &rchunk, uint32_t &rcnt) {
+    GroupWalk<G, LAYOUT, REC, false, WIDE> w(lane, wstk + (lane / G) * bt.stack_cap, bt.stack_cap,
+                                             wrec + (lane / G) * kRecBuf, ar, ctrl);
+    w.rchunk = rchunk;
+    w.rcnt = rcnt;
+    uint32_t nextq = item.q0;   // wave-uniform
+    uint32_t gq = 0;            // global query index of the group's query
+    bool have = false, done = false;
+    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+    while (true) {
+        const bool need = !done && w.sp == 0;
+        if (need && have) {
+            if (w.e == 0) counts[gq] = w.pos;
+            w.pos = 0;
+            have = false;
+        }
+        // leaders of needy groups take consecutive queries of the item
+        const uint64_t lead = __ballot(need && w.e == 0);
+        const uint32_t r = (uint32_t)__popcll(lead & lanes_below);
+        const uint32_t mine = __shfl(nextq + r, (int)w.gbase);
+        nextq += (uint32_t)__popcll(lead);
+        if (need) {
+            if (mine < item.q1) {
+                gq = (uint32_t)bt.q_begin + qorder[bt.q_begin + mine];
+                have = true;
+                q = qs[gq];
+                w.stk[0] = 0u;
+                w.sp = 1;
+            } else {
+                done = true;
+            }
+        }
+        if (__all(done)) break;
+        __builtin_amdgcn_wave_barrier();
+        w.round(bt.t, q, counts, gq);
+        __builtin_amdgcn_wave_barrier();
+    }
+    w.flush(counts, 0);
+    rchunk = w.rchunk;
+    rcnt = w.rcnt;
+}
+
+// One work item of the walking fill (the graph without records, or whose
+// records overflowed).
+template <int G, int LAYOUT>
+__device__ __forceinline__ void batch_fill_item(const BatchTree &bt, const BatchItem &item, const uint32_t *__restrict__ qorder,
+                                                const float4 *__restrict__ qs, const uint64_t *__restrict__ offsets,
+                                                uint32_t *__restrict__ ids, Ctrl *__restrict__ ctrl, uint32_t *wstk,
+                                                uint32_t lane, uint64_t lanes_below) {
     const TreeView &t = bt.t;
     const uint32_t F = t.fanout;
     const uint32_t e = lane & (G - 1);
@@ -90,46 +109,10 @@ __device__ __forceinline__ void batch_item(const BatchTree &bt, const BatchItem 
     uint32_t sp = 0;
     float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
     uint64_t pos = 0, end = 0;
-    // recording count pass: as in the single-tree kernel, records collect in
-    // the group's LDS buffer and go out kRecBuf at a time to the group's
-    // chunk of the arena; the output slot of a record is the global query
-    uint32_t rchunk = kNoNode, rcnt = 0, nbuf = 0;
-    uint4 *rbuf = wrec + (lane / G) * kRecBuf;
-    auto rec_flush = [&]() {   // group-uniform
-        if (nbuf == 0) return;
-        __builtin_amdgcn_wave_barrier();
-        if (rchunk != kRecDead && (rchunk == kNoNode || rcnt + nbuf > kRecChunk)) {
-            if (rchunk != kNoNode && e == 0) rp.rec_count[rchunk] = rcnt;
-            uint32_t c = 0;
-            if (e == 0) c = atomicAdd(&ctrl->rec_chunks, 1u);
-            c = (uint32_t)__shfl((int)c, (int)gbase);
-            if (c < rp.rec_nchunks) {
-                rchunk = c;
-                rcnt = 0;
-            } else {
-                if (e == 0) atomicOr(&ctrl->rec_overflow, 1u);
-                rchunk = kRecDead;
-            }
-        }
-        if (rchunk < kRecDead) {
-            for (uint32_t i = e; i < nbuf; i += G) {
-                const uint4 v = rbuf[i];
-                put_rec(rp.rec + (size_t)rchunk * kRecChunk + rcnt + i, v.x, v.y, v.z, v.w);
-            }
-            rcnt += nbuf;
-        }
-        nbuf = 0;
-        __builtin_amdgcn_wave_barrier();
-    };
 
     while (true) {
         const bool need = !done && sp == 0;
-        if (need && have) {
-            if constexpr (MODE == SEL_COUNT) {
-                if (e == 0) counts[gq] = (uint32_t)pos;
-            }
-            have = false;
-        }
+        if (need) have = false;
         // leaders of needy groups take consecutive queries of the item
         const uint64_t lead = __ballot(need && e == 0);
         const uint32_t r = (uint32_t)__popcll(lead & lanes_below);
@@ -142,12 +125,8 @@ __device__ __forceinline__ void batch_item(const BatchTree &bt, const BatchItem 
                 q = qs[gq];
                 stk[0] = 0u;
                 sp = 1;
-                if constexpr (MODE == SEL_FILL) {
-                    pos = offsets[gq];
-                    end = offsets[gq + 1];
-                } else {
-                    pos = 0;
-                }
+                pos = offsets[gq];
+                end = offsets[gq + 1];
             } else {
                 done = true;
             }
@@ -165,12 +144,9 @@ __device__ __forceinline__ void batch_item(const BatchTree &bt, const BatchItem 
         bool hit = false, cont = false;
         uint32_t ref = 0;
         if (have && e < F) {
-            if (!leaf)
-                ref = batch_ptr<LAYOUT>(nb, F, 0);
-            else if constexpr (MODE == SEL_FILL)
-                ref = batch_ptr<LAYOUT>(nb, F, e);
+            ref = load_ptr<LAYOUT>(nb, F, leaf ? e : 0u);
             float lx, ly, hx, hy;
-            batch_load<LAYOUT>(nb, F, e, lx, ly, hx, hy);
+            load_entry<LAYOUT>(nb, F, e, lx, ly, hx, hy);
             hit = (lx <= q.z) && (q.x <= hx) && (ly <= q.w) && (q.y <= hy);
             // internal entry inside the window: its subtree is taken whole
             cont = hit && !leaf && (q.x <= lx) && (hx <= q.z) && (q.y <= ly) && (hy <= q.w);
@@ -182,67 +158,30 @@ __device__ __forceinline__ void batch_item(const BatchTree &bt, const BatchItem 
         const uint32_t rank = (uint32_t)__popcll(m & below);
         if (have) {
             if (leaf) {
-                if constexpr (MODE == SEL_FILL) {
-                    if (hit) {
-                        const uint64_t o = pos + rank;
-                        if (o < end)
-                            put_id(ids + o, ref);
-                        else
-                            atomicOr(&ctrl->err, kErrBounds);
-                    }
-                }
-                if constexpr (MODE == SEL_COUNT && REC != 0) {
-                    if (n) {   // one record per 32 entries with hits
-                        const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
-                        const uint32_t k = (lo ? 1u : 0u) + (hi ? 1u : 0u);
-                        if (nbuf + k > kRecBuf) rec_flush();
-                        if (e == 0 && lo) rbuf[nbuf] = make_uint4((uint32_t)gq, (uint32_t)pos, node, lo);
-                        if (G == 64 && e == 32 && hi)
-                            rbuf[nbuf + (lo ? 1u : 0u)] =
-                                make_uint4((uint32_t)gq, (uint32_t)pos + (uint32_t)__popc(lo), node | kRecHi, hi);
-                        nbuf += k;
-                    }
+                if (hit) {
+                    const uint64_t o = pos + rank;
+                    if (o < end)
+                        put_id(ids + o, ref);
+                    else
+                        atomicOr(&ctrl->err, kErrBounds);
                 }
                 pos += n;
             } else {
                 const uint32_t first = __shfl(ref, (int)gbase);
                 if (cm) {   // group-uniform: contained subtrees
-                    if constexpr (MODE == SEL_FILL) {
-                        // one contiguous run of the leaf-id array per run
-                        // of consecutive contained children
-                        uint64_t todo = cm;
-                        bool bad = false;
-                        while (todo) {
-                            const uint32_t j0 = (uint32_t)__builtin_ctzll(todo);
-                            const uint64_t sh = todo >> j0;
-                            const uint32_t len = ~sh ? (uint32_t)__builtin_ctzll(~sh) : 64u - j0;
-                            todo = (j0 + len >= 64) ? 0ull : (todo & (~0ull << (j0 + len)));
-                            const uint32_t l0 = t.range[first + j0].x, l1 = t.range[first + j0 + len - 1].y;
-                            pos += copy_leaf_run<4>(t, l0, l1, ids, pos, end, e, G, &bad);
-                        }
-                        if (bad && e == 0) atomicOr(&ctrl->err, kErrBounds);
-                    } else if constexpr (REC != 0) {
-                        // one record per contained child: its leaf range
-                        const uint2 rg = cont ? t.range[first + e] : make_uint2(0u, 0u);
-                        const uint32_t sc = cont ? subtree_objects(t, rg) : 0u;
-                        uint32_t inc = sc;
-                        for (uint32_t d = 1; d < G; d <<= 1) {
-                            const uint32_t x = (uint32_t)__shfl_up((int)inc, d, G);
-                            if (e >= d) inc += x;
-                        }
-                        const uint32_t tot = (uint32_t)__shfl((int)inc, (int)(gbase + G - 1));
-                        const uint32_t k = (uint32_t)__popcll(cm);
-                        if (nbuf + k > kRecBuf) rec_flush();
-                        if (cont)
-                            rbuf[nbuf + (uint32_t)__popcll(cm & below)] =
-                                make_uint4((uint32_t)gq, (uint32_t)pos + inc - sc, kRecRun | rg.x, rg.y);
-                        nbuf += k;
-                        pos += tot;
-                    } else {
-                        uint32_t sc = cont ? subtree_objects(t, t.range[first + e]) : 0u;
-                        for (uint32_t d = 1; d < G; d <<= 1) sc += (uint32_t)__shfl_xor((int)sc, (int)d);
-                        pos += sc;
+                    // one contiguous run of the leaf-id array per run of
+                    // consecutive contained children
+                    uint64_t todo = cm;
+                    bool bad = false;
+                    while (todo) {
+                        const uint32_t j0 = (uint32_t)__builtin_ctzll(todo);
+                        const uint64_t sh = todo >> j0;
+                        const uint32_t len = ~sh ? (uint32_t)__builtin_ctzll(~sh) : 64u - j0;
+                        todo = (j0 + len >= 64) ? 0ull : (todo & (~0ull << (j0 + len)));
+                        const uint32_t l0 = t.range[first + j0].x, l1 = t.range[first + j0 + len - 1].y;
+                        pos += copy_leaf_run<4>(t, l0, l1, ids, pos, end, e, G, &bad);
                     }
+                    if (bad && e == 0) atomicOr(&ctrl->err, kErrBounds);
                 }
                 const uint32_t prank = (uint32_t)__popcll(pm & below);
                 if (hit && !cont) {
@@ -256,13 +195,9 @@ __device__ __forceinline__ void batch_item(const BatchTree &bt, const BatchItem 
         }
         __builtin_amdgcn_wave_barrier();
     }
-    if constexpr (MODE == SEL_COUNT && REC != 0) {
-        rec_flush();
-        if (e == 0 && rchunk < kRecDead) rp.rec_count[rchunk] = rcnt;
-    }
 }
 
-template <int MODE, int REC>
+template <bool COUNT, bool REC, bool WIDE>
 __global__ void __launch_bounds__(256)
 batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ items,
              const uint32_t *__restrict__ list_begin, uint32_t nitems, const uint32_t *__restrict__ qorder,
@@ -270,7 +205,7 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
              uint32_t *__restrict__ ids, uint64_t cap, uint64_t total_q, Ctrl *__restrict__ ctrl, uint32_t slot,
              uint32_t wave_words, BatchRec rp) {
     extern __shared__ uint32_t smem[];
-    if constexpr (MODE == SEL_FILL) {
+    if constexpr (!COUNT) {
         if (offsets[total_q] > cap) return;
         if (rp.fill_guard && ctrl->rec_overflow == 0) return;   // the replay wrote everything
     }
@@ -282,6 +217,9 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
     const uint64_t lanes_below = lane ? (~0ull >> (64 - lane)) : 0ull;
     const uint32_t home = blockIdx.x % kXcds;
     uint32_t visited = 0;
+    const RecArena ar{rp.rec, rp.rec_count, rp.rec_nchunks};
+    // the record chunk of the lane's group, and the group width it belongs to
+    uint32_t rchunk = kNoNode, rcnt = 0, rG = 0;
 
     while (true) {
         uint32_t it = kNoNode;
@@ -292,8 +230,15 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
         const BatchItem item = items[it];
         const BatchTree bt = trees[item.tree];
         const uint32_t G = bt.t.fanout <= 16 ? 16u : (bt.t.fanout <= 32 ? 32u : 64u);
-#define RT_ITEM(G_, L_) \
-    batch_item<MODE, G_, L_, REC>(bt, item, qorder, qs, counts, offsets, ids, ctrl, wstk, lane, lanes_below, rp, wrec)
+        if constexpr (REC) {
+            if (G != rG) {   // the groups change: close the old ones' chunks
+                if (rG && (lane & (rG - 1)) == 0 && rchunk < kRecDead) rp.rec_count[rchunk] = rcnt;
+                rchunk = __any(rchunk == kRecDead) ? kRecDead : kNoNode;   // the same for all lanes
+                rcnt = 0;
+                rG = G;
+            }
+        }
+#define RT_ITEM(G_, L_)                                                                                            do {                                                                                                               if constexpr (COUNT)                                                                                               batch_count_item<G_, L_, REC, WIDE>(bt, item, qorder, qs, counts, ctrl, wstk, lane, lanes_below, ar, wrec,                                           rchunk, rcnt);                                                               else                                                                                                               batch_fill_item<G_, L_>(bt, item, qorder, qs, offsets, ids, ctrl, wstk, lane, lanes_below);            } while (0)
         if (bt.t.layout == LAYOUT_SOA) {
             if (G == 16) RT_ITEM(16, LAYOUT_SOA);
             else if (G == 32) RT_ITEM(32, LAYOUT_SOA);
@@ -309,12 +254,15 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
         }
 #undef RT_ITEM
     }
+    if constexpr (REC) {
+        if (rG && (lane & (rG - 1)) == 0 && rchunk < kRecDead) rp.rec_count[rchunk] = rcnt;
+    }
 }
 
 hipError_t launch_batch_pass(const BatchTree *trees, const BatchItem *items, const uint32_t *list_begin,
                              uint32_t nitems, const uint32_t *qorder, const float4 *q, int mode, uint32_t *counts,
                              const uint64_t *offsets, uint32_t *ids, uint64_t cap, uint64_t total_q, Ctrl *ctrl,
-                             uint32_t slot, uint32_t wave_words, const BatchRec &rp, hipStream_t s) {
+                             uint32_t slot, uint32_t wave_words, bool wide, const BatchRec &rp, hipStream_t s) {
     // wave_words: largest (64 / G) * stack_cap over the trees (one region per wave)
     size_t smem = (size_t)4 * wave_words * sizeof(uint32_t);
     const bool rec = mode == SEL_COUNT && rp.rec;
@@ -323,15 +271,19 @@ hipError_t launch_batch_pass(const BatchTree *trees, const BatchItem *items, con
     const uint32_t want = (nitems + 3) / 4;
     if (want < blocks) blocks = want ? want : 1;
     blocks = (blocks + kXcds - 1) / kXcds * kXcds;   // every XCD gets blocks
-    if (rec)
-        hipLaunchKernelGGL((batch_kernel<SEL_COUNT, 1>), dim3(blocks), dim3(256), smem, s, trees, items, list_begin,
-                           nitems, qorder, q, counts, offsets, ids, cap, total_q, ctrl, slot, wave_words, rp);
-    else if (mode == SEL_COUNT)
-        hipLaunchKernelGGL((batch_kernel<SEL_COUNT, 0>), dim3(blocks), dim3(256), smem, s, trees, items, list_begin,
-                           nitems, qorder, q, counts, offsets, ids, cap, total_q, ctrl, slot, wave_words, rp);
-    else
-        hipLaunchKernelGGL((batch_kernel<SEL_FILL, 0>), dim3(blocks), dim3(256), smem, s, trees, items, list_begin,
-                           nitems, qorder, q, counts, offsets, ids, cap, total_q, ctrl, slot, wave_words, rp);
+#define RT_BATCH(C_, R_, W_)                                                                                    \
+    hipLaunchKernelGGL((batch_kernel<C_, R_, W_>), dim3(blocks), dim3(256), smem, s, trees, items, list_begin, nitems, \
+                       qorder, q, counts, offsets, ids, cap, total_q, ctrl, slot, wave_words, rp)
+    if (rec) {
+        if (wide) RT_BATCH(true, true, true);
+        else RT_BATCH(true, true, false);
+    } else if (mode == SEL_COUNT) {
+        if (wide) RT_BATCH(true, false, true);
+        else RT_BATCH(true, false, false);
+    } else {
+        RT_BATCH(false, false, true);
+    }
+#undef RT_BATCH
     return hipGetLastError();
 }
 

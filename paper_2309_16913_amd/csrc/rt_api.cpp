@@ -109,6 +109,7 @@ TreeView rtk::view_of(const rt_tree *t) {
     v.nodes = static_cast<const uint8_t *>(t->d_nodes);
     v.fanout = t->fanout;
     v.node_bytes = t->node_bytes;
+    v.n_nodes = t->n_nodes;
     v.first_leaf = t->first_leaf;
     v.height = t->height;
     v.layout = t->layout;
@@ -412,17 +413,11 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         return e == hipSuccess ? RT_OK : hip_fail(e, "empty select");
     }
     const TreeView v = view_of(t);
-    const SplitCfg sc = d_counts_out ? SplitCfg() : split_cfg(t, nq);
     auto mark = [&](int k) -> hipError_t {
         return events && events[k] ? hipEventRecord(static_cast<hipEvent_t>(events[k]), s) : hipSuccess;
     };
     hipError_t e = hipSuccess;
     SelectPlan plan;
-    if (sc.on) {
-        plan.slot_first = w.slot_first;
-        plan.heavy = w.heavy;
-        plan.hcap = sc.budget;
-    }
     // records of the count pass (node and leaf indices must leave the two
     // flag bits free), in the rec_bytes after the layout for (nq, cap) in one
     // call, or for (nq, 0) in a separate count stage; the count stage names
@@ -435,8 +430,18 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         plan.rec_count = reinterpret_cast<uint32_t *>(base + align256(16ull * kRecChunk * rec_nchunks));
         plan.rec_nchunks = rec_nchunks;
     }
+    // split mapping: a recording count pass shares the large queries' walks
+    // by itself and its records belong to whole queries; without records the
+    // large queries get one output slot per subtree
+    const SplitCfg sc = d_counts_out ? SplitCfg() : split_cfg(t, nq);
+    const bool slots = sc.on && !rec;
+    auto use_slots = [&](SelectPlan &p) {
+        p.slot_first = w.slot_first;
+        p.heavy = w.heavy;
+        p.hcap = sc.budget;
+    };
     if (stage & 1) {   // count stage: ctrl, order, split, count pass, offsets
-        uint32_t *counts = d_counts_out ? d_counts_out : (sc.on ? w.slot_counts : w.counts);
+        uint32_t *counts = d_counts_out ? d_counts_out : (slots ? w.slot_counts : w.counts);
         e = launch_zero(w.ctrl, sizeof(Ctrl), s);
         if (e == hipSuccess && rec) e = launch_set_rec(w.ctrl, plan, s);
         if (e == hipSuccess) e = mark(0);
@@ -444,7 +449,8 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         if (e == hipSuccess && nq >= kOrderMinQueries)
             e = launch_query_order(dq, (uint32_t)nq, t->mbr, w.order, &order, s);
         plan.order = order;
-        if (sc.on) {
+        if (slots) {
+            use_slots(plan);
             if (e == hipSuccess)
                 e = launch_split(v, dq, (uint32_t)nq, 0, sc.split_first, sc.kmin, sc.budget, sc.min_area, w.nslots,
                                  nullptr, nullptr, order, w.ctrl, s);
@@ -455,13 +461,16 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
                 e = launch_split(v, dq, (uint32_t)nq, 1, sc.split_first, sc.kmin, sc.budget, sc.min_area, nullptr,
                                  w.slot_first, w.heavy, order, w.ctrl, s);
             if (e == hipSuccess) e = launch_zero(w.slot_counts, 4 * w.nslot_max, s);
+            if (e == hipSuccess)
+                e = launch_select_pass(v, dq, (uint32_t)nq, SEL_COUNT, counts, nullptr, nullptr, 0, w.ctrl, 0, plan,
+                                       (uint32_t)nq, s);
+        } else if (e == hipSuccess) {
+            e = launch_walk(v, dq, (uint32_t)nq, counts, w.ctrl, plan,
+                            sc.on ? reinterpret_cast<uint2 *>(w.heavy) : nullptr, sc.budget, s);
         }
-        if (e == hipSuccess)
-            e = launch_select_pass(v, dq, (uint32_t)nq, SEL_COUNT, counts, nullptr, nullptr, 0, w.ctrl, 0, plan,
-                                   (uint32_t)nq, s);
         if (e == hipSuccess) e = mark(1);
         if (d_counts_out || e != hipSuccess) return e == hipSuccess ? RT_OK : hip_fail(e, "count pass");
-        if (sc.on) {
+        if (slots) {
             e = launch_scan_u32(w.slot_counts, w.nslot_max, w.slot_off, w.slot_scan_tmp, s);
             if (e == hipSuccess) e = launch_gather_offsets(w.slot_first, w.slot_off, (uint32_t)nq, d_off, s);
         } else {
@@ -473,8 +482,6 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
     if (stage & 2) {   // fill stage: fill pass, sort, status
         // the processing order written by the count stage is still in the workspace
         if (nq >= kOrderMinQueries) plan.order = query_order_result(w.order, nq);
-        const uint64_t *fo = sc.on ? w.slot_off : d_off;
-        const uint32_t no = sc.on ? (uint32_t)w.nslot_max : (uint32_t)nq;
         // on large trees long contained runs go to the bulk copy after the pass
         if (t->bulk_copy == RT_BULK_ON || (t->bulk_copy == RT_BULK_AUTO && t->n_objects >= kBulkMinObjects)) {
             const uint64_t bcap = bulk_capacity(cap);
@@ -484,12 +491,23 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         // replay the count pass's records (a separate fill stage cannot know
         // whether its count stage made any: the replay checks); the walk then
         // runs only if there were none or they overflowed
-        if (rec || stage == 2) {
-            e = launch_replay(v, fo, no, d_ids, cap, w.ctrl, s);
-            plan.fill_guard = 1;
+        if (rec || stage == 2) e = launch_replay(v, d_off, (uint32_t)nq, d_ids, cap, w.ctrl, plan, s);
+        if (!slots || stage == 2) {   // whole queries
+            plan.fill_guard = rec ? FILL_UNLESS_REPLAYED
+                                  : (stage == 2 ? (sc.on ? FILL_IF_OVERFLOWED : FILL_UNLESS_REPLAYED) : FILL_ALWAYS);
+            plan.slot_first = nullptr;
+            plan.heavy = nullptr;
+            if (e == hipSuccess)
+                e = launch_select_pass(v, dq, (uint32_t)nq, SEL_FILL, nullptr, d_off, d_ids, cap, w.ctrl, 1, plan,
+                                       (uint32_t)nq, s);
         }
-        if (e == hipSuccess)
-            e = launch_select_pass(v, dq, (uint32_t)nq, SEL_FILL, nullptr, fo, d_ids, cap, w.ctrl, 1, plan, no, s);
+        if (slots) {
+            plan.fill_guard = stage == 2 ? FILL_IF_NOT_RECORDED : FILL_ALWAYS;
+            use_slots(plan);
+            if (e == hipSuccess)
+                e = launch_select_pass(v, dq, (uint32_t)nq, SEL_FILL, nullptr, w.slot_off, d_ids, cap, w.ctrl, 1,
+                                       plan, (uint32_t)w.nslot_max, s);
+        }
         if (e == hipSuccess && plan.bulk)
             e = launch_bulk_copy(static_cast<const uint32_t *>(t->d_leaf_ids), plan.bulk, plan.bulk_cap, d_ids, w.ctrl,
                                  s);

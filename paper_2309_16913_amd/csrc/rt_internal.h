@@ -20,6 +20,7 @@ struct TreeView {
     const uint8_t *nodes;
     uint32_t fanout;
     uint32_t node_bytes;
+    uint32_t n_nodes;
     uint32_t first_leaf;
     uint32_t height;
     uint32_t layout;
@@ -124,7 +125,7 @@ struct Ctrl {
     uint32_t work[8];        // work-queue counters (one per pass)
     uint32_t err;            // internal error flags
     uint32_t bulk_n;         // long contained runs deferred to the bulk copy (descriptors appended)
-    uint32_t bulk_taken;     // descriptors taken by the bulk copy
+    uint32_t pad0;
     uint32_t rec_chunks;     // record chunks taken by the count pass
     uint32_t rec_overflow;   // 1: the record arena filled up (the fill walks the tree)
     uint32_t rec_nchunks;    // the count pass's record arena (0: it recorded nothing); set by the
@@ -151,6 +152,7 @@ constexpr uint32_t kErrInput = 4u;     // invalid rectangle found on the device
 // deferral wins (12.9 against 9.2 ms, fanout 32).
 constexpr uint64_t kBulkMinObjects = 1ull << 25;
 constexpr uint32_t kBulkMin = 2048;     // shortest run handed to the bulk copy
+constexpr uint32_t kReplayBulkMin = 4096;   // shortest range the replay hands to it
 constexpr uint32_t kBulkChunk = 8192;   // ids per bulk-copy descriptor
 // Descriptors a fill pass can append for an output of cap ids: a deferred
 // run of n >= kBulkMin ids takes ceil(n / kBulkChunk) <= n / kBulkMin of them.
@@ -194,6 +196,16 @@ inline uint32_t stack_bound(uint32_t height, uint32_t fanout) {
     return height <= 1 ? 1u : (height - 1) * (fanout - 1) + 1;
 }
 
+// Nodes a group of the batched walk visits per round, and the stack it needs.
+// Leaves push nothing.  Two internal nodes are taken at once only from a
+// stack of at most F entries: the pushes then leave at most F + 2 (F - 1)
+// entries, each at most h - 2 levels above the leaves, so one-at-a-time pops
+// from there stay within (h-1)(F-1) + 1 + 2 (F - 1).
+constexpr uint32_t kWalkBatch = 4;   // leaves per round
+inline uint32_t walk_stack_bound(uint32_t height, uint32_t fanout) {
+    return stack_bound(height, fanout) + 2 * fanout;
+}
+
 inline uint32_t group_width(uint32_t fanout) {
     return fanout <= 16 ? 16u : (fanout <= 32 ? 32u : 64u);
 }
@@ -229,10 +241,13 @@ struct SelectPlan {
     uint4 *rec = nullptr;
     uint32_t *rec_count = nullptr;
     uint32_t rec_nchunks = 0;
-    // fill pass: run only if the count pass made no records or they
-    // overflowed (the replay wrote everything otherwise)
-    uint32_t fill_guard = 0;
+    uint32_t fill_guard = 0;   // fill pass: a FillGuard
 };
+
+// When a fill pass that is launched behind a replay runs: always; if the
+// count pass made no records or they overflowed; only if they overflowed;
+// only if it made none.
+enum FillGuard : uint32_t { FILL_ALWAYS = 0, FILL_UNLESS_REPLAYED = 1, FILL_IF_OVERFLOWED = 2, FILL_IF_NOT_RECORDED = 3 };
 
 constexpr uint32_t kRecChunk = 256;          // records per chunk a lane group takes
 // records a lane group collects in LDS before storing them (128 measured no
@@ -250,6 +265,15 @@ hipError_t launch_select_pass(const TreeView &t, const float4 *q, uint32_t nq, i
                               uint32_t *counts, const uint64_t *offsets, uint32_t *ids,
                               uint64_t ids_capacity, Ctrl *ctrl, uint32_t work_slot,
                               const SelectPlan &plan, uint32_t noffsets, hipStream_t s);
+
+// Count pass on the batched walk: counts[q] for every query, in the plan's
+// order, recording into the plan's arena if it names one.  items (NULL, or
+// 2 * kXcds * items_per_list entries; only with an arena): large queries hand
+// the rest of their walk to further launches after kWalkBudget0 nodes, large
+// subtrees after kWalkBudget1.
+constexpr uint32_t kWalkBudget0 = 32, kWalkBudget1 = 64;
+hipError_t launch_walk(const TreeView &t, const float4 *q, uint32_t nq, uint32_t *counts, Ctrl *ctrl,
+                       const SelectPlan &plan, uint2 *items, uint32_t items_per_list, hipStream_t s);
 
 // Split pre-pass (phase 0: slots per query; phase 1: work items).  Queries
 // are taken in the plan's order with the same XCD slices as the passes;
@@ -278,9 +302,10 @@ hipError_t launch_set_rec(Ctrl *ctrl, const SelectPlan &plan, hipStream_t s);
 // Replay of the count pass's records (arena named in the control words):
 // writes every recorded hit and contained leaf range at offsets[slot] +
 // position; does nothing if the count pass made no records, they overflowed,
-// or the result does not fit.
+// or the result does not fit.  With the plan's bulk list, leaf ranges of at
+// least kReplayBulkMin ids are deferred to the bulk copy.
 hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t noffsets, uint32_t *ids,
-                         uint64_t ids_capacity, Ctrl *ctrl, hipStream_t s);
+                         uint64_t ids_capacity, Ctrl *ctrl, const SelectPlan &plan, hipStream_t s);
 
 hipError_t launch_bulk_copy(const uint32_t *leaf_ids, const uint4 *bulk, uint32_t bulk_cap, uint32_t *ids,
                             Ctrl *ctrl, hipStream_t s);
@@ -371,7 +396,8 @@ struct BatchItem {           // a chunk of one tree's queries
 // query index (each tree's queries in the Morton order of their centres).
 // rec (count pass): record arena as SelectPlan::rec / rec_count / rec_nchunks,
 // with global query indices as output slots (NULL: no records).  fill_guard
-// (fill pass): run only if the count pass's records overflowed.
+// (fill pass): run only if the count pass's records overflowed.  wide: some
+// tree's nodes pass 4 GiB.
 struct BatchRec {
     uint4 *rec = nullptr;
     uint32_t *rec_count = nullptr;
@@ -381,7 +407,7 @@ struct BatchRec {
 hipError_t launch_batch_pass(const BatchTree *trees, const BatchItem *items, const uint32_t *list_begin,
                              uint32_t nitems, const uint32_t *qorder, const float4 *q, int mode, uint32_t *counts,
                              const uint64_t *offsets, uint32_t *ids, uint64_t capacity, uint64_t total_q, Ctrl *ctrl,
-                             uint32_t work_slot, uint32_t wave_words, const BatchRec &rec, hipStream_t s);
+                             uint32_t work_slot, uint32_t wave_words, bool wide, const BatchRec &rec, hipStream_t s);
 // Replay of a recording batch count pass; qtree[global query] = its tree.
 hipError_t launch_batch_replay(const BatchTree *trees, const uint32_t *qtree, const BatchRec &rec,
                                const uint64_t *offsets, uint64_t total_q, uint32_t *ids, uint64_t capacity,

@@ -30,41 +30,9 @@
 // tree with the same predicate, so the fill pass writes exactly the count
 // pass's number of ids for every query.
 #include "rt_internal.h"
+#include "walk.h"
 
 namespace rtk {
-
-template <int LAYOUT>
-__device__ __forceinline__ void load_entry(const uint8_t *__restrict__ node, uint32_t F, uint32_t e,
-                                           float &lx, float &ly, float &hx, float &hy) {
-    if constexpr (LAYOUT == LAYOUT_SOA) {
-        const float *f = reinterpret_cast<const float *>(node);
-        lx = f[e];
-        ly = f[F + e];
-        hx = f[2 * F + e];
-        hy = f[3 * F + e];
-    } else if constexpr (LAYOUT == LAYOUT_AOS) {
-        const float *f = reinterpret_cast<const float *>(node) + 5 * e;
-        lx = f[0];
-        ly = f[1];
-        hx = f[2];
-        hy = f[3];
-    } else {
-        const float2 *lo = reinterpret_cast<const float2 *>(node);
-        const float2 a = lo[e];
-        const float2 b = lo[F + e];
-        lx = a.x;
-        ly = a.y;
-        hx = b.x;
-        hy = b.y;
-    }
-}
-
-template <int LAYOUT>
-__device__ __forceinline__ uint32_t load_ptr(const uint8_t *__restrict__ node, uint32_t F, uint32_t e) {
-    const uint32_t *u = reinterpret_cast<const uint32_t *>(node);
-    if constexpr (LAYOUT == LAYOUT_AOS) return u[5 * e + 4];
-    return u[4 * F + e];
-}
 
 // Next query for a group leader.  The processing order is cut into eight
 // slices; a block on XCD `home` drains slice `home` first (the queries of a
@@ -137,19 +105,18 @@ __device__ __forceinline__ Unit next_split_item(Ctrl *ctrl, uint32_t slot, uint3
 // take longer, and a group holding several of them widens the XCD's front in
 // the processing order, which costs L2 hits.  Returns the number taken (0:
 // all handed out) and the first position in *p0.
-template <uint32_t K>
-__device__ __forceinline__ uint32_t grab_chunk(Ctrl *ctrl, uint32_t slot, uint32_t nq, uint32_t home,
-                                               uint32_t &visited, bool look_first, uint32_t *p0) {
+__device__ __forceinline__ uint32_t grab_chunk(uint32_t (*work)[32], uint32_t nq, uint32_t home, uint32_t &visited,
+                                               bool look_first, uint32_t K, uint32_t *p0) {
     while (visited < kXcds) {
         const uint32_t x = (home + visited) % kXcds;
         const uint32_t b0 = (uint32_t)(((uint64_t)x * nq) / kXcds);
         const uint32_t b1 = (uint32_t)(((uint64_t)(x + 1) * nq) / kXcds);
         if (look_first && visited > 0 &&
-            __hip_atomic_load(&ctrl->xwork[slot][x][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= b1 - b0) {
+            __hip_atomic_load(&work[x][0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= b1 - b0) {
             visited += 1;
             continue;
         }
-        const uint32_t k = atomicAdd(&ctrl->xwork[slot][x][0], K);
+        const uint32_t k = atomicAdd(&work[x][0], K);
         if (k < b1 - b0) {
             *p0 = b0 + k;
             return min(K, b1 - b0 - k);
@@ -174,9 +141,7 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
 // loaded ahead there.
 // EXT = 1, fill pass: contained runs of at least kBulkMin ids are appended
 // to the plan's descriptor list for the bulk copy instead of being copied in
-// the pass.  EXT = 1, count pass: every leaf with hits and every contained
-// subtree is also written to the plan's record arena, which the fill stage
-// replays instead of walking the tree again.
+// the pass.
 constexpr uint32_t kCountChunk = 2;
 // Contained runs of at most this many leaves are copied from the leaves' own
 // ptr arrays (layouts D1, D2: a leaf's ids are 4F contiguous bytes of its
@@ -195,7 +160,11 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
     extern __shared__ uint32_t smem[];
     if constexpr (MODE == SEL_FILL) {
         if (offsets[noffsets] > cap) return;   // result does not fit: leave ids untouched
-        if (plan.fill_guard && ctrl->rec_nchunks && !ctrl->rec_overflow) return;   // the replay wrote everything
+        // the replay wrote everything, or the fill over the other mapping does
+        const bool rec = ctrl->rec_nchunks != 0, over = ctrl->rec_overflow != 0;
+        if (plan.fill_guard == FILL_UNLESS_REPLAYED && rec && !over) return;
+        if (plan.fill_guard == FILL_IF_OVERFLOWED && !(rec && over)) return;
+        if (plan.fill_guard == FILL_IF_NOT_RECORDED && rec) return;
     }
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t e = lane & (G - 1);
@@ -224,40 +193,6 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
     // lookahead registers: the node loaded ahead and this lane's entry of it
     uint32_t pf_node = kNoNode, pf_ref = 0;
     float pf_lx = 0.f, pf_ly = 0.f, pf_hx = 0.f, pf_hy = 0.f;
-    // recording count pass: records collect in the group's LDS buffer (after
-    // the stacks) and go out kRecBuf at a time to the group's current chunk
-    // of the arena (rchunk, rcnt records used).  Stores and loads share one
-    // completion counter, so a store issued before a node load delays the
-    // wait for that load: batching the stores keeps such waits rare.
-    uint32_t rchunk = kNoNode, rcnt = 0, nbuf = 0;
-    uint4 *rbuf = reinterpret_cast<uint4 *>(smem + ((256 / G) * stack_cap + 3u) / 4u * 4u) + (threadIdx.x / G) * kRecBuf;
-    auto rec_flush = [&]() {   // group-uniform
-        if (nbuf == 0) return;
-        __builtin_amdgcn_wave_barrier();
-        if (rchunk != kRecDead && (rchunk == kNoNode || rcnt + nbuf > kRecChunk)) {
-            if (rchunk != kNoNode && e == 0) plan.rec_count[rchunk] = rcnt;
-            uint32_t c = 0;
-            if (e == 0) c = atomicAdd(&ctrl->rec_chunks, 1u);
-            c = (uint32_t)__shfl((int)c, (int)gbase);
-            if (c < plan.rec_nchunks) {
-                rchunk = c;
-                rcnt = 0;
-            } else {
-                if (e == 0) atomicOr(&ctrl->rec_overflow, 1u);
-                rchunk = kRecDead;
-            }
-        }
-        if (rchunk < kRecDead) {
-            for (uint32_t i = e; i < nbuf; i += G) {
-                const uint4 v = rbuf[i];
-                put_rec(plan.rec + (size_t)rchunk * kRecChunk + rcnt + i, v.x, v.y, v.z, v.w);
-            }
-            rcnt += nbuf;
-        }
-        nbuf = 0;
-        __builtin_amdgcn_wave_barrier();
-    };
-
     while (true) {
         if (!done && sp == 0) {
             if (have) {
@@ -280,8 +215,8 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
                 if (ci >= cn) {
                     uint32_t p0 = 0, c = 0;
                     if (e == 0)
-                        c = grab_chunk<MODE == SEL_FILL ? 1u : kCountChunk>(ctrl, slot, nq, home, visited,
-                                                                             plan.heavy != nullptr, &p0);
+                        c = grab_chunk(ctrl->xwork[slot], nq, home, visited, plan.heavy != nullptr,
+                                       MODE == SEL_FILL ? 1u : kCountChunk, &p0);
                     c = __shfl(c, (int)gbase);
                     p0 = __shfl(p0, (int)gbase);
                     visited = __shfl(visited, (int)gbase);
@@ -417,18 +352,6 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
                             atomicOr(&ctrl->err, kErrBounds);
                     }
                 }
-                if constexpr (MODE == SEL_COUNT && EXT != 0) {
-                    if (n) {   // one record per 32 entries with hits
-                        const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
-                        const uint32_t k = (lo ? 1u : 0u) + (hi ? 1u : 0u);
-                        if (nbuf + k > kRecBuf) rec_flush();
-                        if (e == 0 && lo) rbuf[nbuf] = make_uint4(oslot, (uint32_t)pos, node, lo);
-                        if (G == 64 && e == 32 && hi)
-                            rbuf[nbuf + (lo ? 1u : 0u)] =
-                                make_uint4(oslot, (uint32_t)pos + (uint32_t)__popc(lo), node | kRecHi, hi);
-                        nbuf += k;
-                    }
-                }
                 pos += n;
             } else {
                 // children of a node are contiguous: entry e points at first + e
@@ -487,24 +410,6 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
                                 pos += copy_leaf_run<EXT != 0 ? 2 : 4>(t, l0, l1, ids, pos, end, e, G, &bad);
                         }
                         if (bad && e == 0) atomicOr(&ctrl->err, kErrBounds);
-                    } else if constexpr (MODE == SEL_COUNT && EXT != 0) {
-                        // one record per contained child: its leaf range, at
-                        // the position after the contained children before it
-                        const uint2 rg = cont ? t.range[first + e] : make_uint2(0u, 0u);
-                        const uint32_t sc = cont ? subtree_objects(t, rg) : 0u;
-                        uint32_t inc = sc;
-                        for (uint32_t d = 1; d < G; d <<= 1) {
-                            const uint32_t x = (uint32_t)__shfl_up((int)inc, d, G);
-                            if (e >= d) inc += x;
-                        }
-                        const uint32_t tot = (uint32_t)__shfl((int)inc, (int)(gbase + G - 1));
-                        const uint32_t k = (uint32_t)__popcll(cm);
-                        if (nbuf + k > kRecBuf) rec_flush();
-                        if (cont)
-                            rbuf[nbuf + (uint32_t)__popcll(cm & below)] =
-                                make_uint4(oslot, (uint32_t)pos + inc - sc, kRecRun | rg.x, rg.y);
-                        nbuf += k;
-                        pos += tot;
                     } else {
                         uint32_t sc = cont ? subtree_objects(t, t.range[first + e]) : 0u;
                         for (uint32_t d = 1; d < G; d <<= 1) sc += (uint32_t)__shfl_xor((int)sc, (int)d);
@@ -524,10 +429,6 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
         }
         __builtin_amdgcn_wave_barrier();
     }
-    if constexpr (MODE == SEL_COUNT && EXT != 0) {
-        rec_flush();
-        if (e == 0 && rchunk < kRecDead) plan.rec_count[rchunk] = rcnt;
-    }
     if constexpr (MODE == SEL_STATS) {
         if (e == 0 && (vnodes | ventries)) {
             atomicAdd((unsigned long long *)&ctrl->stats[0], (unsigned long long)vnodes);
@@ -535,6 +436,115 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
             atomicAdd((unsigned long long *)&ctrl->stats[2], (unsigned long long)vcont);
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// count pass on the batched walk (walk.h)
+// ---------------------------------------------------------------------------
+// SRC 0: units are whole queries, started at the root; the group owns the
+// query's counter.  With DUMP, a group whose unit has visited `budget` nodes
+// hands the rest of its stack to the items of `out` (per-XCD lists), so that
+// the groups of the next launch share one large window's remaining subtrees.
+// SRC 1: units are such items of `in` ({query, node}), whose results are
+// added to the query's counter with atomics (the order of a query's records,
+// and so of its unsorted ids, does not matter: the ids are sorted later).
+struct WalkItems {
+    uint2 *item;         // kXcds lists of cap items
+    uint32_t cap;
+    uint32_t (*n)[32];   // per list: items appended (may pass cap; the rest stayed with their group)
+    uint32_t (*taken)[32];
+};
+
+template <int G, int LAYOUT, bool REC, int SRC, bool DUMP, bool WIDE>
+__global__ void __launch_bounds__(256)
+walk_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, const uint64_t *__restrict__ order,
+            uint32_t *__restrict__ counts, Ctrl *__restrict__ ctrl, uint32_t chunk, uint32_t stack_cap, RecArena ar,
+            uint32_t budget, WalkItems in, WalkItems out) {
+    extern __shared__ uint32_t smem[];
+    const uint32_t lane = threadIdx.x & 63u;
+    uint4 *rbuf = reinterpret_cast<uint4 *>(smem + ((256 / G) * stack_cap + 3u) / 4u * 4u) + (threadIdx.x / G) * kRecBuf;
+    GroupWalk<G, LAYOUT, REC, SRC != 0, WIDE> w(lane, smem + (threadIdx.x / G) * stack_cap, stack_cap, rbuf, ar, ctrl);
+    const uint32_t e = w.e, gbase = w.gbase;
+    __shared__ ListShare share;
+    share.init();
+    ListGrab grab(256 / G, threadIdx.x / G);
+    // the group's chunk of units: lane i < cn holds the i-th unit's query cq,
+    // window cw (and root node cd); ci = next to start
+    uint32_t cn = 0, ci = 0, cq = 0, cd = 0;
+    float4 cw = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 q = cw;
+    uint32_t slot = 0, vis = 0;
+    bool have = false, done = false;
+    while (true) {
+        if (!done && w.sp == 0) {
+            if (have) {
+                if constexpr (SRC == 0) {
+                    if (e == 0) counts[slot] = w.pos;
+                    w.pos = 0;
+                } else {
+                    w.settle(counts, slot);
+                }
+            }
+            if (ci >= cn) {
+                uint32_t p0 = 0, c = 0;
+                if (e == 0) {
+                    if constexpr (SRC == 0) {   // list x: the x-th eighth of the processing order
+                        const auto begin = [&](uint32_t x) { return (uint32_t)(((uint64_t)x * nq) / kXcds); };
+                        c = grab.take(&share, ctrl->xwork[0], chunk, begin,
+                                      [&](uint32_t x) { return begin(x + 1) - begin(x); }, &p0);
+                    } else {
+                        c = grab.take(
+                            &share, in.taken, chunk, [&](uint32_t x) { return x * in.cap; },
+                            [&](uint32_t x) { return min(in.n[x][0], in.cap); }, &p0);
+                    }
+                }
+                c = (uint32_t)__shfl((int)c, (int)gbase);
+                p0 = (uint32_t)__shfl((int)p0, (int)gbase);
+                cn = c;
+                ci = 0;
+                if (e < c) {
+                    if constexpr (SRC == 0) {
+                        cq = order ? (uint32_t)order[p0 + e] : p0 + e;
+                    } else {
+                        const uint2 it = in.item[p0 + e];
+                        cq = it.x;
+                        cd = it.y;
+                    }
+                    cw = qs[cq];
+                }
+            }
+            if (ci < cn) {
+                const int src = (int)(gbase + ci);
+                ci += 1;
+                slot = (uint32_t)__shfl((int)cq, src);
+                q = make_float4(__shfl(cw.x, src), __shfl(cw.y, src), __shfl(cw.z, src), __shfl(cw.w, src));
+                w.stk[0] = SRC == 0 ? 0u : (uint32_t)__shfl((int)cd, src);
+                w.sp = 1;
+                vis = 0;
+                have = true;
+            } else {
+                have = false;
+                done = true;
+            }
+        }
+        if (__all(done)) break;
+        __builtin_amdgcn_wave_barrier();
+        vis += w.round(t, q, counts, slot);
+        __builtin_amdgcn_wave_barrier();
+        if constexpr (DUMP) {
+            if (vis >= budget && w.sp) {   // group-uniform
+                uint32_t b = 0;
+                if (e == 0) b = atomicAdd(&out.n[grab.home][0], w.sp);
+                b = (uint32_t)__shfl((int)b, (int)gbase);
+                const uint32_t n = b < out.cap ? min(w.sp, out.cap - b) : 0u;
+                for (uint32_t i = e; i < n; i += G)
+                    out.item[grab.home * out.cap + b + i] = make_uint2(slot, w.stk[w.sp - 1 - i]);
+                w.sp -= n;
+                if (w.sp) budget = 0xFFFFFFFFu;   // the list is full: the group walks on
+            }
+        }
+    }
+    w.finish(counts);
 }
 
 // Split pre-pass.  Walks only the internal levels above the parents of leaves
@@ -655,22 +665,18 @@ split_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t sp
     }
 }
 
-// Bulk copy of deferred contained runs: one block per descriptor at a time;
+// Bulk copy of deferred contained runs: one block per descriptor at a time,
+// descriptors by stride (they are about the same size; a counter that every
+// block updates took 24 us on its own);
 // stores start at a 64-byte boundary of the destination (the first ids up
 // to it are written by the first lanes), so every store instruction writes
 // whole granules.
 __global__ void __launch_bounds__(256)
 bulk_copy_kernel(const uint32_t *__restrict__ leaf_ids, const uint4 *__restrict__ bulk, uint32_t bulk_cap,
                  uint32_t *__restrict__ ids, Ctrl *__restrict__ ctrl) {
-    __shared__ uint32_t item;
     const uint32_t nitems = min(ctrl->bulk_n, bulk_cap);
     const uint32_t t = threadIdx.x;
-    while (true) {
-        if (t == 0) item = atomicAdd(&ctrl->bulk_taken, 1u);
-        __syncthreads();
-        const uint32_t it = item;
-        __syncthreads();
-        if (it >= nitems) break;
+    for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const uint4 d = bulk[it];
         const uint32_t *__restrict__ src = leaf_ids + d.x;
         uint32_t *__restrict__ dst = ids + (((uint64_t)d.z << 32) | d.y);
@@ -705,10 +711,14 @@ bulk_copy_kernel(const uint32_t *__restrict__ leaf_ids, const uint4 *__restrict_
 // mask), a range record copies the leaves' ids from the leaf-id array
 // (measured faster than from the leaves' own ptr arrays: fill 2.81 against
 // 4.13 ms at 10M rectangles / 1M windows, fanout 64 SoA).
-template <int LAYOUT>
+// BULK: ranges of at least kReplayBulkMin ids are deferred to the bulk copy,
+// whose blocks share them (one half-wave copying a subtree of 32K ids alone
+// takes 150 us); an instance of its own, since the branch costs the in-place
+// copies registers (10M rectangles / 1M windows: fill 2.6 -> 3.6 ms).
+template <int LAYOUT, bool BULK>
 __global__ void __launch_bounds__(256)
 replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffsets, uint32_t *__restrict__ ids,
-              uint64_t cap, Ctrl *__restrict__ ctrl) {
+              uint64_t cap, Ctrl *__restrict__ ctrl, uint4 *__restrict__ bulk, uint32_t bulk_cap) {
     __shared__ uint64_t sbase[kRecChunk], send[kRecChunk];
     __shared__ uint2 sref[kRecChunk];
     const uint32_t nchunks = ctrl->rec_nchunks;
@@ -776,6 +786,14 @@ replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffset
                     if (l == 0) atomicOr(&ctrl->err, kErrBounds);
                     continue;
                 }
+                if constexpr (BULK) {
+                    if (n >= kReplayBulkMin) {   // half-wave-uniform
+                        bool bad = false;
+                        defer_leaf_run(t, l0, l1, ids, b, send[r], l, 32, th & 32u, bulk, bulk_cap, ctrl, &bad);
+                        if (bad && l == 0) atomicOr(&ctrl->err, kErrBounds);
+                        continue;
+                    }
+                }
                 {
                     const uint32_t *__restrict__ src = t.leaf_ids + s0;
                     constexpr uint32_t RU = 8;   // 16: more registers, fill 4.2 ms
@@ -810,14 +828,21 @@ hipError_t launch_set_rec(Ctrl *ctrl, const SelectPlan &plan, hipStream_t s) {
 }
 
 hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t noffsets, uint32_t *ids,
-                         uint64_t cap, Ctrl *ctrl, hipStream_t s) {
+                         uint64_t cap, Ctrl *ctrl, const SelectPlan &plan, hipStream_t s) {
     const dim3 grid((uint32_t)num_cus() * 8), block(256);
-    if (t.layout == LAYOUT_AOS)
-        hipLaunchKernelGGL(replay_kernel<LAYOUT_AOS>, grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl);
-    else if (t.layout == LAYOUT_SOA)
-        hipLaunchKernelGGL(replay_kernel<LAYOUT_SOA>, grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl);
-    else
-        hipLaunchKernelGGL(replay_kernel<LAYOUT_D2>, grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl);
+#define RT_REPLAY(L_)                                                                                              \
+    do {                                                                                                           \
+        if (plan.bulk)                                                                                             \
+            hipLaunchKernelGGL((replay_kernel<L_, true>), grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl, \
+                               plan.bulk, plan.bulk_cap);                                                          \
+        else                                                                                                       \
+            hipLaunchKernelGGL((replay_kernel<L_, false>), grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl, \
+                               (uint4 *)nullptr, 0u);                                                              \
+    } while (0)
+    if (t.layout == LAYOUT_AOS) RT_REPLAY(LAYOUT_AOS);
+    else if (t.layout == LAYOUT_SOA) RT_REPLAY(LAYOUT_SOA);
+    else RT_REPLAY(LAYOUT_D2);
+#undef RT_REPLAY
     return hipGetLastError();
 }
 
@@ -846,9 +871,7 @@ static hipError_t launch_g(const TreeView &t, const float4 *q, uint32_t nq, uint
                            uint32_t slot, const SelectPlan &plan, uint32_t noffsets, hipStream_t s) {
     const uint32_t stack_cap = stack_bound(t.height, t.fanout);
     const uint32_t groups_per_block = 256 / G;
-    size_t smem = (size_t)groups_per_block * stack_cap * sizeof(uint32_t);
-    if (MODE == SEL_COUNT && plan.rec)   // the groups' record buffers follow the stacks, 16-byte aligned
-        smem = (smem + 15) / 16 * 16 + (size_t)groups_per_block * kRecBuf * 16;
+    const size_t smem = (size_t)groups_per_block * stack_cap * sizeof(uint32_t);
     uint64_t want = ((uint64_t)nq + groups_per_block - 1) / groups_per_block;
     uint64_t persistent = (uint64_t)num_cus() * 8;
     uint32_t blocks = (uint32_t)(want < persistent ? want : persistent);
@@ -856,10 +879,9 @@ static hipError_t launch_g(const TreeView &t, const float4 *q, uint32_t nq, uint
     blocks = (blocks + kXcds - 1) / kXcds * kXcds;   // every XCD gets blocks
     // the fill pass with deferred contained runs is an instance of its own:
     // the deferral branch costs the in-pass copies registers and time
-    // (and the recording count pass likewise)
     const bool la = MODE != SEL_STATS && t.lookahead;
-    constexpr int EXT = MODE == SEL_STATS ? 0 : 1;
-    if ((MODE == SEL_FILL && plan.bulk) || (MODE == SEL_COUNT && plan.rec)) {
+    constexpr int EXT = MODE == SEL_FILL ? 1 : 0;
+    if (MODE == SEL_FILL && plan.bulk) {
         if (la)
             hipLaunchKernelGGL((select_kernel<G, LAYOUT, MODE, 1, EXT>), dim3(blocks), dim3(256), smem, s,
                                t, q, nq, counts, offsets, ids, cap, ctrl, slot, stack_cap, plan, noffsets);
@@ -932,6 +954,65 @@ hipError_t launch_select_pass(const TreeView &t, const float4 *q, uint32_t nq, i
     default:
         return launch_l<64>(t, q, nq, mode, counts, offsets, ids, cap, ctrl, slot, plan, noffsets, s);
     }
+}
+
+template <int G, int LAYOUT, bool WIDE>
+static hipError_t launch_walk_w(const TreeView &t, const float4 *q, uint32_t nq, uint32_t *counts, Ctrl *ctrl,
+                                const SelectPlan &plan, uint2 *items, uint32_t icap, hipStream_t s) {
+    const uint32_t stack_cap = walk_stack_bound(t.height, t.fanout);
+    const uint32_t gpb = 256 / G;
+    size_t smem = (size_t)gpb * stack_cap * sizeof(uint32_t);
+    if (plan.rec) smem = (smem + 15) / 16 * 16 + (size_t)gpb * kRecBuf * 16;   // the groups' record buffers
+    const uint32_t persistent = (uint32_t)num_cus() * 8;
+    const uint64_t want = ((uint64_t)nq + gpb - 1) / gpb;
+    uint32_t blocks = (uint32_t)(want < persistent ? want : persistent);
+    blocks = (blocks + kXcds - 1) / kXcds * kXcds;   // every XCD gets blocks
+    // units per counter update: the more each group will take, the more
+    const uint64_t groups = (uint64_t)blocks * gpb;
+    const uint32_t chunk = nq >= 16 * groups ? 8u : nq >= 8 * groups ? 4u : nq >= 2 * groups ? 2u : 1u;
+    const RecArena ar{plan.rec, plan.rec_count, plan.rec_nchunks};
+    const WalkItems none{nullptr, 0, nullptr, nullptr};
+    const dim3 block(256);
+    if (!plan.rec) {
+        hipLaunchKernelGGL((walk_kernel<G, LAYOUT, false, 0, false, WIDE>), dim3(blocks), block, smem, s, t, q, nq,
+                           plan.order, counts, ctrl, chunk, stack_cap, ar, 0u, none, none);
+        return hipGetLastError();
+    }
+    if (!items) {
+        hipLaunchKernelGGL((walk_kernel<G, LAYOUT, true, 0, false, WIDE>), dim3(blocks), block, smem, s, t, q, nq,
+                           plan.order, counts, ctrl, chunk, stack_cap, ar, 0u, none, none);
+        return hipGetLastError();
+    }
+    // three launches: queries, what the large ones left, what the large
+    // subtrees among those left
+    const WalkItems a{items, icap, ctrl->hlist, ctrl->hwork[0]};
+    const WalkItems b{items + (size_t)kXcds * icap, icap, ctrl->budget_used, ctrl->hwork[1]};
+    hipLaunchKernelGGL((walk_kernel<G, LAYOUT, true, 0, true, WIDE>), dim3(blocks), block, smem, s, t, q, nq, plan.order,
+                       counts, ctrl, chunk, stack_cap, ar, kWalkBudget0, none, a);
+    hipLaunchKernelGGL((walk_kernel<G, LAYOUT, true, 1, true, WIDE>), dim3(persistent), block, smem, s, t, q, nq, plan.order,
+                       counts, ctrl, 2u, stack_cap, ar, kWalkBudget1, a, b);
+    hipLaunchKernelGGL((walk_kernel<G, LAYOUT, true, 1, false, WIDE>), dim3(persistent), block, smem, s, t, q, nq,
+                       plan.order, counts, ctrl, 2u, stack_cap, ar, 0u, b, none);
+    return hipGetLastError();
+}
+
+template <int G, int LAYOUT>
+static hipError_t launch_walk_g(const TreeView &t, const float4 *q, uint32_t nq, uint32_t *counts, Ctrl *ctrl,
+                                const SelectPlan &plan, uint2 *items, uint32_t icap, hipStream_t s) {
+    // node offsets fit 32 bits below 4 GiB of nodes
+    if ((uint64_t)t.n_nodes * t.node_bytes <= 0xFFFFFFFFull)
+        return launch_walk_w<G, LAYOUT, false>(t, q, nq, counts, ctrl, plan, items, icap, s);
+    return launch_walk_w<G, LAYOUT, true>(t, q, nq, counts, ctrl, plan, items, icap, s);
+}
+
+hipError_t launch_walk(const TreeView &t, const float4 *q, uint32_t nq, uint32_t *counts, Ctrl *ctrl,
+                       const SelectPlan &plan, uint2 *items, uint32_t items_per_list, hipStream_t s) {
+#define RT_WALK(G_, L_) launch_walk_g<G_, L_>(t, q, nq, counts, ctrl, plan, items, items_per_list, s)
+    const uint32_t G = group_width(t.fanout);
+    if (t.layout == LAYOUT_AOS) return G == 16 ? RT_WALK(16, LAYOUT_AOS) : G == 32 ? RT_WALK(32, LAYOUT_AOS) : RT_WALK(64, LAYOUT_AOS);
+    if (t.layout == LAYOUT_SOA) return G == 16 ? RT_WALK(16, LAYOUT_SOA) : G == 32 ? RT_WALK(32, LAYOUT_SOA) : RT_WALK(64, LAYOUT_SOA);
+    return G == 16 ? RT_WALK(16, LAYOUT_D2) : G == 32 ? RT_WALK(32, LAYOUT_D2) : RT_WALK(64, LAYOUT_D2);
+#undef RT_WALK
 }
 
 template <int PHASE>

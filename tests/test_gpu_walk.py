@@ -1,0 +1,79 @@
+"""The batched count walk at its edges, against the CPU oracle: trees of every
+lane-group width with partly filled groups, grids whose windows are all handed
+out by place or several per counter update, large windows that hand their
+remaining subtrees to further launches, item lists that fill up, and leaf
+ranges deferred by the replay."""
+
+import numpy as np
+import pytest
+
+import oracle
+import rtgen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rt():
+    import torch
+    assert torch.cuda.is_available(), "GPU test needs a GPU"
+    import paper_2309_16913_amd as m
+    return m
+
+
+@pytest.fixture(scope="module")
+def ora():
+    return oracle.get()
+
+
+def device_select(rt, t, q, cap, replay=True):
+    import torch
+    nq = q.shape[0]
+    dq = torch.from_numpy(q).cuda()
+    off = torch.empty(nq + 1, dtype=torch.int64, device="cuda")
+    ids = torch.full((max(cap, 1),), -1, dtype=torch.int32, device="cuda")
+    wb = (rt.select_replay_workspace_bytes if replay else rt.select_workspace_bytes)(nq, cap)
+    w = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    st = torch.zeros(2, dtype=torch.int64, device="cuda")
+    rt.range_select_device(t, dq.data_ptr(), nq, off.data_ptr(), ids.data_ptr(), cap, w.data_ptr(), wb,
+                           st.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert st.cpu().tolist() == [cap, 0]
+    return off.cpu().numpy(), ids[:cap].cpu().numpy().view(np.uint32)
+
+
+def check(rt, ora, r, q, want, fanout, layout, split, bulk="auto", replay=True):
+    print(f"case walk n={r.shape[0]} nq={q.shape[0]} F={fanout} {layout} split={split} bulk={bulk} replay={replay}",
+          flush=True)
+    t = rt.build_str(r, fanout, layout)
+    t.set_split(split)
+    t.set_bulk_copy(bulk)
+    off, ids = device_select(rt, t, q, int(want[1].size), replay)
+    assert np.array_equal(off, want[0].astype(np.int64))
+    assert np.array_equal(ids, want[1])
+    t.free()
+
+
+@pytest.mark.parametrize("fanout,layout", [(2, "soa"), (5, "aos"), (16, "d2"), (17, "soa"), (32, "aos"), (33, "d2"),
+                                           (63, "soa"), (64, "d2")])
+@pytest.mark.parametrize("nq", [1, 7, 2500, 40_000])
+def test_walk_grids(rt, ora, fanout, layout, nq):
+    r = rtgen.c2_rects(30_011)
+    q = rtgen.windows_loguniform(nq, 1e-5, 1e-2 if nq > 7 else 0.3, 31 + nq)
+    want = ora.select(ora.build_str(r, 32), q)
+    check(rt, ora, r, q, want, fanout, layout, 0)
+    check(rt, ora, r, q, want, fanout, layout, 0, replay=False)
+    check(rt, ora, r, q, want, fanout, layout, 1)
+
+
+@pytest.mark.parametrize("fanout,layout,nq", [(2, "soa", 6000), (16, "aos", 3000), (64, "soa", 600)])
+def test_walk_shared_windows(rt, ora, fanout, layout, nq):
+    """Windows large enough to be shared (6000 of them on a binary tree fill
+    the item lists), whole-space windows among them, with and without the
+    replay's deferred ranges."""
+    r = rtgen.c2_rects(25_000 if fanout == 2 else 200_000)
+    q = rtgen.windows_loguniform(nq, 3e-3, 3e-2, 77)
+    q[::97] = (-np.inf, -np.inf, np.inf, np.inf)
+    want = ora.select(ora.build_str(r, 32), q)
+    for bulk in ("off", "on"):
+        check(rt, ora, r, q, want, fanout, layout, 2, bulk)
