@@ -491,7 +491,13 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         // replay the count pass's records (a separate fill stage cannot know
         // whether its count stage made any: the replay checks); the walk then
         // runs only if there were none or they overflowed
-        if (rec || stage == 2) e = launch_replay(v, d_off, (uint32_t)nq, d_ids, cap, w.ctrl, plan, s);
+        // The records of a separate count stage lie where this stage's own
+        // layout has its sort scratch and descriptors, so the replay's
+        // descriptors then go to the item lists, which the count has consumed.
+        BulkList walked{plan.bulk, plan.bulk_cap}, replayed = walked;
+        if (stage == 2 && plan.bulk) replayed = BulkList{w.heavy, (uint32_t)split_budget(nq)};
+        if (rec || stage == 2)
+            e = launch_replay(v, d_off, (uint32_t)nq, d_ids, cap, w.ctrl, replayed.d, replayed.cap, s);
         if (!slots || stage == 2) {   // whole queries
             plan.fill_guard = rec ? FILL_UNLESS_REPLAYED
                                   : (stage == 2 ? (sc.on ? FILL_IF_OVERFLOWED : FILL_UNLESS_REPLAYED) : FILL_ALWAYS);
@@ -509,8 +515,7 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
                                        plan, (uint32_t)w.nslot_max, s);
         }
         if (e == hipSuccess && plan.bulk)
-            e = launch_bulk_copy(static_cast<const uint32_t *>(t->d_leaf_ids), plan.bulk, plan.bulk_cap, d_ids, w.ctrl,
-                                 s);
+            e = launch_bulk_copy(static_cast<const uint32_t *>(t->d_leaf_ids), replayed, walked, d_ids, w.ctrl, s);
         if (e == hipSuccess) e = mark(3);
         if (e == hipSuccess)
             e = launch_segsort(d_off, nq, d_ids, w.scratch, cap, w.lists, t->n_objects, nullptr, s);

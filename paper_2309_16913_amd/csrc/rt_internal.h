@@ -302,13 +302,20 @@ hipError_t launch_set_rec(Ctrl *ctrl, const SelectPlan &plan, hipStream_t s);
 // Replay of the count pass's records (arena named in the control words):
 // writes every recorded hit and contained leaf range at offsets[slot] +
 // position; does nothing if the count pass made no records, they overflowed,
-// or the result does not fit.  With the plan's bulk list, leaf ranges of at
-// least kReplayBulkMin ids are deferred to the bulk copy.
+// or the result does not fit.  With a list of defer_cap descriptors (NULL:
+// none; it must not lie in the record arena), leaf ranges of at least
+// kReplayBulkMin ids are deferred to the bulk copy while the list has room.
 hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t noffsets, uint32_t *ids,
-                         uint64_t ids_capacity, Ctrl *ctrl, const SelectPlan &plan, hipStream_t s);
+                         uint64_t ids_capacity, Ctrl *ctrl, uint4 *defer, uint32_t defer_cap, hipStream_t s);
 
-hipError_t launch_bulk_copy(const uint32_t *leaf_ids, const uint4 *bulk, uint32_t bulk_cap, uint32_t *ids,
-                            Ctrl *ctrl, hipStream_t s);
+// replayed / walked: the descriptor lists of a replay and of a walking fill
+// (one of the two ran).
+struct BulkList {
+    uint4 *d;
+    uint32_t cap;
+};
+hipError_t launch_bulk_copy(const uint32_t *leaf_ids, BulkList replayed, BulkList walked, uint32_t *ids, Ctrl *ctrl,
+                            hipStream_t s);
 
 // ---- scan, sort ---------------------------------------------------------
 // Exclusive scan of n uint32 into n+1 uint64 (out[n] = total).  tmp needs

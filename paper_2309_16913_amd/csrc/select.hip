@@ -672,9 +672,11 @@ split_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t sp
 // to it are written by the first lanes), so every store instruction writes
 // whole granules.
 __global__ void __launch_bounds__(256)
-bulk_copy_kernel(const uint32_t *__restrict__ leaf_ids, const uint4 *__restrict__ bulk, uint32_t bulk_cap,
-                 uint32_t *__restrict__ ids, Ctrl *__restrict__ ctrl) {
-    const uint32_t nitems = min(ctrl->bulk_n, bulk_cap);
+bulk_copy_kernel(const uint32_t *__restrict__ leaf_ids, BulkList replayed, BulkList walked,
+                 uint32_t *__restrict__ ids, const Ctrl *__restrict__ ctrl) {
+    const BulkList list = ctrl->rec_nchunks && !ctrl->rec_overflow ? replayed : walked;
+    const uint4 *__restrict__ bulk = list.d;
+    const uint32_t nitems = min(ctrl->bulk_n, list.cap);
     const uint32_t t = threadIdx.x;
     for (uint32_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const uint4 d = bulk[it];
@@ -788,10 +790,17 @@ replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffset
                 }
                 if constexpr (BULK) {
                     if (n >= kReplayBulkMin) {   // half-wave-uniform
-                        bool bad = false;
-                        defer_leaf_run(t, l0, l1, ids, b, send[r], l, 32, th & 32u, bulk, bulk_cap, ctrl, &bad);
-                        if (bad && l == 0) atomicOr(&ctrl->err, kErrBounds);
-                        continue;
+                        const uint32_t nd = (uint32_t)((n + kBulkChunk - 1) / kBulkChunk);
+                        uint32_t at = 0;
+                        if (l == 0) at = atomicAdd(&ctrl->bulk_n, nd);
+                        at = (uint32_t)__shfl((int)at, (int)(th & 32u));
+                        const bool fits = at < bulk_cap && nd <= bulk_cap - at;
+                        for (uint32_t k = l; k < nd && at + k < bulk_cap; k += 32) {   // empty ones if not all fit
+                            const uint64_t off = (uint64_t)k * kBulkChunk, dst = b + off;
+                            bulk[at + k] = make_uint4((uint32_t)(s0 + off), (uint32_t)dst, (uint32_t)(dst >> 32),
+                                                      fits ? (uint32_t)min((uint64_t)kBulkChunk, n - off) : 0u);
+                        }
+                        if (fits) continue;
                     }
                 }
                 {
@@ -828,13 +837,13 @@ hipError_t launch_set_rec(Ctrl *ctrl, const SelectPlan &plan, hipStream_t s) {
 }
 
 hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t noffsets, uint32_t *ids,
-                         uint64_t cap, Ctrl *ctrl, const SelectPlan &plan, hipStream_t s) {
+                         uint64_t cap, Ctrl *ctrl, uint4 *defer, uint32_t defer_cap, hipStream_t s) {
     const dim3 grid((uint32_t)num_cus() * 8), block(256);
 #define RT_REPLAY(L_)                                                                                              \
     do {                                                                                                           \
-        if (plan.bulk)                                                                                             \
+        if (defer)                                                                                                 \
             hipLaunchKernelGGL((replay_kernel<L_, true>), grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl, \
-                               plan.bulk, plan.bulk_cap);                                                          \
+                               defer, defer_cap);                                                                  \
         else                                                                                                       \
             hipLaunchKernelGGL((replay_kernel<L_, false>), grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl, \
                                (uint4 *)nullptr, 0u);                                                              \
@@ -846,9 +855,9 @@ hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t no
     return hipGetLastError();
 }
 
-hipError_t launch_bulk_copy(const uint32_t *leaf_ids, const uint4 *bulk, uint32_t bulk_cap, uint32_t *ids, Ctrl *ctrl,
+hipError_t launch_bulk_copy(const uint32_t *leaf_ids, BulkList replayed, BulkList walked, uint32_t *ids, Ctrl *ctrl,
                             hipStream_t s) {
-    hipLaunchKernelGGL(bulk_copy_kernel, dim3((uint32_t)num_cus() * 8), dim3(256), 0, s, leaf_ids, bulk, bulk_cap,
+    hipLaunchKernelGGL(bulk_copy_kernel, dim3((uint32_t)num_cus() * 8), dim3(256), 0, s, leaf_ids, replayed, walked,
                        ids, ctrl);
     return hipGetLastError();
 }

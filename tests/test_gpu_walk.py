@@ -77,3 +77,34 @@ def test_walk_shared_windows(rt, ora, fanout, layout, nq):
     want = ora.select(ora.build_str(r, 32), q)
     for bulk in ("off", "on"):
         check(rt, ora, r, q, want, fanout, layout, 2, bulk)
+
+
+@pytest.mark.parametrize("nq,big", [(100, 1), (3, 3), (2000, 40)])
+def test_two_stage_deferred_ranges(rt, ora, nq, big):
+    """Two-stage select whose records (a chunk per lane group) reach past the
+    few ids' sort scratch into the fill stage's own layout while the replay
+    defers long leaf ranges: the descriptors must not land on the records."""
+    import torch
+    r = rtgen.c2_rects(200_000)
+    q = rtgen.windows_loguniform(nq, 1e-8, 1e-7, 61)
+    q[:big] = (-0.5, -0.5, 0.45, 1.5)
+    wo, wi = ora.select(ora.build_str(r, 32), q)
+    total = int(wo[-1])
+    t = rt.build_str(r, 16, "soa")
+    t.set_bulk_copy("on")
+    wb = rt.select_replay_workspace_bytes(nq, 4 * total)
+    work = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    dq = torch.from_numpy(q).cuda()
+    off = torch.empty(nq + 1, dtype=torch.int64, device="cuda")
+    ids = torch.full((total,), -1, dtype=torch.int32, device="cuda")
+    st = torch.zeros(2, dtype=torch.int64, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    rt.range_select_device_count(t, dq.data_ptr(), nq, off.data_ptr(), work.data_ptr(), wb, s)
+    rt.range_select_device_fill(t, dq.data_ptr(), nq, off.data_ptr(), ids.data_ptr(), total, work.data_ptr(), wb,
+                                st.data_ptr(), s)
+    torch.cuda.synchronize()
+    assert st.cpu().tolist() == [total, 0]
+    chunks, over = rt.select_replay_info(work.data_ptr())
+    assert chunks > 0 and not over
+    assert np.array_equal(off.cpu().numpy(), wo.astype(np.int64))
+    assert np.array_equal(ids.cpu().numpy().view(np.uint32), wi)
