@@ -109,10 +109,10 @@ static hipError_t enqueue_all(rt_batch *b, hipStream_t s) {
     if (e == hipSuccess)
         e = launch_segsort(static_cast<uint64_t *>(b->d_off), b->total_q, static_cast<uint32_t *>(b->d_ids),
                            static_cast<uint32_t *>(b->d_scratch), b->cap, static_cast<uint32_t *>(b->d_lists),
-                           b->id_range, static_cast<const uint32_t *>(b->d_qrange), s);
-    if (e == hipSuccess)
-        e = launch_finalize(static_cast<uint64_t *>(b->d_off), b->total_q, b->cap, ctrl,
-                            static_cast<uint64_t *>(b->d_status), s);
+                           b->id_range, static_cast<const uint32_t *>(b->d_qrange), false, ctrl,
+                           static_cast<uint64_t *>(b->d_status), s);
+    if (e == hipSuccess && b->total_q == 0)
+        e = launch_finalize(static_cast<uint64_t *>(b->d_off), 0, b->cap, ctrl, static_cast<uint64_t *>(b->d_status), s);
     return e;
 }
 
@@ -390,7 +390,7 @@ extern "C" int rt_batch_run_plain(rt_batch *b, void *stream) {
                                    (uint32_t)n, s);
         if (e == hipSuccess)
             e = launch_segsort(off, n, ids + base, scratch + base, cap, static_cast<uint32_t *>(b->d_lists),
-                               b->trees[i]->n_objects, nullptr, s);
+                               b->trees[i]->n_objects, nullptr, false, nullptr, nullptr, s);
     }
     return e == hipSuccess ? RT_OK : hip_fail(e, "plain batch launches");
 }

@@ -1,5 +1,6 @@
 // C-ABI entry points: validation, device memory, the launch sequences of a
 // range select and of a join, result copies, and the tagged rt_free.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -180,10 +181,17 @@ static uint64_t sel_ws_bytes(uint64_t nq, uint64_t cap) {
 // (a node's records never straddle two chunks), and one chunk per lane group
 // that can hold a partly used one at the end of the pass; a count pass that
 // needs more sets the overflow flag and the fill walks the tree instead.
+// Small results get the chunks that cannot run out: a record has at least one
+// id, a chunk is closed with at most kRecBuf - 1 records free, and each
+// window's group may hold a partly used one.
+static uint64_t rec_chunks_sure(uint64_t nq, uint64_t cap) { return cap / (kRecChunk - kRecBuf + 1) + nq + 1; }
+constexpr uint64_t kRecSureIds = 65536;
+
 uint64_t rtk::rec_arena_bytes(uint64_t nq, uint64_t cap) {
     const uint64_t recs = (cap / 16 + 16 * nq) * 4 / 3;
     const uint64_t groups = (uint64_t)num_cus() * 8 * 16;
-    const uint64_t chunks = (recs + kRecChunk - 1) / kRecChunk + (nq < groups ? nq : groups);
+    uint64_t chunks = (recs + kRecChunk - 1) / kRecChunk + (nq < groups ? nq : groups);
+    if (cap <= kRecSureIds && nq <= groups) chunks = std::max(chunks, rec_chunks_sure(nq, cap));
     return align256(16 * kRecChunk * chunks) + align256(4 * chunks) + 512;
 }
 
@@ -442,11 +450,12 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
     };
     if (stage & 1) {   // count stage: ctrl, order, split, count pass, offsets
         uint32_t *counts = d_counts_out ? d_counts_out : (slots ? w.slot_counts : w.counts);
-        e = launch_zero(w.ctrl, sizeof(Ctrl), s);
-        if (e == hipSuccess && rec) e = launch_set_rec(w.ctrl, plan, s);
+        const bool ordered = nq >= kOrderMinQueries;
+        e = launch_select_init(w.ctrl, plan, w.lists, kSortCounters, static_cast<uint32_t *>(w.order),
+                               ordered ? kOrderCells : 0u, s);
         if (e == hipSuccess) e = mark(0);
-        const uint64_t *order = nullptr;
-        if (e == hipSuccess && nq >= kOrderMinQueries)
+        const uint32_t *order = nullptr;
+        if (e == hipSuccess && ordered)
             e = launch_query_order(dq, (uint32_t)nq, t->mbr, w.order, &order, s);
         plan.order = order;
         if (slots) {
@@ -497,8 +506,12 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         BulkList walked{plan.bulk, plan.bulk_cap}, replayed = walked;
         if (stage == 2 && plan.bulk) replayed = BulkList{w.heavy, (uint32_t)split_budget(nq)};
         if (rec || stage == 2)
-            e = launch_replay(v, d_off, (uint32_t)nq, d_ids, cap, w.ctrl, replayed.d, replayed.cap, s);
-        if (!slots || stage == 2) {   // whole queries
+            e = launch_replay(v, d_off, (uint32_t)nq, d_ids, cap, w.ctrl, replayed.d, replayed.cap,
+                              rec ? rec_nchunks : 0xFFFFFFFFu, s);
+        // an arena that holds a result of cap ids whatever its records cannot
+        // overflow for one that is written at all
+        const bool sure = rec && !sc.on && rec_nchunks >= rec_chunks_sure(nq, cap);
+        if ((!slots || stage == 2) && !sure) {   // whole queries
             plan.fill_guard = rec ? FILL_UNLESS_REPLAYED
                                   : (stage == 2 ? (sc.on ? FILL_IF_OVERFLOWED : FILL_UNLESS_REPLAYED) : FILL_ALWAYS);
             plan.slot_first = nullptr;
@@ -518,9 +531,9 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
             e = launch_bulk_copy(static_cast<const uint32_t *>(t->d_leaf_ids), replayed, walked, d_ids, w.ctrl, s);
         if (e == hipSuccess) e = mark(3);
         if (e == hipSuccess)
-            e = launch_segsort(d_off, nq, d_ids, w.scratch, cap, w.lists, t->n_objects, nullptr, s);
+            e = launch_segsort(d_off, nq, d_ids, w.scratch, cap, w.lists, t->n_objects, nullptr, true, w.ctrl,
+                               d_status, s);
         if (e == hipSuccess) e = mark(4);
-        if (e == hipSuccess && d_status) e = launch_finalize(d_off, nq, cap, w.ctrl, d_status, s);
         if (e != hipSuccess) return hip_fail(e, "fill stage");
     }
     return RT_OK;

@@ -141,6 +141,14 @@ struct Ctrl {
     uint32_t budget_used[kXcds][32]; // items granted per list
 };
 
+// The status words of a select: [0] = total ids, [1] = flags.
+__device__ __forceinline__ void select_status(const uint64_t *offsets, uint64_t nq, uint64_t cap, const Ctrl *ctrl,
+                                              uint64_t *status) {
+    const uint64_t tot = offsets[nq];
+    status[0] = tot;
+    status[1] = (tot > cap ? 1u : 0u) | (ctrl->err ? 2u : 0u);
+}
+
 constexpr uint32_t kErrStack = 1u;     // traversal stack would overflow
 constexpr uint32_t kErrBounds = 2u;    // an output write would fall outside its range
 constexpr uint32_t kErrInput = 4u;     // invalid rectangle found on the device
@@ -214,8 +222,8 @@ inline uint32_t group_width(uint32_t fanout) {
 enum SelectMode : int { SEL_COUNT = 0, SEL_FILL = 1, SEL_STATS = 2 };
 
 // How a traversal pass finds its work.
-//   order       NULL or nq 64-bit keys whose low 32 bits list the queries in
-//               processing order; XCD x takes the x-th eighth first.
+//   order       NULL or the nq queries in processing order; XCD x takes the
+//               x-th eighth first.
 //   slot_first  NULL (query q writes output slot q) or nq+1 offsets: query q
 //               owns slots [slot_first[q], slot_first[q+1]).
 //   heavy       split work items {query, subtree root, slot, 0} in kXcds
@@ -223,7 +231,7 @@ enum SelectMode : int { SEL_COUNT = 0, SEL_FILL = 1, SEL_STATS = 2 };
 //               length in Ctrl::hlist[x]); handed out before whole queries,
 //               XCD x draining list x first.
 struct SelectPlan {
-    const uint64_t *order = nullptr;
+    const uint32_t *order = nullptr;
     const uint64_t *slot_first = nullptr;
     const uint4 *heavy = nullptr;
     uint32_t hcap = 0;
@@ -280,33 +288,36 @@ hipError_t launch_walk(const TreeView &t, const float4 *q, uint32_t nq, uint32_t
 // hcap: items per list (the budget of each list).
 hipError_t launch_split(const TreeView &t, const float4 *q, uint32_t nq, int phase, uint32_t split_parent,
                         uint32_t kmin, uint32_t hcap, float min_area, uint32_t *nslots,
-                        const uint64_t *slot_first, uint4 *heavy, const uint64_t *order, Ctrl *ctrl,
+                        const uint64_t *slot_first, uint4 *heavy, const uint32_t *order, Ctrl *ctrl,
                         hipStream_t s);
 hipError_t launch_gather_offsets(const uint64_t *slot_first, const uint64_t *slot_off, uint32_t nq,
                                  uint64_t *offsets, hipStream_t s);
 
-// Query order for locality: 64-bit keys (Morton code of the window center
-// over the tree's MBR) << 32 | query index, sorted.  tmp: 2*nq uint64 plus
-// radix temporaries (order_ws_bytes).  *sorted receives the sorted keys.
+// Query order for locality: the queries by the cell of their window center on
+// a 64 x 64 grid over the tree's MBR, cells in Morton order (the order inside
+// a cell is arbitrary).  ws: order_ws_bytes(nq), its first kOrderCells words
+// zero.  Returns the order's place in ws through *order (which depends on nq
+// only).
+constexpr uint32_t kOrderCells = 4096;
 uint64_t order_ws_bytes(uint64_t nq);
-const uint64_t *query_order_result(const void *ws, uint64_t nq);   // where the sorted keys end up
-hipError_t launch_query_order(const float4 *q, uint32_t nq, const float *mbr, void *ws,
-                              const uint64_t **sorted, hipStream_t s);
+const uint32_t *query_order_result(const void *ws, uint64_t nq);
+hipError_t launch_query_order(const float4 *q, uint32_t nq, const float *mbr, void *ws, const uint32_t **order,
+                              hipStream_t s);
 constexpr uint32_t kOrderMinQueries = 8192;   // smaller batches keep input order
 
 // Bulk copy of the long contained runs a fill pass deferred (descriptors in
 // bulk[0 .. min(ctrl->bulk_n, bulk_cap))) into ids: persistent grid, one block
 // per descriptor at a time.  Enqueue right after that fill pass.
-// Store the plan's record arena in the control words (after they are zeroed).
-hipError_t launch_set_rec(Ctrl *ctrl, const SelectPlan &plan, hipStream_t s);
 // Replay of the count pass's records (arena named in the control words):
 // writes every recorded hit and contained leaf range at offsets[slot] +
 // position; does nothing if the count pass made no records, they overflowed,
 // or the result does not fit.  With a list of defer_cap descriptors (NULL:
 // none; it must not lie in the record arena), leaf ranges of at least
 // kReplayBulkMin ids are deferred to the bulk copy while the list has room.
+// max_chunks: bound of the arena's chunks (sizes the grid).
 hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t noffsets, uint32_t *ids,
-                         uint64_t ids_capacity, Ctrl *ctrl, uint4 *defer, uint32_t defer_cap, hipStream_t s);
+                         uint64_t ids_capacity, Ctrl *ctrl, uint4 *defer, uint32_t defer_cap, uint32_t max_chunks,
+                         hipStream_t s);
 
 // replayed / walked: the descriptor lists of a replay and of a walking fill
 // (one of the two ran).
@@ -335,12 +346,15 @@ hipError_t launch_scan_u32_dev(const uint32_t *in, const uint64_t *n_dev, uint64
 // segsort_ws_elems(nq) uint32;
 // id_range: every id is below it (the object count); seg_range (NULL, or nq
 // entries): the bound of each segment's ids when segments come from trees of
-// different sizes.  Skips all work if offsets[nq] > capacity.
+// different sizes.  Skips all work if offsets[nq] > capacity.  zeroed: the
+// first kSortCounters words of ws are zero already.  status (NULL: none): the
+// select's status words, written before the sort (ctrl: its control words).
+constexpr uint32_t kSortCounters = 64;
 uint64_t segsort_ws_elems(uint64_t nq);
 uint64_t segsort_scratch_elems(uint64_t capacity);
 hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, uint32_t *scratch,
                           uint64_t capacity, uint32_t *ws, uint64_t id_range, const uint32_t *seg_range,
-                          hipStream_t s);
+                          bool zeroed, const Ctrl *ctrl, uint64_t *status, hipStream_t s);
 inline int id_bits_for(uint64_t n_objects) {
     int b = 0;
     const uint64_t m = n_objects ? n_objects - 1 : 0;
@@ -362,6 +376,10 @@ hipError_t launch_finalize(const uint64_t *offsets, uint64_t nq, uint64_t capaci
                            const Ctrl *ctrl, uint64_t *status, hipStream_t s);
 
 hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t s);
+// Zero the control words and name the plan's record arena in them; clear na
+// words at a and nb at b.
+hipError_t launch_select_init(Ctrl *ctrl, const SelectPlan &plan, uint32_t *a, uint32_t na, uint32_t *b, uint32_t nb,
+                              hipStream_t s);
 
 // ---- join ---------------------------------------------------------------
 enum JoinMode : int { JOIN_BOTH = 0, JOIN_EMIT = 1, JOIN_DESC_A = 2, JOIN_DESC_B = 3 };

@@ -1,8 +1,8 @@
 // Prefix sums and sorts used to compact and canonicalize results.
 //
-//  * exclusive scan uint32 -> uint64 (counts -> CSR offsets), three kernels:
-//    per-tile sums, a scan of the tile sums, and the per-tile scan with the
-//    tile's base added;
+//  * exclusive scan uint32 -> uint64 (counts -> CSR offsets): one block up to
+//    8192 elements; up to 4096 tiles, per-tile sums and a per-tile scan whose
+//    blocks add the sums before them; beyond that the sums are scanned first;
 //  * LSD radix sort of uint64 keys with 8-bit digits (join pairs), stable
 //    per-tile ranking with wave ballots.
 #include "rt_internal.h"
@@ -24,16 +24,17 @@ __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v) {
     return v;
 }
 
-// Exclusive scan over the 256 threads of a block; returns the exclusive
+// Exclusive scan over the T threads of a block; returns the exclusive
 // prefix and writes the block total to *total.
+template <int T = 256>
 __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t *total) {
-    __shared__ uint64_t wsum[4];
+    __shared__ uint64_t wsum[T / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint64_t inc = wave_incl_scan(v);
     if (lane == 63) wsum[w] = inc;
     __syncthreads();
     uint64_t base = 0, tot = 0;
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < T / 64; ++i) {
         if (i < w) base += wsum[i];
         tot += wsum[i];
     }
@@ -77,7 +78,19 @@ __global__ void __launch_bounds__(256) scan_sums(uint64_t *__restrict__ sums, ui
 
 // With n_dev, the block holding element n - 1 (block 0 for n = 0) writes
 // out[n]; with next (not NULL) it also stores min(total, next_cap) there and
-// sets *over when the total exceeds next_cap.
+// sets *over when the total exceeds next_cap.  RAW: sums holds the tiles' own
+// sums, and each block adds those before its tile itself (a few thousand
+// cached words at most: cheaper than a launch between the two).
+__device__ __forceinline__ void scan_total(uint64_t total, uint64_t n, uint64_t *out, uint64_t *next,
+                                           uint64_t next_cap, uint32_t *over) {
+    out[n] = total;
+    if (next) {
+        next[0] = total < next_cap ? total : next_cap;
+        if (total > next_cap) atomicOr(over, 1u);
+    }
+}
+
+template <bool RAW>
 __global__ void __launch_bounds__(256) scan_tiles(const uint32_t *__restrict__ in, uint64_t n,
                                                   const uint64_t *__restrict__ n_dev,
                                                   const uint64_t *__restrict__ sums,
@@ -86,6 +99,41 @@ __global__ void __launch_bounds__(256) scan_tiles(const uint32_t *__restrict__ i
     const bool dev = n_dev != nullptr;
     if (dev) n = min(n, *n_dev);
     const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanPer;
+    const uint64_t last = dev ? (n ? (n - 1) / kScanTile : 0) : gridDim.x - 1;
+    if (RAW && blockIdx.x > last) return;
+    uint32_t v[kScanPer];
+    uint64_t s = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kScanPer; ++k) {
+        v[k] = base + k < n ? in[base + k] : 0u;
+        s += v[k];
+    }
+    uint64_t before;
+    if constexpr (RAW) {
+        uint64_t p = 0;
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 256) p += sums[i];
+        block_excl_scan(p, &before);
+    } else {
+        before = sums[blockIdx.x];
+    }
+    uint64_t tot;
+    uint64_t run = block_excl_scan(s, &tot) + before;
+#pragma unroll
+    for (uint32_t k = 0; k < kScanPer; ++k) {
+        if (base + k < n) out[base + k] = run;
+        run += v[k];
+    }
+    if (blockIdx.x == last && threadIdx.x == 255) scan_total(before + tot, n, out, next, next_cap, over);
+}
+
+// The whole scan in one block.
+constexpr uint32_t kScanOne = 1024 * kScanPer;
+__global__ void __launch_bounds__(1024) scan_one(const uint32_t *__restrict__ in, uint64_t n,
+                                                 const uint64_t *__restrict__ n_dev, uint64_t *__restrict__ out,
+                                                 uint64_t *__restrict__ next, uint64_t next_cap,
+                                                 uint32_t *__restrict__ over) {
+    if (n_dev) n = min(n, *n_dev);
+    const uint32_t base = threadIdx.x * kScanPer;
     uint32_t v[kScanPer];
     uint64_t s = 0;
 #pragma unroll
@@ -94,21 +142,13 @@ __global__ void __launch_bounds__(256) scan_tiles(const uint32_t *__restrict__ i
         s += v[k];
     }
     uint64_t tot;
-    uint64_t run = block_excl_scan(s, &tot) + sums[blockIdx.x];
+    uint64_t run = block_excl_scan<1024>(s, &tot);
 #pragma unroll
     for (uint32_t k = 0; k < kScanPer; ++k) {
         if (base + k < n) out[base + k] = run;
         run += v[k];
     }
-    const uint64_t last = dev ? (n ? (n - 1) / kScanTile : 0) : gridDim.x - 1;
-    if (blockIdx.x == last && threadIdx.x == 255) {
-        const uint64_t total = sums[blockIdx.x] + tot;
-        out[n] = total;
-        if (next) {
-            next[0] = total < next_cap ? total : next_cap;
-            if (total > next_cap) atomicOr(over, 1u);
-        }
-    }
+    if (threadIdx.x == 0) scan_total(tot, n, out, next, next_cap, over);
 }
 
 __global__ void write_zero_total(uint64_t *out) { out[0] = 0; }
@@ -116,27 +156,33 @@ __global__ void write_zero_total(uint64_t *out) { out[0] = 0; }
 uint64_t scan_tmp_elems(uint64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
 uint64_t scan_tile_elems() { return kScanTile; }
 
+constexpr uint64_t kScanRawTiles = 4096;   // most tiles whose sums every block adds up itself
+
+hipError_t launch_scan_u32_dev(const uint32_t *in, const uint64_t *n_dev, uint64_t n_max, uint64_t *out,
+                               uint64_t *tmp, uint64_t *next, uint64_t next_cap, uint32_t *over, hipStream_t s) {
+    const uint64_t nt = n_max ? (n_max + kScanTile - 1) / kScanTile : 1;
+    if (n_max <= kScanOne) {
+        hipLaunchKernelGGL(scan_one, dim3(1), dim3(1024), 0, s, in, n_max, n_dev, out, next, next_cap, over);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(scan_tile_sums, dim3((uint32_t)nt), dim3(256), 0, s, in, n_max, n_dev, tmp);
+    if (nt <= kScanRawTiles) {
+        hipLaunchKernelGGL(scan_tiles<true>, dim3((uint32_t)nt), dim3(256), 0, s, in, n_max, n_dev, tmp, out, next,
+                           next_cap, over);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(scan_sums, dim3(1), dim3(256), 0, s, tmp, nt);
+    hipLaunchKernelGGL(scan_tiles<false>, dim3((uint32_t)nt), dim3(256), 0, s, in, n_max, n_dev, tmp, out, next,
+                       next_cap, over);
+    return hipGetLastError();
+}
+
 hipError_t launch_scan_u32(const uint32_t *in, uint64_t n, uint64_t *out, uint64_t *tmp, hipStream_t s) {
     if (n == 0) {
         hipLaunchKernelGGL(write_zero_total, dim3(1), dim3(1), 0, s, out);
         return hipGetLastError();
     }
-    const uint64_t nt = (n + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(scan_tile_sums, dim3((uint32_t)nt), dim3(256), 0, s, in, n, (const uint64_t *)nullptr, tmp);
-    hipLaunchKernelGGL(scan_sums, dim3(1), dim3(256), 0, s, tmp, nt);
-    hipLaunchKernelGGL(scan_tiles, dim3((uint32_t)nt), dim3(256), 0, s, in, n, (const uint64_t *)nullptr, tmp, out,
-                       (uint64_t *)nullptr, (uint64_t)0, (uint32_t *)nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_scan_u32_dev(const uint32_t *in, const uint64_t *n_dev, uint64_t n_max, uint64_t *out,
-                               uint64_t *tmp, uint64_t *next, uint64_t next_cap, uint32_t *over, hipStream_t s) {
-    const uint64_t nt = n_max ? (n_max + kScanTile - 1) / kScanTile : 1;
-    hipLaunchKernelGGL(scan_tile_sums, dim3((uint32_t)nt), dim3(256), 0, s, in, n_max, n_dev, tmp);
-    hipLaunchKernelGGL(scan_sums, dim3(1), dim3(256), 0, s, tmp, nt);
-    hipLaunchKernelGGL(scan_tiles, dim3((uint32_t)nt), dim3(256), 0, s, in, n_max, n_dev, tmp, out, next, next_cap,
-                       over);
-    return hipGetLastError();
+    return launch_scan_u32_dev(in, nullptr, n, out, tmp, nullptr, 0, nullptr, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -159,12 +205,41 @@ hipError_t launch_zero(void *p, uint64_t bytes, hipStream_t s) {
 
 __global__ void finalize_kernel(const uint64_t *offsets, uint64_t nq, uint64_t cap, const Ctrl *ctrl,
                                 uint64_t *status) {
-    const uint64_t tot = offsets[nq];
-    uint64_t flags = 0;
-    if (tot > cap) flags |= 1;
-    if (ctrl->err) flags |= 2;
-    status[0] = tot;
-    status[1] = flags;
+    select_status(offsets, nq, cap, ctrl, status);
+}
+
+// Start of a select: control words zeroed and the record arena named in them,
+// and two more arrays of words cleared, in one launch.
+__global__ void select_init_kernel(Ctrl *ctrl, uint4 *rec, uint32_t *rec_count, uint32_t rec_nchunks, uint32_t *a,
+                                   uint32_t na, uint32_t *b, uint32_t nb) {
+    constexpr uint32_t nc = sizeof(Ctrl) / 4;
+    constexpr uint32_t r0 = offsetof(Ctrl, rec_nchunks) / 4, r1 = offsetof(Ctrl, rec_base) / 4,
+                       r2 = offsetof(Ctrl, rec_count) / 4;
+    uint32_t *c = reinterpret_cast<uint32_t *>(ctrl);
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nc + na + nb; i += gridDim.x * blockDim.x) {
+        if (i < nc) {
+            const uint64_t base = reinterpret_cast<uint64_t>(rec), cnt = reinterpret_cast<uint64_t>(rec_count);
+            uint32_t v = 0;
+            if (i == r0) v = rec_nchunks;
+            if (i == r1) v = (uint32_t)base;
+            if (i == r1 + 1) v = (uint32_t)(base >> 32);
+            if (i == r2) v = (uint32_t)cnt;
+            if (i == r2 + 1) v = (uint32_t)(cnt >> 32);
+            c[i] = v;
+        } else if (i < nc + na) {
+            a[i - nc] = 0u;
+        } else {
+            b[i - nc - na] = 0u;
+        }
+    }
+}
+
+hipError_t launch_select_init(Ctrl *ctrl, const SelectPlan &plan, uint32_t *a, uint32_t na, uint32_t *b, uint32_t nb,
+                              hipStream_t s) {
+    const uint32_t n = sizeof(Ctrl) / 4 + na + nb;
+    hipLaunchKernelGGL(select_init_kernel, dim3((n + 1023) / 1024), dim3(1024), 0, s, ctrl, plan.rec, plan.rec_count,
+                       plan.rec_nchunks, a, na, b, nb);
+    return hipGetLastError();
 }
 
 hipError_t launch_finalize(const uint64_t *offsets, uint64_t nq, uint64_t cap, const Ctrl *ctrl,

@@ -26,6 +26,8 @@
 //              LDS (class M) or, for class L with a sub-bucket over 32768 ids,
 //              by sorting 16384-id tiles that way and merging runs pairwise
 //              through LDS-staged merge-path windows.
+#include <algorithm>
+
 #include "rt_internal.h"
 
 namespace rtk {
@@ -124,23 +126,24 @@ __device__ void block_bitonic(uint32_t *a, uint32_t P) {
 // ---------------------------------------------------------------------------
 // classify
 // ---------------------------------------------------------------------------
-constexpr uint32_t kClsPer = 16;                   // queries per thread
-constexpr uint32_t kClsTile = 256 * kClsPer;       // queries per block
-
+// PER queries per thread: 16 for large batches (fewer list reservations), 2
+// where 16 would leave most CUs idle (50k queries: 17.5 -> 6 us).
+template <uint32_t PER>
 __global__ void __launch_bounds__(256)
 seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, uint32_t *__restrict__ lists,
-             uint32_t *__restrict__ counts) {
+             uint32_t *__restrict__ counts, const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
     __shared__ uint32_t bcnt[kNumCls], gbase[kNumCls];
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) select_status(offsets, nq, cap, ctrl, status);
     if (offsets[nq] > cap) return;
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
     if (threadIdx.x < kNumCls) bcnt[threadIdx.x] = 0;
     __syncthreads();
-    const uint64_t q0 = (uint64_t)blockIdx.x * kClsTile;
-    int cls[kClsPer];
-    uint32_t pos[kClsPer];
+    const uint64_t q0 = (uint64_t)blockIdx.x * (256 * PER);
+    int cls[PER];
+    uint32_t pos[PER];
 #pragma unroll
-    for (uint32_t k = 0; k < kClsPer; ++k) {
+    for (uint32_t k = 0; k < PER; ++k) {
         const uint64_t q = q0 + (uint64_t)k * 256 + threadIdx.x;
         int c = -1;
         if (q < nq) {
@@ -166,7 +169,7 @@ seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, ui
         gbase[threadIdx.x] = bcnt[threadIdx.x] ? atomicAdd(&counts[threadIdx.x], bcnt[threadIdx.x]) : 0u;
     __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < kClsPer; ++k) {
+    for (uint32_t k = 0; k < PER; ++k) {
         const int c = cls[k];
         if (c >= 0) lists[(uint64_t)c * nq + gbase[c] + pos[k]] = (uint32_t)(q0 + (uint64_t)k * 256 + threadIdx.x);
     }
@@ -799,25 +802,17 @@ segsort_sub(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, co
 // ---------------------------------------------------------------------------
 // fallback for long segments with skewed ids: sorted tiles + pairwise merges
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024)
-segsort_tiles(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ list,
-              const uint32_t *__restrict__ list_count) {
-    __shared__ uint32_t buf[kTileMax];
-    const uint32_t m = *list_count;
-    for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
-        const uint32_t q = list[li];
-        const uint64_t o = offsets[q];
-        const uint64_t c = offsets[q + 1] - o;
-        for (uint64_t t0 = 0; t0 < c; t0 += kTileMax) {
-            const uint32_t tc = (uint32_t)((c - t0) < kTileMax ? (c - t0) : kTileMax);
-            uint32_t P = 1;
-            while (P < tc) P <<= 1;
-            for (uint32_t i = threadIdx.x; i < P; i += 1024) buf[i] = i < tc ? ids[o + t0 + i] : kKeyPad;
-            __syncthreads();
-            block_bitonic(buf, P);
-            for (uint32_t i = threadIdx.x; i < tc; i += 1024) ids[o + t0 + i] = buf[i];
-            __syncthreads();
-        }
+// Sort the 16384-id tiles of a segment in place (buf: kTileMax words of LDS).
+__device__ void sort_tiles(uint32_t *seg, uint64_t c, uint32_t *buf) {
+    for (uint64_t t0 = 0; t0 < c; t0 += kTileMax) {
+        const uint32_t tc = (uint32_t)((c - t0) < kTileMax ? (c - t0) : kTileMax);
+        uint32_t P = 1;
+        while (P < tc) P <<= 1;
+        for (uint32_t i = threadIdx.x; i < P; i += 1024) buf[i] = i < tc ? seg[t0 + i] : kKeyPad;
+        __syncthreads();
+        block_bitonic(buf, P);
+        for (uint32_t i = threadIdx.x; i < tc; i += 1024) seg[t0 + i] = buf[i];
+        __syncthreads();
     }
 }
 
@@ -851,11 +846,11 @@ __device__ __forceinline__ uint64_t glb_merge_path(const uint32_t *a, uint64_t l
     return lo;
 }
 
-// Merge the sorted 16384-id runs of each listed segment pairwise until one
-// run is left; every merge proceeds in windows of 16384 outputs whose inputs
-// are staged in LDS.
+// Each listed segment: its 16384-id tiles sorted, then the runs merged
+// pairwise until one is left; every merge proceeds in windows of 16384 outputs
+// whose inputs are staged in LDS.
 __global__ void __launch_bounds__(1024)
-segmerge_long(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, uint32_t *__restrict__ scratch,
+segsort_skewed(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, uint32_t *__restrict__ scratch,
               const uint32_t *__restrict__ list, const uint32_t *__restrict__ list_count) {
     constexpr uint32_t T = 1024, K = 16, N = T * K;
     __shared__ uint32_t lds[N + N / 32];
@@ -866,6 +861,7 @@ segmerge_long(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, 
         const uint64_t o = offsets[q];
         const uint64_t c = offsets[q + 1] - o;
         uint32_t *src = ids + o, *dst = scratch + o;
+        sort_tiles(src, c, lds);
         for (uint64_t w = kTileMax; w < c; w <<= 1) {
             for (uint64_t r0 = 0; r0 < c; r0 += 2 * w) {
                 const uint64_t la = (c - r0) < w ? (c - r0) : w;
@@ -928,7 +924,49 @@ segmerge_long(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, 
     }
 }
 
-uint64_t segsort_ws_elems(uint64_t nq) { return (uint64_t)kListCls * nq + 64; }
+// Batches of at most kFewMax segments: one block per segment sorts it if it
+// has at most 4096 ids and lists it for the longer shapes otherwise, so that a
+// small select needs no classification pass and one launch where its ids are
+// few (each launch costs a small call about 3 us).
+constexpr uint32_t kFewMax = 2048;
+constexpr uint32_t kFewIds = 4096;
+
+__global__ void __launch_bounds__(256, 6)
+segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uint32_t *__restrict__ ids,
+            uint32_t *__restrict__ lists, uint32_t *__restrict__ counts, uint32_t id_range,
+            const uint32_t *__restrict__ seg_range, const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
+    constexpr uint32_t T = 256, K = 16, N = T * K;
+    static_assert(N == kFewIds, "one tile per segment");
+    __shared__ uint32_t lds[N + N / 4];
+    const uint32_t q = blockIdx.x;
+    if (status && q == 0 && threadIdx.x == 0) select_status(offsets, nq, cap, ctrl, status);
+    const uint64_t o = offsets[q], len = offsets[q + 1] - o;
+    if (len < 2 || offsets[nq] > cap) return;
+    if (len > kFewIds) {
+        if (threadIdx.x == 0) {
+            const uint32_t j = len <= kMidMax ? 4u : kLong;
+            lists[(uint64_t)j * nq + atomicAdd(&counts[j], 1u)] = q;
+        }
+        return;
+    }
+    const uint32_t c = (uint32_t)len;
+    if (c <= 256) {
+        if (threadIdx.x >= 64) return;   // no barrier below
+        uint32_t v[4];
+#pragma unroll
+        for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t k = r * 64 + threadIdx.x;
+            v[r] = k < c ? ids[o + k] : kKeyPad;
+        }
+        wave_sort_regs4(v, ids + o, c);
+        return;
+    }
+    uint32_t key[K];
+    load_keys<T, K>(ids + o, c, key);
+    block_sort_keys<T, K, false, 4>(key, ids + o, c, seg_id_range(seg_range, q, id_range), lds, lds + N, lds);
+}
+
+uint64_t segsort_ws_elems(uint64_t nq) { return (uint64_t)kListCls * nq + kSortCounters; }
 
 // cap ids, then for each possible class-L segment (> kMidMax ids) its
 // descriptor, then two lists with room for 256 work items per segment
@@ -944,11 +982,12 @@ static uint32_t resident_per_cu(Kern kern, int threads) {
 }
 
 hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, uint32_t *scratch, uint64_t cap,
-                          uint32_t *ws, uint64_t id_range, const uint32_t *seg_range, hipStream_t s) {
+                          uint32_t *ws, uint64_t id_range, const uint32_t *seg_range, bool zeroed, const Ctrl *ctrl,
+                          uint64_t *status, hipStream_t s) {
     if (nq == 0) return hipSuccess;
     const uint32_t range = (uint32_t)(id_range < 0xFFFFFFFFull ? id_range : 0xFFFFFFFFull);
-    uint32_t *counts = ws;            // class counters
-    uint32_t *lists = ws + 64;        // kListCls lists of up to nq query indices
+    uint32_t *counts = ws;                    // class counters
+    uint32_t *lists = ws + kSortCounters;     // kListCls lists of up to nq query indices
     const uint32_t cus = (uint32_t)num_cus();
     // blocks per CU that fit at once (registers and LDS): each persistent
     // grid holds that many, so no block waits for another to finish its share
@@ -960,45 +999,67 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
     static const uint32_t g_long = resident_per_cu(segsort_long<1024>, 1024);
     static const uint32_t g_sub = resident_per_cu(segsort_sub<256, 16, 4, true>, 256);
     static const uint32_t g_subw = resident_per_cu(segsort_sub<1024, 32, 8, false>, 1024);
-    hipError_t e = launch_zero(counts, 64 * 4, s);
-    if (e != hipSuccess) return e;
-    const uint64_t cg = (nq + kClsTile - 1) / kClsTile;
-    hipLaunchKernelGGL(seg_classify, dim3((uint32_t)cg), dim3(256), 0, s, offsets, nq, cap, lists, counts);
-    e = hipGetLastError();
+    // no more blocks than the class can have work items: nq segments, or as
+    // many longer than `longer` as fit the capacity (none: no launch)
+    auto most = [&](uint32_t longer) { return std::min<uint64_t>(nq, cap / (longer + 1ull)); };
+    auto grid = [&](uint32_t resident, uint64_t items) {
+        return dim3((uint32_t)std::min<uint64_t>((uint64_t)cus * resident, items));
+    };
+    hipError_t e = hipSuccess;
+    if (!zeroed) e = launch_zero(counts, kSortCounters * 4, s);
     if (e != hipSuccess) return e;
     // every class on the caller's stream, shortest first (an extra stream
     // per call site would take one of the device's few hardware queues from
     // whatever else the process runs concurrently)
-    // after the cap ids of scratch: kDesc words per class-L segment (257
-    // sub-bucket starts and the group width), then its work items (at most
-    // 256 groups per segment)
-    const uint64_t nlong = cap / (kMidMax + 1) + 1;
-    uint32_t *desc = scratch + cap;
-    uint32_t *sub_list = desc + nlong * kDesc;
-    uint32_t *sub_list_wide = sub_list + nlong * kLongDigits;
-    hipLaunchKernelGGL(segsort_small, dim3(cus * g_small), dim3(256), 0, s, offsets, ids, lists, counts + 0);
-    hipLaunchKernelGGL((segsort_mid<128, 8, true, true, 4>), dim3(cus * g_m1), dim3(128), 0, s, offsets, ids,
-                       lists + nq, counts + 1, range, seg_range);
-    hipLaunchKernelGGL((segsort_mid<256, 16, false, true, 4>), dim3(cus * g_m2), dim3(256), 0, s, offsets, ids,
-                       lists + 2 * nq, counts + 2, range, seg_range);
-    hipLaunchKernelGGL((segsort_mid<512, 32, false, true, 8>), dim3(cus * g_m3), dim3(512), 0, s, offsets, ids,
-                       lists + 3 * nq, counts + 3, range, seg_range);
-    hipLaunchKernelGGL((segsort_mid<1024, 32, false, false, 8>), dim3(cus * g_m4), dim3(1024), 0, s, offsets, ids,
-                       lists + 4 * nq, counts + 4, range, seg_range);
-    hipLaunchKernelGGL(segsort_long<1024>, dim3(cus * g_long), dim3(1024), 0, s, offsets, ids, scratch, desc, sub_list,
-                       sub_list_wide, counts + kSubCounts, lists + kLong * nq, counts + kLong, lists + kFallback * nq,
-                       counts + kFallback, range, seg_range);
-    hipLaunchKernelGGL((segsort_sub<256, 16, 4, true>), dim3(cus * g_sub), dim3(256), 0, s, offsets, ids, scratch,
-                       desc, sub_list, counts + kSubCounts, lists + kLong * nq, range, seg_range);
-    hipLaunchKernelGGL((segsort_sub<1024, 32, 8, false>), dim3(cus * g_subw), dim3(1024), 0, s, offsets, ids,
-                       scratch, desc, sub_list_wide, counts + kSubCounts + 1, lists + kLong * nq, range, seg_range);
-    // the fallback kernels: almost always empty
-    hipLaunchKernelGGL(segsort_tiles, dim3(cus * 2), dim3(1024), 0, s, offsets, ids, lists + kFallback * nq,
-                       counts + kFallback);
-    hipLaunchKernelGGL(segmerge_long, dim3(cus * 2), dim3(1024), 0, s, offsets, ids, scratch, lists + kFallback * nq,
-                       counts + kFallback);
-    e = hipGetLastError();
-    return e;
+    if (nq <= kFewMax) {
+        hipLaunchKernelGGL(segsort_few, dim3((uint32_t)nq), dim3(256), 0, s, offsets, (uint32_t)nq, cap, ids, lists,
+                           counts, range, seg_range, ctrl, status);
+    } else {
+        if (nq <= 262144)
+            hipLaunchKernelGGL(seg_classify<2>, dim3((uint32_t)((nq + 511) / 512)), dim3(256), 0, s, offsets, nq, cap,
+                               lists, counts, ctrl, status);
+        else
+            hipLaunchKernelGGL(seg_classify<16>, dim3((uint32_t)((nq + 4095) / 4096)), dim3(256), 0, s, offsets, nq,
+                               cap, lists, counts, ctrl, status);
+        if (most(1))
+            hipLaunchKernelGGL(segsort_small, grid(g_small, (most(1) + 3) / 4), dim3(256), 0, s, offsets, ids, lists,
+                               counts + 0);
+        if (most(256))
+            hipLaunchKernelGGL((segsort_mid<128, 8, true, true, 4>), grid(g_m1, most(256)), dim3(128), 0, s, offsets,
+                               ids, lists + nq, counts + 1, range, seg_range);
+        if (most(1024))
+            hipLaunchKernelGGL((segsort_mid<256, 16, false, true, 4>), grid(g_m2, most(1024)), dim3(256), 0, s,
+                               offsets, ids, lists + 2 * nq, counts + 2, range, seg_range);
+        if (most(4096))
+            hipLaunchKernelGGL((segsort_mid<512, 32, false, true, 8>), grid(g_m3, most(4096)), dim3(512), 0, s,
+                               offsets, ids, lists + 3 * nq, counts + 3, range, seg_range);
+    }
+    const uint32_t wide_min = nq <= kFewMax ? kFewIds : 16384;
+    if (most(wide_min))
+        hipLaunchKernelGGL((segsort_mid<1024, 32, false, false, 8>), grid(g_m4, most(wide_min)), dim3(1024), 0, s,
+                           offsets, ids, lists + 4 * nq, counts + 4, range, seg_range);
+    const uint64_t nl = most(kMidMax);   // class-L segments at most
+    if (nl) {
+        // after the cap ids of scratch: kDesc words per class-L segment (257
+        // sub-bucket starts and the group width), then its work items (at
+        // most 256 groups per segment)
+        const uint64_t nlong = cap / (kMidMax + 1) + 1;
+        uint32_t *desc = scratch + cap;
+        uint32_t *sub_list = desc + nlong * kDesc;
+        uint32_t *sub_list_wide = sub_list + nlong * kLongDigits;
+        hipLaunchKernelGGL(segsort_long<1024>, grid(g_long, nl), dim3(1024), 0, s, offsets, ids, scratch, desc,
+                           sub_list, sub_list_wide, counts + kSubCounts, lists + kLong * nq, counts + kLong,
+                           lists + kFallback * nq, counts + kFallback, range, seg_range);
+        hipLaunchKernelGGL((segsort_sub<256, 16, 4, true>), grid(g_sub, nl * kLongDigits), dim3(256), 0, s, offsets,
+                           ids, scratch, desc, sub_list, counts + kSubCounts, lists + kLong * nq, range, seg_range);
+        hipLaunchKernelGGL((segsort_sub<1024, 32, 8, false>), grid(g_subw, nl * kLongDigits), dim3(1024), 0, s,
+                           offsets, ids, scratch, desc, sub_list_wide, counts + kSubCounts + 1, lists + kLong * nq,
+                           range, seg_range);
+        // skewed ids: almost always empty
+        hipLaunchKernelGGL(segsort_skewed, grid(2, nl), dim3(1024), 0, s, offsets, ids, scratch,
+                           lists + kFallback * nq, counts + kFallback);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace rtk

@@ -39,7 +39,7 @@ namespace rtk {
 // slice are close in space, so they share tree nodes in that XCD's L2), then
 // the following slices in turn.  `visited` counts the slices found empty.
 // Returns nq when everything has been handed out.
-__device__ __forceinline__ uint32_t grab_query(Ctrl *ctrl, uint32_t slot, uint32_t nq, const uint64_t *order,
+__device__ __forceinline__ uint32_t grab_query(Ctrl *ctrl, uint32_t slot, uint32_t nq, const uint32_t *order,
                                                uint32_t home, uint32_t &visited, uint32_t *slice = nullptr,
                                                bool look_first = false) {
     while (visited < kXcds) {
@@ -60,7 +60,7 @@ __device__ __forceinline__ uint32_t grab_query(Ctrl *ctrl, uint32_t slot, uint32
         const uint32_t k = atomicAdd(&ctrl->xwork[slot][x][0], 1u);
         if (k < b1 - b0) {
             if (slice) *slice = x;
-            return order ? (uint32_t)order[b0 + k] : b0 + k;
+            return order ? order[b0 + k] : b0 + k;
         }
         visited += 1;
     }
@@ -224,7 +224,7 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
                     cn = c;
                     ci = 0;
                     if (e < c) {
-                        cq = plan.order ? (uint32_t)plan.order[p0 + e] : p0 + e;
+                        cq = plan.order ? plan.order[p0 + e] : p0 + e;
                         cw = qs[cq];
                         cs = cq;
                         if (plan.slot_first) {
@@ -457,7 +457,7 @@ struct WalkItems {
 
 template <int G, int LAYOUT, bool REC, int SRC, bool DUMP, bool WIDE>
 __global__ void __launch_bounds__(256)
-walk_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, const uint64_t *__restrict__ order,
+walk_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, const uint32_t *__restrict__ order,
             uint32_t *__restrict__ counts, Ctrl *__restrict__ ctrl, uint32_t chunk, uint32_t stack_cap, RecArena ar,
             uint32_t budget, WalkItems in, WalkItems out) {
     extern __shared__ uint32_t smem[];
@@ -504,7 +504,7 @@ walk_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, const uint64
                 ci = 0;
                 if (e < c) {
                     if constexpr (SRC == 0) {
-                        cq = order ? (uint32_t)order[p0 + e] : p0 + e;
+                        cq = order ? order[p0 + e] : p0 + e;
                     } else {
                         const uint2 it = in.item[p0 + e];
                         cq = it.x;
@@ -558,7 +558,7 @@ template <int G, int LAYOUT, int PHASE>
 __global__ void __launch_bounds__(256)
 split_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t split_parent, uint32_t kmin,
              uint32_t hcap, float min_area, uint32_t *__restrict__ nslots, const uint64_t *__restrict__ slot_first,
-             uint4 *__restrict__ heavy, const uint64_t *__restrict__ order, Ctrl *__restrict__ ctrl,
+             uint4 *__restrict__ heavy, const uint32_t *__restrict__ order, Ctrl *__restrict__ ctrl,
              uint32_t stack_cap) {
     extern __shared__ uint32_t smem[];
     const uint32_t lane = threadIdx.x & 63u;
@@ -825,20 +825,10 @@ replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffset
     }
 }
 
-__global__ void set_rec_kernel(Ctrl *ctrl, uint4 *rec, uint32_t *rec_count, uint32_t nchunks) {
-    ctrl->rec_base = rec;
-    ctrl->rec_count = rec_count;
-    ctrl->rec_nchunks = nchunks;
-}
-
-hipError_t launch_set_rec(Ctrl *ctrl, const SelectPlan &plan, hipStream_t s) {
-    hipLaunchKernelGGL(set_rec_kernel, dim3(1), dim3(1), 0, s, ctrl, plan.rec, plan.rec_count, plan.rec_nchunks);
-    return hipGetLastError();
-}
-
 hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t noffsets, uint32_t *ids,
-                         uint64_t cap, Ctrl *ctrl, uint4 *defer, uint32_t defer_cap, hipStream_t s) {
-    const dim3 grid((uint32_t)num_cus() * 8), block(256);
+                         uint64_t cap, Ctrl *ctrl, uint4 *defer, uint32_t defer_cap, uint32_t max_chunks, hipStream_t s) {
+    const uint32_t most = (uint32_t)num_cus() * 8;   // no more blocks than chunks can be taken
+    const dim3 grid(max_chunks < most ? max_chunks : most), block(256);
 #define RT_REPLAY(L_)                                                                                              \
     do {                                                                                                           \
         if (defer)                                                                                                 \
@@ -909,7 +899,7 @@ static hipError_t launch_g(const TreeView &t, const float4 *q, uint32_t nq, uint
 template <int G, int LAYOUT, int PHASE>
 static hipError_t launch_split_g(const TreeView &t, const float4 *q, uint32_t nq, uint32_t split_first,
                                  uint32_t kmin, uint32_t budget, float min_area, uint32_t *nslots,
-                                 const uint64_t *slot_first, uint4 *heavy, const uint64_t *order, Ctrl *ctrl,
+                                 const uint64_t *slot_first, uint4 *heavy, const uint32_t *order, Ctrl *ctrl,
                                  hipStream_t s) {
     const uint32_t stack_cap = stack_bound(t.height, t.fanout);
     const uint32_t groups_per_block = 256 / G;
@@ -1027,7 +1017,7 @@ hipError_t launch_walk(const TreeView &t, const float4 *q, uint32_t nq, uint32_t
 template <int PHASE>
 static hipError_t launch_split_phase(const TreeView &t, const float4 *q, uint32_t nq, uint32_t split_first,
                                      uint32_t kmin, uint32_t budget, float min_area, uint32_t *nslots,
-                                     const uint64_t *slot_first, uint4 *heavy, const uint64_t *order, Ctrl *ctrl,
+                                     const uint64_t *slot_first, uint4 *heavy, const uint32_t *order, Ctrl *ctrl,
                                      hipStream_t s) {
 #define RT_SPLIT(G_, L_) \
     launch_split_g<G_, L_, PHASE>(t, q, nq, split_first, kmin, budget, min_area, nslots, slot_first, heavy, order, \
@@ -1041,7 +1031,7 @@ static hipError_t launch_split_phase(const TreeView &t, const float4 *q, uint32_
 
 hipError_t launch_split(const TreeView &t, const float4 *q, uint32_t nq, int phase, uint32_t split_parent,
                         uint32_t kmin, uint32_t hcap, float min_area, uint32_t *nslots, const uint64_t *slot_first,
-                        uint4 *heavy, const uint64_t *order, Ctrl *ctrl, hipStream_t s) {
+                        uint4 *heavy, const uint32_t *order, Ctrl *ctrl, hipStream_t s) {
     return phase == 0 ? launch_split_phase<0>(t, q, nq, split_parent, kmin, hcap, min_area, nslots, slot_first,
                                               heavy, order, ctrl, s)
                       : launch_split_phase<1>(t, q, nq, split_parent, kmin, hcap, min_area, nslots, slot_first,
@@ -1076,66 +1066,102 @@ __device__ __forceinline__ uint32_t spread16(uint32_t v) {
     return v;
 }
 
-// Morton (Z-order) code of each window center on a 65536 x 65536 grid over
-// the tree's MBR.  Only the processing order depends on it; no result does.
-__global__ void query_morton(const float4 *__restrict__ q, uint32_t nq, float lx, float ly, float sx, float sy,
-                             uint64_t *__restrict__ keys) {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nq; i += gridDim.x * blockDim.x) {
-        const float4 w = q[i];
-        float cx = (0.5f * w.x + 0.5f * w.z - lx) * sx;
-        float cy = (0.5f * w.y + 0.5f * w.w - ly) * sy;
-        cx = fminf(fmaxf(cx, 0.f), 65535.f);   // NaN -> 0
-        cy = fminf(fmaxf(cy, 0.f), 65535.f);
-        const uint32_t code = spread16((uint32_t)cx) | (spread16((uint32_t)cy) << 1);
-        keys[i] = ((uint64_t)code << 32) | i;
+// Cell of a window center on a 64 x 64 grid over the tree's MBR, cells in
+// Morton (Z) order.  Only the processing order depends on it; no result does.
+__device__ __forceinline__ uint32_t order_cell(const float4 w, float lx, float ly, float sx, float sy) {
+    float cx = (0.5f * w.x + 0.5f * w.z - lx) * sx;
+    float cy = (0.5f * w.y + 0.5f * w.w - ly) * sy;
+    cx = fminf(fmaxf(cx, 0.f), 63.f);   // NaN -> 0
+    cy = fminf(fmaxf(cy, 0.f), 63.f);
+    return spread16((uint32_t)cx) | (spread16((uint32_t)cy) << 1);
+}
+
+// Bucket sort of the queries by cell, three launches: queries per cell (LDS
+// counters per block, one global update per cell a block has), a one-block
+// scan, and the scatter (LDS ranks, each block reserving its share of a cell).
+constexpr uint32_t kOrderT = 1024;
+
+template <bool SCATTER>
+__global__ void __launch_bounds__(kOrderT)
+order_cells(const float4 *__restrict__ q, uint32_t nq, uint32_t per, float lx, float ly, float sx, float sy,
+            uint32_t *__restrict__ cells, uint32_t *__restrict__ order) {
+    __shared__ uint32_t c[kOrderCells];
+    constexpr uint32_t R = 8;   // per <= R queries per thread
+    for (uint32_t i = threadIdx.x; i < kOrderCells; i += kOrderT) c[i] = 0;
+    __syncthreads();
+    const uint32_t i0 = blockIdx.x * kOrderT * per + threadIdx.x;
+    uint32_t cell[R], rank[R];
+#pragma unroll
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint32_t i = i0 + r * kOrderT;
+        if (r < per && i < nq) {
+            cell[r] = order_cell(q[i], lx, ly, sx, sy);
+            rank[r] = atomicAdd(&c[cell[r]], 1u);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < kOrderCells; i += kOrderT)
+        if (c[i]) {
+            const uint32_t at = atomicAdd(&cells[i], c[i]);
+            if (SCATTER) c[i] = at;
+        }
+    if constexpr (SCATTER) {
+        __syncthreads();
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r) {
+            const uint32_t i = i0 + r * kOrderT;
+            if (r < per && i < nq) order[c[cell[r]] + rank[r]] = i;
+        }
     }
 }
 
-static uint64_t al256(uint64_t b) { return (b + 255) & ~255ull; }
-
-// The order sorts on the top 22 bits of the 32-bit Morton code (11 bits per
-// axis, a 2048 x 2048 grid over the tree's MBR) in two 11-bit passes; the
-// order inside a grid cell does not matter for locality.
-constexpr int kOrderDigitBits = 11;
-
-uint64_t order_ws_bytes(uint64_t nq) {
-    const uint64_t he = radix_hist_elems(nq, kOrderDigitBits);
-    return al256(8 * nq) * 2 + al256(4 * he) + al256(8 * (he + 1)) + al256(8 * scan_tmp_elems(he + 1));
+__global__ void __launch_bounds__(1024) order_scan(uint32_t *__restrict__ cells) {
+    __shared__ uint32_t wsum[16];
+    const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
+    uint32_t v[4], sum = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) sum += v[r] = cells[4 * t + r];
+    uint32_t inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t x = __shfl_up(inc, d);
+        if ((int)lane >= d) inc += x;
+    }
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    uint32_t ex = inc - sum;
+    for (uint32_t i = 0; i < w; ++i) ex += wsum[i];
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r) {
+        cells[4 * t + r] = ex;
+        ex += v[r];
+    }
 }
 
-hipError_t launch_query_order(const float4 *q, uint32_t nq, const float *mbr, void *ws, const uint64_t **sorted,
+uint64_t order_ws_bytes(uint64_t nq) { return 4 * kOrderCells + 4 * nq; }
+
+hipError_t launch_query_order(const float4 *q, uint32_t nq, const float *mbr, void *ws, const uint32_t **order,
                               hipStream_t s) {
-    uint8_t *p = static_cast<uint8_t *>(ws);
-    uint64_t *keys = reinterpret_cast<uint64_t *>(p);
-    p += al256(8 * (uint64_t)nq);
-    uint64_t *tmp = reinterpret_cast<uint64_t *>(p);
-    p += al256(8 * (uint64_t)nq);
-    const uint64_t he = radix_hist_elems(nq, kOrderDigitBits);
-    uint32_t *hist = reinterpret_cast<uint32_t *>(p);
-    p += al256(4 * he);
-    uint64_t *hscan = reinterpret_cast<uint64_t *>(p);
-    p += al256(8 * (he + 1));
-    uint64_t *stmp = reinterpret_cast<uint64_t *>(p);
+    uint32_t *cells = static_cast<uint32_t *>(ws);
+    uint32_t *out = cells + kOrderCells;
     float lx = mbr[0], ly = mbr[1], w = mbr[2] - mbr[0], h = mbr[3] - mbr[1];
     const bool ok = (w > 0.f) && (h > 0.f) && (w < 3.0e38f) && (h < 3.0e38f);
-    const float sx = ok ? 65535.f / w : 0.f, sy = ok ? 65535.f / h : 0.f;
+    const float sx = ok ? 64.f / w : 0.f, sy = ok ? 64.f / h : 0.f;
     if (!ok) lx = ly = 0.f;
-    uint32_t blocks = (nq + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(query_morton, dim3(blocks), dim3(256), 0, s, q, nq, lx, ly, sx, sy, keys);
-    // two passes (an even number): the sorted keys end in the first buffer
-    const int shifts[2] = {42, 53};
-    bool in_tmp = false;
-    hipError_t e =
-        launch_radix_sort_u64(keys, tmp, nq, shifts, 2, hist, hscan, stmp, &in_tmp, s, kOrderDigitBits);
-    *sorted = keys;
-    if (e == hipSuccess && in_tmp) e = hipErrorUnknown;
-    return e == hipSuccess ? hipGetLastError() : e;
+    // few queries: one per thread, so that there are blocks to run; many:
+    // eight, so that a block updates each cell's counter once for more of them
+    const uint32_t per = nq <= 131072 ? 1u : 8u;
+    const dim3 grid((nq + kOrderT * per - 1) / (kOrderT * per)), block(kOrderT);
+    hipLaunchKernelGGL(order_cells<false>, grid, block, 0, s, q, nq, per, lx, ly, sx, sy, cells, (uint32_t *)nullptr);
+    hipLaunchKernelGGL(order_scan, dim3(1), dim3(1024), 0, s, cells);
+    hipLaunchKernelGGL(order_cells<true>, grid, block, 0, s, q, nq, per, lx, ly, sx, sy, cells, out);
+    *order = out;
+    return hipGetLastError();
 }
 
-const uint64_t *query_order_result(const void *ws, uint64_t nq) {
+const uint32_t *query_order_result(const void *ws, uint64_t nq) {
     (void)nq;
-    return static_cast<const uint64_t *>(ws);
+    return static_cast<const uint32_t *>(ws) + kOrderCells;
 }
 
 }  // namespace rtk
