@@ -195,6 +195,17 @@ uint64_t rtk::rec_arena_bytes(uint64_t nq, uint64_t cap) {
     return align256(16 * kRecChunk * chunks) + align256(4 * chunks) + 512;
 }
 
+// Up to 512 ids per window on average (fewer than that many records), and a
+// chunk for every lane group that can run at once on this tree.
+uint64_t rtk::rec_arena_guess(const rt_tree *t, uint64_t nq, uint64_t cap) {
+    const uint64_t ids = std::min<uint64_t>(cap, 512 * nq + 65536);
+    const uint64_t groups = (uint64_t)num_cus() * 8 * (256 / group_width(t->fanout));
+    const uint64_t all = rec_arena_bytes(nq, ids), spare = (uint64_t)num_cus() * 8 * 16;
+    // rec_arena_bytes counts the groups of the narrowest trees
+    const uint64_t less = (std::min(nq, spare) - std::min(nq, groups)) * (16ull * kRecChunk);
+    return ids <= kRecSureIds ? all : all - less;
+}
+
 // Chunks of an arena of `bytes` bytes.
 uint32_t rtk::rec_chunks_in(uint64_t bytes) {
     const uint64_t per = 16 * kRecChunk + 4;
@@ -409,7 +420,7 @@ static SplitCfg split_cfg(const rt_tree *t, uint64_t nq) {
 
 int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, uint64_t *d_off, uint32_t *d_ids,
                               uint64_t cap, void *work, uint64_t *d_status, hipStream_t s, int stage,
-                              uint32_t *d_counts_out, void *const *events, uint64_t rec_bytes) {
+                              uint32_t *d_counts_out, void *const *events, uint64_t rec_bytes, uint64_t *total_out) {
     SelWs w = sel_ws(work, nq);
     if (nq == 0) {   // no launch of an empty grid: offsets = {0}, status = {0, 0}
         hipError_t e = hipSuccess;
@@ -480,10 +491,11 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         if (e == hipSuccess) e = mark(1);
         if (d_counts_out || e != hipSuccess) return e == hipSuccess ? RT_OK : hip_fail(e, "count pass");
         if (slots) {
-            e = launch_scan_u32(w.slot_counts, w.nslot_max, w.slot_off, w.slot_scan_tmp, s);
+            e = launch_scan_u32_dev(w.slot_counts, nullptr, w.nslot_max, w.slot_off, w.slot_scan_tmp, total_out, ~0ull,
+                                    nullptr, s);
             if (e == hipSuccess) e = launch_gather_offsets(w.slot_first, w.slot_off, (uint32_t)nq, d_off, s);
         } else {
-            e = launch_scan_u32(w.counts, nq, d_off, w.scan_tmp, s);
+            e = launch_scan_u32_dev(w.counts, nullptr, nq, d_off, w.scan_tmp, total_out, ~0ull, nullptr, s);
         }
         if (e == hipSuccess) e = mark(2);
         if (e != hipSuccess) return hip_fail(e, "count stage");
@@ -627,6 +639,9 @@ int rtk::make_ids(uint64_t nq, uint64_t total, rt_ids **out) {
     return RT_OK;
 }
 
+// Device memory a host select leaves in the pool (larger workspaces are freed).
+constexpr uint64_t kHostSelectKeep = 256ull << 20;
+
 extern "C" int rt_range_select(const rt_tree *t, const float *queries, uint64_t nq, rt_ids **out) {
     if (!out) return fail(RT_EINVAL, "out is NULL");
     *out = nullptr;
@@ -636,42 +651,62 @@ extern "C" int rt_range_select(const rt_tree *t, const float *queries, uint64_t 
         if (int rc = check_rects(queries, nq, "queries")) return rc;
         DevSet ds(t->device);
         if (nq == 0) return make_ids(0, 0, out);
-        DevBuf dq, doff, work, dids;
-        hipError_t e = dq.alloc(nq * 16);
-        if (e == hipSuccess) e = doff.alloc((nq + 1) * 8);
-        if (e == hipSuccess) e = work.alloc(sel_ws_bytes(nq, 0));
-        if (e == hipSuccess) e = hipMemcpy(dq.p, queries, nq * 16, hipMemcpyHostToDevice);
-        if (e != hipSuccess) return hip_fail(e, "select setup");
-        // count stage, then size the output exactly and run the fill stage
-        SelWs w = sel_ws(work.p, nq);
+        // windows, offsets, the count stage's workspace and room for its
+        // records in one pooled workspace; the ids (and the fill stage's
+        // workspace, if the first has too little room past the records) in a
+        // second.  Allocating and freeing them per call took a third of a
+        // 10k-window select.
+        const uint64_t off_at = align256(16 * nq), ws_at = off_at + align256(8 * (nq + 1));
+        const uint64_t ws0 = sel_ws_bytes(nq, 0);
+        const int dev = t->device;
         hipStream_t s = nullptr;
-        int rc = enqueue_select_stage(t, static_cast<const float4 *>(dq.p), nq, static_cast<uint64_t *>(doff.p),
-                                      nullptr, 0, work.p, nullptr, s, 1, nullptr, nullptr);
-        if (rc) return rc;
-        uint64_t total = 0;
-        e = hipMemcpy(&total, static_cast<uint64_t *>(doff.p) + nq, 8, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(e, "count pass");
-        DevBuf work2;
-        e = dids.alloc(total * 4);
-        if (e == hipSuccess) e = work2.alloc(sel_ws_bytes(nq, total));
-        if (e == hipSuccess) e = hipMemcpy(work2.p, work.p, sel_ws_bytes(nq, 0), hipMemcpyDeviceToDevice);
-        if (e != hipSuccess) return hip_fail(e, "allocating the result");
-        w = sel_ws(work2.p, nq);
-        rc = enqueue_select_stage(t, static_cast<const float4 *>(dq.p), nq, static_cast<uint64_t *>(doff.p),
-                                  static_cast<uint32_t *>(dids.p), total, work2.p, nullptr, s, 2, nullptr, nullptr);
-        if (rc) return rc;
-        Ctrl hc;
-        e = hipMemcpy(&hc, w.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(e, "fill pass");
-        if (hc.err) return fail(RT_EDEVICE, "kernel check failed (flags %u)", hc.err);
-        rt_ids *r = nullptr;
-        if (int rc = make_ids(nq, total, &r)) return rc;
-        e = hipMemcpy(r->offsets, doff.p, (nq + 1) * 8, hipMemcpyDeviceToHost);
-        if (e == hipSuccess && total) e = hipMemcpy(r->ids, dids.p, total * 4, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) {
-            rt_free(r);
-            return hip_fail(e, "copying the result");
+        PoolWs *w = nullptr, *w2 = nullptr;
+        hipError_t e = pool_acquire(dev, ws_at + ws0 + rec_arena_guess(t, nq, ~0ull), &w);
+        if (e != hipSuccess) return hip_fail(e, "select setup");
+        auto done = [&](int rc) {
+            (void)hipStreamSynchronize(s);
+            pool_release(dev, w, s, kHostSelectKeep);
+            pool_release(dev, w2, s, kHostSelectKeep);
+            return rc;
+        };
+        uint8_t *base = static_cast<uint8_t *>(w->d);
+        const float4 *dq = reinterpret_cast<const float4 *>(base);
+        uint64_t *doff = reinterpret_cast<uint64_t *>(base + off_at);
+        uint8_t *work = base + ws_at;
+        w->host[0] = 0;
+        e = hipMemcpyAsync(base, queries, nq * 16, hipMemcpyHostToDevice, s);
+        if (e != hipSuccess) return done(hip_fail(e, "select setup"));
+        // count stage, then size the output exactly and run the fill stage
+        int rc = enqueue_select_stage(t, dq, nq, doff, nullptr, 0, work, nullptr, s, 1, nullptr, nullptr,
+                                      w->bytes - ws_at - ws0, w->host);
+        if (rc) return done(rc);
+        e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return done(hip_fail(e, "count pass"));
+        const uint64_t total = w->host[0];
+        const uint64_t ws1 = sel_ws_bytes(nq, total), ids_bytes = align256(total * 4);
+        const bool move = w->bytes - ws_at < ws1;
+        e = pool_acquire(dev, ids_bytes + (move ? ws1 : 0) + 256, &w2);
+        if (e != hipSuccess) return done(hip_fail(e, "allocating the result"));
+        uint32_t *dids = static_cast<uint32_t *>(w2->d);
+        if (move) {
+            work = static_cast<uint8_t *>(w2->d) + ids_bytes;
+            e = hipMemcpyAsync(work, base + ws_at, ws0, hipMemcpyDeviceToDevice, s);
+            if (e != hipSuccess) return done(hip_fail(e, "allocating the result"));
         }
+        rc = enqueue_select_stage(t, dq, nq, doff, dids, total, work, w->host + 2, s, 2, nullptr, nullptr);
+        if (rc) return done(rc);
+        rt_ids *r = nullptr;
+        if (int rc2 = make_ids(nq, total, &r)) return done(rc2);
+        e = hipMemcpyAsync(r->offsets, doff, (nq + 1) * 8, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess && total) e = hipMemcpyAsync(r->ids, dids, total * 4, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess || w->host[3]) {
+            const uint64_t flags = w->host[3];
+            rt_free(r);
+            return done(e != hipSuccess ? hip_fail(e, "copying the result")
+                                        : fail(RT_EDEVICE, "kernel check failed (flags %llu)", (unsigned long long)flags));
+        }
+        (void)done(RT_OK);
         *out = r;
         return RT_OK;
     } catch (const std::bad_alloc &) {

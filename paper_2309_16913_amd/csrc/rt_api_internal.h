@@ -58,11 +58,14 @@ int build_tuned(const float4 *d_rects, uint64_t n, uint32_t fanout, uint32_t lay
 int make_ids(uint64_t nq, uint64_t total, rt_ids **out);
 // stage bit 1: count stage (order, split, count pass, offsets); bit 2: fill
 // stage (fill pass, sort, status).  d_counts_out: count-only mode.
-// rec_bytes: workspace bytes past the select's own layout for (nq, cap) that
-// may hold the count pass's records (both stages in one call only; 0: none).
+// rec_bytes: workspace bytes past the select's own layout -- for (nq, cap) in
+// one call, for (nq, 0) in a count stage of its own -- that may hold the count
+// pass's records (0: none).  total_out (NULL: none): the count stage also
+// stores the total there (device-visible memory).
 int enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, uint64_t *d_off, uint32_t *d_ids,
                          uint64_t cap, void *work, uint64_t *d_status, hipStream_t s, int stage,
-                         uint32_t *d_counts_out, void *const *events, uint64_t rec_bytes = 0);
+                         uint32_t *d_counts_out, void *const *events, uint64_t rec_bytes = 0,
+                         uint64_t *total_out = nullptr);
 int enqueue_select(const rt_tree *t, const float4 *dq, uint64_t nq, uint64_t *d_off, uint32_t *d_ids,
                    uint64_t cap, void *work, uint64_t *d_status, hipStream_t s, bool count_only,
                    uint32_t *d_counts_out, void *const *events = nullptr, uint64_t rec_bytes = 0);
@@ -73,7 +76,22 @@ uint64_t select_replay_ws_bytes(uint64_t nq, uint64_t cap);
 // Record arena for nq queries and cap ids (records, then one count per
 // chunk), and the chunks an arena of `bytes` holds.
 uint64_t rec_arena_bytes(uint64_t nq, uint64_t cap);
+// The same for selects whose result is not known yet, of at most cap ids.
+uint64_t rec_arena_guess(const rt_tree *t, uint64_t nq, uint64_t cap);
 uint32_t rec_chunks_in(uint64_t bytes);
+
+// Device workspaces kept per device between calls, each with a few pinned host
+// words and an event recorded behind its last use: one is handed out again only
+// when that has completed, so calls on different streams or threads never
+// share one while it is in use.
+struct PoolWs {
+    void *d = nullptr;
+    uint64_t bytes = 0;
+    uint64_t *host = nullptr;     // 8 pinned words
+    hipEvent_t done = nullptr;
+};
+hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out);
+void pool_release(int dev, PoolWs *w, hipStream_t s, uint64_t keep = ~0ull);
 
 // Owning device buffer.
 struct DevBuf {

@@ -108,3 +108,37 @@ def test_two_stage_deferred_ranges(rt, ora, nq, big):
     assert chunks > 0 and not over
     assert np.array_equal(off.cpu().numpy(), wo.astype(np.int64))
     assert np.array_equal(ids.cpu().numpy().view(np.uint32), wi)
+
+
+@pytest.mark.parametrize("nq", [1, 9, 3000])
+def test_library_workspaces(rt, ora, nq):
+    """Host and stream-ordered selects whose fill stage outgrows the count
+    stage's workspace (whole-space windows) and so moves to another one while
+    the records stay, twice on two streams, between selects that do not."""
+    import torch
+    r = rtgen.c2_rects(300_000)
+    t = rt.build_str(r, 32, "soa")
+    ot = ora.build_str(r, 32)
+    q = rtgen.windows_loguniform(nq, 1e-7, 1e-4, 5)
+    small = q.copy()
+    q[:9] = (-1.0, -1.0, 2.0, 2.0)
+    for w in (small, q, small):
+        wo, wi = ora.select(ot, w)
+        off, ids = rt.range_select(t, w)
+        assert np.array_equal(off, wo) and np.array_equal(ids, wi)
+        dq = torch.from_numpy(w).cuda()
+        torch.cuda.synchronize()
+        outs = []
+        for s in (torch.cuda.Stream(), torch.cuda.Stream()):
+            d = (torch.empty(nq + 1, dtype=torch.int64, device="cuda"),
+                 torch.full((wi.size + 5,), -1, dtype=torch.int32, device="cuda"),
+                 torch.zeros(1, dtype=torch.int64, device="cuda"))
+            torch.cuda.synchronize()
+            assert rt.range_select_async(t, dq.data_ptr(), nq, d[0].data_ptr(), d[1].data_ptr(), wi.size + 5,
+                                         d[2].data_ptr(), s.cuda_stream)
+            outs.append((d, s))
+        torch.cuda.synchronize()
+        for (off, ids, total), _ in outs:
+            assert int(total.item()) == wi.size
+            assert np.array_equal(off.cpu().numpy(), wo.astype(np.int64))
+            assert np.array_equal(ids[:wi.size].cpu().numpy().view(np.uint32), wi) and bool((ids[wi.size:] == -1).all())
