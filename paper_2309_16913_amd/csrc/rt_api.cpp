@@ -55,10 +55,7 @@ void rtk::tree_release(rt_tree *t) {
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(t->device);
-    if (t->d_nodes) (void)hipFree(t->d_nodes);
-    if (t->d_meta) (void)hipFree(t->d_meta);
-    if (t->d_range) (void)hipFree(t->d_range);
-    if (t->d_leaf_ids) (void)hipFree(t->d_leaf_ids);
+    block_free(t->device, t->d_mem, t->mem_bytes);
     (void)hipSetDevice(cur);
     t->~rt_tree();
 }

@@ -20,6 +20,8 @@ struct rt_tree {
     uint32_t replay = 1;              // 1: one-call selects replay the count pass's records
     uint32_t split_kmin = 0;          // mapping: split queries reaching >= this many
                                       // parents-of-leaves (0 = one group per query)
+    void *d_mem = nullptr;     // the one block that holds the four arrays below
+    uint64_t mem_bytes = 0;
     void *d_nodes = nullptr;   // n_nodes * node_bytes
     void *d_meta = nullptr;    // n_nodes uint32: count | level << 8
     void *d_range = nullptr;   // n_nodes uint2: leaves [x, y) under the node
@@ -90,8 +92,13 @@ struct PoolWs {
     uint64_t *host = nullptr;     // 8 pinned words
     hipEvent_t done = nullptr;
 };
-hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out);
+constexpr int kPoolDevices = 64;
+hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out, bool exact = false);
 void pool_release(int dev, PoolWs *w, hipStream_t s, uint64_t keep = ~0ull);
+// Plain device blocks; freed ones are kept up to a bound and given back to the
+// device when an allocation fails.
+hipError_t block_alloc(int dev, uint64_t bytes, void **p, uint64_t *got);
+void block_free(int dev, void *p, uint64_t bytes);
 
 // Owning device buffer.
 struct DevBuf {

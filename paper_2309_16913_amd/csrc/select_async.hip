@@ -1,5 +1,5 @@
 // rt_range_select_async: a range select into caller-owned device buffers
-// whose workspace the library keeps in a per-device pool, and that pool.
+// whose workspace the library keeps in a per-device pool.
 //
 // The call enqueues the count stage, waits for the total (which the scan
 // writes to pinned host memory), and either refuses the select (RT_ENOMEM, the ids buffer untouched)
@@ -7,91 +7,11 @@
 // pooled workspace is handed to a later call only after the event recorded
 // behind its last use has completed, so calls on different streams never
 // share one while it is in use.
-#include <mutex>
-#include <vector>
+#include <new>
 
 #include "../../include/rt.h"
 #include "rt_api_internal.h"
 #include "rt_internal.h"
-
-namespace rtk {
-namespace {
-
-constexpr int kMaxDevices = 64;
-struct WsPool {
-    std::mutex mu;
-    std::vector<PoolWs *> idle;
-};
-WsPool g_ws_pool[kMaxDevices];
-
-hipError_t ws_alloc(PoolWs *w, uint64_t bytes) {
-    if (w->d) (void)hipFree(w->d);
-    w->d = nullptr;
-    w->bytes = 0;
-    hipError_t e = hipMalloc(&w->d, bytes);
-    if (e == hipSuccess) w->bytes = bytes;
-    return e;
-}
-
-}  // namespace
-
-// A workspace of at least `bytes` whose previous use has finished: the
-// smallest idle one that is large enough, else an idle one (grown by half
-// again) or a new one.
-hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out) {
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    PoolWs *w = nullptr;
-    {
-        WsPool &p = g_ws_pool[dev];
-        std::lock_guard<std::mutex> lk(p.mu);
-        size_t at = 0;
-        for (size_t i = 0; i < p.idle.size(); ++i) {
-            PoolWs *c = p.idle[i];
-            const bool fits = c->bytes >= bytes;
-            if (w && (w->bytes >= bytes ? (!fits || c->bytes >= w->bytes) : !fits)) continue;
-            if (hipEventQuery(c->done) != hipSuccess) continue;
-            w = c;
-            at = i;
-        }
-        if (w) p.idle.erase(p.idle.begin() + (long)at);
-    }
-    hipError_t e = hipSuccess;
-    if (!w) {
-        w = new PoolWs();
-        e = hipEventCreateWithFlags(&w->done, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&w->host), 64, hipHostMallocDefault);
-    }
-    if (e == hipSuccess && w->bytes < bytes) e = ws_alloc(w, bytes + bytes / 2);
-    if (e != hipSuccess) {
-        // keep the object: its event and pinned words stay valid for a later call
-        if (w->done && w->host) {
-            std::lock_guard<std::mutex> lk(g_ws_pool[dev].mu);
-            g_ws_pool[dev].idle.push_back(w);
-        } else {
-            if (w->done) (void)hipEventDestroy(w->done);
-            delete w;
-        }
-        return e;
-    }
-    *out = w;
-    return hipSuccess;
-}
-
-// Hand a workspace back once everything enqueued on s so far has finished.
-// keep: device memory above this is freed first (the caller has waited for s).
-void pool_release(int dev, PoolWs *w, hipStream_t s, uint64_t keep) {
-    if (!w) return;
-    if (w->bytes > keep) {
-        (void)hipFree(w->d);
-        w->d = nullptr;
-        w->bytes = 0;
-    }
-    (void)hipEventRecord(w->done, s);
-    std::lock_guard<std::mutex> lk(g_ws_pool[dev].mu);
-    g_ws_pool[dev].idle.push_back(w);
-}
-
-}  // namespace rtk
 
 using namespace rtk;
 
@@ -108,7 +28,7 @@ extern "C" int rt_range_select_async(const rt_tree *t, const float *d_queries, u
         return fail(RT_EINVAL, "NULL argument");
     if (nq > 0xFFF00000ull) return fail(RT_EINVAL, "nq = %llu too large", (unsigned long long)nq);
     if ((reinterpret_cast<uintptr_t>(d_queries) & 15) != 0) return fail(RT_EINVAL, "queries not 16-byte aligned");
-    if (t->device < 0 || t->device >= kMaxDevices) return fail(RT_EINVAL, "device %d out of range", t->device);
+    if (t->device < 0 || t->device >= kPoolDevices) return fail(RT_EINVAL, "device %d out of range", t->device);
     try {
         DevSet ds(t->device);
         hipStream_t s = static_cast<hipStream_t>(stream);
