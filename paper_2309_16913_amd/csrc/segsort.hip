@@ -16,11 +16,13 @@
 //              then every bucket sorted in place by a register network (or,
 //              for the shortest, each id counts the smaller ids of its own
 //              bucket and is stored at bucket start + that count);
-//   class L    (> 32768)        one block per segment: an MSD pass on the top
-//              8 id bits into global scratch (chunks digit-sorted in LDS and
-//              written as runs), then groups of consecutive sub-buckets
-//              (<= 4096 ids each, or <= 32768 when a sub-bucket holds more)
-//              sorted back by one block each;
+//   class L    (> 32768)        an MSD pass on the top 8 id bits into global
+//              scratch, cut into parts of 16384 ids so that one segment
+//              occupies many blocks (digit counts per part, a scan over a
+//              segment's parts, every part digit-sorted in LDS and written as
+//              runs), then groups of consecutive sub-buckets (<= 4096 ids
+//              each, or <= 32768 when a sub-bucket holds more) sorted back by
+//              one block each;
 //   fallback   a segment with a bucket too long for the in-bucket ranking
 //              (ids far from uniform) is sorted by a block bitonic network in
 //              LDS (class M) or, for class L with a sub-bucket over 32768 ids,
@@ -124,6 +126,31 @@ __device__ void block_bitonic(uint32_t *a, uint32_t P) {
 }
 
 // ---------------------------------------------------------------------------
+// class L work space
+// ---------------------------------------------------------------------------
+constexpr uint32_t kLongDigits = 256;
+constexpr uint32_t kPart = 16384;       // ids per part of a class-L segment
+constexpr uint32_t kSubMax = 4096;      // longest group sorted by a 256-thread block
+constexpr uint32_t kSubBigMax = 32768;  // longest group sorted by a 1024-thread block
+// descriptor of a class-L segment: 257 sub-bucket starts, the digits per
+// group (0: the segment went to the fallback), the index of its first part
+constexpr uint32_t kDescGroup = kLongDigits + 1, kDescPart = kLongDigits + 2, kDesc = kLongDigits + 3;
+constexpr uint32_t kSubCounts = 8;      // counters of the two group work lists (in the class counter block)
+constexpr uint32_t kPartCount = 10;     // counter of the part list
+
+// Behind the cap ids of the scratch.  A part list entry is its segment's
+// place in the class-L list; the parts of a segment are consecutive entries.
+struct LongWs {
+    uint32_t *desc;       // kDesc words per class-L segment
+    uint32_t *sub;        // group lists (256- and 1024-thread sorts), at most 256 groups per segment
+    uint32_t *sub_wide;
+    uint32_t *parts;
+    uint32_t *hist;       // per part: digit counts, then positions in the segment relative to the digits' starts
+};
+
+__device__ __forceinline__ uint32_t num_parts(uint64_t len) { return (uint32_t)((len + kPart - 1) / kPart); }
+
+// ---------------------------------------------------------------------------
 // classify
 // ---------------------------------------------------------------------------
 // PER queries per thread: 16 for large batches (fewer list reservations), 2
@@ -131,13 +158,14 @@ __device__ void block_bitonic(uint32_t *a, uint32_t P) {
 template <uint32_t PER>
 __global__ void __launch_bounds__(256)
 seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, uint32_t *__restrict__ lists,
-             uint32_t *__restrict__ counts, const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
-    __shared__ uint32_t bcnt[kNumCls], gbase[kNumCls];
+             uint32_t *__restrict__ counts, LongWs lw, const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
+    __shared__ uint32_t bcnt[kNumCls], gbase[kNumCls], bparts, pcur;
     if (status && blockIdx.x == 0 && threadIdx.x == 0) select_status(offsets, nq, cap, ctrl, status);
     if (offsets[nq] > cap) return;
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
     if (threadIdx.x < kNumCls) bcnt[threadIdx.x] = 0;
+    if (threadIdx.x == 0) bparts = 0;
     __syncthreads();
     const uint64_t q0 = (uint64_t)blockIdx.x * (256 * PER);
     int cls[PER];
@@ -150,6 +178,7 @@ seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, ui
             const uint64_t len = offsets[q + 1] - offsets[q];
             if (len >= 2)
                 c = len <= 256 ? 0 : len <= 1024 ? 1 : len <= 4096 ? 2 : len <= 16384 ? 3 : len <= kMidMax ? 4 : 5;
+            if (c == (int)kLong) atomicAdd(&bparts, num_parts(len));
         }
         cls[k] = c;
         pos[k] = 0;
@@ -167,11 +196,19 @@ seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, ui
     __syncthreads();
     if (threadIdx.x < kNumCls)
         gbase[threadIdx.x] = bcnt[threadIdx.x] ? atomicAdd(&counts[threadIdx.x], bcnt[threadIdx.x]) : 0u;
+    if (threadIdx.x == 0) pcur = bparts ? atomicAdd(&counts[kPartCount], bparts) : 0u;
     __syncthreads();
 #pragma unroll
     for (uint32_t k = 0; k < PER; ++k) {
         const int c = cls[k];
-        if (c >= 0) lists[(uint64_t)c * nq + gbase[c] + pos[k]] = (uint32_t)(q0 + (uint64_t)k * 256 + threadIdx.x);
+        const uint64_t q = q0 + (uint64_t)k * 256 + threadIdx.x;
+        if (c >= 0) lists[(uint64_t)c * nq + gbase[c] + pos[k]] = (uint32_t)q;
+        if (c == (int)kLong) {
+            const uint32_t li = gbase[kLong] + pos[k], np = num_parts(offsets[q + 1] - offsets[q]);
+            const uint32_t p0 = atomicAdd(&pcur, np);
+            lw.desc[(uint64_t)li * kDesc + kDescPart] = p0;
+            for (uint32_t p = 0; p < np; ++p) lw.parts[p0 + p] = li;
+        }
     }
 }
 
@@ -545,186 +582,257 @@ segsort_mid(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, co
     }
 }
 
-// Class L: two levels.  First (segsort_long, one block per segment) the
-// segment is split by its top 8 id bits into 256 sub-buckets in global
-// scratch: a histogram (per-wave LDS counters, eight loads in flight per
-// thread), a scan, then chunks of 8192
-// ids are counting-sorted by that digit in LDS and written out as contiguous
-// runs, one run per digit and chunk; the 257 sub-bucket starts go to the
-// segment's descriptor.  Then groups of G consecutive sub-buckets are sorted
-// from scratch back into place by the whole grid, one block per group
-// (segsort_sub): G is chosen so that a group holds at most 4096 ids, or at
-// most 32768 (a 1024-thread block) when a sub-bucket holds more than 4096
-// (segments of about a million ids).  A segment with a sub-bucket over 32768
-// ids (ids far from uniform) is left as it is and goes to the fallback list.
-constexpr uint32_t kLongDigits = 256;
-constexpr uint32_t kLongChunk = 8192;   // ids per chunk: 1024 threads x 8
-constexpr uint32_t kSubMax = 4096;      // longest group sorted by a 256-thread block
-constexpr uint32_t kSubBigMax = 32768;  // longest group sorted by a 1024-thread block
-constexpr uint32_t kDesc = kLongDigits + 2;   // 257 sub-bucket starts, group width
-constexpr uint32_t kSubCounts = 8;      // counters of the two group work lists (in the class counter block)
+// Class L: two levels.  First the segment is split by its top 8 id bits into
+// 256 sub-buckets in global scratch, by parts of kPart ids: the digits of
+// every part are counted (segsort_wide), one block per segment turns the
+// counts into the parts' write positions and cuts the sub-buckets into groups
+// (segsort_part_scan), and every part is counting-sorted by digit in LDS and
+// written out as one run per digit (segsort_part_split).  Then groups of G
+// consecutive sub-buckets are sorted from scratch back into place by the
+// whole grid, one block per group (segsort_sub): G is chosen so that a group
+// holds at most 4096 ids, or at most 32768 (a 1024-thread block) when a
+// sub-bucket holds more than 4096 (segments of about a million ids).  A
+// segment with a sub-bucket over 32768 ids (ids far from uniform) is left as
+// it is and goes to the fallback list.
+//
+// Parts keep all CUs at work whatever the number of segments: with one block
+// per segment the split of 24 segments of 33K to 500K ids took 326 us (now
+// 36 us) and that of 12K such segments, 2.0G ids, 8.2 ms (now 6.4 ms: counts
+// 1.8, split 4.5, at 3.6 to 4.5 TB/s).
 
-// 1024 threads held to 64 registers (two blocks, 32 waves per CU; one 4-byte
-// spill, reloaded once per segment): the pass waits on LDS and memory, and
-// at 16 waves per CU (512 threads, 122 registers) the 50M-rectangle loop's
-// sort took 16.1 instead of 15.5 ms.
-template <int T>
-__global__ void __launch_bounds__(T, 8)
-segsort_long(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, uint32_t *__restrict__ scratch,
-             uint32_t *__restrict__ desc, uint32_t *__restrict__ sub_lists, uint32_t *__restrict__ sub_lists_wide,
-             uint32_t *__restrict__ sub_counts,
-             const uint32_t *__restrict__ list, const uint32_t *__restrict__ list_count,
-             uint32_t *__restrict__ fb_list, uint32_t *__restrict__ fb_count, uint32_t id_range,
+// The parts of the XCD-contiguous share that workgroup wg of nwg works on
+// (workgroups go round the 8 XCDs): parts of one segment write into the same
+// lines of scratch, which meet in one XCD's L2 this way.
+struct PartShare {
+    uint32_t k, end, step;
+};
+__device__ __forceinline__ PartShare part_share(uint32_t n, uint32_t wg, uint32_t nwg) {
+    if (nwg < 8 || (nwg & 7u)) return {wg, n, nwg};
+    const uint32_t per = (n + 7) / 8, x = wg & 7u;
+    const uint32_t lo = min(n, x * per), hi = min(n, lo + per);
+    return {lo + (wg >> 3), hi, nwg >> 3};
+}
+
+// Segments of 16385 .. 32768 ids (class M), then the digit counts of the
+// class-L parts: one launch for both, as most batches have few of either.
+__global__ void __launch_bounds__(1024, 4)
+segsort_wide(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ lists,
+             uint64_t nq, const uint32_t *__restrict__ counts, LongWs lw, uint32_t id_range,
              const uint32_t *__restrict__ seg_range) {
-    constexpr uint32_t W = T / 64, R = kLongChunk / T;
-    static_assert(T >= kLongDigits, "one thread per digit");
-    __shared__ uint32_t whist[W * kLongDigits];   // per-wave digit counts
-    __shared__ uint32_t stage[kLongChunk];        // digit-sorted chunk
-    __shared__ uint32_t start[kLongDigits + 1];   // sub-bucket starts (start[256] = c)
-    __shared__ uint32_t cur[kLongDigits];         // write cursor per digit
-    __shared__ uint32_t lh[kLongDigits], loff[kLongDigits], lcur[kLongDigits];
-    __shared__ uint32_t big, subbase[1];
-    const uint32_t m = *list_count;
-    const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
+    constexpr uint32_t T = 1024, K = 32, A = 8, N = T * K, R = kPart / T;
+    __shared__ uint32_t lds[N + N / A];
+    const uint32_t *list = lists + 4 * nq;
+    const uint32_t m = counts[4], np = counts[kPartCount];
     for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
         const uint32_t q = list[li];
-        const int id_bits = range_bits(seg_id_range(seg_range, q, id_range));
-        const int db = id_bits < 8 ? id_bits : 8;
-        const int sh = id_bits - db;
-        const uint32_t dmask = (1u << db) - 1u;
         const uint64_t o = offsets[q];
         const uint32_t c = (uint32_t)(offsets[q + 1] - o);
-        const uint32_t *seg = ids + o;
-        uint32_t *tmp = scratch + o;
-        uint32_t *dsc = desc + (uint64_t)li * kDesc;
-        // digit histogram
-        for (uint32_t i = t; i < W * kLongDigits; i += T) whist[i] = 0;
-        if (t == 0) big = 0;
+        uint32_t key[K];
+        load_keys<T, K>(ids + o, c, key);
+        block_sort_keys<T, K, false, A>(key, ids + o, c, seg_id_range(seg_range, q, id_range), lds, lds + N, lds);
+    }
+    list = lists + kLong * nq;
+    const uint32_t t = threadIdx.x;
+    uint32_t *h = lds;   // two sets of counters in turn: one barrier less per part
+    struct Part {
+        uint64_t o;
+        uint32_t len, sh;
+    };
+    auto part = [&](uint32_t k) {
+        const uint32_t li = lw.parts[k], q = list[li];
+        const uint32_t p = k - lw.desc[(uint64_t)li * kDesc + kDescPart];
+        const uint64_t o = offsets[q], at = (uint64_t)p * kPart, c = offsets[q + 1] - o;
+        const int id_bits = range_bits(seg_id_range(seg_range, q, id_range));
+        Part r;
+        r.o = o + at;
+        r.len = (uint32_t)min((uint64_t)kPart, c - at);
+        r.sh = (uint32_t)(id_bits - (id_bits < 8 ? id_bits : 8));
+        return r;
+    };
+    uint32_t nkey[R];
+    Part nx{0, 0, 0};
+    // the M segments went to the first blocks: the parts start behind them
+    const uint32_t g = gridDim.x, b0 = (blockIdx.x + g - m % g) % g;
+    if (b0 < np) {
+        nx = part(b0);
+        load_keys<T, R>(ids + nx.o, nx.len, nkey);
+    }
+    for (uint32_t k = b0; k < np; k += g) {
+        if (t < kLongDigits) h[t] = 0;
         __syncthreads();
-        constexpr uint32_t U = 8192 / T;   // loads in flight per thread
-        for (uint32_t i0 = t; i0 < c; i0 += T * U) {
-            uint32_t kk[U];
+        const Part cu = nx;
+        uint32_t key[R];
 #pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t i = i0 + u * T;
-                kk[u] = i < c ? seg[i] : 0u;
+        for (uint32_t r = 0; r < R; ++r) key[r] = nkey[r];
+        if (k + g < np) {
+            nx = part(k + g);
+            load_keys<T, R>(ids + nx.o, nx.len, nkey);
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r)
+            if (r * T + t < cu.len) atomicAdd(&h[min(key[r] >> cu.sh, kLongDigits - 1)], 1u);
+        __syncthreads();
+        if (t < kLongDigits) lw.hist[(uint64_t)k * kLongDigits + t] = h[t];
+        h = h == lds ? lds + kLongDigits : lds;
+    }
+}
+
+// Exclusive scan of one value per thread of a 256-thread block; tot and mx:
+// the sum and the largest value.  w4: 8 words of LDS.
+__device__ __forceinline__ uint32_t scan_digits(uint32_t v, uint32_t *w4, uint32_t &tot, uint32_t &mx) {
+    const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+    uint32_t inc = v;
+    mx = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t x = __shfl_up(inc, d);
+        if ((int)lane >= d) inc += x;
+        mx = max(mx, (uint32_t)__shfl_xor((int)mx, d));
+    }
+    if (lane == 63) w4[w] = inc;
+    if (lane == 0) w4[4 + w] = mx;
+    __syncthreads();
+    uint32_t ex = inc - v;
+    tot = mx = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+        if (i < w) ex += w4[i];
+        tot += w4[i];
+        mx = max(mx, w4[4 + i]);
+    }
+    return ex;
+}
+
+// One block per class-L segment, one thread per digit: the parts' counts
+// become positions (exclusive over the parts), the digits' totals the
+// sub-bucket starts, and the groups are listed.  Latency-bound: eight rows of
+// counts in flight.
+__global__ void __launch_bounds__(256)
+segsort_part_scan(const uint64_t *__restrict__ offsets, const uint32_t *__restrict__ list,
+                  const uint32_t *__restrict__ list_count, LongWs lw, uint32_t *__restrict__ sub_counts,
+                  uint32_t *__restrict__ fb_list, uint32_t *__restrict__ fb_count) {
+    __shared__ uint32_t w4[8], subbase;
+    static_assert(kLongDigits == 256, "one thread per digit");
+    const uint32_t m = *list_count, t = threadIdx.x;
+    for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
+        const uint32_t q = list[li];
+        uint32_t *dsc = lw.desc + (uint64_t)li * kDesc;
+        const uint32_t np = num_parts(offsets[q + 1] - offsets[q]);
+        uint32_t *h = lw.hist + (uint64_t)dsc[kDescPart] * kLongDigits + t;
+        uint32_t run = 0;
+        for (uint32_t p = 0; p < np; p += 8) {
+            uint32_t v[8];
+#pragma unroll
+            for (uint32_t j = 0; j < 8; ++j) v[j] = p + j < np ? h[(uint64_t)(p + j) * kLongDigits] : 0u;
+#pragma unroll
+            for (uint32_t j = 0; j < 8; ++j) {
+                if (p + j < np) h[(uint64_t)(p + j) * kLongDigits] = run;
+                run += v[j];
             }
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u)
-                if (i0 + u * T < c) atomicAdd(&whist[w * kLongDigits + ((kk[u] >> sh) & dmask)], 1u);
+        }
+        uint32_t tot, big;
+        const uint32_t st = scan_digits(run, w4, tot, big);
+        dsc[t] = st;
+        // groups of G consecutive digits: G = (group limit) / (largest digit
+        // count), so a group never exceeds the limit: kSubMax ids for the
+        // 256-thread sort, or, when a digit holds more (segments of about a
+        // million ids), kSubBigMax for the 1024-thread sort (its own list);
+        // work items are li << 8 | group
+        const bool fallback = big > kSubBigMax, wide = big > kSubMax;
+        const uint32_t G = fallback ? 0u : (wide ? kSubBigMax : kSubMax) / big;
+        const uint32_t ngroups = G ? (kLongDigits + G - 1) / G : 0u;
+        if (t == 0) {
+            dsc[kLongDigits] = tot;
+            dsc[kDescGroup] = G;
+            if (fallback)
+                fb_list[atomicAdd(fb_count, 1u)] = q;
+            else
+                subbase = atomicAdd(&sub_counts[wide ? 1 : 0], ngroups);
         }
         __syncthreads();
-        if (w == 0) {   // one wave: totals and exclusive scan over the 256 digits
-            uint32_t v[4], sum = 0, mx = 0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t d = lane * 4 + r;
-                uint32_t x = 0;
-                for (uint32_t ww = 0; ww < W; ++ww) x += whist[ww * kLongDigits + d];
-                v[r] = x;
-                sum += x;
-                mx = max(mx, x);
-            }
-            uint32_t inc = sum;
+        if (t < ngroups) (wide ? lw.sub_wide : lw.sub)[subbase + t] = (li << 8) | t;
+        __syncthreads();
+    }
+}
+
+// One block per part: its ids are ranked by digit with LDS cursors (the
+// counts are known, so one atomic per id), staged in digit order and written
+// as one run per group (a group's order within scratch does not matter, as
+// it is sorted next).  Two blocks of 1024 threads per CU.
+template <int T>
+__global__ void __launch_bounds__(T, 8)
+segsort_part_split(const uint64_t *__restrict__ offsets, const uint32_t *__restrict__ ids,
+                   uint32_t *__restrict__ scratch, const uint32_t *__restrict__ list,
+                   const uint32_t *__restrict__ part_count, LongWs lw, uint32_t id_range,
+                   const uint32_t *__restrict__ seg_range) {
+    constexpr uint32_t R = kPart / T;
+    __shared__ uint32_t stage[kPart];
+    __shared__ uint32_t lcur[kLongDigits], gpos[kLongDigits];   // cursor in stage; scratch position minus stage position
+    __shared__ uint32_t psum[kLongDigits + 1], w4[8];
+    const uint32_t t = threadIdx.x;
+    const PartShare ps = part_share(*part_count, blockIdx.x, gridDim.x);
+    for (uint32_t k = ps.k; k < ps.end; k += ps.step) {
+        const uint32_t li = lw.parts[k], q = list[li];
+        const uint32_t *dsc = lw.desc + (uint64_t)li * kDesc;
+        const uint32_t p = k - dsc[kDescPart];
+        const uint32_t G = dsc[kDescGroup];
+        if (G == 0) continue;   // left to the fallback
+        const uint64_t o = offsets[q], at = (uint64_t)p * kPart, c = offsets[q + 1] - o;
+        const uint32_t len = (uint32_t)min((uint64_t)kPart, c - at);
+        const int id_bits = range_bits(seg_id_range(seg_range, q, id_range));
+        const uint32_t sh = (uint32_t)(id_bits - (id_bits < 8 ? id_bits : 8));
+        uint32_t key[R];
+        load_keys<T, R>(ids + o + at, len, key);
+        // thread t: digit t's count in this part and its ids in the parts before
+        uint32_t cnt = 0, pre = 0, ec = 0, ep = 0;
+        const uint32_t lane = t & 63u;
+        if (t < kLongDigits) {
+            const uint32_t *row = lw.hist + (uint64_t)k * kLongDigits + t;
+            pre = row[0];
+            cnt = (at + kPart < c ? row[kLongDigits] : dsc[t + 1] - dsc[t]) - pre;
+            ec = cnt;
+            ep = pre;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t x = __shfl_up(inc, d);
-                if ((int)lane >= d) inc += x;
-                mx = max(mx, (uint32_t)__shfl_xor((int)mx, d));
+                const uint32_t x = __shfl_up(ec, d), y = __shfl_up(ep, d);
+                if ((int)lane >= d) {
+                    ec += x;
+                    ep += y;
+                }
             }
-            uint32_t ex = inc - sum;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                start[lane * 4 + r] = ex;
-                cur[lane * 4 + r] = ex;
-                ex += v[r];
+            if (lane == 63) {
+                w4[t >> 6] = ec;
+                w4[4 + (t >> 6)] = ep;
             }
-            if (lane == 63) start[kLongDigits] = inc;
-            if (lane == 0) big = mx;
         }
         __syncthreads();
-        if (big > kSubBigMax) {   // leave the segment to the fallback
-            if (t == 0) fb_list[atomicAdd(fb_count, 1u)] = q;
-            __syncthreads();
-            continue;
-        }
-        // sub-bucket groups for the block sorts: G consecutive digits each,
-        // G = (group limit) / (largest digit count), so a group never exceeds
-        // the limit: kSubMax ids for the 256-thread sort, or, when a digit
-        // holds more (segments of about a million ids), kSubBigMax for the
-        // 1024-thread sort (its own list); work items are li << 8 | group
-        const bool wide = big > kSubMax;
-        const uint32_t G = (wide ? kSubBigMax : kSubMax) / (big ? big : 1u);
-        const uint32_t ngroups = (kLongDigits + G - 1) / G;
-        for (uint32_t d = t; d <= kLongDigits; d += T) dsc[d] = start[d];
-        if (t == 0) {
-            dsc[kLongDigits + 1] = G;
-            subbase[0] = atomicAdd(&sub_counts[wide ? 1 : 0], ngroups);
+        if (t < kLongDigits) {
+            for (uint32_t i = 0; i < (t >> 6); ++i) {
+                ec += w4[i];
+                ep += w4[4 + i];
+            }
+            lcur[t] = ec -= cnt;
+            psum[t] = ep -= pre;
+            if (t == kLongDigits - 1) psum[kLongDigits] = ep + pre;
         }
         __syncthreads();
-        if (t < ngroups) (wide ? sub_lists_wide : sub_lists)[subbase[0] + t] = (li << 8) | t;
-        // chunks, digit-sorted in LDS, written out as runs; the next chunk's
-        // ids are loaded while this one is sorted and written
-        uint32_t nkey[R];
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r) {
-            const uint32_t i = r * T + t;
-            nkey[r] = i < c ? seg[i] : 0u;
+        if (t < kLongDigits) {
+            // first digit of the group, its end: the part's run goes behind
+            // the group's ids of the parts before
+            const uint32_t d0 = t - t % G, d1 = min(d0 + G, kLongDigits);
+            gpos[t] = dsc[d0] + (psum[d1] - psum[d0]) - lcur[d0];
         }
-        for (uint32_t base = 0; base < c; base += kLongChunk) {
-            const uint32_t len = (c - base) < kLongChunk ? (c - base) : kLongChunk;
-            if (t < kLongDigits) lh[t] = 0;
-            __syncthreads();
-            uint32_t key[R];
+        __syncthreads();
 #pragma unroll
-            for (uint32_t r = 0; r < R; ++r) {
-                key[r] = nkey[r];
-                if (r * T + t < len) atomicAdd(&lh[(key[r] >> sh) & dmask], 1u);
-            }
-            const uint32_t nb = base + kLongChunk;
-#pragma unroll
-            for (uint32_t r = 0; r < R; ++r) {
-                const uint32_t i = r * T + t;
-                nkey[r] = nb + i < c ? seg[nb + i] : 0u;
-            }
-            __syncthreads();
-            if (w == 0) {
-                uint32_t v[4], sum = 0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    v[r] = lh[lane * 4 + r];
-                    sum += v[r];
-                }
-                uint32_t inc = sum;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t x = __shfl_up(inc, d);
-                    if ((int)lane >= d) inc += x;
-                }
-                uint32_t ex = inc - sum;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    loff[lane * 4 + r] = ex;
-                    lcur[lane * 4 + r] = ex;
-                    ex += v[r];
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (uint32_t r = 0; r < R; ++r) {
-                const uint32_t i = r * T + t;
-                if (i < len) stage[atomicAdd(&lcur[(key[r] >> sh) & dmask], 1u)] = key[r];
-            }
-            __syncthreads();
-            for (uint32_t j = t; j < len; j += T) {
-                const uint32_t x = stage[j];
-                const uint32_t d = (x >> sh) & dmask;
-                tmp[cur[d] + (j - loff[d])] = x;
-            }
-            __syncthreads();
-            if (t < kLongDigits) cur[t] += lh[t];
-            __syncthreads();
+        for (uint32_t r = 0; r < R; ++r)
+            if (r * T + t < len) stage[atomicAdd(&lcur[min(key[r] >> sh, kLongDigits - 1)], 1u)] = key[r];
+        __syncthreads();
+        uint32_t *tmp = scratch + o;
+        for (uint32_t j = t; j < len; j += T) {
+            const uint32_t x = stage[j];
+            tmp[gpos[min(x >> sh, kLongDigits - 1)] + j] = x;
         }
+        __syncthreads();
     }
 }
 
@@ -733,22 +841,12 @@ segsort_long(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, u
 // Two shapes: 256 x 16 for groups of at most kSubMax ids, 1024 x 32 for the
 // groups of segments whose digits hold more.  With PF the next group's ids
 // are loaded before the current one is sorted.
-template <int T, int K>
-constexpr int sub_waves_per_simd() {
-    return T == 256 ? 6 : 4;
-}
-
 template <int T, int K, int A, bool PF>
-__global__ void __launch_bounds__(T, (sub_waves_per_simd<T, K>()))
-segsort_sub(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch,
-            const uint32_t *__restrict__ desc, const uint32_t *__restrict__ items,
-            const uint32_t *__restrict__ item_count, const uint32_t *__restrict__ list, uint32_t id_range,
-            const uint32_t *__restrict__ seg_range) {
-    constexpr uint32_t N = T * K;
-    __shared__ uint32_t buf[N];
-    __shared__ uint32_t cnt[N / A];
-    __shared__ uint32_t wsum[2 * (T / 64)];
-    const uint32_t m = *item_count;
+__device__ __forceinline__ void
+sort_groups(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch,
+            const uint32_t *__restrict__ desc, const uint32_t *__restrict__ items, uint32_t m,
+            const uint32_t *__restrict__ list, uint32_t id_range, const uint32_t *__restrict__ seg_range,
+            uint32_t *buf, uint32_t *cnt, uint32_t *wsum) {
     struct Grp {
         uint64_t o;
         uint32_t n, base, range;
@@ -756,7 +854,7 @@ segsort_sub(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, co
     auto group = [&](uint32_t k) {
         const uint32_t it = items[k], li = it >> 8, g = it & 255u;
         const uint32_t *dsc = desc + (uint64_t)li * kDesc;
-        const uint32_t G = dsc[kLongDigits + 1];
+        const uint32_t G = dsc[kDescGroup];
         const uint32_t d0 = g * G, d1 = (d0 + G) < kLongDigits ? (d0 + G) : kLongDigits;
         const uint32_t s0 = dsc[d0];
         const uint32_t q = list[li];
@@ -797,6 +895,16 @@ segsort_sub(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, co
             block_sort_keys<T, K, false, A>(key, ids + cu.o, cu.n, cu.range, buf, cnt, wsum, cu.base);
         }
     }
+}
+
+__global__ void __launch_bounds__(256, 6)
+segsort_sub(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch,
+            LongWs lw, const uint32_t *__restrict__ item_count, const uint32_t *__restrict__ list, uint32_t id_range,
+            const uint32_t *__restrict__ seg_range) {
+    constexpr int T = 256, K = 16, A = 4;
+    __shared__ uint32_t lds[T * K + T * K / A], wsum[2 * (T / 64)];
+    sort_groups<T, K, A, true>(offsets, ids, scratch, lw.desc, lw.sub, *item_count, list, id_range, seg_range, lds,
+                               lds + T * K, wsum);
 }
 
 // ---------------------------------------------------------------------------
@@ -849,13 +957,10 @@ __device__ __forceinline__ uint64_t glb_merge_path(const uint32_t *a, uint64_t l
 // Each listed segment: its 16384-id tiles sorted, then the runs merged
 // pairwise until one is left; every merge proceeds in windows of 16384 outputs
 // whose inputs are staged in LDS.
-__global__ void __launch_bounds__(1024)
-segsort_skewed(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, uint32_t *__restrict__ scratch,
-              const uint32_t *__restrict__ list, const uint32_t *__restrict__ list_count) {
+__device__ void sort_skewed(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids,
+                            uint32_t *__restrict__ scratch, const uint32_t *__restrict__ list, uint32_t m,
+                            uint32_t *lds, uint64_t *split) {
     constexpr uint32_t T = 1024, K = 16, N = T * K;
-    __shared__ uint32_t lds[N + N / 32];
-    __shared__ uint64_t split[2];
-    const uint32_t m = *list_count;
     for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
         const uint64_t q = list[li];
         const uint64_t o = offsets[q];
@@ -924,6 +1029,21 @@ segsort_skewed(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids,
     }
 }
 
+// The wide groups, then the fallback segments: one launch, as both are almost
+// always empty (segments of about a million ids; skewed ids).
+__global__ void __launch_bounds__(1024, 4)
+segsort_rest(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, uint32_t *__restrict__ scratch,
+             LongWs lw, const uint32_t *__restrict__ counts, const uint32_t *__restrict__ lists, uint64_t nq,
+             uint32_t id_range, const uint32_t *__restrict__ seg_range) {
+    constexpr int T = 1024, K = 32, A = 8;
+    __shared__ uint32_t lds[T * K + T * K / A], wsum[2 * (T / 64)];
+    __shared__ uint64_t split[2];
+    static_assert(T * K >= kTileMax + kTileMax / 32, "a padded merge window");
+    sort_groups<T, K, A, false>(offsets, ids, scratch, lw.desc, lw.sub_wide, counts[kSubCounts + 1],
+                                lists + kLong * nq, id_range, seg_range, lds, lds + T * K, wsum);
+    sort_skewed(offsets, ids, scratch, lists + kFallback * nq, counts[kFallback], lds, split);
+}
+
 // Batches of at most kFewMax segments: one block per segment sorts it if it
 // has at most 4096 ids and lists it for the longer shapes otherwise, so that a
 // small select needs no classification pass and one launch where its ids are
@@ -933,7 +1053,7 @@ constexpr uint32_t kFewIds = 4096;
 
 __global__ void __launch_bounds__(256, 6)
 segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uint32_t *__restrict__ ids,
-            uint32_t *__restrict__ lists, uint32_t *__restrict__ counts, uint32_t id_range,
+            uint32_t *__restrict__ lists, uint32_t *__restrict__ counts, LongWs lw, uint32_t id_range,
             const uint32_t *__restrict__ seg_range, const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
     constexpr uint32_t T = 256, K = 16, N = T * K;
     static_assert(N == kFewIds, "one tile per segment");
@@ -943,10 +1063,15 @@ segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uin
     const uint64_t o = offsets[q], len = offsets[q + 1] - o;
     if (len < 2 || offsets[nq] > cap) return;
     if (len > kFewIds) {
+        const uint32_t np = len > kMidMax ? num_parts(len) : 0u;
         if (threadIdx.x == 0) {
-            const uint32_t j = len <= kMidMax ? 4u : kLong;
-            lists[(uint64_t)j * nq + atomicAdd(&counts[j], 1u)] = q;
+            const uint32_t j = np ? kLong : 4u, li = atomicAdd(&counts[j], 1u);
+            lists[(uint64_t)j * nq + li] = q;
+            lds[0] = li;
+            if (np) lw.desc[(uint64_t)li * kDesc + kDescPart] = lds[1] = atomicAdd(&counts[kPartCount], np);
         }
+        __syncthreads();
+        for (uint32_t p = threadIdx.x; p < np; p += T) lw.parts[lds[1] + p] = lds[0];
         return;
     }
     const uint32_t c = (uint32_t)len;
@@ -968,10 +1093,15 @@ segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uin
 
 uint64_t segsort_ws_elems(uint64_t nq) { return (uint64_t)kListCls * nq + kSortCounters; }
 
+// Class-L segments and parts that cap ids can hold at most.
+static uint64_t most_long(uint64_t cap) { return cap / (kMidMax + 1) + 1; }
+static uint64_t most_parts(uint64_t cap) { return cap / kPart + most_long(cap); }
+
 // cap ids, then for each possible class-L segment (> kMidMax ids) its
-// descriptor, then two lists with room for 256 work items per segment
+// descriptor and two lists with room for 256 groups, then the part list and
+// the parts' counts
 uint64_t segsort_scratch_elems(uint64_t cap) {
-    return cap + (cap / (kMidMax + 1) + 1) * (kDesc + 2 * kLongDigits);
+    return cap + most_long(cap) * (kDesc + 2 * kLongDigits) + most_parts(cap) * (1 + kLongDigits);
 }
 
 template <typename Kern>
@@ -995,16 +1125,22 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
     static const uint32_t g_m1 = resident_per_cu(segsort_mid<128, 8, true, true, 4>, 128);
     static const uint32_t g_m2 = resident_per_cu(segsort_mid<256, 16, false, true, 4>, 256);
     static const uint32_t g_m3 = resident_per_cu(segsort_mid<512, 32, false, true, 8>, 512);
-    static const uint32_t g_m4 = resident_per_cu(segsort_mid<1024, 32, false, false, 8>, 1024);
-    static const uint32_t g_long = resident_per_cu(segsort_long<1024>, 1024);
-    static const uint32_t g_sub = resident_per_cu(segsort_sub<256, 16, 4, true>, 256);
-    static const uint32_t g_subw = resident_per_cu(segsort_sub<1024, 32, 8, false>, 1024);
+    static const uint32_t g_wide = resident_per_cu(segsort_wide, 1024);
+    static const uint32_t g_split = resident_per_cu(segsort_part_split<1024>, 1024);
+    static const uint32_t g_sub = resident_per_cu(segsort_sub, 256);
+    static const uint32_t g_rest = resident_per_cu(segsort_rest, 1024);
     // no more blocks than the class can have work items: nq segments, or as
     // many longer than `longer` as fit the capacity (none: no launch)
     auto most = [&](uint32_t longer) { return std::min<uint64_t>(nq, cap / (longer + 1ull)); };
     auto grid = [&](uint32_t resident, uint64_t items) {
         return dim3((uint32_t)std::min<uint64_t>((uint64_t)cus * resident, items));
     };
+    LongWs lw;
+    lw.desc = scratch + cap;
+    lw.sub = lw.desc + most_long(cap) * kDesc;
+    lw.sub_wide = lw.sub + most_long(cap) * kLongDigits;
+    lw.parts = lw.sub_wide + most_long(cap) * kLongDigits;
+    lw.hist = lw.parts + most_parts(cap);
     hipError_t e = hipSuccess;
     if (!zeroed) e = launch_zero(counts, kSortCounters * 4, s);
     if (e != hipSuccess) return e;
@@ -1013,14 +1149,14 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
     // whatever else the process runs concurrently)
     if (nq <= kFewMax) {
         hipLaunchKernelGGL(segsort_few, dim3((uint32_t)nq), dim3(256), 0, s, offsets, (uint32_t)nq, cap, ids, lists,
-                           counts, range, seg_range, ctrl, status);
+                           counts, lw, range, seg_range, ctrl, status);
     } else {
         if (nq <= 262144)
             hipLaunchKernelGGL(seg_classify<2>, dim3((uint32_t)((nq + 511) / 512)), dim3(256), 0, s, offsets, nq, cap,
-                               lists, counts, ctrl, status);
+                               lists, counts, lw, ctrl, status);
         else
             hipLaunchKernelGGL(seg_classify<16>, dim3((uint32_t)((nq + 4095) / 4096)), dim3(256), 0, s, offsets, nq,
-                               cap, lists, counts, ctrl, status);
+                               cap, lists, counts, lw, ctrl, status);
         if (most(1))
             hipLaunchKernelGGL(segsort_small, grid(g_small, (most(1) + 3) / 4), dim3(256), 0, s, offsets, ids, lists,
                                counts + 0);
@@ -1035,29 +1171,19 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
                                offsets, ids, lists + 3 * nq, counts + 3, range, seg_range);
     }
     const uint32_t wide_min = nq <= kFewMax ? kFewIds : 16384;
+    const uint64_t nl = most(kMidMax), np = nl ? cap / kPart + nl : 0;   // class-L segments and parts at most
     if (most(wide_min))
-        hipLaunchKernelGGL((segsort_mid<1024, 32, false, false, 8>), grid(g_m4, most(wide_min)), dim3(1024), 0, s,
-                           offsets, ids, lists + 4 * nq, counts + 4, range, seg_range);
-    const uint64_t nl = most(kMidMax);   // class-L segments at most
+        hipLaunchKernelGGL(segsort_wide, grid(g_wide, std::max(most(wide_min), np)), dim3(1024), 0, s, offsets, ids,
+                           lists, nq, counts, lw, range, seg_range);
     if (nl) {
-        // after the cap ids of scratch: kDesc words per class-L segment (257
-        // sub-bucket starts and the group width), then its work items (at
-        // most 256 groups per segment)
-        const uint64_t nlong = cap / (kMidMax + 1) + 1;
-        uint32_t *desc = scratch + cap;
-        uint32_t *sub_list = desc + nlong * kDesc;
-        uint32_t *sub_list_wide = sub_list + nlong * kLongDigits;
-        hipLaunchKernelGGL(segsort_long<1024>, grid(g_long, nl), dim3(1024), 0, s, offsets, ids, scratch, desc,
-                           sub_list, sub_list_wide, counts + kSubCounts, lists + kLong * nq, counts + kLong,
-                           lists + kFallback * nq, counts + kFallback, range, seg_range);
-        hipLaunchKernelGGL((segsort_sub<256, 16, 4, true>), grid(g_sub, nl * kLongDigits), dim3(256), 0, s, offsets,
-                           ids, scratch, desc, sub_list, counts + kSubCounts, lists + kLong * nq, range, seg_range);
-        hipLaunchKernelGGL((segsort_sub<1024, 32, 8, false>), grid(g_subw, nl * kLongDigits), dim3(1024), 0, s,
-                           offsets, ids, scratch, desc, sub_list_wide, counts + kSubCounts + 1, lists + kLong * nq,
-                           range, seg_range);
-        // skewed ids: almost always empty
-        hipLaunchKernelGGL(segsort_skewed, grid(2, nl), dim3(1024), 0, s, offsets, ids, scratch,
-                           lists + kFallback * nq, counts + kFallback);
+        hipLaunchKernelGGL(segsort_part_scan, grid(8, nl), dim3(256), 0, s, offsets, lists + kLong * nq,
+                           counts + kLong, lw, counts + kSubCounts, lists + kFallback * nq, counts + kFallback);
+        hipLaunchKernelGGL(segsort_part_split<1024>, grid(g_split, np), dim3(1024), 0, s, offsets, ids, scratch,
+                           lists + kLong * nq, counts + kPartCount, lw, range, seg_range);
+        hipLaunchKernelGGL(segsort_sub, grid(g_sub, nl * kLongDigits), dim3(256), 0, s, offsets, ids, scratch, lw,
+                           counts + kSubCounts, lists + kLong * nq, range, seg_range);
+        hipLaunchKernelGGL(segsort_rest, grid(g_rest, nl * kLongDigits), dim3(1024), 0, s, offsets, ids, scratch, lw,
+                           counts, lists, nq, range, seg_range);
     }
     return hipGetLastError();
 }
