@@ -144,13 +144,22 @@ hipError_t block_alloc(int dev, uint64_t bytes, void **p, uint64_t *got) {
 void block_free(int dev, void *p, uint64_t bytes) {
     if (!p) return;
     if (dev >= 0 && dev < kPoolDevices && bytes <= kBlockMax && hipDeviceSynchronize() == hipSuccess) {
-        DevPool &d = g_pool[dev];
-        std::lock_guard<std::mutex> lk(d.mu);
-        if (d.blocks.size() < kBlocksKept && d.block_bytes + bytes <= kBlocksMax) {
+        // the longest kept make room: a program that moved on to other sizes
+        // reuses its own blocks again
+        std::vector<Block> old;
+        {
+            DevPool &d = g_pool[dev];
+            std::lock_guard<std::mutex> lk(d.mu);
+            size_t n = 0;
+            while (d.blocks.size() - n >= kBlocksKept || d.block_bytes + bytes > kBlocksMax)
+                d.block_bytes -= d.blocks[n++].bytes;
+            old.assign(d.blocks.begin(), d.blocks.begin() + (long)n);
+            d.blocks.erase(d.blocks.begin(), d.blocks.begin() + (long)n);
             d.blocks.push_back(Block{p, bytes});
             d.block_bytes += bytes;
-            return;
         }
+        for (const Block &b : old) (void)hipFree(b.p);
+        return;
     }
     (void)hipFree(p);
 }
