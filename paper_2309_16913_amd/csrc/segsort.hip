@@ -9,13 +9,12 @@
 //   class S    (<= 256 ids)     one wave per segment: the ids sit in
 //              registers (up to 4 per lane) and a bitonic network runs over
 //              them with __shfl_xor for cross-lane partners;
-//   class M    (257 .. 32768, in four block shapes: 128 x 8, 256 x 16,
-//              512 x 32 and 1024 x 32 threads x ids)  one block per segment:
-//              ids to registers, a counting sort on the top b id bits
-//              (2^b ~ length/4 buckets, LDS counters), scatter into LDS,
-//              then every bucket sorted in place by a register network (or,
-//              for the shortest, each id counts the smaller ids of its own
-//              bucket and is stored at bucket start + that count);
+//   class M    (257 .. 32768, in four block shapes: 64 x 16, 128 x 32, 512 x 32
+//              and 1024 x 32 threads x ids)  one block per segment: ids to
+//              registers, a counting sort on the top b id bits (2^b ~
+//              length/4 buckets, LDS counters), scatter into LDS, then rounds
+//              that sort and merge neighbouring runs of 8 ids in registers
+//              until every bucket is in order;
 //   class L    (> 32768)        an MSD pass on the top 8 id bits into global
 //              scratch, cut into parts of 16384 ids so that one segment
 //              occupies many blocks (digit counts per part, a scan over a
@@ -23,8 +22,8 @@
 //              runs), then groups of consecutive sub-buckets (<= 4096 ids
 //              each, or <= 32768 when a sub-bucket holds more) sorted back by
 //              one block each;
-//   fallback   a segment with a bucket too long for the in-bucket ranking
-//              (ids far from uniform) is sorted by a block bitonic network in
+//   fallback   a segment with a bucket too long for these rounds (ids far
+//              from uniform) is sorted by a block bitonic network in
 //              LDS (class M) or, for class L with a sub-bucket over 32768 ids,
 //              by sorting 16384-id tiles that way and merging runs pairwise
 //              through LDS-staged merge-path windows.
@@ -53,11 +52,7 @@ __device__ __forceinline__ uint32_t seg_id_range(const uint32_t *seg_range, uint
     return seg_range ? seg_range[q] : id_range;
 }
 
-__device__ __forceinline__ uint32_t ceil_log2(uint32_t v) {
-    uint32_t b = 0;
-    while (b < 31 && (1u << b) < v) ++b;
-    return b;
-}
+__device__ __forceinline__ constexpr uint32_t ceil_log2(uint32_t v) { return v > 1 ? 32 - __builtin_clz(v - 1) : 0; }
 
 // The key of lane (lane ^ j), for the constant distances of a bitonic
 // network: a DPP quad permutation for 1 and 2 (an ordinary vector move), the
@@ -133,22 +128,53 @@ constexpr uint32_t kPart = 16384;       // ids per part of a class-L segment
 constexpr uint32_t kSubMax = 4096;      // longest group sorted by a 256-thread block
 constexpr uint32_t kSubBigMax = 32768;  // longest group sorted by a 1024-thread block
 // descriptor of a class-L segment: 257 sub-bucket starts, the digits per
-// group (0: the segment went to the fallback), the index of its first part
-constexpr uint32_t kDescGroup = kLongDigits + 1, kDescPart = kLongDigits + 2, kDesc = kLongDigits + 3;
+// group (0: the segment went to the fallback), the index of its first part,
+// its place in ids (two words)
+constexpr uint32_t kDescGroup = kLongDigits + 1, kDescPart = kLongDigits + 2, kDescOff = kLongDigits + 3;
+constexpr uint32_t kDesc = kLongDigits + 5;
 constexpr uint32_t kSubCounts = 8;      // counters of the two group work lists (in the class counter block)
 constexpr uint32_t kPartCount = 10;     // counter of the part list
 
-// Behind the cap ids of the scratch.  A part list entry is its segment's
-// place in the class-L list; the parts of a segment are consecutive entries.
+// Work items hold all that is needed to load their ids, so that a block reads
+// one item ahead and never waits for a chain of dependent loads.  A run of at
+// most 32768 ids: its place in ids in y and the low half of z, its length in
+// the high half.
+struct Run {
+    uint64_t o;
+    uint32_t n;
+};
+__device__ __forceinline__ Run run_of(uint4 it) {
+    return {(uint64_t)(it.z & 0xFFFFu) << 32 | it.y, it.z >> 16};
+}
+__device__ __forceinline__ uint4 run_item(uint32_t x, uint64_t o, uint32_t n, uint32_t w) {
+    return make_uint4(x, (uint32_t)o, (uint32_t)(o >> 32) | n << 16, w);
+}
+
+// Behind the cap ids of the scratch.
 struct LongWs {
+    uint4 *sub;           // groups {first id, run, id range}: those of the 256-thread sorts from the front,
+    uint4 *sub_end;       // those of the 1024-thread sorts from the end; at most 256 per segment
+    uint4 *parts;         // parts {place in the class-L list, top bit set in the last, run, digit shift};
+                          // a segment's follow each other
     uint32_t *desc;       // kDesc words per class-L segment
-    uint32_t *sub;        // group lists (256- and 1024-thread sorts), at most 256 groups per segment
-    uint32_t *sub_wide;
-    uint32_t *parts;
     uint32_t *hist;       // per part: digit counts, then positions in the segment relative to the digits' starts
 };
+constexpr uint32_t kLastPart = 0x80000000u;
 
 __device__ __forceinline__ uint32_t num_parts(uint64_t len) { return (uint32_t)((len + kPart - 1) / kPart); }
+
+// Right shift that leaves the digit (the top 8 bits) of ids below range.
+__device__ __forceinline__ uint32_t digit_shift(uint32_t range) {
+    const int b = range_bits(range);
+    return (uint32_t)(b < 8 ? 0 : b - 8);
+}
+
+// Part p of np of the segment of len ids at o, li-th of its class.
+__device__ __forceinline__ uint4 part_item(uint32_t li, uint32_t p, uint32_t np, uint64_t o, uint64_t len,
+                                           uint32_t shift) {
+    const uint64_t at = (uint64_t)p * kPart;
+    return run_item(li | (p + 1 == np ? kLastPart : 0u), o + at, (uint32_t)min((uint64_t)kPart, len - at), shift);
+}
 
 // ---------------------------------------------------------------------------
 // classify
@@ -158,7 +184,8 @@ __device__ __forceinline__ uint32_t num_parts(uint64_t len) { return (uint32_t)(
 template <uint32_t PER>
 __global__ void __launch_bounds__(256)
 seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, uint32_t *__restrict__ lists,
-             uint32_t *__restrict__ counts, LongWs lw, const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
+             uint32_t *__restrict__ counts, LongWs lw, uint32_t id_range, const uint32_t *__restrict__ seg_range,
+             const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
     __shared__ uint32_t bcnt[kNumCls], gbase[kNumCls], bparts, pcur;
     if (status && blockIdx.x == 0 && threadIdx.x == 0) select_status(offsets, nq, cap, ctrl, status);
     if (offsets[nq] > cap) return;
@@ -204,10 +231,11 @@ seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, ui
         const uint64_t q = q0 + (uint64_t)k * 256 + threadIdx.x;
         if (c >= 0) lists[(uint64_t)c * nq + gbase[c] + pos[k]] = (uint32_t)q;
         if (c == (int)kLong) {
-            const uint32_t li = gbase[kLong] + pos[k], np = num_parts(offsets[q + 1] - offsets[q]);
-            const uint32_t p0 = atomicAdd(&pcur, np);
+            const uint64_t o = offsets[q], len = offsets[q + 1] - o;
+            const uint32_t li = gbase[kLong] + pos[k], np = num_parts(len);
+            const uint32_t p0 = atomicAdd(&pcur, np), sh = digit_shift(seg_id_range(seg_range, (uint32_t)q, id_range));
             lw.desc[(uint64_t)li * kDesc + kDescPart] = p0;
-            for (uint32_t p = 0; p < np; ++p) lw.parts[p0 + p] = li;
+            for (uint32_t p = 0; p < np; ++p) lw.parts[p0 + p] = part_item(li, p, np, o, len, sh);
         }
     }
 }
@@ -292,74 +320,90 @@ segsort_small(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, 
 // handful of ids.  One LDS counter per bucket first counts, is then turned
 // into the bucket's start by an exclusive scan, and serves as the scatter
 // cursor; after the scatter counter b holds the end of bucket b, so bucket b
-// spans [end(b-1), end(b)).  Every bucket is then sorted in place (one lane
-// per bucket, a register network).  A bucket of more than kRankMax ids (ids
-// far from uniform) sends the segment to a fallback.
-constexpr uint32_t kRankMax = 64;
+// spans [end(b-1), end(b)).  Then only the order within buckets is open, so
+// every id is within its bucket's length of its place, and a few rounds of
+// sorting and merging neighbouring runs of 8 ids finish the sort
+// (sort_near).  A bucket of more than kNearMax ids (ids far from uniform)
+// sends the segment to a fallback.
+constexpr uint32_t kNearMax = 256;   // 33 rounds; the bitonic fallback over 4096 ids: 78
 
-// Exclusive scan in place of cnt[0 .. nbk) by T threads (nbk <= 4*T or a
-// multiple of 4*T handled in rounds); returns the largest count.
+// Inclusive sum scan over the wave and its running maximum (lane 63: the
+// largest), as ordinary vector moves between lanes.  All lanes active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_0(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t row_sum(uint32_t v) {   // within each row of 16 lanes
+    v += dpp_or_0<0x111, 0xF>(v);
+    v += dpp_or_0<0x112, 0xF>(v);
+    v += dpp_or_0<0x114, 0xF>(v);
+    return v + dpp_or_0<0x118, 0xF>(v);
+}
+__device__ __forceinline__ uint32_t row_max(uint32_t v) {
+    v = max(v, dpp_or_0<0x111, 0xF>(v));
+    v = max(v, dpp_or_0<0x112, 0xF>(v));
+    v = max(v, dpp_or_0<0x114, 0xF>(v));
+    return max(v, dpp_or_0<0x118, 0xF>(v));
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+    v = row_sum(v);
+    v += dpp_or_0<0x142, 0xA>(v);   // last lane of a row to the next row
+    return v + dpp_or_0<0x143, 0xC>(v);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    v = row_max(v);
+    v = max(v, dpp_or_0<0x142, 0xA>(v));
+    return max(v, dpp_or_0<0x143, 0xC>(v));
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)lane);
+}
+
+// Exclusive scan in place of cnt[0 .. nbk) by T threads (nbk a multiple of
+// 4); returns the largest count.  wsum: 2*T/64 words.
 template <int T>
-__device__ uint32_t block_scan_counters(uint32_t *cnt, uint32_t nbk, uint32_t *wsum, uint32_t *scal) {
+__device__ uint32_t block_scan_counters(uint32_t *cnt, uint32_t nbk, uint32_t *wsum) {
     constexpr uint32_t W = T / 64;
-    const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
+    static_assert(W <= 16, "one row of lanes holds the waves' sums");
+    const uint32_t t = threadIdx.x, lane = t & 63u, w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    uint4 *c4 = reinterpret_cast<uint4 *>(cnt);
     uint32_t carry = 0, mxall = 0;
     for (uint32_t b0 = 0; b0 < nbk; b0 += 4 * T) {
-        uint32_t v[4], sum = 0, mx = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t i = b0 + 4 * t + r;
-            v[r] = i < nbk ? cnt[i] : 0u;
-            sum += v[r];
-            mx = max(mx, v[r]);
+        const bool mine = b0 + 4 * t < nbk;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (mine) v = c4[b0 / 4 + t];
+        const uint32_t sum = v.x + v.y + v.z + v.w;
+        const uint32_t inc = wave_sum(sum), mx = wave_max(max(max(v.x, v.y), max(v.z, v.w)));
+        if (lane == 63) {
+            wsum[w] = inc;
+            wsum[W + w] = mx;
         }
-        uint32_t inc = sum;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t x = __shfl_up(inc, d);
-            if ((int)lane >= d) inc += x;
-            mx = max(mx, __shfl_xor(mx, d));
-        }
-        if (lane == 63) wsum[w] = inc;
-        if (lane == 0) wsum[W + w] = mx;
         __syncthreads();
-        uint32_t base = carry, tot = 0;
-        for (uint32_t i = 0; i < W; ++i) {
-            if (i < w) base += wsum[i];
-            tot += wsum[i];
-            mxall = max(mxall, wsum[W + i]);
-        }
-        uint32_t ex = base + inc - sum;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t i = b0 + 4 * t + r;
-            if (i < nbk) cnt[i] = ex;
-            ex += v[r];
-        }
-        carry += tot;
+        const bool in = (lane & 15u) < W;
+        const uint32_t ws = row_sum(in ? wsum[lane & 15u] : 0u), wm = row_max(in ? wsum[W + (lane & 15u)] : 0u);
+        uint32_t ex = carry + inc - sum + (w ? lane_value(ws, w - 1) : 0u);
+        carry += lane_value(ws, 15);
+        mxall = max(mxall, lane_value(wm, 15));
+        if (mine) c4[b0 / 4 + t] = make_uint4(ex, ex + v.x, ex + v.x + v.y, ex + v.x + v.y + v.z);
         __syncthreads();
     }
-    (void)scal;
     return mxall;
 }
 
-// Batcher's odd-even merge sort of N = 2^k inputs, restricted to its first M
-// (all indices fixed at compile time).  With inputs M.. taken as +inf, every
-// comparator touching them is a no-op (a +inf never leaves the top M..N-1
-// positions), so dropping those comparators sorts any M values: 12, 19, 32,
-// 42 and 63 comparators for M = 6, 8, 10, 12, 16 (bitonic over 8 and 16
-// inputs: 24 and 80).
-template <int N, int M>
-__device__ __forceinline__ void reg_oem(uint32_t (&v)[M]) {
+// Batcher's odd-even merge sort of N = 2^k inputs from merges of 2p on (all
+// indices fixed at compile time): p = 1 sorts (63 comparators for 16 inputs),
+// p = N/2 merges two sorted halves (25).
+template <int N, int P0>
+__device__ __forceinline__ void reg_oem(uint32_t (&v)[N]) {
 #pragma unroll
-    for (int p = 1; p < N; p <<= 1) {
+    for (int p = P0; p < N; p <<= 1) {
 #pragma unroll
         for (int k = p; k >= 1; k >>= 1) {
 #pragma unroll
             for (int j = k % p; j + k < N; j += 2 * k) {
 #pragma unroll
                 for (int i = 0; i < k; ++i) {
-                    if (i + j + k < M && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+                    if ((i + j) / (2 * p) == (i + j + k) / (2 * p)) {
                         const uint32_t x = v[i + j], y = v[i + j + k];
                         v[i + j] = x < y ? x : y;
                         v[i + j + k] = x < y ? y : x;
@@ -370,142 +414,163 @@ __device__ __forceinline__ void reg_oem(uint32_t (&v)[M]) {
     }
 }
 
-// Sort the k <= M ids a[s0 .. s0 + k) in place through M registers.
-template <int M>
-__device__ __forceinline__ void sort_run_regs(uint32_t *a, uint32_t s0, uint32_t k) {
-    uint32_t v[M];
+// Where id i of a staged array lies: within its 16 words, the 4-word units
+// are exchanged so that lanes reading a whole run of 16 each, as 16-byte
+// loads, use all banks (without it, two of eight units).
+__device__ __forceinline__ uint32_t near_at(uint32_t i) { return i ^ ((i >> 3) & 12u); }
+
+// The staged ids a (near_at order, pads in the 16 places behind the c ids),
+// grouped into buckets of at most big ids that are in order among themselves:
+// sorted by rounds over the runs of 8.  Round 0 sorts every aligned pair of
+// runs, the odd rounds merge each run with odd place and its successor, the
+// even ones the aligned pairs: an odd-even merge-split sort, which needs as
+// many rounds as a bucket spans runs, at most (big - 2) / 8 + 2.  Per round
+// and 64 ids two 16-byte accesses per 4 lanes and 8 (first) or 3 network
+// instructions; a register network per bucket, padded to the longest bucket
+// of a wave, took three reads and three writes per id instead.
+template <int T>
+__device__ __forceinline__ void sort_near(uint32_t *a, uint32_t c, uint32_t big) {
+    const uint32_t rounds = big < 2 ? 0u : (big + 6) / 8 + 1;
+    uint4 *a4 = reinterpret_cast<uint4 *>(a);
+    for (uint32_t r = 0; r < rounds; ++r) {
+        const uint32_t off = (r & 1u) * 2;
+        for (uint32_t u0 = threadIdx.x * 4 + off; (u0 + off) * 4 < c; u0 += T * 4) {
+            uint32_t v[16];
 #pragma unroll
-    for (int j = 0; j < M; ++j) v[j] = (uint32_t)j < k ? a[s0 + j] : kKeyPad;
-    reg_oem<(M <= 8 ? 8 : (M <= 16 ? 16 : 32)), M>(v);
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t u = u0 + j;
+                const uint4 x = a4[u ^ ((u >> 3) & 3u)];
+                v[4 * j] = x.x, v[4 * j + 1] = x.y, v[4 * j + 2] = x.z, v[4 * j + 3] = x.w;
+            }
+            if (r == 0)
+                reg_oem<16, 1>(v);
+            else
+                reg_oem<16, 8>(v);
 #pragma unroll
-    for (int j = 0; j < M; ++j)
-        if ((uint32_t)j < k) a[s0 + j] = v[j];
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t u = u0 + j;
+                a4[u ^ ((u >> 3) & 3u)] = make_uint4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
+            }
+        }
+        __syncthreads();
+    }
 }
 
-// Sort every bucket [end(b-1), end(b)) of a in place, one lane per bucket:
-// the ids of a bucket go through a register network sized by the longest
-// bucket in the wave (6, 8, 10, 12 or 16 inputs, and 20 or 24 with WIDE),
-// longer buckets (rare) are insertion-sorted.
-template <int T, bool WIDE>
-__device__ __forceinline__ void sort_buckets(uint32_t *a, const uint32_t *end, uint32_t nbk) {
-    for (uint32_t b0 = 0; b0 < nbk; b0 += T) {
-        const uint32_t b = b0 + threadIdx.x;
-        uint32_t s0 = 0, k = 0;
-        if (b < nbk) {
-            s0 = b ? end[b - 1] : 0u;
-            k = end[b] - s0;
-        }
-        uint32_t kmax = k;
-        for (int d = 32; d >= 1; d >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, d));
-        if (kmax <= 6) {
-            sort_run_regs<6>(a, s0, k);
-        } else if (kmax <= 8) {
-            sort_run_regs<8>(a, s0, k);
-        } else if (kmax <= 10) {
-            sort_run_regs<10>(a, s0, k);
-        } else if (kmax <= 12) {
-            sort_run_regs<12>(a, s0, k);
-        } else if (kmax <= 16) {
-            sort_run_regs<16>(a, s0, k);
-        } else {
-            bool done = false;
-            if constexpr (WIDE) {
-                if (kmax <= 20) {
-                    sort_run_regs<20>(a, s0, k);
-                    done = true;
-                } else if (kmax <= 24) {
-                    sort_run_regs<24>(a, s0, k);
-                    done = true;
-                }
-            }
-            for (uint32_t i = 1; !done && i < k; ++i) {
-                const uint32_t x = a[s0 + i];
-                uint32_t j = i;
-                while (j > 0 && a[s0 + j - 1] > x) {
-                    a[s0 + j] = a[s0 + j - 1];
-                    --j;
-                }
-                a[s0 + j] = x;
-            }
+// The n words at p as a buffer: what lies past them reads as 0 and is not
+// written, without a comparison, a mask or a branch, so that many accesses of
+// a ragged run are under way at once (a branch per row made the compiler wait
+// for each load: 2.9 instead of 1.8 ms for the digit counts of 2.0G ids).
+typedef __amdgpu_buffer_rsrc_t Buf;
+__device__ __forceinline__ Buf buf_of(const uint32_t *p, uint32_t n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p), 0, (int)(n * 4), 0x00027000);
+}
+
+// key[k] = src[k*T + thread] for the rows that begin below c (0 past the end).
+// The scalar part of an offset stays below the buffer's size.
+template <int T, int K>
+__device__ __forceinline__ void load_keys(const uint32_t *src, uint32_t c, uint32_t (&key)[K]) {
+    const Buf b = buf_of(src, c);
+#pragma unroll
+    for (int k = 0; k < K; k += 4) {
+        if ((uint32_t)k * T < c) {
+#pragma unroll
+            for (int j = k; j < k + 4; ++j)
+                key[j] = __builtin_amdgcn_raw_buffer_load_b32(b, (int)(((uint32_t)(j - k) * T + threadIdx.x) * 4),
+                                                              k * T * 4, 0);
         }
     }
 }
 
-// Sort c <= T*K ids, given in registers (key[k] holds id k*T + thread, pad
+// first(k, in, i), then second(k, in, i) for the rows k of K that begin below
+// c, four at a time without a branch, so that four memory operations are under
+// way at once; i = k*T + thread is the place, in whether it lies below c.
+// Rows past the end cost nothing: the work follows c rather than the tile.
+template <int T, int K, typename F, typename G>
+__device__ __forceinline__ void rows_by_four(uint32_t c, F &&first, G &&second) {
+    static_assert(K % 4 == 0, "rows by fours");
+#pragma unroll
+    for (int k = 0; k < K; k += 4) {
+        if ((uint32_t)(k + 4) * T <= c) {
+#pragma unroll
+            for (int j = k; j < k + 4; ++j) first(j, true, 0u);
+#pragma unroll
+            for (int j = k; j < k + 4; ++j) second(j, true, 0u);
+        } else if ((uint32_t)k * T < c) {
+#pragma unroll
+            for (int j = k; j < k + 4; ++j) first(j, (uint32_t)j * T + threadIdx.x < c, (uint32_t)j * T + threadIdx.x);
+#pragma unroll
+            for (int j = k; j < k + 4; ++j) second(j, (uint32_t)j * T + threadIdx.x < c, (uint32_t)j * T + threadIdx.x);
+        }
+    }
+}
+
+// Sort c <= T*K ids, given in registers (key[k] holds id k*T + thread; any id
 // beyond c), into dst with one block: counting sort into nbk = 2^b ~ c/4
 // buckets of equal width over the id range (bucket of id x: (x - base) *
 // nbk / range, as a 32-bit multiply-high; LDS counters), scatter into LDS,
-// sort every bucket in place, copy out.  The caller guarantees base <= id <
+// sort within the buckets, copy out.  The caller guarantees base <= id <
 // base + range for every id.  A: target ids per bucket (nbk ~ c/A, at most
-// T*K/A; with A = 8 the bucket networks go up to 24 inputs).  A bucket longer than kRankMax (ids far from uniform) switches the
-// segment to a block bitonic network.  PLACE: instead of sorting the buckets in place and copying
-// out, every key is stored straight at its final place (faster for short
-// segments, where the bucket networks are mostly padding); cnt must then
-// follow buf in LDS.  buf: T*K words, cnt: T*K/A words, wsum: 2*T/64 words
-// of LDS.
-template <int T, int K, bool PLACE = false, int A = 4>
+// T*K/A).  A bucket that is too long (ids far from uniform) switches the
+// segment to a block bitonic network.  buf: T*K + kStagePad words, cnt: T*K/A
+// words, both at 16-byte boundaries, wsum: 2*T/64 words of LDS.
+constexpr uint32_t kStagePad = 16;
+// next() is called as soon as the registers are free, to load the following
+// ids while these are sorted.
+template <int T, int K, int A, typename Next>
 __device__ __forceinline__ void block_sort_keys(uint32_t (&key)[K], uint32_t *dst, uint32_t c, uint32_t range,
-                                                uint32_t *buf, uint32_t *cnt, uint32_t *wsum, uint32_t base = 0) {
+                                                uint32_t *buf, uint32_t *cnt, uint32_t *wsum, uint32_t base,
+                                                Next &&next) {
     constexpr uint32_t N = T * K;
     constexpr uint32_t NB = N / A;   // most buckets
     const uint32_t t = threadIdx.x;
     uint32_t nb = ceil_log2((c + A - 1) / A);
     const uint32_t nbmax = ceil_log2(NB);
-    nb = nb < 1 ? 1 : (nb > nbmax ? nbmax : nb);
+    nb = nb < 2 ? 2 : (nb > nbmax ? nbmax : nb);
     const uint32_t nbk = 1u << nb;
-    // floor(y * mul / 2^32) < nbk for every y < range, and it never decreases
-    // with y; the min() only guards against ids outside the promised range
-    const uint32_t mul = range > nbk ? (uint32_t)(((uint64_t)nbk << 32) / range) : 0xFFFFFFFFu;
+    // floor(y * mul / 2^32) never decreases with y, for any mul: nbk * 2^32 /
+    // range to float precision does, and the min() takes what reaches nbk (a
+    // 64-bit division here was a tenth of a short segment's instructions)
+    const uint32_t mul =
+        range > nbk ? (uint32_t)fminf((float)nbk * 4294967296.0f * __builtin_amdgcn_rcpf((float)range), 4294967040.0f)
+                    : 0xFFFFFFFFu;
     auto bucket = [&](uint32_t x) { return min(__umulhi(x - base, mul), nbk - 1); };
-    for (uint32_t b = t; b < nbk; b += T) cnt[b] = 0;
+    for (uint32_t b = 4 * t; b < nbk; b += 4 * T) *reinterpret_cast<uint4 *>(cnt + b) = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    // rows k with k*T >= c hold nothing: the (block-uniform) row loops stop
-    // there, so the work follows c rather than the tile size
+    // lanes past the end add nothing, in places of their own (in one place
+    // their atomics would go one by one), and fill places past the end
+    auto slot = [&](uint32_t x, bool in) { return in ? bucket(x) : t & (nbk - 1); };
+    rows_by_four<T, K>(
+        c, [&](int k, bool in, uint32_t) { atomicAdd(&cnt[slot(key[k], in)], in ? 1u : 0u); },
+        [](int, bool, uint32_t) {});
+    __syncthreads();
+    const uint32_t big = block_scan_counters<T>(cnt, nbk, wsum);
+    uint32_t at[4];
+    rows_by_four<T, K>(
+        c, [&](int k, bool in, uint32_t) { at[k & 3] = atomicAdd(&cnt[slot(key[k], in)], in ? 1u : 0u); },
+        [&](int k, bool in, uint32_t i) {
+            const uint32_t to = in ? at[k & 3] : i;
+            buf[near_at(to)] = in ? key[k] : kKeyPad;
+        });
+    if (t < kStagePad) buf[near_at(c + t)] = kKeyPad;
+    next();
+    __syncthreads();
+    if (big <= kNearMax) {
+        sort_near<T>(buf, c, big);
+        // near_at(i + T) = near_at(i) + T for multiples of 128
+        auto staged = [&](uint32_t i) { return T % 128 == 0 ? buf[near_at(t) + (i - t)] : buf[near_at(i)]; };
+        const Buf out = buf_of(dst, c);
+        for (uint32_t r = 0; r * T < c; r += 4) {
+            uint32_t x[4];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if ((uint32_t)k * T >= c) break;
-        if ((uint32_t)k * T + t < c) atomicAdd(&cnt[bucket(key[k])], 1u);
-    }
-    __syncthreads();
-    const uint32_t big = block_scan_counters<T>(cnt, nbk, wsum, nullptr);
+            for (uint32_t j = 0; j < 4; ++j) x[j] = staged((r + j) * T + t);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if ((uint32_t)k * T >= c) break;
-        if ((uint32_t)k * T + t < c) buf[atomicAdd(&cnt[bucket(key[k])], 1u)] = key[k];
-    }
-    __syncthreads();
-    if (big <= kRankMax && PLACE) {
-        // buckets are contiguous in buf: the key at position i goes to its
-        // bucket's start plus the number of keys of the bucket that precede
-        // it (smaller, or equal and earlier).  A wave's 64 positions land on
-        // a permutation of about the same 64 outputs, so the stores stay
-        // coalesced.  The 4-wide reads run up to 3 words past the keys: buf
-        // must be followed by at least 3 words of LDS (the counters are).
-        for (uint32_t i = t; i < c; i += T) {
-            const uint32_t x = buf[i];
-            const uint32_t b = bucket(x);
-            const uint32_t s0 = b ? cnt[b - 1] : 0u;
-            const uint32_t e0 = cnt[b];
-            uint32_t r = s0;
-            for (uint32_t j = s0; j < e0; j += 4) {
-                const uint32_t y0 = buf[j], y1 = buf[j + 1], y2 = buf[j + 2], y3 = buf[j + 3];
-                r += (y0 < x || (y0 == x && j < i)) ? 1u : 0u;
-                r += (j + 1 < e0 && (y1 < x || (y1 == x && j + 1 < i))) ? 1u : 0u;
-                r += (j + 2 < e0 && (y2 < x || (y2 == x && j + 2 < i))) ? 1u : 0u;
-                r += (j + 3 < e0 && (y3 < x || (y3 == x && j + 3 < i))) ? 1u : 0u;
-            }
-            dst[r] = x;
+            for (uint32_t j = 0; j < 4; ++j)
+                __builtin_amdgcn_raw_buffer_store_b32(x[j], out, (int)((t + j * T) * 4), (int)(r * T * 4), 0);
         }
-    } else if (big <= kRankMax) {
-        // buckets are contiguous in buf: sort each in place, then one
-        // coalesced copy out
-        sort_buckets<T, (A >= 8)>(buf, cnt, nbk);
-        __syncthreads();
-        for (uint32_t i = t; i < c; i += T) dst[i] = buf[i];
     } else {   // ids far from uniform: block bitonic over the whole segment
         uint32_t P = 1;
         while (P < c) P <<= 1;
-        for (uint32_t i = c + t; i < P; i += T) buf[i] = kKeyPad;
+        for (uint32_t i = c + t; i < P; i += T) buf[near_at(i)] = kKeyPad;
         __syncthreads();
         block_bitonic(buf, P);
         for (uint32_t i = t; i < c; i += T) dst[i] = buf[i];
@@ -513,73 +578,61 @@ __device__ __forceinline__ void block_sort_keys(uint32_t (&key)[K], uint32_t *ds
     __syncthreads();
 }
 
+// One block per segment of the class list.  The next segment's ids are loaded
+// into registers once the current one's are staged, so their load overlaps
+// the rest of the sort.  Few threads with many ids each: what a block does per
+// segment is then shared by fewer waves, and one wave needs no barriers (257
+// to 1024 ids: 64 x 16 0.25 ms, 128 x 8 0.38 ms; 1025 to 4096: 128 x 32 0.93
+// ms, 256 x 16 0.97 ms; 10M rectangles / 1M windows, 0.11G and 0.43G ids: 3.7
+// and 3.8 TB/s).  Shapes of 16384 ids and up are held to 4 waves per SIMD, so
+// that two 512-thread blocks share a CU.
 template <int T, int K>
-__device__ __forceinline__ void load_keys(const uint32_t *src, uint32_t c, uint32_t (&key)[K]) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const uint32_t i = (uint32_t)k * T + threadIdx.x;
-        key[k] = i < c ? src[i] : kKeyPad;
+constexpr int mid_waves_per_simd() {
+    return T * K >= 16384 ? 4 : 1;
+}
+
+// The class-M segments list[0 .. m); buf, cnt, wsum as block_sort_keys'.
+template <int T, int K, int A>
+__device__ __forceinline__ void
+sort_segments(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ list,
+              uint32_t m, uint32_t id_range, const uint32_t *__restrict__ seg_range, uint32_t *buf, uint32_t *cnt,
+              uint32_t *wsum) {
+    if (blockIdx.x >= m) return;
+    // The list entry is read three segments ahead and the offsets two, so that
+    // no load waits for another.
+    const uint32_t g = gridDim.x;
+    auto entry = [&](uint32_t li) { return list[min(li, m - 1)]; };
+    uint32_t q = entry(blockIdx.x), key[K];
+    uint64_t o = offsets[q], o1 = offsets[q + 1];
+    uint32_t r = seg_id_range(seg_range, q, id_range);
+    load_keys<T, K>(ids + o, (uint32_t)(o1 - o), key);
+    q = entry(blockIdx.x + g);
+    uint64_t no = offsets[q], no1 = offsets[q + 1];
+    uint32_t nr = seg_id_range(seg_range, q, id_range);
+    q = entry(blockIdx.x + 2 * g);
+    for (uint32_t li = blockIdx.x; li < m; li += g) {
+        const uint64_t co = o;
+        const uint32_t cn = (uint32_t)(o1 - o), cr = r;
+        block_sort_keys<T, K, A>(key, ids + co, cn, cr, buf, cnt, wsum, 0, [&] {
+            // segments are disjoint: these reads never meet the writes of another
+            o = no, o1 = no1, r = nr;
+            if (li + g < m) load_keys<T, K>(ids + o, (uint32_t)(o1 - o), key);
+            no = offsets[q], no1 = offsets[q + 1];
+            nr = seg_id_range(seg_range, q, id_range);
+            q = entry(li + 3 * g);
+        });
     }
 }
 
-// One block per segment of the class list.  With PF the next segment's ids
-// are loaded into registers before the current one is sorted, so their load
-// overlaps the sort (it costs K registers, which the widest shape cannot
-// spare: a 1024-thread block has 128 per lane).  Register budgets: shapes of
-// 16384 ids and up are held to 4 waves per SIMD, so that two 512-thread
-// blocks share a CU; 256-thread blocks to 6 (six blocks of 20 KB LDS each).
-template <int T, int K>
-constexpr int mid_waves_per_simd() {
-    return T * K >= 16384 ? 4 : (T == 256 ? 6 : 1);
-}
-
-template <int T, int K, bool PLACE, bool PF, int A>
+template <int T, int K, int A>
 __global__ void __launch_bounds__(T, (mid_waves_per_simd<T, K>()))
 segsort_mid(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ list,
             const uint32_t *__restrict__ list_count, uint32_t id_range, const uint32_t *__restrict__ seg_range) {
     constexpr uint32_t N = T * K;
     // keys, then the bucket counters; the scan's per-wave sums use the head
-    // of buf, which holds nothing while the counters are scanned
-    __shared__ uint32_t lds[N + N / A];
-    uint32_t *buf = lds, *cnt = lds + N, *wsum = lds;
-    const uint32_t m = *list_count;
-    if constexpr (PF) {
-        uint32_t nkey[K];
-        uint64_t no = 0;
-        uint32_t nc = 0, nr = id_range;
-        if (blockIdx.x < m) {
-            const uint32_t q = list[blockIdx.x];
-            no = offsets[q];
-            nc = (uint32_t)(offsets[q + 1] - no);
-            nr = seg_id_range(seg_range, q, id_range);
-            load_keys<T, K>(ids + no, nc, nkey);
-        }
-        for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
-            uint32_t key[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) key[k] = nkey[k];
-            const uint64_t o = no;
-            const uint32_t c = nc, rng = nr;
-            const uint32_t ln = li + gridDim.x;
-            if (ln < m) {   // segments are disjoint: this read never meets the writes below
-                const uint32_t q = list[ln];
-                no = offsets[q];
-                nc = (uint32_t)(offsets[q + 1] - no);
-                nr = seg_id_range(seg_range, q, id_range);
-                load_keys<T, K>(ids + no, nc, nkey);
-            }
-            block_sort_keys<T, K, PLACE, A>(key, ids + o, c, rng, buf, cnt, wsum);
-        }
-    } else {
-        for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
-            const uint32_t q = list[li];
-            const uint64_t o = offsets[q];
-            const uint32_t c = (uint32_t)(offsets[q + 1] - o);
-            uint32_t key[K];
-            load_keys<T, K>(ids + o, c, key);
-            block_sort_keys<T, K, PLACE, A>(key, ids + o, c, seg_id_range(seg_range, q, id_range), buf, cnt, wsum);
-        }
-    }
+    // of the keys, which hold nothing while the counters are scanned
+    __shared__ __align__(16) uint32_t lds[N + kStagePad + N / A];
+    sort_segments<T, K, A>(offsets, ids, list, *list_count, id_range, seg_range, lds, lds + N + kStagePad, lds);
 }
 
 // Class L: two levels.  First the segment is split by its top 8 id bits into
@@ -620,60 +673,42 @@ segsort_wide(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, c
              uint64_t nq, const uint32_t *__restrict__ counts, LongWs lw, uint32_t id_range,
              const uint32_t *__restrict__ seg_range) {
     constexpr uint32_t T = 1024, K = 32, A = 8, N = T * K, R = kPart / T;
-    __shared__ uint32_t lds[N + N / A];
-    const uint32_t *list = lists + 4 * nq;
+    __shared__ __align__(16) uint32_t lds[N + kStagePad + N / A];
     const uint32_t m = counts[4], np = counts[kPartCount];
-    for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
-        const uint32_t q = list[li];
-        const uint64_t o = offsets[q];
-        const uint32_t c = (uint32_t)(offsets[q + 1] - o);
-        uint32_t key[K];
-        load_keys<T, K>(ids + o, c, key);
-        block_sort_keys<T, K, false, A>(key, ids + o, c, seg_id_range(seg_range, q, id_range), lds, lds + N, lds);
-    }
-    list = lists + kLong * nq;
-    const uint32_t t = threadIdx.x;
-    uint32_t *h = lds;   // two sets of counters in turn: one barrier less per part
-    struct Part {
-        uint64_t o;
-        uint32_t len, sh;
-    };
-    auto part = [&](uint32_t k) {
-        const uint32_t li = lw.parts[k], q = list[li];
-        const uint32_t p = k - lw.desc[(uint64_t)li * kDesc + kDescPart];
-        const uint64_t o = offsets[q], at = (uint64_t)p * kPart, c = offsets[q + 1] - o;
-        const int id_bits = range_bits(seg_id_range(seg_range, q, id_range));
-        Part r;
-        r.o = o + at;
-        r.len = (uint32_t)min((uint64_t)kPart, c - at);
-        r.sh = (uint32_t)(id_bits - (id_bits < 8 ? id_bits : 8));
-        return r;
-    };
-    uint32_t nkey[R];
-    Part nx{0, 0, 0};
+    sort_segments<T, K, A>(offsets, ids, lists + 4 * nq, m, id_range, seg_range, lds, lds + N + kStagePad, lds);
+    const uint32_t t = threadIdx.x, g = gridDim.x;
     // the M segments went to the first blocks: the parts start behind them
-    const uint32_t g = gridDim.x, b0 = (blockIdx.x + g - m % g) % g;
-    if (b0 < np) {
-        nx = part(b0);
-        load_keys<T, R>(ids + nx.o, nx.len, nkey);
-    }
-    for (uint32_t k = b0; k < np; k += g) {
+    uint32_t k = (blockIdx.x + g - m % g) % g;
+    if (k >= np) return;
+    uint32_t *h = lds;   // two sets of counters in turn: one barrier less per part
+    // two parts under way, the items one further ahead
+    auto item = [&](uint32_t i) { return lw.parts[min(i, np - 1)]; };
+    uint32_t ka[R], kb[R];
+    uint4 ia = item(k), ib = item(k + g);
+    load_keys<T, R>(ids + run_of(ia).o, run_of(ia).n, ka);
+    auto count = [&](uint32_t (&key)[R], uint4 it) {
         if (t < kLongDigits) h[t] = 0;
         __syncthreads();
-        const Part cu = nx;
-        uint32_t key[R];
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r) key[r] = nkey[r];
-        if (k + g < np) {
-            nx = part(k + g);
-            load_keys<T, R>(ids + nx.o, nx.len, nkey);
-        }
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r)
-            if (r * T + t < cu.len) atomicAdd(&h[min(key[r] >> cu.sh, kLongDigits - 1)], 1u);
+        const uint32_t sh = it.w;
+        rows_by_four<T, R>(
+            run_of(it).n, [&](int r, bool in, uint32_t) {
+                atomicAdd(&h[in ? min(key[r] >> sh, kLongDigits - 1) : t % kLongDigits], in ? 1u : 0u);
+            },
+            [](int, bool, uint32_t) {});
         __syncthreads();
         if (t < kLongDigits) lw.hist[(uint64_t)k * kLongDigits + t] = h[t];
         h = h == lds ? lds + kLongDigits : lds;
+    };
+    for (; k < np; k += g) {
+        load_keys<T, R>(ids + run_of(ib).o, run_of(ib).n, kb);   // of the last part again at the end
+        uint4 ic = item(k + 2 * g);
+        count(ka, ia);
+        ia = ic;
+        if ((k += g) >= np) break;
+        load_keys<T, R>(ids + run_of(ia).o, run_of(ia).n, ka);
+        ic = item(k + 2 * g);
+        count(kb, ib);
+        ib = ic;
     }
 }
 
@@ -710,14 +745,16 @@ __device__ __forceinline__ uint32_t scan_digits(uint32_t v, uint32_t *w4, uint32
 __global__ void __launch_bounds__(256)
 segsort_part_scan(const uint64_t *__restrict__ offsets, const uint32_t *__restrict__ list,
                   const uint32_t *__restrict__ list_count, LongWs lw, uint32_t *__restrict__ sub_counts,
-                  uint32_t *__restrict__ fb_list, uint32_t *__restrict__ fb_count) {
-    __shared__ uint32_t w4[8], subbase;
+                  uint32_t *__restrict__ fb_list, uint32_t *__restrict__ fb_count, uint32_t id_range,
+                  const uint32_t *__restrict__ seg_range) {
+    __shared__ uint32_t w4[8], subbase, start[kLongDigits + 1];
     static_assert(kLongDigits == 256, "one thread per digit");
     const uint32_t m = *list_count, t = threadIdx.x;
     for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
         const uint32_t q = list[li];
         uint32_t *dsc = lw.desc + (uint64_t)li * kDesc;
-        const uint32_t np = num_parts(offsets[q + 1] - offsets[q]);
+        const uint64_t o = offsets[q];
+        const uint32_t np = num_parts(offsets[q + 1] - o);
         uint32_t *h = lw.hist + (uint64_t)dsc[kDescPart] * kLongDigits + t;
         uint32_t run = 0;
         for (uint32_t p = 0; p < np; p += 8) {
@@ -732,25 +769,38 @@ segsort_part_scan(const uint64_t *__restrict__ offsets, const uint32_t *__restri
         }
         uint32_t tot, big;
         const uint32_t st = scan_digits(run, w4, tot, big);
-        dsc[t] = st;
+        dsc[t] = start[t] = st;
         // groups of G consecutive digits: G = (group limit) / (largest digit
         // count), so a group never exceeds the limit: kSubMax ids for the
         // 256-thread sort, or, when a digit holds more (segments of about a
-        // million ids), kSubBigMax for the 1024-thread sort (its own list);
-        // work items are li << 8 | group
+        // million ids), kSubBigMax for the 1024-thread sort (its own list)
         const bool fallback = big > kSubBigMax, wide = big > kSubMax;
         const uint32_t G = fallback ? 0u : (wide ? kSubBigMax : kSubMax) / big;
         const uint32_t ngroups = G ? (kLongDigits + G - 1) / G : 0u;
         if (t == 0) {
-            dsc[kLongDigits] = tot;
+            dsc[kLongDigits] = start[kLongDigits] = tot;
             dsc[kDescGroup] = G;
+            dsc[kDescOff] = (uint32_t)o;
+            dsc[kDescOff + 1] = (uint32_t)(o >> 32);
             if (fallback)
                 fb_list[atomicAdd(fb_count, 1u)] = q;
             else
                 subbase = atomicAdd(&sub_counts[wide ? 1 : 0], ngroups);
         }
         __syncthreads();
-        if (t < ngroups) (wide ? lw.sub_wide : lw.sub)[subbase + t] = (li << 8) | t;
+        if (t < ngroups) {
+            // ids of digits [d0, d1): [d0 << sh, d1 << sh) within [0, rng)
+            const uint32_t d0 = t * G, d1 = min(d0 + G, kLongDigits), rng = seg_id_range(seg_range, q, id_range);
+            const uint32_t sh = digit_shift(rng), base = d0 << sh;
+            const uint64_t hi = min((uint64_t)d1 << sh, (uint64_t)rng);
+            const uint4 it = run_item(base, o + start[d0], start[d1] - start[d0],
+                                      hi > base ? (uint32_t)(hi - base) : 0u);
+            const uint32_t i = subbase + t;
+            if (wide)
+                *(lw.sub_end - 1 - i) = it;
+            else
+                lw.sub[i] = it;
+        }
         __syncthreads();
     }
 }
@@ -761,35 +811,32 @@ segsort_part_scan(const uint64_t *__restrict__ offsets, const uint32_t *__restri
 // it is sorted next).  Two blocks of 1024 threads per CU.
 template <int T>
 __global__ void __launch_bounds__(T, 8)
-segsort_part_split(const uint64_t *__restrict__ offsets, const uint32_t *__restrict__ ids,
-                   uint32_t *__restrict__ scratch, const uint32_t *__restrict__ list,
-                   const uint32_t *__restrict__ part_count, LongWs lw, uint32_t id_range,
-                   const uint32_t *__restrict__ seg_range) {
+segsort_part_split(const uint32_t *__restrict__ ids, uint32_t *__restrict__ scratch,
+                   const uint32_t *__restrict__ part_count, LongWs lw) {
     constexpr uint32_t R = kPart / T;
     __shared__ uint32_t stage[kPart];
     __shared__ uint32_t lcur[kLongDigits], gpos[kLongDigits];   // cursor in stage; scratch position minus stage position
     __shared__ uint32_t psum[kLongDigits + 1], w4[8];
-    const uint32_t t = threadIdx.x;
-    const PartShare ps = part_share(*part_count, blockIdx.x, gridDim.x);
+    const uint32_t t = threadIdx.x, np = *part_count;
+    const PartShare ps = part_share(np, blockIdx.x, gridDim.x);
+    if (ps.k >= ps.end) return;
+    uint4 nx = lw.parts[ps.k];
     for (uint32_t k = ps.k; k < ps.end; k += ps.step) {
-        const uint32_t li = lw.parts[k], q = list[li];
-        const uint32_t *dsc = lw.desc + (uint64_t)li * kDesc;
-        const uint32_t p = k - dsc[kDescPart];
+        const uint4 it = nx;
+        nx = lw.parts[min(k + ps.step, np - 1)];
+        const uint32_t *dsc = lw.desc + (uint64_t)(it.x & ~kLastPart) * kDesc;
         const uint32_t G = dsc[kDescGroup];
         if (G == 0) continue;   // left to the fallback
-        const uint64_t o = offsets[q], at = (uint64_t)p * kPart, c = offsets[q + 1] - o;
-        const uint32_t len = (uint32_t)min((uint64_t)kPart, c - at);
-        const int id_bits = range_bits(seg_id_range(seg_range, q, id_range));
-        const uint32_t sh = (uint32_t)(id_bits - (id_bits < 8 ? id_bits : 8));
+        const uint32_t len = run_of(it).n, sh = it.w;
         uint32_t key[R];
-        load_keys<T, R>(ids + o + at, len, key);
+        load_keys<T, R>(ids + run_of(it).o, len, key);
         // thread t: digit t's count in this part and its ids in the parts before
         uint32_t cnt = 0, pre = 0, ec = 0, ep = 0;
         const uint32_t lane = t & 63u;
         if (t < kLongDigits) {
             const uint32_t *row = lw.hist + (uint64_t)k * kLongDigits + t;
             pre = row[0];
-            cnt = (at + kPart < c ? row[kLongDigits] : dsc[t + 1] - dsc[t]) - pre;
+            cnt = (it.x & kLastPart ? dsc[t + 1] - dsc[t] : row[kLongDigits]) - pre;
             ec = cnt;
             ep = pre;
 #pragma unroll
@@ -823,14 +870,24 @@ segsort_part_split(const uint64_t *__restrict__ offsets, const uint32_t *__restr
             gpos[t] = dsc[d0] + (psum[d1] - psum[d0]) - lcur[d0];
         }
         __syncthreads();
-#pragma unroll
-        for (uint32_t r = 0; r < R; ++r)
-            if (r * T + t < len) stage[atomicAdd(&lcur[min(key[r] >> sh, kLongDigits - 1)], 1u)] = key[r];
+        uint32_t to[4];
+        rows_by_four<T, R>(
+            len,
+            [&](int r, bool in, uint32_t) {
+                to[r & 3] = atomicAdd(&lcur[in ? min(key[r] >> sh, kLongDigits - 1) : t % kLongDigits], in ? 1u : 0u);
+            },
+            [&](int r, bool in, uint32_t i) { stage[in ? to[r & 3] : i] = key[r]; });
         __syncthreads();
-        uint32_t *tmp = scratch + o;
-        for (uint32_t j = t; j < len; j += T) {
-            const uint32_t x = stage[j];
-            tmp[gpos[min(x >> sh, kLongDigits - 1)] + j] = x;
+        uint32_t *tmp = scratch + ((uint64_t)dsc[kDescOff + 1] << 32 | dsc[kDescOff]);
+        for (uint32_t r = 0; r * T < len; r += 4) {
+            uint32_t x[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) x[j] = stage[(r + j) * T + t];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) to[j] = gpos[min(x[j] >> sh, kLongDigits - 1)] + (r + j) * T + t;
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j)
+                if ((r + j) * T + t < len) tmp[to[j]] = x[j];
         }
         __syncthreads();
     }
@@ -838,73 +895,34 @@ segsort_part_split(const uint64_t *__restrict__ offsets, const uint32_t *__restr
 
 // Groups of sub-buckets (digits [gG, gG + G)): one block each, sorted from
 // scratch into place; the ids of a group lie in [gG << sh, (gG + G) << sh).
-// Two shapes: 256 x 16 for groups of at most kSubMax ids, 1024 x 32 for the
-// groups of segments whose digits hold more.  With PF the next group's ids
-// are loaded before the current one is sorted.
-template <int T, int K, int A, bool PF>
+// Two shapes: 128 x 32 for groups of at most kSubMax ids, 1024 x 32 for the
+// groups of segments whose digits hold more.  item(k): the k-th of m > 0.
+template <int T, int K, int A, typename Item>
 __device__ __forceinline__ void
-sort_groups(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch,
-            const uint32_t *__restrict__ desc, const uint32_t *__restrict__ items, uint32_t m,
-            const uint32_t *__restrict__ list, uint32_t id_range, const uint32_t *__restrict__ seg_range,
-            uint32_t *buf, uint32_t *cnt, uint32_t *wsum) {
-    struct Grp {
-        uint64_t o;
-        uint32_t n, base, range;
-    };
-    auto group = [&](uint32_t k) {
-        const uint32_t it = items[k], li = it >> 8, g = it & 255u;
-        const uint32_t *dsc = desc + (uint64_t)li * kDesc;
-        const uint32_t G = dsc[kDescGroup];
-        const uint32_t d0 = g * G, d1 = (d0 + G) < kLongDigits ? (d0 + G) : kLongDigits;
-        const uint32_t s0 = dsc[d0];
-        const uint32_t q = list[li];
-        const uint32_t rng = seg_id_range(seg_range, q, id_range);
-        const int id_bits = range_bits(rng);
-        const int sh = id_bits - (id_bits < 8 ? id_bits : 8);
-        Grp r;
-        r.o = offsets[q] + s0;
-        r.n = dsc[d1] - s0;
-        r.base = d0 << sh;   // ids of digits [d0, d1): [d0 << sh, d1 << sh) within [0, rng)
-        const uint64_t hi = (uint64_t)d1 << sh;
-        r.range = (uint32_t)((hi < rng ? hi : (uint64_t)rng) - r.base);
-        return r;
-    };
-    if constexpr (PF) {
-        uint32_t nkey[K];
-        Grp nx{0, 0, 0, 1};
-        if (blockIdx.x < m) {
-            nx = group(blockIdx.x);
-            load_keys<T, K>(scratch + nx.o, nx.n, nkey);
-        }
-        for (uint32_t k = blockIdx.x; k < m; k += gridDim.x) {
-            uint32_t key[K];
-#pragma unroll
-            for (int r = 0; r < (int)K; ++r) key[r] = nkey[r];
-            const Grp cu = nx;
-            if (k + gridDim.x < m) {
-                nx = group(k + gridDim.x);
-                load_keys<T, K>(scratch + nx.o, nx.n, nkey);
-            }
-            block_sort_keys<T, K, false, A>(key, ids + cu.o, cu.n, cu.range, buf, cnt, wsum, cu.base);
-        }
-    } else {
-        for (uint32_t k = blockIdx.x; k < m; k += gridDim.x) {
-            const Grp cu = group(k);
-            uint32_t key[K];
-            load_keys<T, K>(scratch + cu.o, cu.n, key);
-            block_sort_keys<T, K, false, A>(key, ids + cu.o, cu.n, cu.range, buf, cnt, wsum, cu.base);
-        }
+sort_groups(uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch, uint32_t m, Item &&item, uint32_t *buf,
+            uint32_t *cnt, uint32_t *wsum) {
+    if (blockIdx.x >= m) return;
+    const uint32_t g = gridDim.x;
+    uint32_t key[K];
+    uint4 it = item(blockIdx.x), nx = item(min(blockIdx.x + g, m - 1));
+    load_keys<T, K>(scratch + run_of(it).o, run_of(it).n, key);
+    for (uint32_t k = blockIdx.x; k < m; k += g) {
+        const uint4 cu = it;
+        block_sort_keys<T, K, A>(key, ids + run_of(cu).o, run_of(cu).n, cu.w, buf, cnt, wsum, cu.x, [&] {
+            it = nx;
+            if (k + g < m) load_keys<T, K>(scratch + run_of(it).o, run_of(it).n, key);
+            nx = item(min(k + 2 * g, m - 1));
+        });
     }
 }
 
-__global__ void __launch_bounds__(256, 6)
-segsort_sub(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch,
-            LongWs lw, const uint32_t *__restrict__ item_count, const uint32_t *__restrict__ list, uint32_t id_range,
-            const uint32_t *__restrict__ seg_range) {
-    constexpr int T = 256, K = 16, A = 4;
-    __shared__ uint32_t lds[T * K + T * K / A], wsum[2 * (T / 64)];
-    sort_groups<T, K, A, true>(offsets, ids, scratch, lw.desc, lw.sub, *item_count, list, id_range, seg_range, lds,
-                               lds + T * K, wsum);
+__global__ void __launch_bounds__(128)
+segsort_sub(uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch, LongWs lw,
+            const uint32_t *__restrict__ item_count) {
+    constexpr int T = 128, K = 32, A = 4;
+    __shared__ __align__(16) uint32_t lds[T * K + kStagePad + T * K / A];
+    sort_groups<T, K, A>(ids, scratch, *item_count, [&](uint32_t k) { return lw.sub[k]; }, lds,
+                         lds + T * K + kStagePad, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1033,14 +1051,13 @@ __device__ void sort_skewed(const uint64_t *__restrict__ offsets, uint32_t *__re
 // always empty (segments of about a million ids; skewed ids).
 __global__ void __launch_bounds__(1024, 4)
 segsort_rest(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, uint32_t *__restrict__ scratch,
-             LongWs lw, const uint32_t *__restrict__ counts, const uint32_t *__restrict__ lists, uint64_t nq,
-             uint32_t id_range, const uint32_t *__restrict__ seg_range) {
+             LongWs lw, const uint32_t *__restrict__ counts, const uint32_t *__restrict__ lists, uint64_t nq) {
     constexpr int T = 1024, K = 32, A = 8;
-    __shared__ uint32_t lds[T * K + T * K / A], wsum[2 * (T / 64)];
+    __shared__ __align__(16) uint32_t lds[T * K + kStagePad + T * K / A];
     __shared__ uint64_t split[2];
     static_assert(T * K >= kTileMax + kTileMax / 32, "a padded merge window");
-    sort_groups<T, K, A, false>(offsets, ids, scratch, lw.desc, lw.sub_wide, counts[kSubCounts + 1],
-                                lists + kLong * nq, id_range, seg_range, lds, lds + T * K, wsum);
+    sort_groups<T, K, A>(ids, scratch, counts[kSubCounts + 1], [&](uint32_t k) { return *(lw.sub_end - 1 - k); }, lds,
+                         lds + T * K + kStagePad, lds);
     sort_skewed(offsets, ids, scratch, lists + kFallback * nq, counts[kFallback], lds, split);
 }
 
@@ -1057,7 +1074,7 @@ segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uin
             const uint32_t *__restrict__ seg_range, const Ctrl *__restrict__ ctrl, uint64_t *__restrict__ status) {
     constexpr uint32_t T = 256, K = 16, N = T * K;
     static_assert(N == kFewIds, "one tile per segment");
-    __shared__ uint32_t lds[N + N / 4];
+    __shared__ __align__(16) uint32_t lds[N + kStagePad + N / 4];
     const uint32_t q = blockIdx.x;
     if (status && q == 0 && threadIdx.x == 0) select_status(offsets, nq, cap, ctrl, status);
     const uint64_t o = offsets[q], len = offsets[q + 1] - o;
@@ -1071,7 +1088,8 @@ segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uin
             if (np) lw.desc[(uint64_t)li * kDesc + kDescPart] = lds[1] = atomicAdd(&counts[kPartCount], np);
         }
         __syncthreads();
-        for (uint32_t p = threadIdx.x; p < np; p += T) lw.parts[lds[1] + p] = lds[0];
+        const uint32_t sh = digit_shift(seg_id_range(seg_range, q, id_range));
+        for (uint32_t p = threadIdx.x; p < np; p += T) lw.parts[lds[1] + p] = part_item(lds[0], p, np, o, len, sh);
         return;
     }
     const uint32_t c = (uint32_t)len;
@@ -1088,7 +1106,8 @@ segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uin
     }
     uint32_t key[K];
     load_keys<T, K>(ids + o, c, key);
-    block_sort_keys<T, K, false, 4>(key, ids + o, c, seg_id_range(seg_range, q, id_range), lds, lds + N, lds);
+    block_sort_keys<T, K, 4>(key, ids + o, c, seg_id_range(seg_range, q, id_range), lds, lds + N + kStagePad, lds,
+                                 0, [] {});
 }
 
 uint64_t segsort_ws_elems(uint64_t nq) { return (uint64_t)kListCls * nq + kSortCounters; }
@@ -1097,11 +1116,11 @@ uint64_t segsort_ws_elems(uint64_t nq) { return (uint64_t)kListCls * nq + kSortC
 static uint64_t most_long(uint64_t cap) { return cap / (kMidMax + 1) + 1; }
 static uint64_t most_parts(uint64_t cap) { return cap / kPart + most_long(cap); }
 
-// cap ids, then for each possible class-L segment (> kMidMax ids) its
-// descriptor and two lists with room for 256 groups, then the part list and
-// the parts' counts
+// cap ids (rounded up to 16 bytes), then room for 256 groups of each possible
+// class-L segment, the part list, the segments' descriptors and the parts'
+// counts
 uint64_t segsort_scratch_elems(uint64_t cap) {
-    return cap + most_long(cap) * (kDesc + 2 * kLongDigits) + most_parts(cap) * (1 + kLongDigits);
+    return (cap + 3) / 4 * 4 + most_long(cap) * (4 * kLongDigits + kDesc) + most_parts(cap) * (4 + kLongDigits);
 }
 
 template <typename Kern>
@@ -1122,12 +1141,12 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
     // blocks per CU that fit at once (registers and LDS): each persistent
     // grid holds that many, so no block waits for another to finish its share
     static const uint32_t g_small = resident_per_cu(segsort_small, 256);
-    static const uint32_t g_m1 = resident_per_cu(segsort_mid<128, 8, true, true, 4>, 128);
-    static const uint32_t g_m2 = resident_per_cu(segsort_mid<256, 16, false, true, 4>, 256);
-    static const uint32_t g_m3 = resident_per_cu(segsort_mid<512, 32, false, true, 8>, 512);
+    static const uint32_t g_m1 = resident_per_cu(segsort_mid<64, 16, 4>, 64);
+    static const uint32_t g_m2 = resident_per_cu(segsort_mid<128, 32, 4>, 128);
+    static const uint32_t g_m3 = resident_per_cu(segsort_mid<512, 32, 8>, 512);
     static const uint32_t g_wide = resident_per_cu(segsort_wide, 1024);
     static const uint32_t g_split = resident_per_cu(segsort_part_split<1024>, 1024);
-    static const uint32_t g_sub = resident_per_cu(segsort_sub, 256);
+    static const uint32_t g_sub = resident_per_cu(segsort_sub, 128);
     static const uint32_t g_rest = resident_per_cu(segsort_rest, 1024);
     // no more blocks than the class can have work items: nq segments, or as
     // many longer than `longer` as fit the capacity (none: no launch)
@@ -1136,11 +1155,11 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
         return dim3((uint32_t)std::min<uint64_t>((uint64_t)cus * resident, items));
     };
     LongWs lw;
-    lw.desc = scratch + cap;
-    lw.sub = lw.desc + most_long(cap) * kDesc;
-    lw.sub_wide = lw.sub + most_long(cap) * kLongDigits;
-    lw.parts = lw.sub_wide + most_long(cap) * kLongDigits;
-    lw.hist = lw.parts + most_parts(cap);
+    lw.sub = reinterpret_cast<uint4 *>(scratch + (cap + 3) / 4 * 4);
+    lw.sub_end = lw.sub + most_long(cap) * kLongDigits;
+    lw.parts = lw.sub_end;
+    lw.desc = reinterpret_cast<uint32_t *>(lw.parts + most_parts(cap));
+    lw.hist = lw.desc + most_long(cap) * kDesc;
     hipError_t e = hipSuccess;
     if (!zeroed) e = launch_zero(counts, kSortCounters * 4, s);
     if (e != hipSuccess) return e;
@@ -1153,21 +1172,21 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
     } else {
         if (nq <= 262144)
             hipLaunchKernelGGL(seg_classify<2>, dim3((uint32_t)((nq + 511) / 512)), dim3(256), 0, s, offsets, nq, cap,
-                               lists, counts, lw, ctrl, status);
+                               lists, counts, lw, range, seg_range, ctrl, status);
         else
             hipLaunchKernelGGL(seg_classify<16>, dim3((uint32_t)((nq + 4095) / 4096)), dim3(256), 0, s, offsets, nq,
-                               cap, lists, counts, lw, ctrl, status);
+                               cap, lists, counts, lw, range, seg_range, ctrl, status);
         if (most(1))
             hipLaunchKernelGGL(segsort_small, grid(g_small, (most(1) + 3) / 4), dim3(256), 0, s, offsets, ids, lists,
                                counts + 0);
         if (most(256))
-            hipLaunchKernelGGL((segsort_mid<128, 8, true, true, 4>), grid(g_m1, most(256)), dim3(128), 0, s, offsets,
+            hipLaunchKernelGGL((segsort_mid<64, 16, 4>), grid(g_m1, most(256)), dim3(64), 0, s, offsets,
                                ids, lists + nq, counts + 1, range, seg_range);
         if (most(1024))
-            hipLaunchKernelGGL((segsort_mid<256, 16, false, true, 4>), grid(g_m2, most(1024)), dim3(256), 0, s,
+            hipLaunchKernelGGL((segsort_mid<128, 32, 4>), grid(g_m2, most(1024)), dim3(128), 0, s,
                                offsets, ids, lists + 2 * nq, counts + 2, range, seg_range);
         if (most(4096))
-            hipLaunchKernelGGL((segsort_mid<512, 32, false, true, 8>), grid(g_m3, most(4096)), dim3(512), 0, s,
+            hipLaunchKernelGGL((segsort_mid<512, 32, 8>), grid(g_m3, most(4096)), dim3(512), 0, s,
                                offsets, ids, lists + 3 * nq, counts + 3, range, seg_range);
     }
     const uint32_t wide_min = nq <= kFewMax ? kFewIds : 16384;
@@ -1177,13 +1196,14 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
                            lists, nq, counts, lw, range, seg_range);
     if (nl) {
         hipLaunchKernelGGL(segsort_part_scan, grid(8, nl), dim3(256), 0, s, offsets, lists + kLong * nq,
-                           counts + kLong, lw, counts + kSubCounts, lists + kFallback * nq, counts + kFallback);
-        hipLaunchKernelGGL(segsort_part_split<1024>, grid(g_split, np), dim3(1024), 0, s, offsets, ids, scratch,
-                           lists + kLong * nq, counts + kPartCount, lw, range, seg_range);
-        hipLaunchKernelGGL(segsort_sub, grid(g_sub, nl * kLongDigits), dim3(256), 0, s, offsets, ids, scratch, lw,
-                           counts + kSubCounts, lists + kLong * nq, range, seg_range);
+                           counts + kLong, lw, counts + kSubCounts, lists + kFallback * nq, counts + kFallback, range,
+                           seg_range);
+        hipLaunchKernelGGL(segsort_part_split<1024>, grid(g_split, np), dim3(1024), 0, s, ids, scratch,
+                           counts + kPartCount, lw);
+        hipLaunchKernelGGL(segsort_sub, grid(g_sub, nl * kLongDigits), dim3(128), 0, s, ids, scratch, lw,
+                           counts + kSubCounts);
         hipLaunchKernelGGL(segsort_rest, grid(g_rest, nl * kLongDigits), dim3(1024), 0, s, offsets, ids, scratch, lw,
-                           counts, lists, nq, range, seg_range);
+                           counts, lists, nq);
     }
     return hipGetLastError();
 }

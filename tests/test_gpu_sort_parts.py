@@ -65,3 +65,30 @@ def test_parts_of_several_trees(rt):
         off, ids = b.result(i)
         assert np.array_equal(np.asarray(off).astype(np.int64), want[0].astype(np.int64))
         assert np.array_equal(ids, want[1])
+
+
+@pytest.mark.parametrize("few", [True, False])
+@pytest.mark.parametrize("length", [300, 1000, 1024, 1500, 4096, 12_000, 30_000, 40_000])
+def test_bucket_lengths(rt, few, length):
+    """Results that are one run of consecutive ids, in random spatial order, of
+    1 / ratio of the id range: the sort's buckets then hold 1 to about 260 ids,
+    which takes from none to all rounds of the in-bucket merging, and beyond
+    its limit the bitonic fallback."""
+    for ratio in [1, 2, 3, 5, 8, 16, 40, 63, 64, 65]:
+        n = length * ratio
+        i = np.arange(n)
+        x = (i // length).astype(np.float32)
+        y = np.random.default_rng(length + ratio).permutation(n).astype(np.float32)
+        r = np.stack([x, y, x, y], axis=1)
+        at = sorted({0, ratio // 2, ratio - 1})
+        q = [[j - 0.25, -1.0, j + 0.25, float(n)] for j in at]
+        if not few:
+            q += [[-9.0, -9.0, -8.0, -8.0]] * 2100
+        q = np.array(q, np.float32)
+        print(f"case bucket lengths few={few} length={length} ratio={ratio}", flush=True)
+        t = rt.build_str(r, 64, "soa")
+        off, ids = device_select(rt, t, q, length * len(at))
+        assert np.array_equal(off[: len(at) + 1], np.arange(len(at) + 1) * length)
+        for k, j in enumerate(at):
+            assert np.array_equal(ids[k * length:(k + 1) * length], np.arange(j * length, (j + 1) * length)), ratio
+        t.free()
