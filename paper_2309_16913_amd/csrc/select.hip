@@ -684,144 +684,223 @@ bulk_copy_kernel(const uint32_t *__restrict__ leaf_ids, BulkList replayed, BulkL
         uint32_t *__restrict__ dst = ids + (((uint64_t)d.z << 32) | d.y);
         const uint32_t len = d.w;
         const uint32_t head = min((16u - (uint32_t)((reinterpret_cast<uintptr_t>(dst) >> 2) & 15u)) & 15u, len);
+        // four ids per lane: stores at 16-byte boundaries, loads at any word
+        typedef uint32_t vec4 __attribute__((ext_vector_type(4)));
+        typedef uint32_t vec4_any __attribute__((ext_vector_type(4), aligned(4)));
         constexpr uint32_t U = 8;
-        const uint32_t hv = t < head ? src[t] : 0u;   // loaded with the first round
-        uint32_t k = head;
-        do {
-            uint32_t v[U];
+        static_assert(kBulkChunk <= U * 1024, "one round per descriptor");
+        const uint32_t body = (len - head) / 4, tail = head + 4 * body;   // vectors; the first id behind them
+        const vec4_any *__restrict__ src4 = reinterpret_cast<const vec4_any *>(src + head);
+        vec4 *__restrict__ dst4 = reinterpret_cast<vec4 *>(dst + head);
+        // ids of the unaligned ends, loaded with the rest: lanes below 16 the
+        // head, the next four the tail
+        const uint32_t ei = t < 16 ? t : tail + (t - 16);
+        const bool edge = t < 16 ? t < head : t < 20 && ei < len;
+        const uint32_t ev = edge ? src[ei] : 0u;
+        vec4 v[U];
 #pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t i = k + u * 256 + t;
-                v[u] = i < len ? src[i] : 0u;
-            }
-            if (k == head && t < head) put_id(dst + t, hv);
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t i = u * 256 + t;
+            if (u * 256 < body) v[u] = src4[min(i, body - 1)];
+        }
+        asm volatile("" ::: "memory");
+        if (edge) put_id(dst + ei, ev);
 #pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t i = k + u * 256 + t;
-                if (i < len) put_id(dst + i, v[u]);
-            }
-            k += 256 * U;
-        } while (k < len);
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t i = u * 256 + t;
+            if (i < body) __builtin_nontemporal_store(v[u], dst4 + i);
+        }
     }
 }
 
-// Replay of the recording count pass: persistent blocks take record chunks;
-// a chunk's records are staged in LDS with their absolute output positions
-// (one offsets lookup per record, all loaded at once), then every half-wave
-// takes records 8 apart, RU at a time: a leaf record writes the ids of its
-// hit entries (lane l: entry l of the record's 32, at its rank in the hit
-// mask), a range record copies the leaves' ids from the leaf-id array
-// (measured faster than from the leaves' own ptr arrays: fill 2.81 against
-// 4.13 ms at 10M rectangles / 1M windows, fanout 64 SoA).
+// A lane's 64-bit value as a scalar, and a run of n words as a buffer whose
+// bounds drop what lies past it.
+template <typename P>
+__device__ __forceinline__ P *scalar64(P *p, int lane) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+    return reinterpret_cast<P *>((uint64_t)hi << 32 | lo);
+}
+typedef __amdgpu_buffer_rsrc_t RunBuf;
+constexpr int kStoreNt = 2;   // non-temporal
+constexpr uint32_t kRunMax = 1u << 28;   // ids in one buffer at most: its size in bytes stays a positive int
+__device__ __forceinline__ RunBuf run_buf(const uint32_t *p, uint32_t n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p), 0, (int)(min(n, kRunMax) * 4), 0x00027000);
+}
+
+// Replay of the recording count pass: persistent waves take quarters of record
+// chunks, one record per lane.  A lane works out its record once (output
+// address, source address in the leaf-id array, bounds check); the next
+// quarter's records, then their offsets, are loaded meanwhile.  Leaf records
+// go through a list in LDS, of which every half-wave takes every other one, RU
+// at a time: lane l reads entry l of the record's 32 and stores it at its rank
+// in the hit mask.  Ranges are copied by the whole wave.  Bound by memory
+// (10M rectangles / 1M windows, 1.44G ids, fanout 64 SoA: 2.24 ms, 5.8 GB
+// written and the leaf ids read through L2 and Infinity Cache); with addresses
+// and bounds worked out by every lane, 40 vector instructions per 64 entries,
+// and one range per half-wave at a time it took 2.65 ms, and 2.5 instead of
+// 1.1 ms on 50M rectangles.
 // BULK: ranges of at least kReplayBulkMin ids are deferred to the bulk copy,
 // whose blocks share them (one half-wave copying a subtree of 32K ids alone
-// takes 150 us); an instance of its own, since the branch costs the in-place
-// copies registers (10M rectangles / 1M windows: fill 2.6 -> 3.6 ms).
-template <int LAYOUT, bool BULK>
-__global__ void __launch_bounds__(256)
+// takes 150 us); an instance of its own, since the branch costs registers.
+template <bool BULK>
+__global__ void __launch_bounds__(256, 8)   // the whole grid resident: the work is dealt by stride
 replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffsets, uint32_t *__restrict__ ids,
               uint64_t cap, Ctrl *__restrict__ ctrl, uint4 *__restrict__ bulk, uint32_t bulk_cap) {
-    __shared__ uint64_t sbase[kRecChunk], send[kRecChunk];
-    __shared__ uint2 sref[kRecChunk];
+    constexpr uint32_t W = 4;   // waves per block
+    // addresses are kept as pointers to global memory (through LDS
+    // or a structure the compiler would lose that and use flat accesses)
+    typedef const __attribute__((address_space(1))) uint32_t *Src;
+    typedef __attribute__((address_space(1))) uint32_t *Dst;
+    __shared__ Src lsrc[W][64];
+    __shared__ Dst ldst[W][64];
+    __shared__ uint32_t lmask[W][64];
     const uint32_t nchunks = ctrl->rec_nchunks;
     if (!nchunks || ctrl->rec_overflow || offsets[noffsets] > cap) return;
-    const uint4 *__restrict__ rec = ctrl->rec_base;
-    const uint32_t *__restrict__ rec_count = ctrl->rec_count;
-    const uint32_t nch = min(ctrl->rec_chunks, nchunks);
-    const uint32_t th = threadIdx.x, hw = th >> 5, l = th & 31u;
-    const uint32_t F = t.fanout;
-    // records in flight per half-wave (4: fill 2.89 ms, 8: 2.81 at 10M rectangles / 1M windows, fanout 64
-    // SoA; on the 50M-rectangle tree 5.70 against 4.05 ms); half-waves per block
-    constexpr uint32_t U = 8, HW = 8;
-    for (uint32_t c = blockIdx.x; c < nch; c += gridDim.x) {
-        const uint32_t cnt = min(rec_count[c], kRecChunk);
-        __syncthreads();   // the previous chunk's records are consumed
-        if (th < cnt) {
-            const uint4 d = get_rec(rec + (size_t)c * kRecChunk + th);
-            sbase[th] = offsets[d.x] + d.y;
-            send[th] = offsets[d.x + 1];
-            sref[th] = make_uint2(d.z, d.w);
+    typedef const __attribute__((address_space(1))) rec_vec *Rec;
+    const Rec rec = (Rec)ctrl->rec_base;
+    const Src rec_count = (Src)ctrl->rec_count;
+    const uint32_t nunits = min(ctrl->rec_chunks, nchunks) * (kRecChunk / 64);
+    const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6, half = lane >> 5, l = lane & 31u;
+    const uint64_t below = lane ? ~0ull >> (64 - lane) : 0ull;
+    const uint32_t lbit = 1u << l;
+    // Unit u: records [64 * (u % 4), + 64) of chunk u / 4.  What is read ahead
+    // (past the last unit: of the last one again) is looked at when its turn
+    // comes; lanes past the chunk's records then take an empty record.
+    const uint32_t step = gridDim.x * W;
+    rec_vec rv;
+    uint32_t rcnt;
+    auto load = [&](uint32_t u) {
+        const uint32_t v = min(u, nunits - 1), c = v / (kRecChunk / 64);
+        rv = __builtin_nontemporal_load(rec + (size_t)c * kRecChunk + (v % (kRecChunk / 64)) * 64 + lane);
+        rcnt = rec_count[c];
+    };
+    uint4 d;
+    uint64_t o0, o1;
+    bool in;
+    auto arrive = [&](uint32_t u) {   // the loaded record, and its slot's offsets
+        in = (u % (kRecChunk / 64)) * 64 + lane < min(rcnt, kRecChunk);
+        d = in ? make_uint4(rv.x, rv.y, rv.z, rv.w) : make_uint4(0u, 0u, t.first_leaf, 0u);
+        o0 = offsets[d.x], o1 = offsets[d.x + 1];
+    };
+    // Hands a range to the bulk copy (the whole wave; scalars); false if its list is full.
+    auto defer = [&](const uint32_t *src, uint32_t *dst, uint32_t n) {
+        const uint32_t nd = (n + kBulkChunk - 1) / kBulkChunk;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&ctrl->bulk_n, nd);
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        const bool fits = at < bulk_cap && nd <= bulk_cap - at;
+        for (uint32_t k = lane; k < nd && at + k < bulk_cap; k += 64) {   // empty ones if not all fit
+            const uint32_t off = k * kBulkChunk;
+            const uint64_t to = (uint64_t)(dst - ids) + off;
+            bulk[at + k] = make_uint4((uint32_t)(src - t.leaf_ids) + off, (uint32_t)to, (uint32_t)(to >> 32),
+                                      fits ? min(kBulkChunk, n - off) : 0u);
         }
-        __syncthreads();
-        for (uint32_t r0 = hw; r0 < cnt; r0 += HW * U) {
-            uint32_t v[U];
-            uint64_t o[U];
+        return fits;
+    };
+    uint32_t unit = blockIdx.x * W + w;
+    if (unit >= nunits) return;   // no block barriers below
+    load(unit);
+    arrive(unit);
+    for (; unit < nunits; unit += step) {
+        const bool run = in && (d.z & kRecRun);
+        const uint64_t b = o0 + d.y;
+        uint64_t n;
+        const uint32_t *src;
+        if (run) {
+            const uint64_t s0 = leaf_start(t, d.z & ~kRecRun);
+            n = leaf_start(t, d.w) - s0;
+            src = t.leaf_ids + s0;
+        } else {
+            n = (uint32_t)__popc(d.w);
+            src = t.leaf_ids + leaf_start(t, d.z & ~kRecHi) + ((d.z & kRecHi) ? 32u : 0u);
+        }
+        const bool bad = in && b + n > o1;
+        if (bad) atomicOr(&ctrl->err, kErrBounds);
+        const bool leaf = in && !run && !bad;
+        const uint64_t lm = __ballot(leaf), rm = __ballot(run && !bad);
+        const uint32_t nl = (uint32_t)__popcll(lm);
+        // leaf records to the front, in order; the lanes without one fill the
+        // places behind with records without hits
+        {
+            const uint32_t at = leaf ? (uint32_t)__popcll(lm & below) : nl + (uint32_t)__popcll(~lm & below);
+            lsrc[w][at] = (Src)(leaf ? src : t.leaf_ids);
+            ldst[w][at] = (Dst)(ids + b);
+            lmask[w][at] = leaf ? d.w : 0u;
+        }
+        const uint32_t rn = (uint32_t)n;   // n ids of one tree: fewer than 2^32
+        uint32_t *const dst = ids + b;
+        __builtin_amdgcn_wave_barrier();
+        load(unit + step);
+        constexpr uint32_t RU = 8;   // leaf records in flight per half-wave
+        // A leaf record's ids are a short run next to the runs of the records
+        // beside it (the same wave, the same L2): cached stores let L2 merge
+        // their partly written lines, where stores that bypass it write each
+        // part to memory on its own (fill 2.83 -> 2.67 ms at 10M rectangles /
+        // 1M windows).  Range copies write whole lines and keep the bypassing
+        // stores.
+        for (uint32_t r0 = 0; r0 < nl; r0 += 2 * RU) {
+            uint32_t v[RU], m[RU];
 #pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t r = r0 + u * HW;
-                o[u] = ~0ull;
-                v[u] = 0;
-                if (r < cnt) {
-                    const uint2 d = sref[r];
-                    if (!(d.x & kRecRun) && ((d.y >> l) & 1u)) {
-                        const uint32_t node = d.x & ~kRecHi;
-                        const uint32_t ent = ((d.x & kRecHi) ? 32u : 0u) + l;
-                        v[u] = load_ptr<LAYOUT>(t.nodes + (size_t)node * t.node_bytes, F, ent);
-                        o[u] = sbase[r] + (uint32_t)__popc(d.y & ((1u << l) - 1u));
-                        if (o[u] >= send[r]) {
-                            atomicOr(&ctrl->err, kErrBounds);
-                            o[u] = ~0ull;
-                        }
+            for (uint32_t u = 0; u < RU; ++u) {
+                const uint32_t r = r0 + 2 * u + half;
+                m[u] = lmask[w][r];
+                // lanes without a hit read the first entry: no branch
+                v[u] = lsrc[w][r][(m[u] & lbit) ? l : 0u];
+            }
+            asm volatile("" ::: "memory");   // keeps the loads above the conditional stores
+#pragma unroll
+            for (uint32_t u = 0; u < RU; ++u)
+                if (m[u] & lbit) ldst[w][r0 + 2 * u + half][__popc(m[u] & (lbit - 1))] = v[u];
+        }
+        // Ranges: the whole wave copies one, four at a time; addresses and
+        // lengths are scalars, the buffers' bounds take the ragged ends.
+        constexpr uint32_t QU = 4, CU = 4;   // ranges in flight, loads of each
+        for (uint64_t left = rm; left;) {
+            RunBuf from[QU], to[QU];
+            const uint32_t *rs[QU];
+            uint32_t *rd[QU];
+            uint32_t x[QU][CU], len[QU];
+#pragma unroll
+            for (uint32_t u = 0; u < QU; ++u) {
+                const int at = left ? __builtin_ctzll(left) : 0;
+                len[u] = left ? (uint32_t)__builtin_amdgcn_readlane((int)rn, at) : 0u;
+                left &= left - 1;
+                rs[u] = scalar64(src, at);
+                rd[u] = scalar64(dst, at);
+                if (BULK && len[u] >= kReplayBulkMin && defer(rs[u], rd[u], len[u])) len[u] = 0;
+                from[u] = run_buf(rs[u], len[u]);
+                to[u] = run_buf(rd[u], len[u]);
+#pragma unroll
+                for (uint32_t k = 0; k < CU; ++k)
+                    x[u][k] = __builtin_amdgcn_raw_buffer_load_b32(from[u], (int)(lane * 4 + k * 256), 0, 0);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < QU; ++u) {
+#pragma unroll
+                for (uint32_t k = 0; k < CU; ++k)
+                    __builtin_amdgcn_raw_buffer_store_b32(x[u][k], to[u], (int)(lane * 4 + k * 256), 0, kStoreNt);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < QU; ++u) {
+                for (uint32_t i = 64 * CU; i < len[u]; i += 64 * CU) {
+                    if (i % kRunMax == 0) {   // the next buffer of a very long run
+                        from[u] = run_buf(rs[u] + i, len[u] - i);
+                        to[u] = run_buf(rd[u] + i, len[u] - i);
                     }
+                    const int o = (int)(i % kRunMax * 4);   // scalar part of the offset: below the buffer's size
+#pragma unroll
+                    for (uint32_t k = 0; k < CU; ++k)
+                        x[u][k] = __builtin_amdgcn_raw_buffer_load_b32(from[u], (int)(lane * 4 + k * 256), o, 0);
+#pragma unroll
+                    for (uint32_t k = 0; k < CU; ++k)
+                        __builtin_amdgcn_raw_buffer_store_b32(x[u][k], to[u], (int)(lane * 4 + k * 256), o, kStoreNt);
                 }
             }
-            // a leaf record's ids are a short run next to the runs of the
-            // records beside it in the chunk (the same block, the same L2):
-            // cached stores let L2 merge their partly written lines, where
-            // stores that bypass it write each part to memory on its own
-            // (fill 2.83 -> 2.67 ms at 10M rectangles / 1M windows).  Range
-            // copies write whole lines and keep the bypassing stores.
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u)
-                if (o[u] != ~0ull) ids[o[u]] = v[u];
-#pragma unroll 1
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t r = r0 + u * HW;
-                if (r >= cnt) break;
-                const uint2 d = sref[r];
-                if (!(d.x & kRecRun)) continue;
-                const uint32_t l0 = d.x & ~kRecRun, l1 = d.y;
-                const uint64_t s0 = leaf_start(t, l0);
-                const uint64_t n = leaf_start(t, l1) - s0;
-                const uint64_t b = sbase[r];
-                if (b + n > send[r]) {
-                    if (l == 0) atomicOr(&ctrl->err, kErrBounds);
-                    continue;
-                }
-                if constexpr (BULK) {
-                    if (n >= kReplayBulkMin) {   // half-wave-uniform
-                        const uint32_t nd = (uint32_t)((n + kBulkChunk - 1) / kBulkChunk);
-                        uint32_t at = 0;
-                        if (l == 0) at = atomicAdd(&ctrl->bulk_n, nd);
-                        at = (uint32_t)__shfl((int)at, (int)(th & 32u));
-                        const bool fits = at < bulk_cap && nd <= bulk_cap - at;
-                        for (uint32_t k = l; k < nd && at + k < bulk_cap; k += 32) {   // empty ones if not all fit
-                            const uint64_t off = (uint64_t)k * kBulkChunk, dst = b + off;
-                            bulk[at + k] = make_uint4((uint32_t)(s0 + off), (uint32_t)dst, (uint32_t)(dst >> 32),
-                                                      fits ? (uint32_t)min((uint64_t)kBulkChunk, n - off) : 0u);
-                        }
-                        if (fits) continue;
-                    }
-                }
-                {
-                    const uint32_t *__restrict__ src = t.leaf_ids + s0;
-                    constexpr uint32_t RU = 8;   // 16: more registers, fill 4.2 ms
-                    for (uint64_t i0 = l; i0 < n; i0 += 32 * RU) {
-                        uint32_t w[RU];
-#pragma unroll
-                        for (uint32_t k = 0; k < RU; ++k) {
-                            const uint64_t i = i0 + 32 * k;
-                            w[k] = i < n ? src[i] : 0u;
-                        }
-#pragma unroll
-                        for (uint32_t k = 0; k < RU; ++k) {
-                            const uint64_t i = i0 + 32 * k;
-                            if (i < n) put_id(ids + b + i, w[k]);
-                        }
-                    }
-                }
-            }
         }
+        __builtin_amdgcn_wave_barrier();
+        arrive(unit + step);
     }
 }
 
@@ -829,19 +908,12 @@ hipError_t launch_replay(const TreeView &t, const uint64_t *offsets, uint32_t no
                          uint64_t cap, Ctrl *ctrl, uint4 *defer, uint32_t defer_cap, uint32_t max_chunks, hipStream_t s) {
     const uint32_t most = (uint32_t)num_cus() * 8;   // no more blocks than chunks can be taken
     const dim3 grid(max_chunks < most ? max_chunks : most), block(256);
-#define RT_REPLAY(L_)                                                                                              \
-    do {                                                                                                           \
-        if (defer)                                                                                                 \
-            hipLaunchKernelGGL((replay_kernel<L_, true>), grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl, \
-                               defer, defer_cap);                                                                  \
-        else                                                                                                       \
-            hipLaunchKernelGGL((replay_kernel<L_, false>), grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl, \
-                               (uint4 *)nullptr, 0u);                                                              \
-    } while (0)
-    if (t.layout == LAYOUT_AOS) RT_REPLAY(LAYOUT_AOS);
-    else if (t.layout == LAYOUT_SOA) RT_REPLAY(LAYOUT_SOA);
-    else RT_REPLAY(LAYOUT_D2);
-#undef RT_REPLAY
+    if (defer)
+        hipLaunchKernelGGL(replay_kernel<true>, grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl, defer,
+                           defer_cap);
+    else
+        hipLaunchKernelGGL(replay_kernel<false>, grid, block, 0, s, t, offsets, noffsets, ids, cap, ctrl,
+                           (uint4 *)nullptr, 0u);
     return hipGetLastError();
 }
 

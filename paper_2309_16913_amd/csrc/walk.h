@@ -273,21 +273,27 @@ struct GroupWalk {
         const uint64_t cm = (__ballot(cont) >> gbase) & fmask;
         const uint64_t pm = m & ~cm;   // children to descend into
         if (cm) {                      // group-uniform: contained subtrees
-            const bool mine = (cm >> e) & 1u;
-            const uint2 rg = mine ? t.range[first + e] : make_uint2(0u, 0u);
+            // Neighbouring contained children hold one run of leaves: their
+            // first one stands for all of them.
+            const uint64_t starts = cm & ~(cm << 1);
+            const bool mine = (starts >> e) & 1u;
+            const uint64_t after = ~(cm >> e);   // 0 if all 64 are contained
+            const uint32_t last = after ? e + (uint32_t)__builtin_ctzll(after) - 1 : 63u;   // of the run that begins here
+            uint2 rg = make_uint2(0u, 0u);
+            if (mine) rg = make_uint2(t.range[first + e].x, t.range[first + last].y);
             uint32_t sc = mine ? subtree_objects(t, rg) : 0u;
             if constexpr (REC) {
-                // one record per contained child: its leaf range, at the
-                // position after the contained children before it
+                // one record per run: its leaf range, at the position after
+                // the runs before it
                 uint32_t inc = sc;
                 for (uint32_t d = 1; d < G; d <<= 1) {
                     const uint32_t x = (uint32_t)__shfl_up((int)inc, d, G);
                     if (e >= d) inc += x;
                 }
-                const uint32_t n = (uint32_t)__popcll(cm);
+                const uint32_t n = (uint32_t)__popcll(starts);
                 if (nbuf + n > kRecBuf) flush(counts, slot);
                 if (mine)
-                    rbuf[nbuf + (uint32_t)__popcll(cm & below)] =
+                    rbuf[nbuf + (uint32_t)__popcll(starts & below)] =
                         make_uint4(slot, pos + inc - sc, kRecRun | rg.x, rg.y);
                 nbuf += n;
                 pos += uni((uint32_t)__shfl((int)inc, (int)(gbase + G - 1)));

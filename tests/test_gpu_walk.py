@@ -142,3 +142,23 @@ def test_library_workspaces(rt, ora, nq):
             assert int(total.item()) == wi.size
             assert np.array_equal(off.cpu().numpy(), wo.astype(np.int64))
             assert np.array_equal(ids[:wi.size].cpu().numpy().view(np.uint32), wi) and bool((ids[wi.size:] == -1).all())
+
+
+@pytest.mark.parametrize("fanout,layout", [(64, "soa"), (64, "aos"), (63, "d2"), (32, "soa"), (16, "aos"), (3, "soa")])
+def test_runs_of_contained_children(rt, ora, fanout, layout):
+    """Windows over the whole space, over its halves and over strips, one
+    tree of fanout ** 2 objects (the root's children are full leaves) and one
+    of a few more: contained children at the front, in the middle, at the end
+    or all of a node's become runs of one leaf up to the whole node, of 3 ids
+    up to several rounds of the copy."""
+    g = np.random.default_rng(fanout)
+    for n in [fanout * fanout, fanout * fanout + 1, 6 * fanout * fanout + 5]:
+        r = np.tile(g.random((n, 2), np.float32), (1, 2))
+        e = np.linspace(-0.01, 1.01, 9, dtype=np.float32)
+        q = [[-1, -1, 2, 2]]
+        q += [[-1, lo, 2, hi] for lo in e for hi in e if lo < hi]
+        q += [[lo, -1, hi, 2] for lo in e for hi in e if lo < hi]
+        q = np.array(q, np.float32)
+        want = ora.select(ora.build_str(r, fanout), q)
+        check(rt, ora, r, q, want, fanout, layout, 0)
+        check(rt, ora, r, q, want, fanout, layout, 2, "on")
