@@ -20,6 +20,8 @@
 // Trees of unequal height: only the deeper side descends, with each of its
 // children tested against the MBR of the whole shallower tree, until both
 // sides are at the same level (this can only happen at the roots).
+#include <algorithm>
+
 #include "pair_sort.h"
 #include "rt_internal.h"
 
@@ -172,6 +174,248 @@ join_level_kernel(TreeView A, TreeView B, const uint2 *__restrict__ fr, uint32_t
         }
     }
     if (!FILL && lane == 0) counts[p] = total;
+}
+
+// ---------------------------------------------------------------------------
+// A level in one pass (replayed joins, whose buffers are sized already).
+//
+// The order of a frontier and of the keys is free (the keys are sorted at the
+// end), so no offsets are needed: a block enumerates a few pairs per wave,
+// collects the hits as (pair, i, j) codes in LDS, reserves as many places as
+// there are with one atomic (one per wave would be 17 ns each, one after the
+// other) and writes them, the child ids of all hits looked up at once.  If
+// they outgrow the LDS list the block enumerates its pairs again and writes
+// directly.  Places past out_cap are not written and set *over.
+//
+// Enumerating a pair: the entries of both nodes that do not reach into the
+// other node's MBR have no hits; the rest are packed in LDS, the inner ones
+// held one per lane (in as many copies as fit the wave), the outer ones read
+// as broadcasts, 64 predicates a round.  Of 32 entries about 12 stay, three
+// rounds in place of 16; the candidate lists by low x (below) cut about as
+// many predicates but took some 60 lane permutes per pair, and bound the
+// count pass by the LDS (2M x 2M rectangles, about 0.2M leaf pairs: count,
+// scan and fill 253 us, here 89 us, bound by vector instructions, some 210 per
+// pair).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kOnceWaves = 16;
+constexpr uint32_t kOncePairs = 8;     // pairs per wave at most
+constexpr uint32_t kOnceBuf = 4096;    // hits a block collects
+
+// Floats as integers of the same order (-0 below +0), and back.
+__device__ __forceinline__ int ordered(float v) {
+    const int i = __float_as_int(v);
+    return i ^ ((i >> 31) & 0x7FFFFFFF);
+}
+__device__ __forceinline__ float unordered(int i) { return __int_as_float(i ^ ((i >> 31) & 0x7FFFFFFF)); }
+// Smallest (SIGN < 0) or largest value of lanes 0..31 (in lane 31) and of
+// 32..63, of all lanes with WAVE (in lane 63).  As integers, a step is one
+// instruction; as floats each would canonicalize first.
+template <int CTRL, int ROWS, int SIGN>
+__device__ __forceinline__ int lanes_step(int v) {
+    const int o = __builtin_amdgcn_update_dpp(SIGN < 0 ? 0x7FFFFFFF : -0x7FFFFFFF - 1, v, CTRL, ROWS, 0xF, false);
+    return SIGN < 0 ? min(v, o) : max(v, o);
+}
+template <bool WAVE, int SIGN>
+__device__ __forceinline__ int lanes_extreme(int v) {
+    v = lanes_step<0x111, 0xF, SIGN>(v);
+    v = lanes_step<0x112, 0xF, SIGN>(v);
+    v = lanes_step<0x114, 0xF, SIGN>(v);
+    v = lanes_step<0x118, 0xF, SIGN>(v);
+    v = lanes_step<0x142, 0xA, SIGN>(v);
+    if (WAVE) v = lanes_step<0x143, 0xC, SIGN>(v);
+    return v;
+}
+__device__ __forceinline__ float lane_f(int v, int lane) { return unordered(__builtin_amdgcn_readlane(v, lane)); }
+
+// PACK: both nodes have at most 32 entries, so lanes 0..31 take one and lanes
+// 32..63 the other.
+template <int MODE, bool PACK>
+__global__ void __launch_bounds__(1024, 8)
+join_once_kernel(TreeView A, TreeView B, const uint2 *__restrict__ fr, uint32_t nfr,
+                 const uint64_t *__restrict__ nfr_dev, uint32_t per_wave, uint2 *__restrict__ next,
+                 uint64_t *__restrict__ keys, uint64_t out_cap, unsigned long long *__restrict__ count,
+                 uint32_t *__restrict__ over) {
+    __shared__ float4 box[kOnceWaves][128];     // packed outer entries, then (from 64) inner ones
+    __shared__ uint8_t at[kOnceWaves][128];     // their places in the nodes
+    __shared__ uint32_t buf[kOnceBuf], bn;
+    __shared__ unsigned long long gbase;
+    if (nfr_dev && *nfr_dev < nfr) nfr = (uint32_t)*nfr_dev;
+    const uint32_t t = threadIdx.x, lane = t & 63u, w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    const uint32_t p0 = blockIdx.x * (kOnceWaves * per_wave);
+    if (p0 >= nfr) return;   // the whole block
+    const uint32_t pend = min(nfr - p0, kOnceWaves * per_wave);
+    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+    const uint32_t Fa = A.fanout, Fb = B.fanout;
+    auto put = [&](uint32_t code, uint64_t o) {
+        if (o >= out_cap) return;
+        const uint2 pr = fr[p0 + (code >> 12)];
+        const uint32_t ca = ptr_any(A, pr.x, (code >> 6) & 63u), cb = ptr_any(B, pr.y, code & 63u);
+        if (MODE == JOIN_EMIT)
+            keys[o] = ((uint64_t)ca << 32) | cb;
+        else
+            next[o] = make_uint2(ca, cb);
+    };
+    struct Entry {
+        float lx, ly, hx, hy;
+    };
+    // lane's entry of the pair: NaN past the node's entries, as unused slots
+    Entry a, b;
+    auto load = [&](uint32_t k) {
+        const uint2 pr = fr[p0 + min(k, pend - 1)];
+        a = b = {NAN, NAN, NAN, NAN};
+        if constexpr (PACK) {
+            const uint32_t e = lane & 31u;
+            if (lane < 32) {
+                if (e < Fa) load_any(A, pr.x, e, a.lx, a.ly, a.hx, a.hy);
+            } else {
+                if (e < Fb) load_any(B, pr.y, e, a.lx, a.ly, a.hx, a.hy);
+            }
+        } else {
+            if (lane < Fa) load_any(A, pr.x, lane, a.lx, a.ly, a.hx, a.hy);
+            if (lane < Fb) load_any(B, pr.y, lane, b.lx, b.ly, b.hx, b.hy);
+        }
+    };
+    // all pairs of the wave; sink(code, hit, hits of the round)
+    auto pairs = [&](auto &&sink) {
+        load(w);
+        for (uint32_t k = w; k < pend; k += kOnceWaves) {
+            const Entry ca = a, cb = b;
+            if (k + kOnceWaves < pend) load(k + kOnceWaves);
+            uint32_t na, nb;
+            if constexpr (PACK) {
+                const bool real = ca.lx == ca.lx;
+                const int lo = ordered(INFINITY), up = ordered(-INFINITY);   // of unused slots
+                const int lx = lanes_extreme<false, -1>(real ? ordered(ca.lx) : lo);
+                const int ly = lanes_extreme<false, -1>(real ? ordered(ca.ly) : lo);
+                const int hx = lanes_extreme<false, 1>(real ? ordered(ca.hx) : up);
+                const int hy = lanes_extreme<false, 1>(real ? ordered(ca.hy) : up);
+                // the other half's MBR
+                const bool hi = lane >= 32;
+                const float olx = hi ? lane_f(lx, 31) : lane_f(lx, 63), oly = hi ? lane_f(ly, 31) : lane_f(ly, 63);
+                const float ohx = hi ? lane_f(hx, 31) : lane_f(hx, 63), ohy = hi ? lane_f(hy, 31) : lane_f(hy, 63);
+                const bool keep = ca.lx <= ohx && olx <= ca.hx && ca.ly <= ohy && oly <= ca.hy;
+                const uint64_t m = __ballot(keep);
+                na = (uint32_t)__popc((uint32_t)m);
+                nb = (uint32_t)__popc((uint32_t)(m >> 32));
+                if (keep) {
+                    const uint32_t r = (uint32_t)__popcll(m & below);
+                    const uint32_t to = hi ? 64 + r - na : r;
+                    box[w][to] = make_float4(ca.lx, ca.ly, ca.hx, ca.hy);
+                    at[w][to] = (uint8_t)(lane & 31u);
+                }
+            } else {
+                const bool ra = ca.lx == ca.lx, rb = cb.lx == cb.lx;
+                const int lo = ordered(INFINITY), up = ordered(-INFINITY);   // of unused slots
+                const float alx = lane_f(lanes_extreme<true, -1>(ra ? ordered(ca.lx) : lo), 63);
+                const float aly = lane_f(lanes_extreme<true, -1>(ra ? ordered(ca.ly) : lo), 63);
+                const float ahx = lane_f(lanes_extreme<true, 1>(ra ? ordered(ca.hx) : up), 63);
+                const float ahy = lane_f(lanes_extreme<true, 1>(ra ? ordered(ca.hy) : up), 63);
+                const float blx = lane_f(lanes_extreme<true, -1>(rb ? ordered(cb.lx) : lo), 63);
+                const float bly = lane_f(lanes_extreme<true, -1>(rb ? ordered(cb.ly) : lo), 63);
+                const float bhx = lane_f(lanes_extreme<true, 1>(rb ? ordered(cb.hx) : up), 63);
+                const float bhy = lane_f(lanes_extreme<true, 1>(rb ? ordered(cb.hy) : up), 63);
+                const bool ka = ca.lx <= bhx && blx <= ca.hx && ca.ly <= bhy && bly <= ca.hy;
+                const bool kb = cb.lx <= ahx && alx <= cb.hx && cb.ly <= ahy && aly <= cb.hy;
+                const uint64_t ma = __ballot(ka), mb = __ballot(kb);
+                na = (uint32_t)__popcll(ma);
+                nb = (uint32_t)__popcll(mb);
+                if (ka) {
+                    const uint32_t to = (uint32_t)__popcll(ma & below);
+                    box[w][to] = make_float4(ca.lx, ca.ly, ca.hx, ca.hy);
+                    at[w][to] = (uint8_t)lane;
+                }
+                if (kb) {
+                    const uint32_t to = 64 + (uint32_t)__popcll(mb & below);
+                    box[w][to] = make_float4(cb.lx, cb.ly, cb.hx, cb.hy);
+                    at[w][to] = (uint8_t)lane;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (na && nb) {   // wave-uniform
+                // copies of the inner entries side by side: 64 >> sh outer ones a round
+                const uint32_t sh = nb > 1 ? 32 - __builtin_clz(nb - 1) : 0;
+                const uint32_t j = lane & ((1u << sh) - 1u), row = lane >> sh, rows = 64u >> sh;
+                const float4 in = box[w][64 + min(j, nb - 1)];
+                for (uint32_t r = 0; r < na; r += rows) {
+                    const uint32_t i = r + row;
+                    const float4 o = box[w][min(i, na - 1)];
+                    const bool hit = j < nb && i < na && o.x <= in.z && in.x <= o.z && o.y <= in.w && in.y <= o.w;
+                    const uint64_t m = __ballot(hit);
+                    if (m) {
+                        const uint32_t code = hit ? k << 12 | (uint32_t)at[w][i] << 6 | at[w][64 + j] : 0u;
+                        uint32_t pos = 0;
+                        if (lane == 0) pos = atomicAdd(&bn, (uint32_t)__popcll(m));
+                        pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + (uint32_t)__popcll(m & below);
+                        sink(code, hit, pos);
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    if (t == 0) bn = 0;
+    __syncthreads();
+    pairs([&](uint32_t code, bool hit, uint32_t pos) {
+        if (hit && pos < kOnceBuf) buf[pos] = code;
+    });
+    __syncthreads();
+    const uint32_t n = bn;
+    if (n == 0) return;
+    if (t == 0) {
+        gbase = atomicAdd(count, (unsigned long long)n);
+        if (gbase + n > out_cap) atomicOr(over, 1u);
+    }
+    __syncthreads();
+    const uint64_t base = gbase;
+    if (n <= kOnceBuf) {
+        for (uint32_t x = t; x < n; x += 1024) put(buf[x], base + x);
+        return;
+    }
+    if (t == 0) bn = 0;
+    __syncthreads();
+    pairs([&](uint32_t code, bool hit, uint32_t pos) {
+        if (hit) put(code, base + pos);
+    });
+}
+
+hipError_t launch_join_once(const TreeView &a, const TreeView &b, const uint2 *fr, uint32_t nfr, const uint64_t *nd,
+                            int mode, uint2 *next, uint64_t *keys, uint64_t cap, uint64_t *count, uint32_t *over,
+                            hipStream_t s) {
+    if (nfr == 0) return hipSuccess;
+    // about three blocks per CU before a wave takes a second pair
+    const uint32_t per = std::min(kOncePairs, nfr / (kOnceWaves * 3 * (uint32_t)num_cus()) + 1);
+    const dim3 grid((nfr + kOnceWaves * per - 1) / (kOnceWaves * per)), block(kOnceWaves * 64);
+    unsigned long long *c = reinterpret_cast<unsigned long long *>(count);
+    const bool pack = a.fanout <= 32 && b.fanout <= 32;
+#define RT_ONCE(M_, P_) \
+    hipLaunchKernelGGL((join_once_kernel<M_, P_>), grid, block, 0, s, a, b, fr, nfr, nd, per, next, keys, cap, c, over)
+    if (mode == JOIN_EMIT) {
+        if (pack) RT_ONCE(JOIN_EMIT, true);
+        else RT_ONCE(JOIN_EMIT, false);
+    } else {
+        if (pack) RT_ONCE(JOIN_BOTH, true);
+        else RT_ONCE(JOIN_BOTH, false);
+    }
+#undef RT_ONCE
+    return hipGetLastError();
+}
+
+// Clears what a replayed join counts into: the status, the level sizes and
+// the overflow flag (nlv words), the bucket counts (if not NULL), and sets
+// level 0 to the pair of roots.
+__global__ void __launch_bounds__(256)
+join_init_kernel(Ctrl *__restrict__ ctrl, uint64_t *__restrict__ lv, uint32_t nlv, uint2 *__restrict__ fr0,
+                 uint32_t *__restrict__ cnt) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    for (uint32_t k = i; k < sizeof(Ctrl) / 4; k += gridDim.x * 256) reinterpret_cast<uint32_t *>(ctrl)[k] = 0;
+    for (uint32_t k = i; k < nlv; k += gridDim.x * 256) lv[k] = 0;
+    if (i == 0) *fr0 = make_uint2(0u, 0u);
+    if (cnt && i < kPairBuckets) cnt[i] = 0;
+}
+
+hipError_t launch_join_init(Ctrl *ctrl, uint64_t *lv, uint32_t nlv, uint2 *fr0, uint32_t *cnt, hipStream_t s) {
+    hipLaunchKernelGGL(join_init_kernel, dim3(kPairBuckets / 256), dim3(256), 0, s, ctrl, lv, nlv, fr0, cnt);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -458,30 +702,6 @@ __global__ void keys_to_pairs_kernel(const uint64_t *__restrict__ keys, uint64_t
     }
 }
 
-// The same with the count on the device (at most n_max): writes nothing if the
-// count exceeds capacity or *skip has bit 0 set.
-__global__ void keys_to_pairs_dev_kernel(const uint64_t *__restrict__ keys, const uint64_t *__restrict__ n_dev,
-                                         uint64_t capacity, const uint32_t *__restrict__ skip,
-                                         uint32_t *__restrict__ pairs) {
-    const uint64_t n = *n_dev;
-    if (n > capacity || (*skip & 1u)) return;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = keys[i];
-        pairs[2 * i] = (uint32_t)(k >> 32);
-        pairs[2 * i + 1] = (uint32_t)k;
-    }
-}
-
-hipError_t launch_keys_to_pairs_dev(const uint64_t *keys, const uint64_t *n_dev, uint64_t n_max, uint64_t capacity,
-                                    const uint32_t *skip, uint32_t *pairs, hipStream_t s) {
-    uint64_t blocks = (n_max + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    if (blocks == 0) blocks = 1;
-    hipLaunchKernelGGL(keys_to_pairs_dev_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, keys, n_dev, capacity, skip,
-                       pairs);
-    return hipGetLastError();
-}
-
 __global__ void copy_err_kernel(const Ctrl *__restrict__ ctrl, uint32_t *__restrict__ dst) { *dst = ctrl->err; }
 
 hipError_t launch_copy_err(const Ctrl *ctrl, uint32_t *dst, hipStream_t s) {
@@ -498,9 +718,12 @@ hipError_t launch_keys_to_pairs(const uint64_t *keys, uint64_t n, uint32_t *pair
 }
 
 // ---- pair keys: bucket sort by the top digit --------------------------------
-constexpr uint32_t kPairTile = 4096;   // keys per block in the scatter (256 x 16)
+// Keys per block in the scatter, 4 per thread: both passes wait on memory, and
+// a result of a million keys has no more tiles than the chip has CUs (with 256
+// threads and 16 keys each they took 10 and 23 us, now 7 and 16).
+constexpr uint32_t kPairTile = 4096, kPairThreads = 1024;
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kPairThreads)
 pair_bucket_hist(const uint64_t *__restrict__ keys, uint64_t n, const uint64_t *__restrict__ n_dev, int shift,
                  uint32_t *__restrict__ cnt) {
     __shared__ uint32_t h[kPairBuckets];
@@ -543,30 +766,30 @@ pair_bucket_scan(const uint32_t *__restrict__ cnt, uint32_t *__restrict__ start,
 // A block takes a tile of keys: LDS ranks per bucket, one global reservation
 // per bucket present in the tile, then every key goes to its bucket.  The
 // order inside a bucket is arbitrary (the bucket is sorted next).
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kPairThreads)
 pair_bucket_scatter(const uint64_t *__restrict__ keys, uint64_t n, const uint64_t *__restrict__ n_dev, int shift,
                     const uint32_t *__restrict__ start, uint32_t *__restrict__ cursor, uint64_t *__restrict__ out) {
-    constexpr uint32_t R = kPairTile / 256;
+    constexpr uint32_t R = kPairTile / kPairThreads;
     __shared__ uint32_t c[kPairBuckets];
     if (n_dev) n = min(n, *n_dev);
     for (uint64_t t0 = (uint64_t)blockIdx.x * kPairTile; t0 < n; t0 += (uint64_t)gridDim.x * kPairTile) {
-        for (uint32_t i = threadIdx.x; i < kPairBuckets; i += 256) c[i] = 0;
+        for (uint32_t i = threadIdx.x; i < kPairBuckets; i += kPairThreads) c[i] = 0;
         __syncthreads();
         uint64_t k[R];
         uint32_t rk[R];
 #pragma unroll
         for (uint32_t r = 0; r < R; ++r) {
-            const uint64_t i = t0 + r * 256 + threadIdx.x;
+            const uint64_t i = t0 + r * kPairThreads + threadIdx.x;
             k[r] = i < n ? keys[i] : 0ull;
             rk[r] = i < n ? atomicAdd(&c[(uint32_t)(k[r] >> shift)], 1u) : 0u;
         }
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < kPairBuckets; i += 256)
+        for (uint32_t i = threadIdx.x; i < kPairBuckets; i += kPairThreads)
             if (c[i]) c[i] = start[i] + atomicAdd(&cursor[i], c[i]);
         __syncthreads();
 #pragma unroll
         for (uint32_t r = 0; r < R; ++r) {
-            const uint64_t i = t0 + r * 256 + threadIdx.x;
+            const uint64_t i = t0 + r * kPairThreads + threadIdx.x;
             if (i < n) out[c[(uint32_t)(k[r] >> shift)] + rk[r]] = k[r];
         }
         __syncthreads();
@@ -603,65 +826,137 @@ __device__ __forceinline__ uint32_t count_below(const uint64_t *v, uint32_t n, u
     return lo;
 }
 
-// One block per bucket: bitonic sort in LDS over the bucket padded to a power
-// of two (keys are distinct; padding with all ones sorts last).  A bucket over
-// the LDS cap (ids far from uniform) is sorted in runs of the cap, which are
-// then merged pairwise through tmp (the partition's input, free by now) at the
-// bucket's own positions: every key finds its place as its index in its run
-// plus the number of keys below it in the other run.
+// One block per bucket: a counting sort in LDS on the next kPairSub bits of
+// the keys, then every key counts the smaller ones of its sub-bucket (about
+// one key each) and is written at its place.  Keys that crowd a sub-bucket
+// (ids far from uniform) are sorted by a bitonic network instead, over the
+// bucket padded to a power of two (keys are distinct; padding with all ones
+// sorts last); for every bucket that network took 45 us where the counting
+// takes 14 to 30 us (780K keys).  A bucket over the LDS cap is sorted that way in
+// runs of the cap, which are then merged pairwise through tmp (the partition's
+// input, free by now) at the bucket's own positions: every key finds its
+// place as its index in its run plus the number of keys below it in the other
+// run.  With `pairs` the results are (a, b) words there (which may be tmp:
+// a block only touches its bucket's places), written if the count *n_dev fits
+// `capacity` and bit 0 of *skip is clear, and *err_out receives the error
+// word; else sorted keys, in place.
+constexpr int kPairSub = 9;
+typedef uint32_t Words __attribute__((ext_vector_type(2), aligned(4)));   // the caller's pairs: any word
+
 __global__ void __launch_bounds__(256)
-pair_bucket_sort(uint64_t *__restrict__ keys, uint64_t *__restrict__ tmp, const uint32_t *__restrict__ start) {
+pair_bucket_sort(uint64_t *__restrict__ keys, uint64_t *tmp, const uint32_t *__restrict__ start, int shift,
+                 PairsOut po) {
+    constexpr uint32_t NS = 1u << kPairSub;
     __shared__ uint64_t buf[kPairBucketCap];
-    for (uint32_t bk = blockIdx.x; bk < kPairBuckets; bk += gridDim.x) {
-        const uint32_t s0 = start[bk], c = start[bk + 1] - s0;
-        if (c < 2) continue;
-        for (uint32_t r0 = 0; r0 < c; r0 += kPairBucketCap) {
-            const uint32_t rc = min(c - r0, kPairBucketCap);
-            uint32_t P = 2;
-            while (P < rc) P <<= 1;
-            for (uint32_t i = threadIdx.x; i < P; i += blockDim.x) buf[i] = i < rc ? keys[s0 + r0 + i] : ~0ull;
-            __syncthreads();
-            lds_bitonic_u64(buf, P);
-            for (uint32_t i = threadIdx.x; i < rc; i += blockDim.x) keys[s0 + r0 + i] = buf[i];
-            __syncthreads();
+    __shared__ uint32_t sub[NS + 1], wsum[4], wmax[4];
+    if (po.err_out && blockIdx.x == 0 && threadIdx.x == 0) *po.err_out = po.ctrl->err;
+    if (po.pairs && (*po.n_dev > po.capacity || (*po.skip & 1u))) return;
+    const uint32_t bk = blockIdx.x, t = threadIdx.x, lane = t & 63u, w = t >> 6;
+    const uint32_t s0 = start[bk], c = start[bk + 1] - s0;
+    if (c == 0 || (c == 1 && !po.pairs)) return;
+    auto put = [&](uint32_t i, uint64_t x) {
+        if (po.pairs)
+            reinterpret_cast<Words *>(po.pairs)[s0 + i] = Words{(uint32_t)(x >> 32), (uint32_t)x};
+        else
+            keys[s0 + i] = x;
+    };
+    if (c <= kPairBucketCap) {
+        const int sh = shift > kPairSub ? shift - kPairSub : 0;
+        auto digit = [&](uint64_t x) { return (uint32_t)(x >> sh) & (NS - 1u); };
+        for (uint32_t i = t; i < NS; i += 256) sub[i] = 0;
+        __syncthreads();
+        for (uint32_t i = t; i < c; i += 256) atomicAdd(&sub[digit(keys[s0 + i])], 1u);
+        __syncthreads();
+        const uint32_t x0 = sub[2 * t], x1 = sub[2 * t + 1];
+        uint32_t inc = x0 + x1, mx = max(x0, x1);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(inc, d);
+            if ((int)lane >= d) inc += y;
+            mx = max(mx, (uint32_t)__shfl_xor((int)mx, d));
         }
-        if (c <= kPairBucketCap) continue;
-        uint64_t *src = keys + s0, *dst = tmp + s0;
-        for (uint32_t w = kPairBucketCap; w < c; w *= 2) {
-            for (uint32_t i = threadIdx.x; i < c; i += blockDim.x) {
-                const uint32_t a0 = i / (2 * w) * (2 * w);
-                const uint32_t b0 = min(a0 + w, c), b1 = min(a0 + 2 * w, c);
-                const uint64_t x = src[i];
-                const uint32_t pos = i < b0 ? i + count_below(src + b0, b1 - b0, x)
-                                            : (i - b0) + a0 + count_below(src + a0, b0 - a0, x);
-                dst[pos] = x;
+        if (lane == 63) {
+            wsum[w] = inc;
+            wmax[w] = mx;
+        }
+        __syncthreads();
+        uint32_t ex = inc - x0 - x1;
+        for (uint32_t i = 0; i < w; ++i) ex += wsum[i];
+        mx = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+        sub[2 * t] = ex;
+        sub[2 * t + 1] = ex + x0;
+        __syncthreads();
+        for (uint32_t i = t; i < c; i += 256) {
+            const uint64_t x = keys[s0 + i];
+            buf[atomicAdd(&sub[digit(x)], 1u)] = x;   // sub: now the ends
+        }
+        __syncthreads();
+        if (mx <= 32) {
+            for (uint32_t i = t; i < c; i += 256) {
+                const uint64_t x = buf[i];
+                const uint32_t d = digit(x), b = d ? sub[d - 1] : 0u, e = sub[d];
+                uint32_t r = b;
+                for (uint32_t k = b; k < e; ++k) r += buf[k] < x ? 1u : 0u;
+                put(r, x);
             }
-            __syncthreads();
-            uint64_t *t2 = src;
-            src = dst;
-            dst = t2;
+            return;
         }
-        if (src != keys + s0) {
-            for (uint32_t i = threadIdx.x; i < c; i += blockDim.x) keys[s0 + i] = src[i];
-            __syncthreads();
+        uint32_t P = 2;
+        while (P < c) P <<= 1;
+        for (uint32_t i = c + t; i < P; i += 256) buf[i] = ~0ull;
+        __syncthreads();
+        lds_bitonic_u64(buf, P);
+        for (uint32_t i = t; i < c; i += 256) put(i, buf[i]);
+        return;
+    }
+    for (uint32_t r0 = 0; r0 < c; r0 += kPairBucketCap) {
+        const uint32_t rc = min(c - r0, kPairBucketCap);
+        uint32_t P = 2;
+        while (P < rc) P <<= 1;
+        for (uint32_t i = t; i < P; i += 256) buf[i] = i < rc ? keys[s0 + r0 + i] : ~0ull;
+        __syncthreads();
+        lds_bitonic_u64(buf, P);
+        for (uint32_t i = t; i < rc; i += 256) keys[s0 + r0 + i] = buf[i];
+        __syncthreads();
+    }
+    uint64_t *src = keys + s0, *dst = tmp + s0;
+    for (uint32_t wd = kPairBucketCap; wd < c; wd *= 2) {
+        for (uint32_t i = t; i < c; i += 256) {
+            const uint32_t a0 = i / (2 * wd) * (2 * wd);
+            const uint32_t b0 = min(a0 + wd, c), b1 = min(a0 + 2 * wd, c);
+            const uint64_t x = src[i];
+            const uint32_t pos = i < b0 ? i + count_below(src + b0, b1 - b0, x)
+                                        : (i - b0) + a0 + count_below(src + a0, b0 - a0, x);
+            dst[pos] = x;
         }
+        __syncthreads();
+        uint64_t *t2 = src;
+        src = dst;
+        dst = t2;
+    }
+    if (po.pairs || src != keys + s0) {
+        for (uint32_t i = t; i < c; i += 256) put(i, src[i]);
     }
 }
 
 hipError_t launch_pair_bucket_sort(uint64_t *keys, uint64_t n, int shift, uint64_t *out, uint32_t *ws,
-                                   hipStream_t s, const uint64_t *n_dev) {
+                                   hipStream_t s, const PairsOut *po) {
     if (n == 0) return hipSuccess;
     uint32_t *cnt = ws, *start = ws + kPairBuckets, *cursor = ws + 2 * kPairBuckets + 4;
-    hipError_t e = launch_zero(cnt, 4 * kPairBuckets, s);
-    if (e != hipSuccess) return e;
+    const uint64_t *n_dev = po ? po->n_dev : nullptr;
+    if (!po) {
+        hipError_t e = launch_zero(cnt, 4 * kPairBuckets, s);
+        if (e != hipSuccess) return e;
+    }
     const uint64_t tiles = (n + kPairTile - 1) / kPairTile;
     const uint32_t cus = (uint32_t)num_cus();
     const uint32_t hb = (uint32_t)(tiles < (uint64_t)cus * 4 ? tiles : (uint64_t)cus * 4);
-    hipLaunchKernelGGL(pair_bucket_hist, dim3(hb), dim3(256), 0, s, keys, n, n_dev, shift, cnt);
+    hipLaunchKernelGGL(pair_bucket_hist, dim3(hb), dim3(kPairThreads), 0, s, keys, n, n_dev, shift, cnt);
     hipLaunchKernelGGL(pair_bucket_scan, dim3(1), dim3(1024), 0, s, cnt, start, cursor);
     const uint32_t sb = (uint32_t)(tiles < (uint64_t)cus * 8 ? tiles : (uint64_t)cus * 8);
-    hipLaunchKernelGGL(pair_bucket_scatter, dim3(sb), dim3(256), 0, s, keys, n, n_dev, shift, start, cursor, out);
-    hipLaunchKernelGGL(pair_bucket_sort, dim3(kPairBuckets), dim3(256), 0, s, out, keys, start);
+    hipLaunchKernelGGL(pair_bucket_scatter, dim3(sb), dim3(kPairThreads), 0, s, keys, n, n_dev, shift, start, cursor, out);
+    hipLaunchKernelGGL(pair_bucket_sort, dim3(kPairBuckets), dim3(256), 0, s, out, keys, start, shift,
+                       po ? *po : PairsOut{});
     return hipGetLastError();
 }
 

@@ -1,11 +1,13 @@
 // Spatial join entry points: level-synchronous traversal of both trees
 // (section 4) driven from the host, one frontier of node pairs per level.
 //
-// Per level: a count pass gives each frontier pair its number of qualifying
-// child pairs, a scan turns the counts into output offsets, the host reads
-// the total, and a fill pass writes the next frontier (or, at the leaves,
-// the (idA << 32 | idB) keys).  The keys are radix sorted into the canonical
-// lexicographic order.  Device buffers are kept across levels and across
+// Per level of a first run: a count pass gives each frontier pair its number
+// of qualifying child pairs, a scan turns the counts into output offsets, the
+// host reads the total, and a fill pass writes the next frontier (or, at the
+// leaves, the (idA << 32 | idB) keys).  Later runs, whose buffers have their
+// size, take one pass per level (2M x 2M rectangles: 478 -> 202 us), whatever
+// the flags: these choose how a first or counted run expands a node pair.  The
+// keys are sorted into the canonical lexicographic order.  Device buffers are kept across levels and across
 // calls (a per-device pool of workspaces, grown geometrically), so a join
 // allocates only when it outgrows every earlier one on its device.
 #include <cstdlib>
@@ -193,9 +195,8 @@ int join_keys_replay(const rt_tree *a, const rt_tree *b, int flags, hipStream_t 
     }
     // every launch of the replay; RT_OK, kReplayMiss or an error
     auto enqueue = [&](hipStream_t st) -> int {
-        hipError_t e2 = launch_zero(ctrl, sizeof(Ctrl), st);
-        if (e2 == hipSuccess) e2 = launch_zero(lv, (H + 2) * 8, st);   // and the overflow flag
-        if (e2 == hipSuccess) e2 = launch_zero(w.fr[0].b.p, 8, st);   // (root A, root B) = (0, 0)
+        hipError_t e2 = launch_join_init(ctrl, lv, (uint32_t)(H + 2), w.fr[0].as<uint2>(),
+                                         fused ? w.hist.as<uint32_t>() : nullptr, st);
         if (e2 != hipSuccess) return hip_fail(e2, "join setup");
         int la = (int)a->height - 1, lb = (int)b->height - 1;
         int cur = 0;
@@ -211,31 +212,41 @@ int join_keys_replay(const rt_tree *a, const rt_tree *b, int flags, hipStream_t 
             const uint2 *fr = w.fr[cur].as<uint2>();
             uint64_t *off = w.off.as<uint64_t>();
             uint16_t *slots = w.slot.as<uint16_t>();
-            e2 = launch_join_level(va, vb, fr, (uint32_t)lim, nd, mode, false, w.cnt.as<uint32_t>(), nullptr,
-                                   nullptr, nullptr, 0, slots, ctrl, flags, nullptr, st);
-            if (e2 == hipSuccess)
-                e2 = launch_scan_u32_dev(w.cnt.as<uint32_t>(), nd, lim, off, w.stmp.as<uint64_t>(), lv + L + 1,
-                                         next_lim, over, st);
-            if (e2 == hipSuccess)
-                e2 = launch_join_level(va, vb, fr, (uint32_t)lim, nd, mode, true, nullptr, off,
-                                       emit ? nullptr : w.fr[1 - cur].as<uint2>(),
-                                       emit ? w.keys.as<uint64_t>() : nullptr, next_lim, slots, ctrl, flags,
-                                       nullptr, st);
+            if (mode == JOIN_BOTH || emit) {
+                e2 = launch_join_once(va, vb, fr, (uint32_t)lim, nd, mode, w.fr[1 - cur].as<uint2>(),
+                                      w.keys.as<uint64_t>(), next_lim, lv + L + 1, over, st);
+            } else {
+                e2 = launch_join_level(va, vb, fr, (uint32_t)lim, nd, mode, false, w.cnt.as<uint32_t>(), nullptr,
+                                       nullptr, nullptr, 0, slots, ctrl, flags, nullptr, st);
+                if (e2 == hipSuccess)
+                    e2 = launch_scan_u32_dev(w.cnt.as<uint32_t>(), nd, lim, off, w.stmp.as<uint64_t>(), lv + L + 1,
+                                             next_lim, over, st);
+                if (e2 == hipSuccess)
+                    e2 = launch_join_level(va, vb, fr, (uint32_t)lim, nd, mode, true, nullptr, off,
+                                           emit ? nullptr : w.fr[1 - cur].as<uint2>(),
+                                           emit ? w.keys.as<uint64_t>() : nullptr, next_lim, slots, ctrl, flags,
+                                           nullptr, st);
+            }
             if (e2 != hipSuccess) return hip_fail(e2, "join level");
             cur = 1 - cur;
             lim = next_lim;
             descend(mode, la, lb);
         }
         if (fused) {
+            PairsOut po;
+            po.n_dev = lv + H;
+            po.capacity = cap_out;
+            po.skip = over;
+            po.pairs = out;
+            po.ctrl = ctrl;
+            po.err_out = over + 1;   // beside the overflow flag: the status is one read
             e2 = launch_pair_bucket_sort(w.keys.as<uint64_t>(), kmax, 21 + ba, w.ktmp.as<uint64_t>(),
-                                         w.hist.as<uint32_t>(), st, lv + H);
-            if (e2 == hipSuccess)
-                e2 = launch_keys_to_pairs_dev(w.ktmp.as<uint64_t>(), lv + H, kmax, cap_out, over, out, st);
+                                         w.hist.as<uint32_t>(), st, &po);
             if (e2 != hipSuccess) return hip_fail(e2, "join sort");
+        } else {
+            e2 = launch_copy_err(ctrl, over + 1, st);
+            if (e2 != hipSuccess) return hip_fail(e2, "join status");
         }
-        // the error word beside the overflow flag: the status is one read
-        e2 = launch_copy_err(ctrl, over + 1, st);
-        if (e2 != hipSuccess) return hip_fail(e2, "join status");
         return RT_OK;
     };
     // what the launches depend on: both tree views, the flags, the level

@@ -19,20 +19,26 @@ constexpr uint32_t kPairBucketCap = 4096;    // keys a bucket may hold to be sor
 // cursors.
 constexpr uint64_t kPairSortWords = 3 * kPairBuckets + 8;
 
+// What a replayed join's sort reads from and leaves on the device.
+struct Ctrl;
+struct PairsOut {
+    const uint64_t *n_dev = nullptr;   // the key count (at most n)
+    uint64_t capacity = 0;             // (a, b) words are written to pairs if it fits this
+    const uint32_t *skip = nullptr;    // and bit 0 here is clear
+    uint32_t *pairs = nullptr;         // may be the keys' own buffer
+    const Ctrl *ctrl = nullptr;        // ctrl->err is copied to err_out
+    uint32_t *err_out = nullptr;
+};
+
 // keys (n) -> out (n), sorted; keys is overwritten (merge space for buckets
 // over the LDS cap).  shift: every key is below 2^(shift + 11).  ws:
-// kPairSortWords uint32.  n_dev (if not NULL): the key count on the device,
-// at most n (n then only sizes the grids).
+// kPairSortWords uint32.  po (if not NULL): the count is on the device (n then
+// only sizes the grids), ws holds zeroed bucket counts, and the result are (a,
+// b) words (out is left unsorted).
 hipError_t launch_pair_bucket_sort(uint64_t *keys, uint64_t n, int shift, uint64_t *out, uint32_t *ws,
-                                   hipStream_t s, const uint64_t *n_dev = nullptr);
-
-// Keys to (a, b) words with the count on the device (at most n_max): writes
-// nothing when the count exceeds capacity or bit 0 of *skip is set.
-hipError_t launch_keys_to_pairs_dev(const uint64_t *keys, const uint64_t *n_dev, uint64_t n_max, uint64_t capacity,
-                                    const uint32_t *skip, uint32_t *pairs, hipStream_t s);
+                                   hipStream_t s, const PairsOut *po = nullptr);
 
 // Join status for a single read: *dst = ctrl->err (one thread).
-struct Ctrl;
 hipError_t launch_copy_err(const Ctrl *ctrl, uint32_t *dst, hipStream_t s);
 
 }  // namespace rtk

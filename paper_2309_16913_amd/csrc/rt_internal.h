@@ -402,6 +402,13 @@ hipError_t launch_join_level(const TreeView &a, const TreeView &b, const uint2 *
                              uint32_t nfr, const uint64_t *nfr_dev, int mode, bool fill, uint32_t *counts,
                              const uint64_t *offsets, uint2 *next, uint64_t *keys, uint64_t out_cap,
                              uint16_t *slots, Ctrl *ctrl, int flags, unsigned long long *tests_acc, hipStream_t s);
+// A level (JOIN_BOTH or JOIN_EMIT) in one pass: the frontier's child pairs or
+// keys in any order, *count of them added (zeroed before), those past cap not
+// written and bit 0 of *over set.
+hipError_t launch_join_once(const TreeView &a, const TreeView &b, const uint2 *fr, uint32_t nfr, const uint64_t *nd,
+                            int mode, uint2 *next, uint64_t *keys, uint64_t cap, uint64_t *count, uint32_t *over,
+                            hipStream_t s);
+hipError_t launch_join_init(Ctrl *ctrl, uint64_t *lv, uint32_t nlv, uint2 *fr0, uint32_t *cnt, hipStream_t s);
 hipError_t launch_keys_to_pairs(const uint64_t *keys, uint64_t n, uint32_t *pairs, hipStream_t s);
 
 // ---- batch --------------------------------------------------------------
