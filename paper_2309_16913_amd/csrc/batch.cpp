@@ -71,13 +71,20 @@ static BatchRec batch_rec(const rt_batch *b) {
     r.rec_count = reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(b->d_rec) +
                                                ((16ull * kRecChunk * b->rec_nchunks + 255) & ~255ull));
     r.rec_nchunks = b->rec_nchunks;
+    r.width = group_width(b->trees.empty() ? 64 : b->trees[0]->fanout);
+    bool same = true;
+    for (const rt_tree *t : b->trees) same = same && group_width(t->fanout) == r.width;
+    const uint32_t n = same ? batch_blocks(b->nitems) * 4 * (64 / r.width) : 0u;
+    if (r.rec_nchunks >= n && r.rec_nchunks - n >= n / 16) r.rec_fixed = n;   // as walk_fixed_chunks
     return r;
 }
 
 // Persistent count pass (recording with rp.rec) + scan over all instances' queries.
 static hipError_t enqueue_count_scan(rt_batch *b, hipStream_t s, const BatchRec &rp = BatchRec()) {
     Ctrl *ctrl = static_cast<Ctrl *>(b->d_ctrl);
-    hipError_t e = launch_zero(ctrl, sizeof(Ctrl), s);
+    SelectPlan plan;   // for the control words
+    plan.rec_fixed = rp.rec_fixed;
+    hipError_t e = launch_select_init(ctrl, plan, nullptr, 0, nullptr, 0, s);
     if (e == hipSuccess)
         e = launch_batch_pass(static_cast<BatchTree *>(b->d_trees), static_cast<BatchItem *>(b->d_items),
                               static_cast<const uint32_t *>(b->d_list_begin), b->nitems,

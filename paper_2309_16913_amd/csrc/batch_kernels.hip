@@ -47,11 +47,13 @@ __device__ __forceinline__ void batch_count_item(const BatchTree &bt, const Batc
                                                  const uint32_t *__restrict__ qorder, const float4 *__restrict__ qs,
                                                  uint32_t *__restrict__ counts, Ctrl *__restrict__ ctrl,
                                                  uint32_t *wstk, uint32_t lane, uint64_t lanes_below,
-                                                 const RecArena &ar, uint4 *wrec, uint32_t &rchunk, uint32_t &rcnt) {
+                                                 const RecArena &ar, uint4 *wrec, uint32_t &rchunk, uint32_t &rcnt,
+                                                 uint32_t &own) {
     GroupWalk<G, LAYOUT, REC, false, WIDE> w(lane, wstk + (lane / G) * bt.stack_cap, bt.stack_cap,
                                              wrec + (lane / G) * kRecBuf, ar, ctrl);
     w.rchunk = rchunk;
     w.rcnt = rcnt;
+    w.own = own;
     uint32_t nextq = item.q0;   // wave-uniform
     uint32_t gq = 0;            // global query index of the group's query
     bool have = false, done = false;
@@ -87,6 +89,7 @@ __device__ __forceinline__ void batch_count_item(const BatchTree &bt, const Batc
     w.flush(counts, 0);
     rchunk = w.rchunk;
     rcnt = w.rcnt;
+    own = w.own;
 }
 
 // One work item of the walking fill (the graph without records, or whose
@@ -217,9 +220,15 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
     const uint64_t lanes_below = lane ? (~0ull >> (64 - lane)) : 0ull;
     const uint32_t home = blockIdx.x % kXcds;
     uint32_t visited = 0;
-    const RecArena ar{rp.rec, rp.rec_count, rp.rec_nchunks};
+    const RecArena ar{rp.rec, rp.rec_count, rp.rec_nchunks, rp.rec_fixed};
     // the record chunk of the lane's group, and the group width it belongs to
     uint32_t rchunk = kNoNode, rcnt = 0, rG = 0;
+    // by its place (only with one group width in the batch), until it is used
+    uint32_t own = kNoNode;
+    if (REC && rp.rec_fixed) {
+        const uint32_t c = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / rp.width) + lane / rp.width;
+        if (c < rp.rec_fixed) own = c;
+    }
 
     while (true) {
         uint32_t it = kNoNode;
@@ -238,7 +247,7 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
                 rG = G;
             }
         }
-#define RT_ITEM(G_, L_)                                                                                            do {                                                                                                               if constexpr (COUNT)                                                                                               batch_count_item<G_, L_, REC, WIDE>(bt, item, qorder, qs, counts, ctrl, wstk, lane, lanes_below, ar, wrec,                                           rchunk, rcnt);                                                               else                                                                                                               batch_fill_item<G_, L_>(bt, item, qorder, qs, offsets, ids, ctrl, wstk, lane, lanes_below);            } while (0)
+#define RT_ITEM(G_, L_)                                                                                            do {                                                                                                               if constexpr (COUNT)                                                                                               batch_count_item<G_, L_, REC, WIDE>(bt, item, qorder, qs, counts, ctrl, wstk, lane, lanes_below, ar, wrec,                                           rchunk, rcnt, own);                                                               else                                                                                                               batch_fill_item<G_, L_>(bt, item, qorder, qs, offsets, ids, ctrl, wstk, lane, lanes_below);            } while (0)
         if (bt.t.layout == LAYOUT_SOA) {
             if (G == 16) RT_ITEM(16, LAYOUT_SOA);
             else if (G == 32) RT_ITEM(32, LAYOUT_SOA);
@@ -256,7 +265,15 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
     }
     if constexpr (REC) {
         if (rG && (lane & (rG - 1)) == 0 && rchunk < kRecDead) rp.rec_count[rchunk] = rcnt;
+        if (rp.rec_fixed && lane % rp.width == 0 && own != kNoNode) rp.rec_count[own] = 0;
     }
+}
+
+uint32_t batch_blocks(uint32_t nitems) {
+    uint32_t blocks = (uint32_t)num_cus() * 8;
+    const uint32_t want = (nitems + 3) / 4;
+    if (want < blocks) blocks = want ? want : 1;
+    return (blocks + kXcds - 1) / kXcds * kXcds;   // every XCD gets blocks
 }
 
 hipError_t launch_batch_pass(const BatchTree *trees, const BatchItem *items, const uint32_t *list_begin,
@@ -267,10 +284,7 @@ hipError_t launch_batch_pass(const BatchTree *trees, const BatchItem *items, con
     size_t smem = (size_t)4 * wave_words * sizeof(uint32_t);
     const bool rec = mode == SEL_COUNT && rp.rec;
     if (rec) smem = (smem + 15) / 16 * 16 + (size_t)4 * 4 * kRecBuf * 16;
-    uint32_t blocks = (uint32_t)num_cus() * 8;
-    const uint32_t want = (nitems + 3) / 4;
-    if (want < blocks) blocks = want ? want : 1;
-    blocks = (blocks + kXcds - 1) / kXcds * kXcds;   // every XCD gets blocks
+    const uint32_t blocks = batch_blocks(nitems);
 #define RT_BATCH(C_, R_, W_)                                                                                    \
     hipLaunchKernelGGL((batch_kernel<C_, R_, W_>), dim3(blocks), dim3(256), smem, s, trees, items, list_begin, nitems, \
                        qorder, q, counts, offsets, ids, cap, total_q, ctrl, slot, wave_words, rp)

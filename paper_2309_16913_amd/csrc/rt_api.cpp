@@ -451,6 +451,7 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
     // large queries get one output slot per subtree
     const SplitCfg sc = d_counts_out ? SplitCfg() : split_cfg(t, nq);
     const bool slots = sc.on && !rec;
+    if (rec && !sc.on) plan.rec_fixed = walk_fixed_chunks(t->fanout, (uint32_t)nq, rec_nchunks);
     auto use_slots = [&](SelectPlan &p) {
         p.slot_first = w.slot_first;
         p.heavy = w.heavy;

@@ -205,13 +205,16 @@ inline uint32_t stack_bound(uint32_t height, uint32_t fanout) {
 }
 
 // Nodes a group of the batched walk visits per round, and the stack it needs.
-// Leaves push nothing.  Two internal nodes are taken at once only from a
-// stack of at most F entries: the pushes then leave at most F + 2 (F - 1)
-// entries, each at most h - 2 levels above the leaves, so one-at-a-time pops
-// from there stay within (h-1)(F-1) + 1 + 2 (F - 1).
+// Leaves push nothing.  k internal nodes are taken at once only if the stack
+// then holds at most F + extra entries, each at most h - 2 levels above the
+// leaves, so one-at-a-time pops from there stay within F + extra +
+// (h-2)(F-1) = (h-1)(F-1) + 1 + extra.  (Less room for narrow nodes, whose
+// many groups per block would cost resident blocks.)
 constexpr uint32_t kWalkBatch = 4;   // leaves per round
+constexpr uint32_t kWalkInner = 4;   // internal nodes per round
+__host__ __device__ __forceinline__ uint32_t walk_extra(uint32_t F) { return (F <= 16 ? 4u : 6u) * F; }
 inline uint32_t walk_stack_bound(uint32_t height, uint32_t fanout) {
-    return stack_bound(height, fanout) + 2 * fanout;
+    return stack_bound(height, fanout) + walk_extra(fanout);
 }
 
 inline uint32_t group_width(uint32_t fanout) {
@@ -249,6 +252,7 @@ struct SelectPlan {
     uint4 *rec = nullptr;
     uint32_t *rec_count = nullptr;
     uint32_t rec_nchunks = 0;
+    uint32_t rec_fixed = 0;    // chunks taken by place (walk_fixed_chunks)
     uint32_t fill_guard = 0;   // fill pass: a FillGuard
 };
 
@@ -280,6 +284,13 @@ hipError_t launch_select_pass(const TreeView &t, const float4 *q, uint32_t nq, i
 // the rest of their walk to further launches after kWalkBudget0 nodes, large
 // subtrees after kWalkBudget1.
 constexpr uint32_t kWalkBudget0 = 32, kWalkBudget1 = 64;
+// Record chunks of an unshared count walk that belong to its lane groups by
+// their place in the grid, out of nchunks.  A counter update per group for its
+// first chunk is serialized (13 ns each) and took half of a walk in which a
+// group has few windows: 50k windows on 1.2M rectangles 220 us, now 170; 10k on
+// 10M 205 us, now 150; a batch of 48k on 16 trees 150 us, now 105.  None when that would leave less than a sixteenth as
+// many for the groups that need a second one.
+uint32_t walk_fixed_chunks(uint32_t fanout, uint32_t nq, uint32_t nchunks);
 hipError_t launch_walk(const TreeView &t, const float4 *q, uint32_t nq, uint32_t *counts, Ctrl *ctrl,
                        const SelectPlan &plan, uint2 *items, uint32_t items_per_list, hipStream_t s);
 
@@ -434,8 +445,11 @@ struct BatchRec {
     uint4 *rec = nullptr;
     uint32_t *rec_count = nullptr;
     uint32_t rec_nchunks = 0;
+    uint32_t rec_fixed = 0;   // chunks that belong to the groups by place, if all have the same
+    uint32_t width = 64;      // width
     uint32_t fill_guard = 0;
 };
+uint32_t batch_blocks(uint32_t nitems);   // of the persistent passes
 hipError_t launch_batch_pass(const BatchTree *trees, const BatchItem *items, const uint32_t *list_begin,
                              uint32_t nitems, const uint32_t *qorder, const float4 *q, int mode, uint32_t *counts,
                              const uint64_t *offsets, uint32_t *ids, uint64_t capacity, uint64_t total_q, Ctrl *ctrl,

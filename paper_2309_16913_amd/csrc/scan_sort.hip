@@ -210,17 +210,18 @@ __global__ void finalize_kernel(const uint64_t *offsets, uint64_t nq, uint64_t c
 
 // Start of a select: control words zeroed and the record arena named in them,
 // and two more arrays of words cleared, in one launch.
-__global__ void select_init_kernel(Ctrl *ctrl, uint4 *rec, uint32_t *rec_count, uint32_t rec_nchunks, uint32_t *a,
-                                   uint32_t na, uint32_t *b, uint32_t nb) {
+__global__ void select_init_kernel(Ctrl *ctrl, uint4 *rec, uint32_t *rec_count, uint32_t rec_nchunks, uint32_t rec_fixed,
+                                   uint32_t *a, uint32_t na, uint32_t *b, uint32_t nb) {
     constexpr uint32_t nc = sizeof(Ctrl) / 4;
     constexpr uint32_t r0 = offsetof(Ctrl, rec_nchunks) / 4, r1 = offsetof(Ctrl, rec_base) / 4,
-                       r2 = offsetof(Ctrl, rec_count) / 4;
+                       r2 = offsetof(Ctrl, rec_count) / 4, r3 = offsetof(Ctrl, rec_chunks) / 4;
     uint32_t *c = reinterpret_cast<uint32_t *>(ctrl);
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nc + na + nb; i += gridDim.x * blockDim.x) {
         if (i < nc) {
             const uint64_t base = reinterpret_cast<uint64_t>(rec), cnt = reinterpret_cast<uint64_t>(rec_count);
             uint32_t v = 0;
             if (i == r0) v = rec_nchunks;
+            if (i == r3) v = rec_fixed;
             if (i == r1) v = (uint32_t)base;
             if (i == r1 + 1) v = (uint32_t)(base >> 32);
             if (i == r2) v = (uint32_t)cnt;
@@ -238,7 +239,7 @@ hipError_t launch_select_init(Ctrl *ctrl, const SelectPlan &plan, uint32_t *a, u
                               hipStream_t s) {
     const uint32_t n = sizeof(Ctrl) / 4 + na + nb;
     hipLaunchKernelGGL(select_init_kernel, dim3((n + 1023) / 1024), dim3(1024), 0, s, ctrl, plan.rec, plan.rec_count,
-                       plan.rec_nchunks, a, na, b, nb);
+                       plan.rec_nchunks, plan.rec_fixed, a, na, b, nb);
     return hipGetLastError();
 }
 

@@ -468,6 +468,15 @@ walk_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, const uint32
     __shared__ ListShare share;
     share.init();
     ListGrab grab(256 / G, threadIdx.x / G);
+    if constexpr (REC && SRC == 0) {
+        // With no more units than groups only the groups with a first unit
+        // have a chunk: that unit's.
+        const uint32_t groups = gridDim.x * (256 / G), x = grab.home;
+        const uint32_t b = (uint32_t)(((uint64_t)x * nq) / kXcds), n = (uint32_t)(((uint64_t)(x + 1) * nq) / kXcds) - b;
+        const uint32_t c = nq > groups ? blockIdx.x * (256 / G) + threadIdx.x / G
+                                       : (grab.first < n ? b + grab.first : kNoNode);
+        if (c < ar.nfixed) w.own = c;
+    }
     // the group's chunk of units: lane i < cn holds the i-th unit's query cq,
     // window cw (and root node cd); ci = next to start
     uint32_t cn = 0, ci = 0, cq = 0, cd = 0;
@@ -1027,6 +1036,20 @@ hipError_t launch_select_pass(const TreeView &t, const float4 *q, uint32_t nq, i
     }
 }
 
+// Blocks of gpb groups for nq windows.
+static uint32_t walk_blocks(uint32_t nq, uint32_t gpb) {
+    const uint32_t persistent = (uint32_t)num_cus() * 8;
+    const uint64_t want = ((uint64_t)nq + gpb - 1) / gpb;
+    const uint32_t blocks = (uint32_t)(want < persistent ? want : persistent);
+    return (blocks + kXcds - 1) / kXcds * kXcds;   // every XCD gets blocks
+}
+
+uint32_t walk_fixed_chunks(uint32_t fanout, uint32_t nq, uint32_t nchunks) {
+    const uint32_t gpb = 256 / group_width(fanout);
+    const uint32_t n = std::min(nq, walk_blocks(nq, gpb) * gpb);
+    return nchunks >= n && nchunks - n >= n / 16 ? n : 0u;
+}
+
 template <int G, int LAYOUT, bool WIDE>
 static hipError_t launch_walk_w(const TreeView &t, const float4 *q, uint32_t nq, uint32_t *counts, Ctrl *ctrl,
                                 const SelectPlan &plan, uint2 *items, uint32_t icap, hipStream_t s) {
@@ -1035,13 +1058,11 @@ static hipError_t launch_walk_w(const TreeView &t, const float4 *q, uint32_t nq,
     size_t smem = (size_t)gpb * stack_cap * sizeof(uint32_t);
     if (plan.rec) smem = (smem + 15) / 16 * 16 + (size_t)gpb * kRecBuf * 16;   // the groups' record buffers
     const uint32_t persistent = (uint32_t)num_cus() * 8;
-    const uint64_t want = ((uint64_t)nq + gpb - 1) / gpb;
-    uint32_t blocks = (uint32_t)(want < persistent ? want : persistent);
-    blocks = (blocks + kXcds - 1) / kXcds * kXcds;   // every XCD gets blocks
+    const uint32_t blocks = walk_blocks(nq, gpb);
     // units per counter update: the more each group will take, the more
     const uint64_t groups = (uint64_t)blocks * gpb;
     const uint32_t chunk = nq >= 16 * groups ? 8u : nq >= 8 * groups ? 4u : nq >= 2 * groups ? 2u : 1u;
-    const RecArena ar{plan.rec, plan.rec_count, plan.rec_nchunks};
+    const RecArena ar{plan.rec, plan.rec_count, plan.rec_nchunks, plan.rec_fixed};
     const WalkItems none{nullptr, 0, nullptr, nullptr};
     const dim3 block(256);
     if (!plan.rec) {

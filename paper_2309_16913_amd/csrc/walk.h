@@ -4,7 +4,7 @@
 // A walk that pops one node at a time waits one full memory latency per node
 // (its next node is known only after the compare), so a window that reaches a
 // few hundred nodes takes a few hundred latencies however idle the chip is.
-// Here a round takes up to kWalkBatch leaves, or up to two internal nodes while
+// Here a round takes up to kWalkBatch leaves, or up to kWalkInner internal nodes while
 // the stack is short (see walk_stack_bound), from the top of the stack and
 // issues all their loads before the first compare.  What bounds the pass is
 // vector instructions where many windows run (the loads take one scalar base
@@ -170,6 +170,7 @@ struct RecArena {
     uint4 *rec;
     uint32_t *count;    // records per chunk
     uint32_t nchunks;
+    uint32_t nfixed;    // chunks [0, nfixed) belong to groups by their place (ctrl->rec_chunks starts there)
 };
 
 // The state of one lane group (G lanes, lane e in the group, wave lane gbase
@@ -192,6 +193,7 @@ struct GroupWalk {
     // counter, so a store issued before a node load delays the wait for it
     uint4 *rbuf;
     uint32_t nbuf = 0, rchunk = kNoNode, rcnt = 0, ustart = 0;
+    uint32_t own = kNoNode;   // the chunk that is the group's by its place, until it is used
     RecArena ar;
     Ctrl *ctrl;
 
@@ -226,9 +228,12 @@ struct GroupWalk {
             __builtin_amdgcn_wave_barrier();
             if (rchunk != kRecDead && (rchunk == kNoNode || rcnt + nbuf > kRecChunk)) {
                 if (rchunk != kNoNode && e == 0) ar.count[rchunk] = rcnt;
-                uint32_t c = 0;
-                if (e == 0) c = atomicAdd(&ctrl->rec_chunks, 1u);
-                c = (uint32_t)__shfl((int)c, (int)gbase);
+                uint32_t c = own;
+                if (own == kNoNode) {   // group-uniform
+                    if (e == 0) c = atomicAdd(&ctrl->rec_chunks, 1u);
+                    c = (uint32_t)__shfl((int)c, (int)gbase);
+                }
+                own = kNoNode;
                 if (c < ar.nchunks) {
                     rchunk = c;
                     rcnt = 0;
@@ -253,6 +258,7 @@ struct GroupWalk {
         if constexpr (REC) {
             flush(counts, 0);
             if (e == 0 && rchunk < kRecDead) ar.count[rchunk] = rcnt;
+            if (e == 0 && own != kNoNode) ar.count[own] = 0;
         }
     }
 
@@ -262,26 +268,21 @@ struct GroupWalk {
         return G == 64 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)v) : v;
     }
 
-    __device__ __forceinline__ void push_children(const TreeView &t, const float4 q, uint32_t *counts, uint32_t slot,
-                                                  uint64_t fmask, float lx, float ly, float hx, float hy,
-                                                  uint32_t first) {
-        const bool hit = (lx <= q.z) && (q.x <= hx) && (ly <= q.w) && (q.y <= hy);
-        // an entry whose MBR lies inside the window: every object below it
-        // qualifies, so its subtree is taken whole
-        const bool cont = hit && (q.x <= lx) && (hx <= q.z) && (q.y <= ly) && (hy <= q.w);
-        const uint64_t m = (__ballot(hit) >> gbase) & fmask;
-        const uint64_t cm = (__ballot(cont) >> gbase) & fmask;
-        const uint64_t pm = m & ~cm;   // children to descend into
-        if (cm) {                      // group-uniform: contained subtrees
-            // Neighbouring contained children hold one run of leaves: their
-            // first one stands for all of them.
-            const uint64_t starts = cm & ~(cm << 1);
+    // One of N internal nodes that a round visits together.
+    struct Children {
+        uint64_t cm, pm;   // contained children, children to descend into
+        uint32_t first, lo, hi;   // first child; lanes where a run of contained children begins: its leaf range
+    };
+
+    // Neighbouring contained children hold one run of leaves: their first one
+    // stands for all of them.
+    static __device__ __forceinline__ uint64_t run_starts(uint64_t cm) { return cm & ~(cm << 1); }
+
+    __device__ __forceinline__ void push_children(const TreeView &t, uint32_t *counts, uint32_t slot, const Children &c) {
+        if (c.cm) {   // group-uniform: contained subtrees
+            const uint64_t starts = run_starts(c.cm);
             const bool mine = (starts >> e) & 1u;
-            const uint64_t after = ~(cm >> e);   // 0 if all 64 are contained
-            const uint32_t last = after ? e + (uint32_t)__builtin_ctzll(after) - 1 : 63u;   // of the run that begins here
-            uint2 rg = make_uint2(0u, 0u);
-            if (mine) rg = make_uint2(t.range[first + e].x, t.range[first + last].y);
-            uint32_t sc = mine ? subtree_objects(t, rg) : 0u;
+            uint32_t sc = mine ? subtree_objects(t, make_uint2(c.lo, c.hi)) : 0u;
             if constexpr (REC) {
                 // one record per run: its leaf range, at the position after
                 // the runs before it
@@ -294,7 +295,7 @@ struct GroupWalk {
                 if (nbuf + n > kRecBuf) flush(counts, slot);
                 if (mine)
                     rbuf[nbuf + (uint32_t)__popcll(starts & below)] =
-                        make_uint4(slot, pos + inc - sc, kRecRun | rg.x, rg.y);
+                        make_uint4(slot, pos + inc - sc, kRecRun | c.lo, c.hi);
                 nbuf += n;
                 pos += uni((uint32_t)__shfl((int)inc, (int)(gbase + G - 1)));
             } else {
@@ -302,14 +303,56 @@ struct GroupWalk {
                 pos += uni(sc);
             }
         }
-        if ((pm >> e) & 1u) {
-            const uint32_t at = sp + (uint32_t)__popcll(pm & below);
+        if ((c.pm >> e) & 1u) {
+            const uint32_t at = sp + (uint32_t)__popcll(c.pm & below);
             if (at < stack_cap)
-                stk[at] = first + e;   // children of a node are contiguous
+                stk[at] = c.first + e;   // children of a node are contiguous
             else
                 atomicOr(&ctrl->err, kErrStack);
         }
-        sp = min(sp + (uint32_t)__popcll(pm), stack_cap);
+        sp = min(sp + (uint32_t)__popcll(c.pm), stack_cap);
+    }
+
+    // Visits the k <= N internal nodes nd (those past k repeat the first one
+    // and are dropped).  The leaf ranges of all contained children are loaded
+    // at once: a round waits twice for memory, however many nodes it visits.
+    template <uint32_t N>
+    __device__ __forceinline__ void descend(const TreeView &t, const float4 q, uint32_t *counts, uint32_t slot,
+                                            const uint32_t *nd, uint32_t k, uint64_t fmask, uint32_t en) {
+        const uint32_t F = t.fanout;
+        float lx[N], ly[N], hx[N], hy[N];
+        Children c[N];
+#pragma unroll
+        for (uint32_t u = 0; u < N; ++u) {
+            const Off o = (Off)nd[u] * t.node_bytes;
+            c[u].first = *reinterpret_cast<const uint32_t *>(t.nodes + (Off)(o + 16u * (LAYOUT == LAYOUT_AOS ? 1u : F)));
+            load_entry_at<LAYOUT, Off>(t.nodes, o, F, en, lx[u], ly[u], hx[u], hy[u]);
+        }
+        uint64_t any = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < N; ++u) {
+            const bool hit = (lx[u] <= q.z) && (q.x <= hx[u]) && (ly[u] <= q.w) && (q.y <= hy[u]);
+            // an entry whose MBR lies inside the window: every object below it
+            // qualifies, so its subtree is taken whole
+            const bool cont = hit && (q.x <= lx[u]) && (hx[u] <= q.z) && (q.y <= ly[u]) && (hy[u] <= q.w);
+            const uint64_t m = u < k ? (__ballot(hit) >> gbase) & fmask : 0ull;
+            c[u].cm = u < k ? (__ballot(cont) >> gbase) & fmask : 0ull;
+            c[u].pm = m & ~c[u].cm;
+            c[u].first = uni(c[u].first);
+            any |= c[u].cm;
+        }
+        if (any) {
+#pragma unroll
+            for (uint32_t u = 0; u < N; ++u) {
+                const bool mine = (run_starts(c[u].cm) >> e) & 1u;
+                const uint64_t after = ~(c[u].cm >> e);   // 0 if all 64 are contained
+                const uint32_t last = after ? e + (uint32_t)__builtin_ctzll(after) - 1 : 63u;   // of the run begun here
+                c[u].lo = t.range[c[u].first + (mine ? e : 0u)].x;
+                c[u].hi = t.range[c[u].first + (mine ? last : 0u)].y;
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < N; ++u) push_children(t, counts, slot, c[u]);
     }
 
     // One round on the stack of the group's unit (window q, output slot
@@ -363,21 +406,20 @@ struct GroupWalk {
             }
             return k;
         }
-        // internal nodes: two at a time while the stack is short
-        const bool two = sp > 1 && sp <= F && nd[1] < t.first_leaf;
-        if (!two) nd[1] = nd[0];
-        sp -= two ? 2u : 1u;
-        float lx[2], ly[2], hx[2], hy[2];
-        uint32_t first[2];   // first child
+        // internal nodes: several at a time while the stack leaves room
+        const bool room = sp + kWalkInner * (F - 1) <= F + walk_extra(F);
+        uint32_t k = 1;
 #pragma unroll
-        for (uint32_t u = 0; u < 2; ++u) {
-            const Off o = (Off)nd[u] * t.node_bytes;
-            first[u] = *reinterpret_cast<const uint32_t *>(t.nodes + (Off)(o + 16u * (LAYOUT == LAYOUT_AOS ? 1u : F)));
-            load_entry_at<LAYOUT, Off>(t.nodes, o, F, en, lx[u], ly[u], hx[u], hy[u]);
+        for (uint32_t u = 1; u < kWalkInner; ++u) {
+            if (k == u && u < sp && room && nd[u] < t.first_leaf) k = u + 1;
+            nd[u] = k > u ? nd[u] : nd[0];
         }
-        push_children(t, q, counts, slot, fmask, lx[0], ly[0], hx[0], hy[0], uni(first[0]));
-        if (two) push_children(t, q, counts, slot, fmask, lx[1], ly[1], hx[1], hy[1], uni(first[1]));
-        return two ? 2u : 1u;
+        sp -= k;
+        if (k > 2)
+            descend<kWalkInner>(t, q, counts, slot, nd, k, fmask, en);
+        else
+            descend<2>(t, q, counts, slot, nd, k, fmask, en);
+        return k;
     }
 };
 

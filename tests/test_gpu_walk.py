@@ -162,3 +162,28 @@ def test_runs_of_contained_children(rt, ora, fanout, layout):
         want = ora.select(ora.build_str(r, fanout), q)
         check(rt, ora, r, q, want, fanout, layout, 0)
         check(rt, ora, r, q, want, fanout, layout, 2, "on")
+
+
+@pytest.mark.parametrize("fanout", [16, 32, 64])
+@pytest.mark.parametrize("nq", [1, 9, 4095, 16_383, 16_385, 40_000])
+def test_chunks_by_place(rt, ora, fanout, nq):
+    """Window counts below, at and above the number of lane groups, most of
+    the windows empty and one with most of the records, so that groups that own
+    a record chunk leave it empty and others need many."""
+    r = rtgen.c2_rects(60_000)
+    g = np.random.default_rng(nq)
+    lo = g.random((nq, 2), np.float32) + 2
+    q = np.concatenate([lo, lo + np.float32(0.01)], axis=1)
+    some = g.integers(0, nq, max(nq // 50, 1))
+    q[some] = np.concatenate([lo[some] - 2, lo[some] - 2 + np.float32(0.03)], axis=1)
+    q[nq // 2] = [0.01, 0.01, 0.99, 0.99]
+    want = ora.select(ora.build_str(r, fanout), q)
+    for split in [0, 2]:
+        check(rt, ora, r, q, want, fanout, "soa", split)
+    b = rt.Batch([rt.build_str(r, fanout, "soa"), rt.build_str(r, fanout, "aos")], [q, q[: nq // 2 + 1]])
+    for _ in range(3):
+        b.run()
+        for i, n in enumerate([nq, nq // 2 + 1]):
+            off, ids = b.result(i)
+            assert np.array_equal(np.asarray(off).astype(np.int64), want[0][: n + 1].astype(np.int64))
+            assert np.array_equal(ids, want[1][: int(want[0][n])])
