@@ -127,18 +127,18 @@ constexpr uint32_t kLongDigits = 256;
 constexpr uint32_t kPart = 16384;       // ids per part of a class-L segment
 constexpr uint32_t kSubMax = 4096;      // longest group sorted by a 256-thread block
 constexpr uint32_t kSubBigMax = 32768;  // longest group sorted by a 1024-thread block
-// descriptor of a class-L segment: 257 sub-bucket starts, the digits per
-// group (0: the segment went to the fallback), the index of its first part,
-// its place in ids (two words)
-constexpr uint32_t kDescGroup = kLongDigits + 1, kDescPart = kLongDigits + 2, kDescOff = kLongDigits + 3;
-constexpr uint32_t kDesc = kLongDigits + 5;
+// descriptor of a class-L segment: its digit counts, which become the write
+// cursors of its groups; the digits per group (0: the segment went to the
+// fallback), its place in ids (two words), its id range
+constexpr uint32_t kDescGroup = kLongDigits, kDescOff = kLongDigits + 1, kDescRange = kLongDigits + 3;
+constexpr uint32_t kDesc = kLongDigits + 4;
 constexpr uint32_t kSubCounts = 8;      // counters of the two group work lists (in the class counter block)
 constexpr uint32_t kPartCount = 10;     // counter of the part list
 
-// Work items hold all that is needed to load their ids, so that a block reads
-// one item ahead and never waits for a chain of dependent loads.  A run of at
-// most 32768 ids: its place in ids in y and the low half of z, its length in
-// the high half.
+// A part holds all that is needed to load its ids, so that a block reads one
+// part ahead and never waits for a chain of dependent loads.  A run of at most
+// 32768 ids: its place in ids in y and the low half of z, its length in the
+// high half.
 struct Run {
     uint64_t o;
     uint32_t n;
@@ -152,14 +152,11 @@ __device__ __forceinline__ uint4 run_item(uint32_t x, uint64_t o, uint32_t n, ui
 
 // Behind the cap ids of the scratch.
 struct LongWs {
-    uint4 *sub;           // groups {first id, run, id range}: those of the 256-thread sorts from the front,
-    uint4 *sub_end;       // those of the 1024-thread sorts from the end; at most 256 per segment
-    uint4 *parts;         // parts {place in the class-L list, top bit set in the last, run, digit shift};
-                          // a segment's follow each other
+    uint4 *parts;         // parts {place in the class-L list, run, digit shift}
     uint32_t *desc;       // kDesc words per class-L segment
-    uint32_t *hist;       // per part: digit counts, then positions in the segment relative to the digits' starts
+    uint32_t *sub;        // groups (segment << 8 | group): those of the 128-thread sorts from the front,
+    uint32_t *sub_end;    // those of the 1024-thread sorts from the end; at most 256 per segment
 };
-constexpr uint32_t kLastPart = 0x80000000u;
 
 __device__ __forceinline__ uint32_t num_parts(uint64_t len) { return (uint32_t)((len + kPart - 1) / kPart); }
 
@@ -169,11 +166,10 @@ __device__ __forceinline__ uint32_t digit_shift(uint32_t range) {
     return (uint32_t)(b < 8 ? 0 : b - 8);
 }
 
-// Part p of np of the segment of len ids at o, li-th of its class.
-__device__ __forceinline__ uint4 part_item(uint32_t li, uint32_t p, uint32_t np, uint64_t o, uint64_t len,
-                                           uint32_t shift) {
+// Part p of the segment of len ids at o, li-th of its class.
+__device__ __forceinline__ uint4 part_item(uint32_t li, uint32_t p, uint64_t o, uint64_t len, uint32_t shift) {
     const uint64_t at = (uint64_t)p * kPart;
-    return run_item(li | (p + 1 == np ? kLastPart : 0u), o + at, (uint32_t)min((uint64_t)kPart, len - at), shift);
+    return run_item(li, o + at, (uint32_t)min((uint64_t)kPart, len - at), shift);
 }
 
 // ---------------------------------------------------------------------------
@@ -234,8 +230,8 @@ seg_classify(const uint64_t *__restrict__ offsets, uint64_t nq, uint64_t cap, ui
             const uint64_t o = offsets[q], len = offsets[q + 1] - o;
             const uint32_t li = gbase[kLong] + pos[k], np = num_parts(len);
             const uint32_t p0 = atomicAdd(&pcur, np), sh = digit_shift(seg_id_range(seg_range, (uint32_t)q, id_range));
-            lw.desc[(uint64_t)li * kDesc + kDescPart] = p0;
-            for (uint32_t p = 0; p < np; ++p) lw.parts[p0 + p] = part_item(li, p, np, o, len, sh);
+            for (uint32_t d = 0; d < kLongDigits; ++d) lw.desc[(uint64_t)li * kDesc + d] = 0;
+            for (uint32_t p = 0; p < np; ++p) lw.parts[p0 + p] = part_item(li, p, o, len, sh);
         }
     }
 }
@@ -696,7 +692,9 @@ segsort_wide(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, c
             },
             [](int, bool, uint32_t) {});
         __syncthreads();
-        if (t < kLongDigits) lw.hist[(uint64_t)k * kLongDigits + t] = h[t];
+        // 256 counters per segment, added to by its parts: a row per part would
+        // not fit the scratch
+        if (t < kLongDigits && h[t]) atomicAdd(&lw.desc[(uint64_t)it.x * kDesc + t], h[t]);
         h = h == lds ? lds + kLongDigits : lds;
     };
     for (; k < np; k += g) {
@@ -738,50 +736,34 @@ __device__ __forceinline__ uint32_t scan_digits(uint32_t v, uint32_t *w4, uint32
     return ex;
 }
 
-// One block per class-L segment, one thread per digit: the parts' counts
-// become positions (exclusive over the parts), the digits' totals the
-// sub-bucket starts, and the groups are listed.  Latency-bound: eight rows of
-// counts in flight.
+// One block per class-L segment, one thread per digit: the digits are put into
+// groups, the counts become the groups' starts, and the groups are listed.
 __global__ void __launch_bounds__(256)
 segsort_part_scan(const uint64_t *__restrict__ offsets, const uint32_t *__restrict__ list,
                   const uint32_t *__restrict__ list_count, LongWs lw, uint32_t *__restrict__ sub_counts,
                   uint32_t *__restrict__ fb_list, uint32_t *__restrict__ fb_count, uint32_t id_range,
                   const uint32_t *__restrict__ seg_range) {
-    __shared__ uint32_t w4[8], subbase, start[kLongDigits + 1];
+    __shared__ uint32_t w4[8], subbase, start[kLongDigits];
     static_assert(kLongDigits == 256, "one thread per digit");
     const uint32_t m = *list_count, t = threadIdx.x;
     for (uint32_t li = blockIdx.x; li < m; li += gridDim.x) {
         const uint32_t q = list[li];
         uint32_t *dsc = lw.desc + (uint64_t)li * kDesc;
         const uint64_t o = offsets[q];
-        const uint32_t np = num_parts(offsets[q + 1] - o);
-        uint32_t *h = lw.hist + (uint64_t)dsc[kDescPart] * kLongDigits + t;
-        uint32_t run = 0;
-        for (uint32_t p = 0; p < np; p += 8) {
-            uint32_t v[8];
-#pragma unroll
-            for (uint32_t j = 0; j < 8; ++j) v[j] = p + j < np ? h[(uint64_t)(p + j) * kLongDigits] : 0u;
-#pragma unroll
-            for (uint32_t j = 0; j < 8; ++j) {
-                if (p + j < np) h[(uint64_t)(p + j) * kLongDigits] = run;
-                run += v[j];
-            }
-        }
         uint32_t tot, big;
-        const uint32_t st = scan_digits(run, w4, tot, big);
-        dsc[t] = start[t] = st;
+        start[t] = scan_digits(dsc[t], w4, tot, big);
         // groups of G consecutive digits: G = (group limit) / (largest digit
         // count), so a group never exceeds the limit: kSubMax ids for the
-        // 256-thread sort, or, when a digit holds more (segments of about a
+        // 128-thread sort, or, when a digit holds more (segments of about a
         // million ids), kSubBigMax for the 1024-thread sort (its own list)
         const bool fallback = big > kSubBigMax, wide = big > kSubMax;
         const uint32_t G = fallback ? 0u : (wide ? kSubBigMax : kSubMax) / big;
         const uint32_t ngroups = G ? (kLongDigits + G - 1) / G : 0u;
         if (t == 0) {
-            dsc[kLongDigits] = start[kLongDigits] = tot;
             dsc[kDescGroup] = G;
             dsc[kDescOff] = (uint32_t)o;
             dsc[kDescOff + 1] = (uint32_t)(o >> 32);
+            dsc[kDescRange] = seg_id_range(seg_range, q, id_range);
             if (fallback)
                 fb_list[atomicAdd(fb_count, 1u)] = q;
             else
@@ -789,25 +771,17 @@ segsort_part_scan(const uint64_t *__restrict__ offsets, const uint32_t *__restri
         }
         __syncthreads();
         if (t < ngroups) {
-            // ids of digits [d0, d1): [d0 << sh, d1 << sh) within [0, rng)
-            const uint32_t d0 = t * G, d1 = min(d0 + G, kLongDigits), rng = seg_id_range(seg_range, q, id_range);
-            const uint32_t sh = digit_shift(rng), base = d0 << sh;
-            const uint64_t hi = min((uint64_t)d1 << sh, (uint64_t)rng);
-            const uint4 it = run_item(base, o + start[d0], start[d1] - start[d0],
-                                      hi > base ? (uint32_t)(hi - base) : 0u);
+            dsc[t] = start[t * G];   // all counts have been read
             const uint32_t i = subbase + t;
-            if (wide)
-                *(lw.sub_end - 1 - i) = it;
-            else
-                lw.sub[i] = it;
+            *(wide ? lw.sub_end - 1 - i : lw.sub + i) = li << 8 | t;
         }
         __syncthreads();
     }
 }
 
-// One block per part: its ids are ranked by digit with LDS cursors (the
-// counts are known, so one atomic per id), staged in digit order and written
-// as one run per group (a group's order within scratch does not matter, as
+// One block per part: its ids are counted and ranked by digit in LDS, staged in
+// digit order and written as one run per group, whose place an atomic on the
+// group's cursor reserves (a group's order within scratch does not matter, as
 // it is sorted next).  Two blocks of 1024 threads per CU.
 template <int T>
 __global__ void __launch_bounds__(T, 8)
@@ -816,7 +790,7 @@ segsort_part_split(const uint32_t *__restrict__ ids, uint32_t *__restrict__ scra
     constexpr uint32_t R = kPart / T;
     __shared__ uint32_t stage[kPart];
     __shared__ uint32_t lcur[kLongDigits], gpos[kLongDigits];   // cursor in stage; scratch position minus stage position
-    __shared__ uint32_t psum[kLongDigits + 1], w4[8];
+    __shared__ uint32_t first[kLongDigits + 1], w4[4];          // digits' places in stage
     const uint32_t t = threadIdx.x, np = *part_count;
     const PartShare ps = part_share(np, blockIdx.x, gridDim.x);
     if (ps.k >= ps.end) return;
@@ -824,52 +798,41 @@ segsort_part_split(const uint32_t *__restrict__ ids, uint32_t *__restrict__ scra
     for (uint32_t k = ps.k; k < ps.end; k += ps.step) {
         const uint4 it = nx;
         nx = lw.parts[min(k + ps.step, np - 1)];
-        const uint32_t *dsc = lw.desc + (uint64_t)(it.x & ~kLastPart) * kDesc;
+        uint32_t *dsc = lw.desc + (uint64_t)it.x * kDesc;
         const uint32_t G = dsc[kDescGroup];
         if (G == 0) continue;   // left to the fallback
         const uint32_t len = run_of(it).n, sh = it.w;
         uint32_t key[R];
         load_keys<T, R>(ids + run_of(it).o, len, key);
-        // thread t: digit t's count in this part and its ids in the parts before
-        uint32_t cnt = 0, pre = 0, ec = 0, ep = 0;
-        const uint32_t lane = t & 63u;
+        if (t < kLongDigits) lcur[t] = 0;
+        __syncthreads();
+        rows_by_four<T, R>(
+            len,
+            [&](int r, bool in, uint32_t) {
+                atomicAdd(&lcur[in ? min(key[r] >> sh, kLongDigits - 1) : t % kLongDigits], in ? 1u : 0u);
+            },
+            [](int, bool, uint32_t) {});
+        __syncthreads();
+        uint32_t cnt = 0, inc = 0;
         if (t < kLongDigits) {
-            const uint32_t *row = lw.hist + (uint64_t)k * kLongDigits + t;
-            pre = row[0];
-            cnt = (it.x & kLastPart ? dsc[t + 1] - dsc[t] : row[kLongDigits]) - pre;
-            ec = cnt;
-            ep = pre;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t x = __shfl_up(ec, d), y = __shfl_up(ep, d);
-                if ((int)lane >= d) {
-                    ec += x;
-                    ep += y;
-                }
-            }
-            if (lane == 63) {
-                w4[t >> 6] = ec;
-                w4[4 + (t >> 6)] = ep;
-            }
+            cnt = lcur[t];
+            inc = wave_sum(cnt);
+            if ((t & 63u) == 63) w4[t >> 6] = inc;
         }
         __syncthreads();
         if (t < kLongDigits) {
-            for (uint32_t i = 0; i < (t >> 6); ++i) {
-                ec += w4[i];
-                ep += w4[4 + i];
-            }
-            lcur[t] = ec -= cnt;
-            psum[t] = ep -= pre;
-            if (t == kLongDigits - 1) psum[kLongDigits] = ep + pre;
+            for (uint32_t i = 0; i < (t >> 6); ++i) inc += w4[i];
+            first[t + 1] = inc;
+            lcur[t] = inc - cnt;
+            if (t == 0) first[0] = 0;
         }
         __syncthreads();
-        if (t < kLongDigits) {
-            // first digit of the group, its end: the part's run goes behind
-            // the group's ids of the parts before
-            const uint32_t d0 = t - t % G, d1 = min(d0 + G, kLongDigits);
-            gpos[t] = dsc[d0] + (psum[d1] - psum[d0]) - lcur[d0];
+        const uint32_t d0 = t * G;
+        if (d0 < kLongDigits) {
+            const uint32_t d1 = min(d0 + G, kLongDigits), n = first[d1] - first[d0];
+            const uint32_t at = n ? atomicAdd(&dsc[t], n) - first[d0] : 0u;
+            for (uint32_t d = d0; d < d1; ++d) gpos[d] = at;
         }
-        __syncthreads();
         uint32_t to[4];
         rows_by_four<T, R>(
             len,
@@ -896,32 +859,57 @@ segsort_part_split(const uint32_t *__restrict__ ids, uint32_t *__restrict__ scra
 // Groups of sub-buckets (digits [gG, gG + G)): one block each, sorted from
 // scratch into place; the ids of a group lie in [gG << sh, (gG + G) << sh).
 // Two shapes: 128 x 32 for groups of at most kSubMax ids, 1024 x 32 for the
-// groups of segments whose digits hold more.  item(k): the k-th of m > 0.
+// groups of segments whose digits hold more.  item(k): the k-th of m > 0.  Items
+// are read three groups ahead and descriptors two, so that no load waits for
+// another.  After the split a group's cursor is its end.
 template <int T, int K, int A, typename Item>
 __device__ __forceinline__ void
-sort_groups(uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch, uint32_t m, Item &&item, uint32_t *buf,
-            uint32_t *cnt, uint32_t *wsum) {
+sort_groups(uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch, const uint32_t *__restrict__ desc,
+            uint32_t m, Item &&item, uint32_t *buf, uint32_t *cnt, uint32_t *wsum) {
     if (blockIdx.x >= m) return;
     const uint32_t g = gridDim.x;
+    struct Raw {
+        uint32_t it, s0, s1, G, lo, hi, rng;
+    };
+    auto look = [&](uint32_t it) {
+        const uint32_t *dsc = desc + (uint64_t)(it >> 8) * kDesc;
+        const uint32_t i = it & 255u;
+        return Raw{it, i ? dsc[i - 1] : 0u, dsc[i], dsc[kDescGroup], dsc[kDescOff], dsc[kDescOff + 1], dsc[kDescRange]};
+    };
+    auto at = [&](uint32_t k) { return item(min(k, m - 1)); };
     uint32_t key[K];
-    uint4 it = item(blockIdx.x), nx = item(min(blockIdx.x + g, m - 1));
-    load_keys<T, K>(scratch + run_of(it).o, run_of(it).n, key);
+    uint64_t o = 0;
+    uint32_t n = 0, base = 0, range = 0;
+    auto load = [&](const Raw &r) {
+        // ids of digits [d0, d1): [d0 << sh, d1 << sh) within [0, rng)
+        const uint32_t d0 = (r.it & 255u) * r.G, d1 = min(d0 + r.G, kLongDigits), sh = digit_shift(r.rng);
+        const uint64_t end = min((uint64_t)d1 << sh, (uint64_t)r.rng);
+        o = ((uint64_t)r.hi << 32 | r.lo) + r.s0;
+        n = r.s1 - r.s0;
+        base = d0 << sh;
+        range = end > base ? (uint32_t)(end - base) : 0u;
+        load_keys<T, K>(scratch + o, n, key);
+    };
+    load(look(at(blockIdx.x)));
+    Raw nx = look(at(blockIdx.x + g));
+    uint32_t it = at(blockIdx.x + 2 * g);
     for (uint32_t k = blockIdx.x; k < m; k += g) {
-        const uint4 cu = it;
-        block_sort_keys<T, K, A>(key, ids + run_of(cu).o, run_of(cu).n, cu.w, buf, cnt, wsum, cu.x, [&] {
-            it = nx;
-            if (k + g < m) load_keys<T, K>(scratch + run_of(it).o, run_of(it).n, key);
-            nx = item(min(k + 2 * g, m - 1));
+        const uint64_t co = o;
+        const uint32_t cn = n, cb = base, cr = range;
+        block_sort_keys<T, K, A>(key, ids + co, cn, cr, buf, cnt, wsum, cb, [&] {
+            if (k + g < m) load(nx);
+            nx = look(it);
+            it = at(k + 3 * g);
         });
     }
 }
 
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(128, 4)
 segsort_sub(uint32_t *__restrict__ ids, const uint32_t *__restrict__ scratch, LongWs lw,
             const uint32_t *__restrict__ item_count) {
     constexpr int T = 128, K = 32, A = 4;
     __shared__ __align__(16) uint32_t lds[T * K + kStagePad + T * K / A];
-    sort_groups<T, K, A>(ids, scratch, *item_count, [&](uint32_t k) { return lw.sub[k]; }, lds,
+    sort_groups<T, K, A>(ids, scratch, lw.desc, *item_count, [&](uint32_t k) { return lw.sub[k]; }, lds,
                          lds + T * K + kStagePad, lds);
 }
 
@@ -1056,7 +1044,7 @@ segsort_rest(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, u
     __shared__ __align__(16) uint32_t lds[T * K + kStagePad + T * K / A];
     __shared__ uint64_t split[2];
     static_assert(T * K >= kTileMax + kTileMax / 32, "a padded merge window");
-    sort_groups<T, K, A>(ids, scratch, counts[kSubCounts + 1], [&](uint32_t k) { return *(lw.sub_end - 1 - k); }, lds,
+    sort_groups<T, K, A>(ids, scratch, lw.desc, counts[kSubCounts + 1], [&](uint32_t k) { return *(lw.sub_end - 1 - k); }, lds,
                          lds + T * K + kStagePad, lds);
     sort_skewed(offsets, ids, scratch, lists + kFallback * nq, counts[kFallback], lds, split);
 }
@@ -1085,11 +1073,12 @@ segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uin
             const uint32_t j = np ? kLong : 4u, li = atomicAdd(&counts[j], 1u);
             lists[(uint64_t)j * nq + li] = q;
             lds[0] = li;
-            if (np) lw.desc[(uint64_t)li * kDesc + kDescPart] = lds[1] = atomicAdd(&counts[kPartCount], np);
+            if (np) lds[1] = atomicAdd(&counts[kPartCount], np);
         }
         __syncthreads();
         const uint32_t sh = digit_shift(seg_id_range(seg_range, q, id_range));
-        for (uint32_t p = threadIdx.x; p < np; p += T) lw.parts[lds[1] + p] = part_item(lds[0], p, np, o, len, sh);
+        for (uint32_t d = threadIdx.x; np && d < kLongDigits; d += T) lw.desc[(uint64_t)lds[0] * kDesc + d] = 0;
+        for (uint32_t p = threadIdx.x; p < np; p += T) lw.parts[lds[1] + p] = part_item(lds[0], p, o, len, sh);
         return;
     }
     const uint32_t c = (uint32_t)len;
@@ -1116,12 +1105,12 @@ uint64_t segsort_ws_elems(uint64_t nq) { return (uint64_t)kListCls * nq + kSortC
 static uint64_t most_long(uint64_t cap) { return cap / (kMidMax + 1) + 1; }
 static uint64_t most_parts(uint64_t cap) { return cap / kPart + most_long(cap); }
 
-// cap ids (rounded up to 16 bytes), then room for 256 groups of each possible
-// class-L segment, the part list, the segments' descriptors and the parts'
-// counts
-uint64_t segsort_scratch_elems(uint64_t cap) {
-    return (cap + 3) / 4 * 4 + most_long(cap) * (4 * kLongDigits + kDesc) + most_parts(cap) * (4 + kLongDigits);
-}
+// cap ids (rounded up to 16 bytes), then the part list and for each possible
+// class-L segment its descriptor and room for 256 groups: with all parts at
+// most 530 words per segment.  The size is that of an earlier layout of 770,
+// which keeps the sizes that a fixed scratch accepts.
+constexpr uint64_t kLongWords = 770;
+uint64_t segsort_scratch_elems(uint64_t cap) { return cap + most_long(cap) * kLongWords; }
 
 template <typename Kern>
 static uint32_t resident_per_cu(Kern kern, int threads) {
@@ -1155,11 +1144,12 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
         return dim3((uint32_t)std::min<uint64_t>((uint64_t)cus * resident, items));
     };
     LongWs lw;
-    lw.sub = reinterpret_cast<uint4 *>(scratch + (cap + 3) / 4 * 4);
-    lw.sub_end = lw.sub + most_long(cap) * kLongDigits;
-    lw.parts = lw.sub_end;
+    // about three parts per class-L segment that fits cap
+    static_assert(4 * 4 + kDesc + kLongDigits + 4 <= kLongWords, "class-L work space");
+    lw.parts = reinterpret_cast<uint4 *>(scratch + (cap + 3) / 4 * 4);
     lw.desc = reinterpret_cast<uint32_t *>(lw.parts + most_parts(cap));
-    lw.hist = lw.desc + most_long(cap) * kDesc;
+    lw.sub = lw.desc + most_long(cap) * kDesc;
+    lw.sub_end = lw.sub + most_long(cap) * kLongDigits;
     hipError_t e = hipSuccess;
     if (!zeroed) e = launch_zero(counts, kSortCounters * 4, s);
     if (e != hipSuccess) return e;

@@ -1231,7 +1231,15 @@ __global__ void __launch_bounds__(1024) order_scan(uint32_t *__restrict__ cells)
     }
 }
 
-uint64_t order_ws_bytes(uint64_t nq) { return 4 * kOrderCells + 4 * nq; }
+// 4 * kOrderCells + 4 * nq bytes are used, of batches that are ordered at all.
+// The size is that of an earlier layout (two key buffers and the tables of
+// 11-bit radix passes, more than that from kOrderMinQueries on), which keeps
+// the sizes that a fixed scratch accepts.
+uint64_t order_ws_bytes(uint64_t nq) {
+    const auto al = [](uint64_t b) { return (b + 255) & ~255ull; };
+    const uint64_t he = radix_hist_elems(nq, 11);
+    return al(8 * nq) * 2 + al(4 * he) + al(8 * (he + 1)) + al(8 * scan_tmp_elems(he + 1));
+}
 
 hipError_t launch_query_order(const float4 *q, uint32_t nq, const float *mbr, void *ws, const uint32_t **order,
                               hipStream_t s) {
