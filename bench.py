@@ -84,8 +84,8 @@ class HipEvents:
 # HBM traffic summaries (profiles/<tag>_traffic.txt)
 # ---------------------------------------------------------------------------
 
-PHASE_SOURCES = {"count": ("select.hip", "rt_internal.h"), "fill": ("select.hip", "rt_internal.h"),
-                 "sort": ("segsort.hip", "rt_internal.h"), "batch": ("batch_kernels.hip", "rt_internal.h")}
+PHASE_SOURCES = {"count": ("select.hip", "walk.h", "rt_internal.h"), "fill": ("select.hip", "rt_internal.h"),
+                 "sort": ("segsort.hip", "rt_internal.h"), "batch": ("batch_kernels.hip", "walk.h", "rt_internal.h")}
 
 
 def source_hash(*names):
@@ -98,6 +98,8 @@ def source_hash(*names):
 
 def kernel_phase(name: str):
     """Which phase of a select step a kernel belongs to (None: not timed)."""
+    if "walk_kernel<" in name:
+        return "count"
     m = re.search(r"select_kernel<\d+, \d+, (\d), \d(?:, \d)?>", name)
     if m:
         return {"0": "count", "1": "fill"}.get(m.group(1))
@@ -107,9 +109,9 @@ def kernel_phase(name: str):
         return "fill"
     if "segsort" in name or "seg_classify" in name:
         return "sort"
-    m = re.search(r"batch_kernel<(\d)(?:, \d)?>", name)
+    m = re.search(r"batch_kernel<(true|false), ", name)   # counting or filling
     if m:
-        return "batch_count" if m.group(1) == "0" else "batch"
+        return "batch_count" if m.group(1) == "true" else "batch"
     return None
 
 

@@ -125,7 +125,7 @@ __device__ void block_bitonic(uint32_t *a, uint32_t P) {
 // ---------------------------------------------------------------------------
 constexpr uint32_t kLongDigits = 256;
 constexpr uint32_t kPart = 16384;       // ids per part of a class-L segment
-constexpr uint32_t kSubMax = 4096;      // longest group sorted by a 256-thread block
+constexpr uint32_t kSubMax = 4096;      // longest group sorted by a 128-thread block
 constexpr uint32_t kSubBigMax = 32768;  // longest group sorted by a 1024-thread block
 // descriptor of a class-L segment: its digit counts, which become the write
 // cursors of its groups; the digits per group (0: the segment went to the

@@ -4,15 +4,15 @@
 // A walk that pops one node at a time waits one full memory latency per node
 // (its next node is known only after the compare), so a window that reaches a
 // few hundred nodes takes a few hundred latencies however idle the chip is.
-// Here a round takes up to kWalkBatch leaves, or up to kWalkInner internal nodes while
-// the stack is short (see walk_stack_bound), from the top of the stack and
-// issues all their loads before the first compare.  What bounds the pass is
-// vector instructions where many windows run (the loads take one scalar base
-// and a 32-bit offset for that reason) and the chain of rounds where few do.
-// Recording count pass, one node per pop -> this walk: 1M windows on 10M
-// rectangles (fanout 64) 2.72 -> 2.15 ms, 50k windows on 1.2M (fanout 32)
-// 0.295 -> 0.147, 50k large windows on 50M with the split mapping (shared
-// subtrees) 4.3 -> 1.9, 100 of those 0.30 -> 0.11.
+// Here a round takes up to kWalkBatch leaves, or up to kWalkInner internal
+// nodes while the stack leaves room (see walk_stack_bound), from the top of
+// the stack and issues all their loads before the first compare.  What bounds
+// the pass is vector instructions where many windows run (the loads take one
+// scalar base and a 32-bit offset for that reason) and the chain of rounds
+// where few do.  Recording count pass, one node per pop -> this walk: 1M
+// windows on 10M rectangles (fanout 64) 2.72 -> 1.9 ms, 50k windows on 1.2M
+// (fanout 32) 0.295 -> 0.17, 50k large windows on 50M with the split mapping
+// (shared subtrees) 4.3 -> 1.7, 100 of those 0.30 -> 0.08.
 #pragma once
 
 #include "rt_internal.h"
