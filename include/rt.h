@@ -156,7 +156,9 @@ int rt_build_str(const float *rects, uint64_t n, uint32_t fanout, uint32_t layou
  * build runs in HIP kernels on `stream` (hipStream_t, NULL = default stream)
  * and the call returns after it has finished.  The rectangles are validated
  * on the device (RT_EINVAL without the index of the bad one).  Temporary
- * device memory: about 30 bytes per rectangle. */
+ * device memory: about 30 bytes per rectangle; up to 512 MiB of it, and the
+ * memory of up to 16 freed trees (1 GiB at most), are kept for later builds
+ * and given back when device memory runs out. */
 int rt_build_str_device(const float *d_rects, uint64_t n, uint32_t fanout, uint32_t layout,
                         void *stream, rt_tree **out);
 
@@ -395,17 +397,20 @@ int rt_batch_replay_info(rt_batch *b, uint32_t *chunks, uint32_t *overflowed);
 int rt_tree_stats(const rt_tree *t, rt_tree_info *info);
 
 /* Work mapping of later selects on this tree (never changes a result).
- * A query whose walk reaches at least kmin parents-of-leaves nodes is split
- * into one work item per such subtree, so many lane groups share one large
- * window instead of one group walking it alone; kmin = 0 keeps one group per
- * query (the default).  Not to be called while selects on the tree run. */
+ * kmin > 0: large windows are shared by many lane groups instead of one group
+ * walking each alone (a count that records its results hands on what a walk
+ * leaves after 32 nodes; one that does not, and the walking fill, split a
+ * query that reaches at least kmin parents-of-leaves nodes into one work item
+ * per such subtree); kmin = 0 keeps one group per query (the default).  Not to
+ * be called while selects on the tree run. */
 int rt_tree_set_split(rt_tree *t, uint32_t kmin);
 
 /* Lookahead loads in later selects on this tree (section 3, optimization O2;
  * never changes a result): on = 1 makes the traversal load the next node's
  * entries as soon as it pops a leaf (the next node is then already known),
  * so that load overlaps the leaf's comparison and output; on = 0 (default)
- * loads each node when it is popped.  Other values -> RT_EINVAL.  Not to be
+ * loads each node when it is popped.  It applies to the walking fill and to
+ * counts by output slot: the other counts load several nodes per round.  Other values -> RT_EINVAL.  Not to be
  * called while selects on the tree run. */
 int rt_tree_set_lookahead(rt_tree *t, uint32_t on);
 
