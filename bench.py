@@ -201,7 +201,9 @@ def pmc_summary(args):
     if args.last:
         first = "batch_count" if "batch_count" in phases else "count"
         for key in thr:
-            ids = sorted(did for k in phases.get(first, {}).values() for did, _ in k[key])
+            # by the kernel that ends a step's first phase (it may have several)
+            ids = max((sorted(did for did, _ in k[key]) for k in phases.get(first, {}).values() if k[key]),
+                      key=lambda v: v[-1], default=[])
             thr[key] = ids[-args.last] if len(ids) >= args.last else 0
     lines = [f"# {args.title}",
              "# Two counter runs of the same command (FETCH_SIZE, then WRITE_SIZE):",
