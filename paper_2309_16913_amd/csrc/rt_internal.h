@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "replay_units.h"
+
 namespace rtk {
 
 enum : uint32_t { LAYOUT_AOS = 0, LAYOUT_SOA = 1, LAYOUT_D2 = 3 };
@@ -261,7 +263,6 @@ struct SelectPlan {
 // only if it made none.
 enum FillGuard : uint32_t { FILL_ALWAYS = 0, FILL_UNLESS_REPLAYED = 1, FILL_IF_OVERFLOWED = 2, FILL_IF_NOT_RECORDED = 3 };
 
-constexpr uint32_t kRecChunk = 256;          // records per chunk a lane group takes
 // records a lane group collects in LDS before storing them (128 measured no
 // faster for groups of 64 lanes)
 constexpr uint32_t kRecBuf = 64;

@@ -770,26 +770,27 @@ replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffset
     typedef const __attribute__((address_space(1))) rec_vec *Rec;
     const Rec rec = (Rec)ctrl->rec_base;
     const Src rec_count = (Src)ctrl->rec_count;
-    const uint32_t nunits = min(ctrl->rec_chunks, nchunks) * (kRecChunk / 64);
+    const uint32_t nunits = min(ctrl->rec_chunks, nchunks) * kChunkUnits;
     const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6, half = lane >> 5, l = lane & 31u;
     const uint64_t below = lane ? ~0ull >> (64 - lane) : 0ull;
     const uint32_t lbit = 1u << l;
     // Unit u: records [64 * (u % 4), + 64) of chunk u / 4.  What is read ahead
     // (past the last unit: of the last one again) is looked at when its turn
-    // comes; lanes past the chunk's records then take an empty record.
+    // comes; lanes without a record, all of them past the last unit, then take
+    // an empty one.
     const uint32_t step = gridDim.x * W;
     rec_vec rv;
     uint32_t rcnt;
     auto load = [&](uint32_t u) {
-        const uint32_t v = min(u, nunits - 1), c = v / (kRecChunk / 64);
-        rv = __builtin_nontemporal_load(rec + (size_t)c * kRecChunk + (v % (kRecChunk / 64)) * 64 + lane);
+        const uint32_t v = unit_loaded(u, nunits), c = v / kChunkUnits;
+        rv = __builtin_nontemporal_load(rec + (size_t)c * kRecChunk + (v % kChunkUnits) * kUnitRecs + lane);
         rcnt = rec_count[c];
     };
     uint4 d;
     uint64_t o0, o1;
     bool in;
     auto arrive = [&](uint32_t u) {   // the loaded record, and its slot's offsets
-        in = (u % (kRecChunk / 64)) * 64 + lane < min(rcnt, kRecChunk);
+        in = unit_has(u, nunits, lane, rcnt);
         d = in ? make_uint4(rv.x, rv.y, rv.z, rv.w) : make_uint4(0u, 0u, t.first_leaf, 0u);
         o0 = offsets[d.x], o1 = offsets[d.x + 1];
     };
