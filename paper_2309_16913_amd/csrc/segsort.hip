@@ -30,11 +30,11 @@
 #include <algorithm>
 
 #include "rt_internal.h"
+#include "sort_space.h"
 
 namespace rtk {
 
 constexpr uint32_t kKeyPad = 0xFFFFFFFFu;   // never an object id (ids < 2^32 - 1)
-constexpr uint32_t kMidMax = 32768;         // longest class-M segment
 constexpr uint32_t kTileMax = 16384;        // tile of the class-L fallback
 constexpr uint32_t kNumCls = 6;             // S, M1, M2, M3, M4, L (by length)
 constexpr uint32_t kLong = 5;
@@ -123,15 +123,8 @@ __device__ void block_bitonic(uint32_t *a, uint32_t P) {
 // ---------------------------------------------------------------------------
 // class L work space
 // ---------------------------------------------------------------------------
-constexpr uint32_t kLongDigits = 256;
-constexpr uint32_t kPart = 16384;       // ids per part of a class-L segment
 constexpr uint32_t kSubMax = 4096;      // longest group sorted by a 128-thread block
 constexpr uint32_t kSubBigMax = 32768;  // longest group sorted by a 1024-thread block
-// descriptor of a class-L segment: its digit counts, which become the write
-// cursors of its groups; the digits per group (0: the segment went to the
-// fallback), its place in ids (two words), its id range
-constexpr uint32_t kDescGroup = kLongDigits, kDescOff = kLongDigits + 1, kDescRange = kLongDigits + 3;
-constexpr uint32_t kDesc = kLongDigits + 4;
 constexpr uint32_t kSubCounts = 8;      // counters of the two group work lists (in the class counter block)
 constexpr uint32_t kPartCount = 10;     // counter of the part list
 
@@ -150,7 +143,7 @@ __device__ __forceinline__ uint4 run_item(uint32_t x, uint64_t o, uint32_t n, ui
     return make_uint4(x, (uint32_t)o, (uint32_t)(o >> 32) | n << 16, w);
 }
 
-// Behind the cap ids of the scratch.
+// Behind the cap ids of the scratch (sort_space.h).
 struct LongWs {
     uint4 *parts;         // parts {place in the class-L list, run, digit shift}
     uint32_t *desc;       // kDesc words per class-L segment
@@ -1101,16 +1094,7 @@ segsort_few(const uint64_t *__restrict__ offsets, uint32_t nq, uint64_t cap, uin
 
 uint64_t segsort_ws_elems(uint64_t nq) { return (uint64_t)kListCls * nq + kSortCounters; }
 
-// Class-L segments and parts that cap ids can hold at most.
-static uint64_t most_long(uint64_t cap) { return cap / (kMidMax + 1) + 1; }
-static uint64_t most_parts(uint64_t cap) { return cap / kPart + most_long(cap); }
-
-// cap ids (rounded up to 16 bytes), then the part list and for each possible
-// class-L segment its descriptor and room for 256 groups: with all parts at
-// most 530 words per segment.  The size is that of an earlier layout of 770,
-// which keeps the sizes that a fixed scratch accepts.
-constexpr uint64_t kLongWords = 770;
-uint64_t segsort_scratch_elems(uint64_t cap) { return cap + most_long(cap) * kLongWords; }
+uint64_t segsort_scratch_elems(uint64_t cap) { return sort_scratch_words(cap); }
 
 template <typename Kern>
 static uint32_t resident_per_cu(Kern kern, int threads) {
@@ -1143,13 +1127,8 @@ hipError_t launch_segsort(const uint64_t *offsets, uint64_t nq, uint32_t *ids, u
     auto grid = [&](uint32_t resident, uint64_t items) {
         return dim3((uint32_t)std::min<uint64_t>((uint64_t)cus * resident, items));
     };
-    LongWs lw;
-    // about three parts per class-L segment that fits cap
-    static_assert(4 * 4 + kDesc + kLongDigits + 4 <= kLongWords, "class-L work space");
-    lw.parts = reinterpret_cast<uint4 *>(scratch + (cap + 3) / 4 * 4);
-    lw.desc = reinterpret_cast<uint32_t *>(lw.parts + most_parts(cap));
-    lw.sub = lw.desc + most_long(cap) * kDesc;
-    lw.sub_end = lw.sub + most_long(cap) * kLongDigits;
+    const LongSpace at = long_space(reinterpret_cast<uintptr_t>(scratch), cap);
+    const LongWs lw{reinterpret_cast<uint4 *>(scratch + at.parts), scratch + at.desc, scratch + at.sub, scratch + at.end};
     hipError_t e = hipSuccess;
     if (!zeroed) e = launch_zero(counts, kSortCounters * 4, s);
     if (e != hipSuccess) return e;
