@@ -157,8 +157,10 @@ int rt_build_str(const float *rects, uint64_t n, uint32_t fanout, uint32_t layou
  * and the call returns after it has finished.  The rectangles are validated
  * on the device (RT_EINVAL without the index of the bad one).  Temporary
  * device memory: about 30 bytes per rectangle; up to 512 MiB of it, and the
- * memory of up to 16 freed trees (1 GiB at most), are kept for later builds
- * and given back when device memory runs out. */
+ * memory of up to 16 freed trees (1 GiB at most), are kept for later builds.
+ * What the library keeps between builds and selects goes back to the device
+ * when one of its own allocations, for whatever call, finds too little memory
+ * (it does not learn of the caller's). */
 int rt_build_str_device(const float *d_rects, uint64_t n, uint32_t fanout, uint32_t layout,
                         void *stream, rt_tree **out);
 
@@ -297,9 +299,10 @@ int rt_range_select_device_timed(const rt_tree *t, const float *d_queries, uint6
 
 /*
  * Range select (section 3) into caller-owned device buffers, the output
- * placed by the caller.  The library keeps the workspace (a per-device pool,
- * held until the process ends; a workspace is reused only after the work
- * enqueued on it has finished).
+ * placed by the caller.  The library keeps the workspace (a per-device pool;
+ * a workspace is reused only after the work enqueued on it has finished; idle
+ * ones hold at most 8 GiB together, or what the last one used holds, and are
+ * given back when the library runs out of device memory).
  *   d_queries    device, nq*4 floats, 16-byte aligned (not validated: the
  *                caller guarantees no NaN and lx <= hx, ly <= hy)
  *   d_offsets    device, nq+1 uint64: the CSR offsets (always written)

@@ -59,7 +59,11 @@ void rtk::batch_release(rt_batch *b) {
     b->~rt_batch();
 }
 
-static hipError_t dmalloc(void **p, size_t bytes) { return hipMalloc(p, bytes ? bytes : 16); }
+static hipError_t dmalloc(int dev, void **p, size_t bytes) {
+    const hipError_t e = dev_malloc(dev, p, bytes ? bytes : 16);
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
 
 // The record arena as the kernels take it (rec = NULL: no records).
 static BatchRec batch_rec(const rt_batch *b) {
@@ -276,26 +280,26 @@ extern "C" int rt_batch_create(const rt_tree *const *trees, uint32_t ntrees, con
         list_begin[kXcds] = (uint32_t)items.size();
         b->nitems = (uint32_t)items.size();
 
-        hipError_t e = dmalloc(&b->d_trees, bt.size() * sizeof(BatchTree));
-        if (e == hipSuccess) e = dmalloc(&b->d_items, items.size() * sizeof(BatchItem));
-        if (e == hipSuccess) e = dmalloc(&b->d_q, total * 16);
-        if (e == hipSuccess) e = dmalloc(&b->d_counts, total * 4);
-        if (e == hipSuccess) e = dmalloc(&b->d_off, (total + 1) * 8);
-        if (e == hipSuccess) e = dmalloc(&b->d_ctrl, sizeof(Ctrl));
-        if (e == hipSuccess) e = dmalloc(&b->d_scan, scan_tmp_elems(std::max<uint64_t>(total, 1)) * 8);
-        if (e == hipSuccess) e = dmalloc(&b->d_status, 16);
-        if (e == hipSuccess) e = dmalloc(&b->d_lists, segsort_ws_elems(std::max<uint64_t>(total, 1)) * 4);
-        if (e == hipSuccess) e = dmalloc(&b->d_qrange, std::max<uint64_t>(total, 1) * 4);
-        if (e == hipSuccess) e = dmalloc(&b->d_qorder, std::max<uint64_t>(total, 1) * 4);
-        if (e == hipSuccess) e = dmalloc(&b->d_list_begin, (kXcds + 1) * 4);
-        if (e == hipSuccess) e = dmalloc(&b->d_qtree, std::max<uint64_t>(total, 1) * 4);
+        hipError_t e = dmalloc(dev, &b->d_trees, bt.size() * sizeof(BatchTree));
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_items, items.size() * sizeof(BatchItem));
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_q, total * 16);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_counts, total * 4);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_off, (total + 1) * 8);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_ctrl, sizeof(Ctrl));
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_scan, scan_tmp_elems(std::max<uint64_t>(total, 1)) * 8);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_status, 16);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_lists, segsort_ws_elems(std::max<uint64_t>(total, 1)) * 4);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_qrange, std::max<uint64_t>(total, 1) * 4);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_qorder, std::max<uint64_t>(total, 1) * 4);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_list_begin, (kXcds + 1) * 4);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_qtree, std::max<uint64_t>(total, 1) * 4);
         uint64_t plain_total = 0;
         b->plain_begin.resize(ntrees);
         for (uint32_t i = 0; i < ntrees; ++i) {
             b->plain_begin[i] = plain_total;
             plain_total += nq[i] + 1;
         }
-        if (e == hipSuccess) e = dmalloc(&b->d_plain_off, plain_total * 8);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_plain_off, plain_total * 8);
         if (e == hipSuccess) e = hipMemcpy(b->d_trees, bt.data(), bt.size() * sizeof(BatchTree), hipMemcpyHostToDevice);
         if (e == hipSuccess && !items.empty())
             e = hipMemcpy(b->d_items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice);
@@ -321,11 +325,11 @@ extern "C" int rt_batch_create(const rt_tree *const *trees, uint32_t ntrees, con
             b->id_count[i] = off[b->q_begin[i] + nq[i]] - off[b->q_begin[i]];
         }
         b->cap = ids_capacity ? ids_capacity : off[total];
-        e = dmalloc(&b->d_ids, b->cap * 4);
-        if (e == hipSuccess) e = dmalloc(&b->d_scratch, segsort_scratch_elems(b->cap) * 4);
+        e = dmalloc(dev, &b->d_ids, b->cap * 4);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_scratch, segsort_scratch_elems(b->cap) * 4);
         // the record arena for the count pass inside the graph
         const uint64_t rb = rec_arena_bytes(total, b->cap);
-        if (e == hipSuccess) e = dmalloc(&b->d_rec, rb);
+        if (e == hipSuccess) e = dmalloc(dev, &b->d_rec, rb);
         b->rec_nchunks = rec_chunks_in(rb);
         if (e != hipSuccess) return bail(hip_fail(e, "batch output pool"));
 

@@ -126,7 +126,11 @@ DevBuf::~DevBuf() {
 hipError_t DevBuf::alloc(size_t bytes) {
     if (p) (void)hipFree(p);
     p = nullptr;
-    return hipMalloc(&p, bytes ? bytes : 16);
+    int dev = -1;
+    (void)hipGetDevice(&dev);
+    const hipError_t e = dev_malloc(dev, &p, bytes ? bytes : 16);
+    if (e != hipSuccess) p = nullptr;
+    return e;
 }
 
 static uint64_t align256(uint64_t b) { return (b + 255) & ~255ull; }
@@ -637,8 +641,9 @@ int rtk::make_ids(uint64_t nq, uint64_t total, rt_ids **out) {
     return RT_OK;
 }
 
-// Device memory a host select leaves in the pool (larger workspaces are freed).
-constexpr uint64_t kHostSelectKeep = 256ull << 20;
+// Device memory a host select leaves in the pool per workspace (larger ones are
+// freed).
+constexpr uint64_t kHostSelectKeep = 1ull << 30;
 
 extern "C" int rt_range_select(const rt_tree *t, const float *queries, uint64_t nq, rt_ids **out) {
     if (!out) return fail(RT_EINVAL, "out is NULL");

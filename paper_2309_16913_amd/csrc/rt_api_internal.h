@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "../../include/rt.h"
+#include "dev_pool.h"
 #include "rt_internal.h"
 
 struct rt_tree {
@@ -82,25 +83,7 @@ uint64_t rec_arena_bytes(uint64_t nq, uint64_t cap);
 uint64_t rec_arena_guess(const rt_tree *t, uint64_t nq, uint64_t cap);
 uint32_t rec_chunks_in(uint64_t bytes);
 
-// Device workspaces kept per device between calls, each with a few pinned host
-// words and an event recorded behind its last use: one is handed out again only
-// when that has completed, so calls on different streams or threads never
-// share one while it is in use.
-struct PoolWs {
-    void *d = nullptr;
-    uint64_t bytes = 0;
-    uint64_t *host = nullptr;     // 8 pinned words
-    hipEvent_t done = nullptr;
-};
-constexpr int kPoolDevices = 64;
-hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out, bool exact = false);
-void pool_release(int dev, PoolWs *w, hipStream_t s, uint64_t keep = ~0ull);
-// Plain device blocks; freed ones are kept up to a bound and given back to the
-// device when an allocation fails.
-hipError_t block_alloc(int dev, uint64_t bytes, void **p, uint64_t *got);
-void block_free(int dev, void *p, uint64_t bytes);
-
-// Owning device buffer.
+// Owning device buffer, on the current device.
 struct DevBuf {
     void *p = nullptr;
     DevBuf() = default;
