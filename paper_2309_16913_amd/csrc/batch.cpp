@@ -328,7 +328,7 @@ extern "C" int rt_batch_create(const rt_tree *const *trees, uint32_t ntrees, con
         e = dmalloc(dev, &b->d_ids, b->cap * 4);
         if (e == hipSuccess) e = dmalloc(dev, &b->d_scratch, segsort_scratch_elems(b->cap) * 4);
         // the record arena for the count pass inside the graph
-        const uint64_t rb = rec_arena_bytes(total, b->cap);
+        const uint64_t rb = rec_arena_bytes((uint32_t)num_cus(), total, b->cap);
         if (e == hipSuccess) e = dmalloc(dev, &b->d_rec, rb);
         b->rec_nchunks = rec_chunks_in(rb);
         if (e != hipSuccess) return bail(hip_fail(e, "batch output pool"));

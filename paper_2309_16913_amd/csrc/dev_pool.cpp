@@ -91,17 +91,18 @@ hipError_t dev_malloc(int dev, void **p, uint64_t bytes) {
 
 // The smallest idle workspace that is large enough, else an idle one (grown) or
 // a new one.
-hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out, bool exact) {
+hipError_t pool_acquire(int dev, uint64_t bytes, uint64_t extra, PoolWs **out, bool exact) {
     if (!pooled(dev)) return hipErrorInvalidDevice;
     DevPool &p = g_pool[dev];
+    const uint64_t want = bytes + extra;
     PoolWs *w = nullptr;
     {
         std::lock_guard<std::mutex> lk(p.mu);
         size_t at = 0;
         for (size_t i = 0; i < p.idle.size(); ++i) {
             PoolWs *c = p.idle[i];
-            const bool fits = c->bytes >= bytes;
-            if (w && (w->bytes >= bytes ? (!fits || c->bytes >= w->bytes) : !fits)) continue;
+            const bool fits = c->bytes >= want;
+            if (w && (w->bytes >= want ? (!fits || c->bytes >= w->bytes) : !fits)) continue;
             if (hipEventQuery(c->done) != hipSuccess) continue;
             w = c;
             at = i;
@@ -127,10 +128,14 @@ hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out, bool exact) {
             return e;
         }
     }
-    if (w->bytes < bytes) {
+    if (w->bytes < want) {
         // by half again for the next larger call, but not by much of the device
-        e = ws_alloc(dev, w, exact ? bytes : bytes + std::min<uint64_t>(bytes / 2, 256ull << 20));
+        e = ws_alloc(dev, w, exact ? want : want + std::min<uint64_t>(want / 2, 256ull << 20));
         if (e == hipErrorOutOfMemory && !exact) {
+            (void)hipGetLastError();
+            e = ws_alloc(dev, w, want);
+        }
+        if (e == hipErrorOutOfMemory && extra) {
             (void)hipGetLastError();
             e = ws_alloc(dev, w, bytes);
         }

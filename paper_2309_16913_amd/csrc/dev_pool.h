@@ -23,8 +23,9 @@ constexpr int kPoolDevices = 64;
 // one released last holds; the longest idle are freed first.
 constexpr uint64_t kIdleMax = 8ull << 30;
 
-// A workspace of at least `bytes`.  More is taken for growth unless exact.
-hipError_t pool_acquire(int dev, uint64_t bytes, PoolWs **out, bool exact = false);
+// A workspace of at least `bytes`, and of `bytes + extra` if the device has that
+// much: what is extra is only worth having.  More is taken for growth unless exact.
+hipError_t pool_acquire(int dev, uint64_t bytes, uint64_t extra, PoolWs **out, bool exact = false);
 // Hands a workspace back once everything enqueued on s so far has finished.
 // keep: device memory above this is freed first (the caller has waited for s).
 void pool_release(int dev, PoolWs *w, hipStream_t s, uint64_t keep = ~0ull);

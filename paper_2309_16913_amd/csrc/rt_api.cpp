@@ -175,48 +175,13 @@ static uint64_t sel_ws_bytes(uint64_t nq, uint64_t cap) {
            align256(16 * bulk_capacity(cap));
 }
 
-// Record arena past the select's own layout: chunks of kRecChunk 16-byte
-// records, then one count per chunk.  Sized for cap / 16 + 16 nq records
-// (leaf visits with hits and contained subtrees: about cap / 64 at 10M
-// rectangles / 1M windows, fanout 64), a third more for chunks closed early
-// (a node's records never straddle two chunks), and one chunk per lane group
-// that can hold a partly used one at the end of the pass; a count pass that
-// needs more sets the overflow flag and the fill walks the tree instead.
-// Small results get the chunks that cannot run out: a record has at least one
-// id, a chunk is closed with at most kRecBuf - 1 records free, and each
-// window's group may hold a partly used one.
-static uint64_t rec_chunks_sure(uint64_t nq, uint64_t cap) { return cap / (kRecChunk - kRecBuf + 1) + nq + 1; }
-constexpr uint64_t kRecSureIds = 65536;
-
-uint64_t rtk::rec_arena_bytes(uint64_t nq, uint64_t cap) {
-    const uint64_t recs = (cap / 16 + 16 * nq) * 4 / 3;
-    const uint64_t groups = (uint64_t)num_cus() * 8 * 16;
-    uint64_t chunks = (recs + kRecChunk - 1) / kRecChunk + (nq < groups ? nq : groups);
-    if (cap <= kRecSureIds && nq <= groups) chunks = std::max(chunks, rec_chunks_sure(nq, cap));
-    return align256(16 * kRecChunk * chunks) + align256(4 * chunks) + 512;
-}
-
-// Up to 512 ids per window on average (fewer than that many records), and a
-// chunk for every lane group that can run at once on this tree.
-uint64_t rtk::rec_arena_guess(const rt_tree *t, uint64_t nq, uint64_t cap) {
-    const uint64_t ids = std::min<uint64_t>(cap, 512 * nq + 65536);
-    const uint64_t groups = (uint64_t)num_cus() * 8 * (256 / group_width(t->fanout));
-    const uint64_t all = rec_arena_bytes(nq, ids), spare = (uint64_t)num_cus() * 8 * 16;
-    // rec_arena_bytes counts the groups of the narrowest trees
-    const uint64_t less = (std::min(nq, spare) - std::min(nq, groups)) * (16ull * kRecChunk);
-    return ids <= kRecSureIds ? all : all - less;
-}
-
-// Chunks of an arena of `bytes` bytes.
-uint32_t rtk::rec_chunks_in(uint64_t bytes) {
-    const uint64_t per = 16 * kRecChunk + 4;
-    const uint64_t c = bytes > 512 ? (bytes - 512) / per : 0;
-    return (uint32_t)(c < 0xFFFFFFF0ull ? c : 0xFFFFFFF0ull);
-}
-
 uint64_t rtk::select_ws_bytes(uint64_t nq, uint64_t cap) { return sel_ws_bytes(nq, cap); }
 uint64_t rtk::select_replay_ws_bytes(uint64_t nq, uint64_t cap) {
-    return sel_ws_bytes(nq, cap) + rec_arena_bytes(nq, cap);
+    return sel_ws_bytes(nq, cap) + rec_arena_bytes((uint32_t)num_cus(), nq, cap);
+}
+
+uint64_t rtk::select_rec_guess(const rt_tree *t, uint64_t nq, uint64_t cap) {
+    return rec_arena_guess((uint32_t)num_cus(), group_width(t->fanout), nq, cap);
 }
 
 // The bulk-copy descriptors of a workspace for (nq, cap).
@@ -664,7 +629,7 @@ extern "C" int rt_range_select(const rt_tree *t, const float *queries, uint64_t 
         const int dev = t->device;
         hipStream_t s = nullptr;
         PoolWs *w = nullptr, *w2 = nullptr;
-        hipError_t e = pool_acquire(dev, ws_at + ws0 + rec_arena_guess(t, nq, ~0ull), &w);
+        hipError_t e = pool_acquire(dev, ws_at + ws0, select_rec_guess(t, nq, ~0ull), &w);
         if (e != hipSuccess) return hip_fail(e, "select setup");
         auto done = [&](int rc) {
             (void)hipStreamSynchronize(s);
@@ -688,7 +653,7 @@ extern "C" int rt_range_select(const rt_tree *t, const float *queries, uint64_t 
         const uint64_t total = w->host[0];
         const uint64_t ws1 = sel_ws_bytes(nq, total), ids_bytes = align256(total * 4);
         const bool move = w->bytes - ws_at < ws1;
-        e = pool_acquire(dev, ids_bytes + (move ? ws1 : 0) + 256, &w2);
+        e = pool_acquire(dev, ids_bytes + (move ? ws1 : 0) + 256, 0, &w2);
         if (e != hipSuccess) return done(hip_fail(e, "allocating the result"));
         uint32_t *dids = static_cast<uint32_t *>(w2->d);
         if (move) {

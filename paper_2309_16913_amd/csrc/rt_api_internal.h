@@ -7,6 +7,7 @@
 
 #include "../../include/rt.h"
 #include "dev_pool.h"
+#include "rec_space.h"
 #include "rt_internal.h"
 
 struct rt_tree {
@@ -76,12 +77,8 @@ int enqueue_select(const rt_tree *t, const float4 *dq, uint64_t nq, uint64_t *d_
 // records of the count pass.
 uint64_t select_ws_bytes(uint64_t nq, uint64_t cap);
 uint64_t select_replay_ws_bytes(uint64_t nq, uint64_t cap);
-// Record arena for nq queries and cap ids (records, then one count per
-// chunk), and the chunks an arena of `bytes` holds.
-uint64_t rec_arena_bytes(uint64_t nq, uint64_t cap);
-// The same for selects whose result is not known yet, of at most cap ids.
-uint64_t rec_arena_guess(const rt_tree *t, uint64_t nq, uint64_t cap);
-uint32_t rec_chunks_in(uint64_t bytes);
+// Record room worth having for a select of at most cap ids, not known yet.
+uint64_t select_rec_guess(const rt_tree *t, uint64_t nq, uint64_t cap);
 
 // Owning device buffer, on the current device.
 struct DevBuf {

@@ -6,7 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 
-#include "replay_units.h"
+#include "rec_space.h"
 
 namespace rtk {
 
@@ -263,9 +263,6 @@ struct SelectPlan {
 // only if it made none.
 enum FillGuard : uint32_t { FILL_ALWAYS = 0, FILL_UNLESS_REPLAYED = 1, FILL_IF_OVERFLOWED = 2, FILL_IF_NOT_RECORDED = 3 };
 
-// records a lane group collects in LDS before storing them (128 measured no
-// faster for groups of 64 lanes)
-constexpr uint32_t kRecBuf = 64;
 constexpr uint32_t kRecRun = 0x80000000u;    // record of a contained leaf range
 constexpr uint32_t kRecHi = 0x40000000u;     // leaf record of entries 32..63
 constexpr uint32_t kRecDead = 0xFFFFFFFEu;   // the group's chunk state after an overflow

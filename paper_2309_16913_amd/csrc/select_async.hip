@@ -38,7 +38,7 @@ extern "C" int rt_range_select_async(const rt_tree *t, const float *d_queries, u
         // rectangles: fill 457 -> 45 us); whatever more the workspace has is used too
         const uint64_t ws0 = select_ws_bytes(nq, 0);
         PoolWs *w = nullptr, *w2 = nullptr;
-        hipError_t e = pool_acquire(dev, ws0 + rec_arena_guess(t, nq, ids_capacity), &w);
+        hipError_t e = pool_acquire(dev, ws0, select_rec_guess(t, nq, ids_capacity), &w);
         if (e != hipSuccess) return hip_fail(e, "select workspace");
         // hands both workspaces back behind everything enqueued so far (a
         // moved fill stage still replays the records of the first)
@@ -69,7 +69,7 @@ extern "C" int rt_range_select_async(const rt_tree *t, const float *d_queries, u
         if (w->bytes < need) {
             // the sort needs more scratch than this workspace has: move the
             // count stage's part (order, split plan) into a larger one
-            e = pool_acquire(dev, need, &w2);
+            e = pool_acquire(dev, need, 0, &w2);
             if (e == hipSuccess) e = hipMemcpyAsync(w2->d, w->d, ws0, hipMemcpyDeviceToDevice, s);
             if (e != hipSuccess) return done(hip_fail(e, "select workspace"));
             work = w2->d;

@@ -1077,7 +1077,7 @@ static int build_str_levels(const float4 *d_rects, uint64_t n, uint32_t F, uint3
     // one allocation: nodes, ranges, entry counts, leaf ids
     const uint64_t nodes_at = 0, range_at = al(total * t->node_bytes), meta_at = range_at + al(total * 8),
                    ids_at = meta_at + al(total * 4);
-    hipError_t e = pool_acquire(dev, ws, &pw, true);
+    hipError_t e = pool_acquire(dev, ws, 0, &pw, true);
     if (e != hipSuccess) return bail(hip_fail(e, "device build allocation"));
     e = block_alloc(dev, ids_at + al(n ? n * 4 : 16), &t->d_mem, &t->mem_bytes);
     if (e != hipSuccess) return bail(hip_fail(e, "device build allocation"));

@@ -53,7 +53,7 @@ hipError_t hipDeviceSynchronize(void) { finished = queued; return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 }
 constexpr uint64_t MiB = 1 << 20, GiB = 1 << 30;
-static PoolWs *take(uint64_t n) { PoolWs *w = nullptr; CHECK(pool_acquire(0, n, &w) == hipSuccess); CHECK(w->bytes >= n && mem.at(w->d) == w->bytes); return w; }
+static PoolWs *take(uint64_t n) { PoolWs *w = nullptr; CHECK(pool_acquire(0, n, 0, &w) == hipSuccess); CHECK(w->bytes >= n && mem.at(w->d) == w->bytes); return w; }
 """
 
 PROGRAMS = {
@@ -129,7 +129,7 @@ int main() {
     a = take(10 * GiB);
     CHECK(a->bytes == 10 * GiB);
     PoolWs *b = nullptr;
-    CHECK(pool_acquire(0, 1 * MiB, &b) == hipErrorOutOfMemory && !b);
+    CHECK(pool_acquire(0, 1 * MiB, 0, &b) == hipErrorOutOfMemory && !b);
     pool_release(0, a, nullptr);
     b = take(1 * MiB);
     return 0;
