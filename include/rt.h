@@ -247,7 +247,8 @@ int rt_tree_set_replay(rt_tree *t, uint32_t on);
 
 /* After a one-call select on the workspace d_work has finished (the caller
  * synchronizes its stream): *chunks = record chunks of 256 records its count
- * pass took (0 if it did not record), *overflowed = 1 if the records did not
+ * pass took (0 if it did not record; records that it placed one by one are
+ * rounded up to chunks), *overflowed = 1 if the records did not
  * fit and the fill walked the tree.  Blocking copy of 64 bytes. */
 int rt_select_replay_info(const void *d_work, uint32_t *chunks, uint32_t *overflowed);
 

@@ -181,7 +181,7 @@ uint64_t rtk::select_replay_ws_bytes(uint64_t nq, uint64_t cap) {
 }
 
 uint64_t rtk::select_rec_guess(const rt_tree *t, uint64_t nq, uint64_t cap) {
-    return rec_arena_guess((uint32_t)num_cus(), group_width(t->fanout), nq, cap);
+    return rec_arena_guess((uint32_t)num_cus(), group_width(t->fanout), t->split_kmin != 0, nq, cap);
 }
 
 // The bulk-copy descriptors of a workspace for (nq, cap).
@@ -269,7 +269,7 @@ extern "C" int rt_select_replay_info(const void *d_work, uint32_t *chunks, uint3
     Ctrl hc;
     const hipError_t e = hipMemcpy(&hc, d_work, sizeof(Ctrl), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "reading the select's control words");
-    *chunks = hc.rec_chunks;
+    *chunks = hc.rec_chunks + (hc.rec_tail + kRecChunk - 1) / kRecChunk;
     *overflowed = hc.rec_overflow;
     return RT_OK;
 }

@@ -127,7 +127,7 @@ struct Ctrl {
     uint32_t work[8];        // work-queue counters (one per pass)
     uint32_t err;            // internal error flags
     uint32_t bulk_n;         // long contained runs deferred to the bulk copy (descriptors appended)
-    uint32_t pad0;
+    uint32_t rec_tail;       // single records taken from the arena's end by shared walks
     uint32_t rec_chunks;     // record chunks taken by the count pass
     uint32_t rec_overflow;   // 1: the record arena filled up (the fill walks the tree)
     uint32_t rec_nchunks;    // the count pass's record arena (0: it recorded nothing); set by the
@@ -247,10 +247,11 @@ struct SelectPlan {
     uint4 *bulk = nullptr;
     uint32_t bulk_cap = 0;
     // count pass: every leaf with hits and every contained subtree is also
-    // recorded in chunks of kRecChunk records {output slot, position in the
-    // slot, leaf node (| kRecHi: entries 32..63) or kRecRun | first leaf,
-    // hit mask or end leaf}; rec_count[c] = records in chunk c.  The fill
-    // stage replays them instead of walking the tree (NULL: no records).
+    // recorded as {output slot, position in the slot, leaf node (| kRecHi:
+    // entries 32..63) or kRecRun | first leaf, hit mask or end leaf}, in chunks
+    // of kRecChunk records (rec_count[c] = records in chunk c) or, by the item
+    // launches of a shared walk, from the arena's end.  The fill stage replays
+    // them instead of walking the tree (NULL: no records).
     uint4 *rec = nullptr;
     uint32_t *rec_count = nullptr;
     uint32_t rec_nchunks = 0;
@@ -266,6 +267,8 @@ enum FillGuard : uint32_t { FILL_ALWAYS = 0, FILL_UNLESS_REPLAYED = 1, FILL_IF_O
 constexpr uint32_t kRecRun = 0x80000000u;    // record of a contained leaf range
 constexpr uint32_t kRecHi = 0x40000000u;     // leaf record of entries 32..63
 constexpr uint32_t kRecDead = 0xFFFFFFFEu;   // the group's chunk state after an overflow
+// A record has a hit mask or an end leaf that is not 0: one of zeros, as places
+// that were taken but not used are filled with, is none.
 
 
 

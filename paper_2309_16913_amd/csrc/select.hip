@@ -770,11 +770,13 @@ replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffset
     typedef const __attribute__((address_space(1))) rec_vec *Rec;
     const Rec rec = (Rec)ctrl->rec_base;
     const Src rec_count = (Src)ctrl->rec_count;
-    const uint32_t nunits = min(ctrl->rec_chunks, nchunks) * kChunkUnits;
+    const uint32_t taken = min(ctrl->rec_chunks, nchunks), tail = ctrl->rec_tail;
+    const uint32_t nunits = units_of(taken, tail);
+    const uint64_t nrec = (uint64_t)nchunks * kRecChunk;
     const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6, half = lane >> 5, l = lane & 31u;
     const uint64_t below = lane ? ~0ull >> (64 - lane) : 0ull;
     const uint32_t lbit = 1u << l;
-    // Unit u: records [64 * (u % 4), + 64) of chunk u / 4.  What is read ahead
+    // Unit u: records [64 * (u % 4), + 64) of chunk u / 4 (replay_units.h).  What is read ahead
     // (past the last unit: of the last one again) is looked at when its turn
     // comes; lanes without a record, all of them past the last unit, then take
     // an empty one.
@@ -783,14 +785,14 @@ replay_kernel(TreeView t, const uint64_t *__restrict__ offsets, uint32_t noffset
     uint32_t rcnt;
     auto load = [&](uint32_t u) {
         const uint32_t v = unit_loaded(u, nunits), c = v / kChunkUnits;
-        rv = __builtin_nontemporal_load(rec + (size_t)c * kRecChunk + (v % kChunkUnits) * kUnitRecs + lane);
-        rcnt = rec_count[c];
+        rv = __builtin_nontemporal_load(rec + unit_place(v, lane, taken, nrec));
+        rcnt = c < taken ? rec_count[c] : tail_count(c, taken, tail);
     };
     uint4 d;
     uint64_t o0, o1;
     bool in;
     auto arrive = [&](uint32_t u) {   // the loaded record, and its slot's offsets
-        in = unit_has(u, nunits, lane, rcnt);
+        in = unit_has(u, nunits, lane, rcnt) && rv.w != 0;
         d = in ? make_uint4(rv.x, rv.y, rv.z, rv.w) : make_uint4(0u, 0u, t.first_leaf, 0u);
         o0 = offsets[d.x], o1 = offsets[d.x + 1];
     };

@@ -191,8 +191,16 @@ struct GroupWalk {
     // records collect in LDS and go out to the group's chunk of the arena up
     // to kRecBuf at a time: loads and stores share one in-order completion
     // counter, so a store issued before a node load delays the wait for it
+    // (SHARED: to places reserved at the arena's end, a chunk's worth at a time
+    // if the buffer fills up, and exactly as many as there are at the end.  Such
+    // a launch has a group for every few items, and most groups write a handful
+    // of records: with a chunk each, 1000 windows of up to 1e-2 of the space on
+    // 10M rectangles took 8.7K chunks for 0.04M records, more than twice the
+    // arena.  An update per 64 records instead of 256 is no way out: 0.40 ->
+    // 1.66 ms for the large subtrees of 50k windows on 50M rectangles.)
     uint4 *rbuf;
     uint32_t nbuf = 0, rchunk = kNoNode, rcnt = 0, ustart = 0;
+    uint32_t room = 0, limit = 0;   // SHARED: places reserved from rchunk on, and those there are
     uint32_t own = kNoNode;   // the chunk that is the group's by its place, until it is used
     RecArena ar;
     Ctrl *ctrl;
@@ -201,6 +209,8 @@ struct GroupWalk {
                                          const RecArena &arena, Ctrl *c)
         : e(lane & (G - 1)), gbase(lane & ~(uint32_t)(G - 1)), stk(stack), stack_cap(cap), rbuf(records), ar(arena),
           ctrl(c) {
+        // the launches of items take no chunks: how many are taken is settled
+        if (REC && SHARED) limit = tail_limit(c->rec_chunks, arena.nchunks);
         below = e == 0 ? 0ull : (~0ull >> (64 - e));
     }
 
@@ -221,10 +231,47 @@ struct GroupWalk {
         }
     }
 
-    __device__ __forceinline__ void flush(uint32_t *counts, uint32_t slot) {   // group-uniform
-        if constexpr (REC) {
+    // SHARED: place of record i of the group's reservation.
+    __device__ __forceinline__ uint4 *tail_place(uint32_t i) {
+        return ar.rec + ((size_t)ar.nchunks * kRecChunk - 1 - rchunk - i);
+    }
+
+    // SHARED: room for the buffered records; what is left of the room before is
+    // filled with records of nothing.
+    __device__ __forceinline__ void reserve(bool last) {   // group-uniform
+        if (rchunk == kRecDead || rcnt + nbuf <= room) return;
+        for (uint32_t i = rcnt + e; i < room; i += G) put_rec(tail_place(i), 0u, 0u, 0u, 0u);
+        const uint32_t n = last ? nbuf : kRecChunk;
+        uint32_t at = 0;
+        if (e == 0) {
+            at = atomicAdd(&ctrl->rec_tail, n);
+            if (at + n > limit) {
+                atomicOr(&ctrl->rec_overflow, 1u);
+                at = kRecDead;
+            }
+        }
+        rchunk = (uint32_t)__shfl((int)at, (int)gbase);
+        rcnt = 0;
+        room = n;
+    }
+
+    __device__ __forceinline__ void flush(uint32_t *counts, uint32_t slot, bool last = false) {   // group-uniform
+        if constexpr (REC && SHARED) {
             if (nbuf == 0) return;
             settle(counts, slot);
+            reserve(last);
+            __builtin_amdgcn_wave_barrier();
+            if (rchunk != kRecDead) {
+                for (uint32_t i = e; i < nbuf; i += G) {
+                    const uint4 v = rbuf[i];
+                    put_rec(tail_place(rcnt + i), v.x, v.y, v.z, v.w);
+                }
+                rcnt += nbuf;
+            }
+            nbuf = ustart = 0;
+            __builtin_amdgcn_wave_barrier();
+        } else if constexpr (REC) {
+            if (nbuf == 0) return;
             __builtin_amdgcn_wave_barrier();
             if (rchunk != kRecDead && (rchunk == kNoNode || rcnt + nbuf > kRecChunk)) {
                 if (rchunk != kNoNode && e == 0) ar.count[rchunk] = rcnt;
@@ -255,7 +302,11 @@ struct GroupWalk {
     }
 
     __device__ __forceinline__ void finish(uint32_t *counts) {   // after the group's last unit
-        if constexpr (REC) {
+        if constexpr (REC && SHARED) {
+            flush(counts, 0, true);
+            if (rchunk != kRecDead)
+                for (uint32_t i = rcnt + e; i < room; i += G) put_rec(tail_place(i), 0u, 0u, 0u, 0u);
+        } else if constexpr (REC) {
             flush(counts, 0);
             if (e == 0 && rchunk < kRecDead) ar.count[rchunk] = rcnt;
             if (e == 0 && own != kNoNode) ar.count[own] = 0;

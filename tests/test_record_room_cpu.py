@@ -15,10 +15,11 @@ PROGRAMS = {
     "asked_for": r"""
 #include "rec_space.h"
 int main() {
+    for (bool shared : {false, true})
     for (uint32_t width : {16u, 32u, 64u})
         for (uint64_t nq = 1; nq <= 4000000000ull; nq = nq * 3 + 1)
             for (uint64_t cap : {(uint64_t)0, (uint64_t)1000, (uint64_t)1 << 20, (uint64_t)1 << 34, ~(uint64_t)0}) {
-                const uint64_t b = rec_arena_guess(256, width, nq, cap);
+                const uint64_t b = rec_arena_guess(256, width, shared, nq, cap);
                 CHECK(b <= (1ull << 30));
                 CHECK(rec_chunks_in(b) >= 1);
                 // small calls get what cannot run out
