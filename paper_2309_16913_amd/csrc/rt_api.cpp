@@ -490,9 +490,12 @@ int rtk::enqueue_select_stage(const rt_tree *t, const float4 *dq, uint64_t nq, u
         // an arena that holds a result of cap ids whatever its records cannot
         // overflow for one that is written at all
         const bool sure = rec && !sc.on && rec_nchunks >= rec_chunks_sure(nq, cap);
-        if ((!slots || stage == 2) && !sure) {   // whole queries
-            plan.fill_guard = rec ? FILL_UNLESS_REPLAYED
-                                  : (stage == 2 ? (sc.on ? FILL_IF_OVERFLOWED : FILL_UNLESS_REPLAYED) : FILL_ALWAYS);
+        if ((rec || stage == 2) && sc.on) {   // shared queries whose records overflowed
+            if (e == hipSuccess)
+                e = launch_shared_fill(v, dq, (uint32_t)nq, plan.order, w.counts, d_off, d_ids, cap, w.ctrl,
+                                       sc.split_first, t->level_start[1], s);
+        } else if (!slots && !sure) {   // whole queries
+            plan.fill_guard = rec || stage == 2 ? FILL_UNLESS_REPLAYED : FILL_ALWAYS;
             plan.slot_first = nullptr;
             plan.heavy = nullptr;
             if (e == hipSuccess)

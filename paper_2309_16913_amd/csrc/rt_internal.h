@@ -260,9 +260,8 @@ struct SelectPlan {
 };
 
 // When a fill pass that is launched behind a replay runs: always; if the
-// count pass made no records or they overflowed; only if they overflowed;
-// only if it made none.
-enum FillGuard : uint32_t { FILL_ALWAYS = 0, FILL_UNLESS_REPLAYED = 1, FILL_IF_OVERFLOWED = 2, FILL_IF_NOT_RECORDED = 3 };
+// count pass made no records or they overflowed; only if it made none.
+enum FillGuard : uint32_t { FILL_ALWAYS = 0, FILL_UNLESS_REPLAYED = 1, FILL_IF_NOT_RECORDED = 2 };
 
 constexpr uint32_t kRecRun = 0x80000000u;    // record of a contained leaf range
 constexpr uint32_t kRecHi = 0x40000000u;     // leaf record of entries 32..63
@@ -294,6 +293,14 @@ constexpr uint32_t kWalkBudget0 = 32, kWalkBudget1 = 64;
 uint32_t walk_fixed_chunks(uint32_t fanout, uint32_t nq, uint32_t nchunks);
 hipError_t launch_walk(const TreeView &t, const float4 *q, uint32_t nq, uint32_t *counts, Ctrl *ctrl,
                        const SelectPlan &plan, uint2 *items, uint32_t items_per_list, hipStream_t s);
+
+// Walking fill of windows that are shared by many lane groups; runs only if the
+// count pass's records overflowed.  counts: the count pass's, used up.
+// split_parent, parents: the first nodes of the levels two and one above the
+// leaves.
+hipError_t launch_shared_fill(const TreeView &t, const float4 *q, uint32_t nq, const uint32_t *order, uint32_t *counts,
+                              const uint64_t *offsets, uint32_t *ids, uint64_t cap, Ctrl *ctrl, uint32_t split_parent,
+                              uint32_t parents, hipStream_t s);
 
 // Split pre-pass (phase 0: slots per query; phase 1: work items).  Queries
 // are taken in the plan's order with the same XCD slices as the passes;

@@ -160,10 +160,9 @@ select_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, uint32_t *
     extern __shared__ uint32_t smem[];
     if constexpr (MODE == SEL_FILL) {
         if (offsets[noffsets] > cap) return;   // result does not fit: leave ids untouched
-        // the replay wrote everything, or the fill over the other mapping does
+        // the replay wrote everything, or the shared fill does
         const bool rec = ctrl->rec_nchunks != 0, over = ctrl->rec_overflow != 0;
         if (plan.fill_guard == FILL_UNLESS_REPLAYED && rec && !over) return;
-        if (plan.fill_guard == FILL_IF_OVERFLOWED && !(rec && over)) return;
         if (plan.fill_guard == FILL_IF_NOT_RECORDED && rec) return;
     }
     const uint32_t lane = threadIdx.x & 63u;
@@ -554,6 +553,164 @@ walk_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, const uint32
         }
     }
     w.finish(counts);
+}
+
+// ---------------------------------------------------------------------------
+// walking fill of shared windows
+// ---------------------------------------------------------------------------
+// The fill of a select with the split mapping whose records did not fit their
+// arena.  A window of n ids is cut into 1 + n / kShareIds shares, at most
+// max_shares: each walks the levels above the parents of leaves on its own (a
+// thousandth of the window's nodes) and takes those of the parents of leaves
+// whose number falls to it.  A share's ids go wherever the window's range has
+// room -- `left` holds the ids still to come, the count pass's counts at first
+// -- as the sort puts them in order afterwards.  Bound by the latency of one
+// node and one update of `left` per step, so a share is short: with 8192 ids
+// and up to 64 shares 100 windows of up to 1e-2 of the space on 10M rectangles
+// (fanout 32) took 1.22 ms, with 512 ids 0.55, with 256 ids and up to 256
+// shares 0.47, now 0.40; one group per window 1.16.
+constexpr uint32_t kShareIds = 64;
+constexpr uint32_t kMaxShares = 512;
+constexpr uint32_t kShareChunk = 16;   // units taken per counter update, one per lane
+
+template <int G, int LAYOUT>
+__global__ void __launch_bounds__(256)
+shared_fill_kernel(TreeView t, const float4 *__restrict__ qs, uint32_t nq, const uint32_t *__restrict__ order,
+                   uint32_t *__restrict__ left, const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids,
+                   uint64_t cap, Ctrl *__restrict__ ctrl, uint32_t split_parent, uint32_t parents, uint32_t max_shares,
+                   uint32_t stack_cap) {
+    extern __shared__ uint32_t smem[];
+    if (!ctrl->rec_nchunks || !ctrl->rec_overflow || offsets[nq] > cap) return;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t e = lane & (G - 1);
+    const uint32_t gbase = lane & ~(uint32_t)(G - 1);
+    uint32_t *stk = smem + (threadIdx.x / G) * stack_cap;
+    const uint32_t F = t.fanout;
+    const uint64_t gmask = (G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull);
+    const uint64_t below = (e == 0) ? 0ull : (~0ull >> (64 - e));
+    const uint32_t home = blockIdx.x % kXcds;
+    uint32_t visited = 0;
+    // the group's units: bit i of pend: lane i's (window cq, its share cs of cn) is still to do
+    uint64_t pend = 0;
+    uint32_t cq = 0, cs = 0, cn = 1;
+    bool have = false, done = false;
+    uint32_t sp = 0, qi = 0, share = 0, shares = 1;
+    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+    bool bad = false;
+    // the place of n more ids of the window (group-uniform)
+    auto place = [&](uint32_t n) {
+        uint32_t rest = 0;
+        if (e == 0) rest = atomicSub(&left[qi], n);
+        rest = (uint32_t)__shfl((int)rest, (int)gbase);
+        if (rest < n) bad = true;
+        return offsets[qi] + (uint64_t)(rest - n);
+    };
+    while (true) {
+        while (!done && sp == 0) {
+            if (pend == 0) {
+                // units of slice x of the order, share by share: the first
+                // shares of all its windows, then the second ones, ...
+                uint32_t x = 0, v = 0, c = 0;
+                if (e == 0) {
+                    for (; visited < kXcds; ++visited) {
+                        x = (home + visited) % kXcds;
+                        const uint32_t m = (uint32_t)(((uint64_t)(x + 1) * nq) / kXcds) - (uint32_t)(((uint64_t)x * nq) / kXcds);
+                        v = atomicAdd(&ctrl->xwork[1][x][0], kShareChunk);
+                        if (v < m * max_shares) {
+                            c = min(kShareChunk, m * max_shares - v);
+                            break;
+                        }
+                    }
+                }
+                x = (uint32_t)__shfl((int)x, (int)gbase);
+                v = (uint32_t)__shfl((int)v, (int)gbase);
+                c = (uint32_t)__shfl((int)c, (int)gbase);
+                if (c == 0) {
+                    have = false;
+                    done = true;
+                    break;
+                }
+                bool mine = false;
+                if (e < c) {
+                    const uint32_t b0 = (uint32_t)(((uint64_t)x * nq) / kXcds);
+                    const uint32_t m = (uint32_t)(((uint64_t)(x + 1) * nq) / kXcds) - b0;
+                    const uint32_t p = b0 + (v + e) % m;
+                    cs = (v + e) / m;
+                    cq = order ? order[p] : p;
+                    const uint64_t n = offsets[cq + 1] - offsets[cq];
+                    cn = (uint32_t)min((uint64_t)max_shares, 1 + n / kShareIds);
+                    mine = n && cs < cn;
+                }
+                pend = (__ballot(mine) >> gbase) & gmask;
+                continue;
+            }
+            const int src = (int)(gbase + (uint32_t)__builtin_ctzll(pend));
+            pend &= pend - 1;
+            qi = (uint32_t)__shfl((int)cq, src);
+            share = (uint32_t)__shfl((int)cs, src);
+            shares = (uint32_t)__shfl((int)cn, src);
+            q = qs[qi];
+            stk[0] = 0u;
+            sp = 1;
+            have = true;
+        }
+        if (__all(done)) break;
+        __builtin_amdgcn_wave_barrier();
+        uint32_t node = 0;
+        if (have) {
+            sp -= 1;
+            node = stk[sp];
+        }
+        const uint8_t *nb = t.nodes + (size_t)node * t.node_bytes;
+        const bool leaf = node >= t.first_leaf;
+        bool hit = false, cont = false;
+        uint32_t ref = 0;
+        if (have && e < F) {
+            ref = load_ptr<LAYOUT>(nb, F, leaf ? e : 0u);
+            float lx, ly, hx, hy;
+            load_entry<LAYOUT>(nb, F, e, lx, ly, hx, hy);
+            hit = (lx <= q.z) && (q.x <= hx) && (ly <= q.w) && (q.y <= hy);
+            // subtrees are taken whole from the parents of leaves down, so
+            // that shares split everything above
+            cont = hit && !leaf && node >= split_parent && (q.x <= lx) && (hx <= q.z) && (q.y <= ly) && (hy <= q.w);
+        }
+        const uint32_t first = (uint32_t)__shfl((int)ref, (int)gbase);
+        if (hit && node >= split_parent && node < parents && (first + e) % shares != share) hit = cont = false;
+        const uint64_t m = (__ballot(hit) >> gbase) & gmask;
+        const uint64_t cm = (__ballot(cont) >> gbase) & gmask;
+        const uint64_t pm = m & ~cm;
+        if (have && leaf) {
+            if (m) {   // group-uniform
+                const uint64_t o = place((uint32_t)__popcll(m)) + (uint32_t)__popcll(m & below);
+                if (hit && !bad) put_id(ids + o, ref);
+            }
+        } else if (have) {
+            if (cm) {   // group-uniform: contained subtrees
+                uint32_t n = cont ? subtree_objects(t, t.range[first + e]) : 0u;
+                for (uint32_t d = 1; d < G; d <<= 1) n += (uint32_t)__shfl_xor((int)n, (int)d);
+                uint64_t pos = place(n);
+                const uint64_t end = pos + n;
+                for (uint64_t todo = cm; todo && !bad;) {
+                    // a run of neighbouring children is one run of ids
+                    const uint32_t j0 = (uint32_t)__builtin_ctzll(todo);
+                    const uint64_t sh = todo >> j0;
+                    const uint32_t len = ~sh ? (uint32_t)__builtin_ctzll(~sh) : 64u - j0;
+                    todo = (j0 + len >= 64) ? 0ull : (todo & (~0ull << (j0 + len)));
+                    pos += copy_leaf_run<4>(t, t.range[first + j0].x, t.range[first + j0 + len - 1].y, ids, pos, end, e, G, &bad);
+                }
+            }
+            if ((pm >> e) & 1u) {
+                const uint32_t at = sp + (uint32_t)__popcll(pm & below);
+                if (at < stack_cap)
+                    stk[at] = first + e;
+                else
+                    atomicOr(&ctrl->err, kErrStack);
+            }
+            sp = min(sp + (uint32_t)__popcll(pm), stack_cap);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (bad && e == 0) atomicOr(&ctrl->err, kErrBounds);
 }
 
 // Split pre-pass.  Walks only the internal levels above the parents of leaves
@@ -1108,6 +1265,31 @@ hipError_t launch_walk(const TreeView &t, const float4 *q, uint32_t nq, uint32_t
     if (t.layout == LAYOUT_SOA) return G == 16 ? RT_WALK(16, LAYOUT_SOA) : G == 32 ? RT_WALK(32, LAYOUT_SOA) : RT_WALK(64, LAYOUT_SOA);
     return G == 16 ? RT_WALK(16, LAYOUT_D2) : G == 32 ? RT_WALK(32, LAYOUT_D2) : RT_WALK(64, LAYOUT_D2);
 #undef RT_WALK
+}
+
+template <int G, int LAYOUT>
+static hipError_t launch_shared_fill_g(const TreeView &t, const float4 *q, uint32_t nq, const uint32_t *order,
+                                       uint32_t *counts, const uint64_t *offsets, uint32_t *ids, uint64_t cap, Ctrl *ctrl,
+                                       uint32_t split_parent, uint32_t parents, hipStream_t s) {
+    const uint32_t stack_cap = stack_bound(t.height, t.fanout);
+    const size_t smem = (size_t)(256 / G) * stack_cap * sizeof(uint32_t);
+    // at most about 4M units, which are looked at 16 per counter update
+    const uint32_t shares = std::min(kMaxShares, std::max((1u << 22) / nq, 1u));
+    hipLaunchKernelGGL((shared_fill_kernel<G, LAYOUT>), dim3((uint32_t)num_cus() * 8), dim3(256), smem, s, t, q, nq, order,
+                       counts, offsets, ids, cap, ctrl, split_parent, parents, shares, stack_cap);
+    return hipGetLastError();
+}
+
+hipError_t launch_shared_fill(const TreeView &t, const float4 *q, uint32_t nq, const uint32_t *order, uint32_t *counts,
+                              const uint64_t *offsets, uint32_t *ids, uint64_t cap, Ctrl *ctrl, uint32_t split_parent,
+                              uint32_t parents, hipStream_t s) {
+#define RT_SHARED(G_, L_) \
+    launch_shared_fill_g<G_, L_>(t, q, nq, order, counts, offsets, ids, cap, ctrl, split_parent, parents, s)
+    const uint32_t G = group_width(t.fanout);
+    if (t.layout == LAYOUT_AOS) return G == 16 ? RT_SHARED(16, LAYOUT_AOS) : G == 32 ? RT_SHARED(32, LAYOUT_AOS) : RT_SHARED(64, LAYOUT_AOS);
+    if (t.layout == LAYOUT_SOA) return G == 16 ? RT_SHARED(16, LAYOUT_SOA) : G == 32 ? RT_SHARED(32, LAYOUT_SOA) : RT_SHARED(64, LAYOUT_SOA);
+    return G == 16 ? RT_SHARED(16, LAYOUT_D2) : G == 32 ? RT_SHARED(32, LAYOUT_D2) : RT_SHARED(64, LAYOUT_D2);
+#undef RT_SHARED
 }
 
 template <int PHASE>
