@@ -83,8 +83,11 @@ enum { RT_LAYOUT_AOS = 0, RT_LAYOUT_SOA = 1, RT_LAYOUT_AUTO = 2, RT_LAYOUT_D2 = 
  *                 end left of the outer child and are skipped, found by the
  *                 same many-to-many search
  * O3, O4, O5 and LB need both trees built with RT_BUILD_SORT_LX.  No flag
- * gives candidate lists without pruning.  RT_JOIN_DEFAULT picks
- * O3|O5|LB when both trees are sorted, else RT_JOIN_TILE. */
+ * gives candidate lists without pruning.  RT_JOIN_DEFAULT leaves the expansion
+ * to the library: O3|O5|LB when both trees are sorted, else RT_JOIN_TILE, in a
+ * counted join and in one whose sizes are not known yet; a repeated join runs
+ * each level in a single pass that tests only entries reaching into the other
+ * node.  Every other value runs the expansion it names, every time. */
 enum { RT_JOIN_O3 = 1, RT_JOIN_O4 = 2, RT_JOIN_O5 = 4, RT_JOIN_TILE = 8, RT_JOIN_LB = 16, RT_JOIN_DEFAULT = -1 };
 
 typedef struct rt_tree rt_tree;   /* opaque; device-resident; immutable */

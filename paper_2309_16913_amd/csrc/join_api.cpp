@@ -5,11 +5,13 @@
 // of qualifying child pairs, a scan turns the counts into output offsets, the
 // host reads the total, and a fill pass writes the next frontier (or, at the
 // leaves, the (idA << 32 | idB) keys).  Later runs, whose buffers have their
-// size, take one pass per level (2M x 2M rectangles: 478 -> 202 us), whatever
-// the flags: these choose how a first or counted run expands a node pair.  The
-// keys are sorted into the canonical lexicographic order.  Device buffers are kept across levels and across
-// calls (a per-device pool of workspaces, grown geometrically), so a join
-// allocates only when it outgrows every earlier one on its device.
+// size, do the same without the host, and one pass per level where the caller
+// leaves the expansion to the library (2M x 2M rectangles: 478 -> 202 us); an
+// expansion that is asked for is the one that runs, every time.  The keys are
+// sorted into the canonical lexicographic order.  Device buffers are kept
+// across levels and across calls (a per-device pool of workspaces, grown
+// geometrically), so a join allocates only when it outgrows every earlier one
+// on its device.
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -155,9 +157,10 @@ inline void descend(int mode, int &la, int &lb) {
 // next level's buffers and grid allow), grids are sized from the last run's
 // level sizes plus slack, and the host reads only the key count at the end.
 // A level that outgrew those bounds marks the run, which then returns
-// kReplayMiss (the caller runs level by level, growing the buffers).
-int join_keys_replay(const rt_tree *a, const rt_tree *b, int flags, hipStream_t s, JoinRun &w, uint32_t *d_out,
-                     uint64_t out_cap) {
+// kReplayMiss (the caller runs level by level, growing the buffers).  once: the
+// expansion is the library's choice, so levels may run in one pass.
+int join_keys_replay(const rt_tree *a, const rt_tree *b, int flags, bool once, hipStream_t s, JoinRun &w,
+                     uint32_t *d_out, uint64_t out_cap) {
     const std::vector<uint64_t> rec = w.last_levels;
     const size_t H = rec.size();
     if (H == 0) return kReplayMiss;
@@ -212,7 +215,7 @@ int join_keys_replay(const rt_tree *a, const rt_tree *b, int flags, hipStream_t 
             const uint2 *fr = w.fr[cur].as<uint2>();
             uint64_t *off = w.off.as<uint64_t>();
             uint16_t *slots = w.slot.as<uint16_t>();
-            if (mode == JOIN_BOTH || emit) {
+            if (once && (mode == JOIN_BOTH || emit)) {
                 e2 = launch_join_once(va, vb, fr, (uint32_t)lim, nd, mode, w.fr[1 - cur].as<uint2>(),
                                       w.keys.as<uint64_t>(), next_lim, lv + L + 1, over, st);
             } else {
@@ -259,7 +262,7 @@ int join_keys_replay(const rt_tree *a, const rt_tree *b, int flags, hipStream_t 
     };
     put(&va, sizeof(va));
     put(&vb, sizeof(vb));
-    key.push_back((uint64_t)(uint32_t)flags);
+    key.push_back((uint64_t)(uint32_t)flags | (uint64_t)once << 32);
     key.push_back(H);
     key.insert(key.end(), rec.begin(), rec.end());
     for (const Grow *g : {&w.ctrl, &w.lvl, &w.fr[0], &w.fr[1], &w.cnt, &w.off, &w.stmp, &w.slot, &w.keys, &w.ktmp,
@@ -339,13 +342,13 @@ int join_keys_replay(const rt_tree *a, const rt_tree *b, int flags, hipStream_t 
 // Runs the join up to the sorted keys on the device; a replay may also write
 // the (a, b) words (w.pairs_done): to d_out if not NULL and the pairs fit
 // out_cap, else to the key buffer.
-int join_keys(const rt_tree *a, const rt_tree *b, int flags, bool count_tests, hipStream_t s, JoinRun &w,
+int join_keys(const rt_tree *a, const rt_tree *b, int flags, bool once, bool count_tests, hipStream_t s, JoinRun &w,
               uint32_t *d_out, uint64_t out_cap) {
     hipError_t e = w.ctrl.need(sizeof(Ctrl));
     if (e != hipSuccess) return hip_fail(e, "join setup");
     w.pairs_done = false;
     if (!count_tests) {
-        const int rc = join_keys_replay(a, b, flags, s, w, d_out, out_cap);
+        const int rc = join_keys_replay(a, b, flags, once, s, w, d_out, out_cap);
         if (rc != kReplayMiss) return rc;
     }
     // level by level, each level's size read on the host
@@ -457,6 +460,7 @@ extern "C" int rt_spatial_join_ex(const rt_tree *a, const rt_tree *b, int32_t fl
     if (!out) return fail(RT_EINVAL, "out is NULL");
     *out = nullptr;
     if (tests) *tests = 0;
+    const bool once = flags == RT_JOIN_DEFAULT;
     int rc = check_join_args(a, b, &flags);
     if (rc) return rc;
     try {
@@ -464,7 +468,7 @@ extern "C" int rt_spatial_join_ex(const rt_tree *a, const rt_tree *b, int32_t fl
         hipStream_t s = nullptr;
         PooledRun run(a->device, s);
         JoinRun &w = *run.w;
-        rc = join_keys(a, b, flags, tests != nullptr, s, w, nullptr, 0);
+        rc = join_keys(a, b, flags, once, tests != nullptr, s, w, nullptr, 0);
         if (rc) return rc;
         if (tests) *tests = w.tests;
         void *mem = obj_alloc(KIND_PAIRS, sizeof(rt_pairs));
@@ -509,7 +513,7 @@ extern "C" int rt_join_visit_stats(const rt_tree *a, const rt_tree *b, uint64_t 
         hipStream_t s = nullptr;
         PooledRun run(a->device, s);
         JoinRun &w = *run.w;
-        rc = join_keys(a, b, flags, true, s, w, nullptr, 0);
+        rc = join_keys(a, b, flags, false, true, s, w, nullptr, 0);
         if (rc) return rc;
         *node_pairs = w.node_pairs;
         *entry_pairs = w.tests + w.test_desc;
@@ -526,6 +530,7 @@ extern "C" int rt_spatial_join_device(const rt_tree *a, const rt_tree *b, int32_
                                       uint64_t capacity, uint64_t *n_pairs, void *stream) {
     if (!n_pairs) return fail(RT_EINVAL, "n_pairs is NULL");
     *n_pairs = 0;
+    const bool once = flags == RT_JOIN_DEFAULT;
     int rc = check_join_args(a, b, &flags);
     if (rc) return rc;
     if (capacity && !d_pairs) return fail(RT_EINVAL, "d_pairs is NULL with capacity > 0");
@@ -534,7 +539,7 @@ extern "C" int rt_spatial_join_device(const rt_tree *a, const rt_tree *b, int32_
         hipStream_t s = static_cast<hipStream_t>(stream);
         PooledRun run(a->device, s);
         JoinRun &w = *run.w;
-        rc = join_keys(a, b, flags, false, s, w, d_pairs, capacity);
+        rc = join_keys(a, b, flags, once, false, s, w, d_pairs, capacity);
         if (rc) return rc;
         *n_pairs = w.npairs;
         if (w.npairs > capacity)
