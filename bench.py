@@ -382,16 +382,21 @@ def select_leg(rt, torch, ev, args, rects, queries, kmin=0):
               "replayed": bool(args.replay and rec_chunks and not rec_over)}
     lookahead = None
     if args.lookahead:
-        # the lookahead variant (loads one node ahead after each leaf), timed
-        # the same way on the same buffers, then switched off again
-        tree.set_lookahead(True)
-        la_ev = ev.create(5)
-        step()
-        step(la_ev)
-        torch.cuda.synchronize()
+        # the lookahead variant of the walking fill (loads one node ahead after
+        # each leaf; a replayed fill visits no nodes), timed on the same buffers
+        # with the replay off, beside the walking fill without it
+        lookahead = {}
+        tree.set_replay(False)
+        for on in (False, True):
+            tree.set_lookahead(on)
+            la_ev = ev.create(5)
+            step()
+            step(la_ev)
+            torch.cuda.synchronize()
+            lookahead["lookahead" if on else "walking"] = {
+                "count": ev.ms(la_ev[0], la_ev[1]), "fill": ev.ms(la_ev[2], la_ev[3]), "step": ev.ms(la_ev[0], la_ev[4])}
         tree.set_lookahead(False)
-        lookahead = {"count": ev.ms(la_ev[0], la_ev[1]), "fill": ev.ms(la_ev[2], la_ev[3]),
-                     "step": ev.ms(la_ev[0], la_ev[4])}
+        tree.set_replay(bool(args.replay))
     phases = {"count": [], "scan": [], "fill": [], "sort": []}
     for e in events:
         phases["count"].append(ev.ms(e[0], e[1]))

@@ -416,9 +416,12 @@ int rt_tree_set_split(rt_tree *t, uint32_t kmin);
  * never changes a result): on = 1 makes the traversal load the next node's
  * entries as soon as it pops a leaf (the next node is then already known),
  * so that load overlaps the leaf's comparison and output; on = 0 (default)
- * loads each node when it is popped.  It applies to the walking fill and to
- * counts by output slot: the other counts load several nodes per round.  Other values -> RT_EINVAL.  Not to be
- * called while selects on the tree run. */
+ * loads each node when it is popped.  It applies to walks of one node at a
+ * time: the walking fill of whole windows and of output slots, and counts by
+ * output slot -- so only to selects that do not replay records
+ * (rt_tree_set_replay, or a workspace without room for them).  The other counts
+ * load several nodes per round and a replay visits none.  Other values ->
+ * RT_EINVAL.  Not to be called while selects on the tree run. */
 int rt_tree_set_lookahead(rt_tree *t, uint32_t on);
 
 /* Where the fill pass of later selects on this tree copies contained runs

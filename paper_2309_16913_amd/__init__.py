@@ -160,7 +160,8 @@ class Tree:
         _check(_L.rt_tree_set_split(self.h, int(kmin)))
 
     def set_lookahead(self, on: bool):
-        """Load the next node ahead after a leaf in later selects (never
+        """Load the next node ahead after a leaf in later selects that walk
+        the tree one node at a time, that is, do not replay records (never
         changes results)."""
         _check(_L.rt_tree_set_lookahead(self.h, 1 if on else 0))
 
