@@ -84,8 +84,10 @@ class HipEvents:
 # HBM traffic summaries (profiles/<tag>_traffic.txt)
 # ---------------------------------------------------------------------------
 
-PHASE_SOURCES = {"count": ("select.hip", "walk.h", "rt_internal.h"), "fill": ("select.hip", "rt_internal.h"),
-                 "sort": ("segsort.hip", "rt_internal.h"), "batch": ("batch_kernels.hip", "walk.h", "rt_internal.h")}
+PHASE_SOURCES = {"count": ("select.hip", "walk.h", "rt_internal.h"),
+                 "fill": ("select.hip", "replay_units.h", "rt_internal.h"),
+                 "sort": ("segsort.hip", "sort_space.h", "rt_internal.h"),
+                 "batch": ("batch_kernels.hip", "walk.h", "rt_internal.h")}
 
 
 def source_hash(*names):
@@ -100,6 +102,8 @@ def kernel_phase(name: str):
     """Which phase of a select step a kernel belongs to (None: not timed)."""
     if "walk_kernel<" in name:
         return "count"
+    if "shared_fill_kernel<" in name:
+        return "fill"
     m = re.search(r"select_kernel<\d+, \d+, (\d), \d(?:, \d)?>", name)
     if m:
         return {"0": "count", "1": "fill"}.get(m.group(1))
@@ -816,6 +820,8 @@ def serve_device_leg(rt, torch, ev, args, tb):
         rb = 16 * 256 * rec_chunks
         visit_fill = rb + 8 * (nq + 1) + 8 * cap
         comp_fill = rb + 8 * (nq + 1) + 4 * cap + min(int(info.device_bytes), 4 * cap)
+    fill_kernel = ("replay_kernel + bulk_copy_kernel (fill from records)" if args.replay and rec_chunks and not rec_over
+                   else "select_kernel (fill pass)")
     tr = read_traffic(f"select_serve50m_w{nq}")
     out = {"workload": f"select_clustered{info.n_objects}_f{info.fanout}_soa_windows{nq}_device",
            "windows": nq, "ids": cap, "ms_per_select": step, "phases_ms": ph,
@@ -823,7 +829,7 @@ def serve_device_leg(rt, torch, ev, args, tb):
                       "replayed": bool(args.replay and rec_chunks and not rec_over)},
            "queries_per_s": nq / (step / 1e3), "ids_per_s": cap / (step / 1e3),
            "visited": {"nodes": vn, "entries": ve, "ids_from_contained_subtrees": vc},
-           "roofline_fill": roofline_entry("select_kernel (fill pass)", ph["fill"], comp_fill, visit_fill,
+           "roofline_fill": roofline_entry(fill_kernel, ph["fill"], comp_fill, visit_fill,
                                            tr.get("fill"))}
     if "count" in tr:
         out["count_traffic_frac"] = tr["count"] / (ph["count"] / 1e3) / 1e9 / HBM_PEAK_GBS
@@ -941,13 +947,15 @@ def main():
         ms_step = s["wall"] / args.steps * 1e3
         tr = read_traffic(f"select_c2_f{args.fanout}_{args.layout}")
         dom = max(("count", "fill"), key=lambda k: s["avg"][k])
+        dom_kernel = ("walk_kernel (count pass)" if dom == "count" else
+                      "replay_kernel (fill from records)" if s["replay"]["replayed"] else "select_kernel (fill pass)")
         result.update(
             value=args.nq / (s["wall"] / args.steps), ms_per_step=ms_step,
             config={"workload": f"select_mixed{args.n}_windows{args.nq}_f{args.fanout}_{args.layout}",
                     "n_rects": args.n, "n_queries": args.nq, "fanout": args.fanout, "layout": args.layout,
                     "split_kmin": kmin, "selectivity": "loguniform[1e-6,1e-3]", "ids_out": s["cap"]},
             variants_ms=tune["timings_ms"] if tune else None,
-            roofline=roofline_entry(f"select_kernel ({dom} pass)", s["avg"][dom], s["comp"][dom], s["visit"][dom],
+            roofline=roofline_entry(dom_kernel, s["avg"][dom], s["comp"][dom], s["visit"][dom],
                                     tr.get(dom)),
             phases_ms=s["avg"],
             phases_roofline={ph: roofline_entry(ph, s["avg"][ph], s["comp"][ph], s["visit"][ph], tr.get(ph))

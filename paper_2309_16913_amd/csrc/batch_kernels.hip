@@ -7,8 +7,8 @@
 // nodes are shared in one XCD's L2.  A wave takes one item at a time from its
 // XCD's list (then from the others when that is drained), configures its
 // lanes into groups of G = group_width(F) lanes for that tree, and runs the
-// same per-query depth-first traversal as the single-tree kernel (lanes over
-// node entries, __ballot masks, LDS stacks).  Groups of a wave pick the
+// same per-query depth-first traversals as the single-tree kernels (lanes over
+// node entries, __ballot masks, LDS stacks; counts on the batched walk).  Groups of a wave pick the
 // item's queries in order with a wave-local ballot, so only one global
 // atomic is spent per item; the queries of a tree are visited in the Morton
 // order of their centres, so consecutive queries share nodes.
@@ -247,7 +247,14 @@ batch_kernel(const BatchTree *__restrict__ trees, const BatchItem *__restrict__ 
                 rG = G;
             }
         }
-#define RT_ITEM(G_, L_)                                                                                            do {                                                                                                               if constexpr (COUNT)                                                                                               batch_count_item<G_, L_, REC, WIDE>(bt, item, qorder, qs, counts, ctrl, wstk, lane, lanes_below, ar, wrec,                                           rchunk, rcnt, own);                                                               else                                                                                                               batch_fill_item<G_, L_>(bt, item, qorder, qs, offsets, ids, ctrl, wstk, lane, lanes_below);            } while (0)
+#define RT_ITEM(G_, L_)                                                                                             \
+    do {                                                                                                            \
+        if constexpr (COUNT)                                                                                        \
+            batch_count_item<G_, L_, REC, WIDE>(bt, item, qorder, qs, counts, ctrl, wstk, lane, lanes_below, ar, wrec, \
+                                                rchunk, rcnt, own);                                                 \
+        else                                                                                                        \
+            batch_fill_item<G_, L_>(bt, item, qorder, qs, offsets, ids, ctrl, wstk, lane, lanes_below);             \
+    } while (0)
         if (bt.t.layout == LAYOUT_SOA) {
             if (G == 16) RT_ITEM(16, LAYOUT_SOA);
             else if (G == 32) RT_ITEM(32, LAYOUT_SOA);

@@ -17,9 +17,9 @@
 //              until every bucket is in order;
 //   class L    (> 32768)        an MSD pass on the top 8 id bits into global
 //              scratch, cut into parts of 16384 ids so that one segment
-//              occupies many blocks (digit counts per part, a scan over a
-//              segment's parts, every part digit-sorted in LDS and written as
-//              runs), then groups of consecutive sub-buckets (<= 4096 ids
+//              occupies many blocks (digit counts of a segment's parts added
+//              up, every part digit-sorted in LDS and written as a run per
+//              group of consecutive sub-buckets), then the groups (<= 4096 ids
 //              each, or <= 32768 when a sub-bucket holds more) sorted back by
 //              one block each;
 //   fallback   a segment with a bucket too long for these rounds (ids far
@@ -626,12 +626,13 @@ segsort_mid(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, co
 
 // Class L: two levels.  First the segment is split by its top 8 id bits into
 // 256 sub-buckets in global scratch, by parts of kPart ids: the digits of
-// every part are counted (segsort_wide), one block per segment turns the
-// counts into the parts' write positions and cuts the sub-buckets into groups
-// (segsort_part_scan), and every part is counting-sorted by digit in LDS and
-// written out as one run per digit (segsort_part_split).  Then groups of G
-// consecutive sub-buckets are sorted from scratch back into place by the
-// whole grid, one block per group (segsort_sub): G is chosen so that a group
+// every part are counted and added to the segment's (segsort_wide), one block
+// per segment cuts the sub-buckets into groups of G consecutive ones and turns
+// the counts into the groups' write cursors (segsort_part_scan), and every part
+// is counting-sorted by digit in LDS and written out as one run per group, whose
+// place it reserves with an update of the group's cursor (segsort_part_split).
+// Then the groups are sorted from scratch back into place by the whole grid, one
+// block per group (segsort_sub): G is chosen so that a group
 // holds at most 4096 ids, or at most 32768 (a 1024-thread block) when a
 // sub-bucket holds more than 4096 (segments of about a million ids).  A
 // segment with a sub-bucket over 32768 ids (ids far from uniform) is left as
@@ -639,8 +640,8 @@ segsort_mid(const uint64_t *__restrict__ offsets, uint32_t *__restrict__ ids, co
 //
 // Parts keep all CUs at work whatever the number of segments: with one block
 // per segment the split of 24 segments of 33K to 500K ids took 326 us (now
-// 36 us) and that of 12K such segments, 2.0G ids, 8.2 ms (now 6.4 ms: counts
-// 1.8, split 4.5, at 3.6 to 4.5 TB/s).
+// 39 us) and that of 12K such segments, 2.0G ids, 8.2 ms (now 5.7 ms: counts
+// 1.8, scan 0.1, split 3.8, at 4.3 to 4.6 TB/s).
 
 // The parts of the XCD-contiguous share that workgroup wg of nwg works on
 // (workgroups go round the 8 XCDs): parts of one segment write into the same

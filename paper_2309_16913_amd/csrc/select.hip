@@ -22,13 +22,18 @@
 //      group counts its hits (count pass) or writes the object ids at the
 //      query's output cursor + rank (fill pass).
 // The stack is depth-first (a LIFO of node ids) so its size stays bounded by
-// (h-1)(F-1)+1 entries instead of a whole tree level.
+// (h-1)(F-1)+1 entries instead of a whole tree level.  The count passes of whole
+// queries take several nodes from it per round (walk.h), which needs some more.
 //
-// Work distribution: the grid is persistent; a group that empties its stack
-// takes the next query index from a device counter (the count pass two at a
-// time, see grab_chunk).  Both passes walk the same
-// tree with the same predicate, so the fill pass writes exactly the count
-// pass's number of ids for every query.
+// Usually the count pass records what it finds and the fill writes the ids from
+// the records (replay_kernel); walks by one node at a time fill what was not
+// recorded, count by output slot, and make the visit statistics.
+//
+// Work distribution: the grids are persistent; a group that empties its stack
+// takes further queries from device counters (grab_chunk; ListGrab in walk.h,
+// whose first ones go by the group's place).  Both passes walk the same tree
+// with the same predicate, so the fill writes exactly the count pass's number of
+// ids for every query.
 #include "rt_internal.h"
 #include "walk.h"
 

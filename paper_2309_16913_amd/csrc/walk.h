@@ -181,7 +181,6 @@ template <int G, int LAYOUT, bool REC, bool SHARED, bool WIDE>
 struct GroupWalk {
     typedef typename NodeOffset<WIDE>::type Off;
     static constexpr uint32_t U = kWalkBatch;
-    static constexpr uint64_t gmask = (G == 64) ? ~0ull : ((1ull << (G & 63)) - 1ull);
     uint32_t e, gbase;
     uint64_t below;
     uint32_t *stk;
