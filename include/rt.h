@@ -406,10 +406,11 @@ int rt_tree_stats(const rt_tree *t, rt_tree_info *info);
 /* Work mapping of later selects on this tree (never changes a result).
  * kmin > 0: large windows are shared by many lane groups instead of one group
  * walking each alone (a count that records its results hands on what a walk
- * leaves after 32 nodes; one that does not, and the walking fill, split a
- * query that reaches at least kmin parents-of-leaves nodes into one work item
- * per such subtree); kmin = 0 keeps one group per query (the default).  Not to
- * be called while selects on the tree run. */
+ * leaves after 32 nodes, and if the records do not fit, the fill shares a
+ * query's parents-of-leaves nodes; a count that does not record, and its fill,
+ * split a query that reaches at least kmin parents-of-leaves nodes into one
+ * work item per such subtree); kmin = 0 keeps one group per query (the
+ * default).  Not to be called while selects on the tree run. */
 int rt_tree_set_split(rt_tree *t, uint32_t kmin);
 
 /* Lookahead loads in later selects on this tree (section 3, optimization O2;
